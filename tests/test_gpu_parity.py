@@ -390,3 +390,28 @@ def test_random_configurations():
         pr = Pair(small_workload(sizes, P, thr, dtype, index=1000 + case), layout=layout)
         pr.run(2, per_bucket=per_bucket, fused=fused, width=width, priority=case % 4)
         pr.close()
+
+
+@pytest.mark.parametrize("n", [1 << 22, (1 << 22) + 1, (1 << 22) - 4096, 2 * (1 << 22) + 70001, 5])
+def test_all_gather_whole_and_short_chunks(n):
+    """The all-gather orders its work in chunks of 4 Mi elements with a short last one: around the
+    chunk's edges, for all replicas and for a range of them; the others stay as they are."""
+    say("case: all-gather, %d elements in one layer and a ragged one" % n)
+    pair = Pair(small_workload([n, 777], 3, W.NO_LIMIT))
+    pair.seed_shards()
+    em = pair.em
+    for first, count in ((0, 3), (1, 2), (2, 1)):
+        em.shard_param.copy_(torch.randn(em.shard_param.shape, generator=torch.Generator().manual_seed(n + first)))
+        for rep in em.params:
+            for t in rep:
+                t.fill_(7.0)
+        for rep in pair.params:
+            for t in rep:
+                t.fill(7.0)
+        torch.cuda.synchronize()
+        from paper_2302_12445_amd import dear_all_gather_workers
+        dear_all_gather_workers(em.ctx, -1, em.shard_param.data_ptr(), first, count)
+        torch.cuda.synchronize()
+        oracle.all_gather(pair.op, -1, to_numpy(em.shard_param), pair.params, workers=range(first, first + count))
+        pair.compare_params("workers %d..%d" % (first, first + count - 1))
+    pair.close()
