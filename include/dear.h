@@ -305,6 +305,21 @@ int dear_all_gather(dear_ctx_t *ctx, int32_t bucket, const float *shard_param, v
 int dear_update_all_gather(dear_ctx_t *ctx, int32_t bucket, const float *shard_grad, float *shard_param,
                            float *shard_mom, float lr, float momentum, void *hip_stream);
 
+/* ---------------------------------------------------------------------------------
+ * dear_iteration -- the whole pass over a bucket (or all of them) on one stream, for callers
+ * whose gradients are all in place: reduce-scatter, update and all-gather.  Results are
+ * bit-identical to dear_reduce_scatter, dear_shard_update and dear_all_gather in a row.  The
+ * update is applied in the reduce-scatter's kernel, small buckets share a launch, and the
+ * all-gather of a group of buckets follows its reduce-scatter directly, while the parameter
+ * shards are in the last-level cache.  (The decoupled schedule, paper Section III-B, issues
+ * the halves separately with the calls above.)
+ *   shard_grad   device, written; NULL if the averaged gradients are not wanted
+ *   shard_param, shard_mom  device, updated in place
+ * Errors: DEAR_EINVAL, DEAR_ERANGE, DEAR_EALIGN, DEAR_EHIP.
+ */
+int dear_iteration(dear_ctx_t *ctx, int32_t bucket, float *shard_grad, float *shard_param, float *shard_mom,
+                   float lr, float momentum, void *hip_stream);
+
 /* dear_all_gather_workers -- dear_all_gather restricted to the workers
  * first_worker .. first_worker+n_workers-1 (only their parameter tensors are written).
  * With one worker it turns any shard buffer (e.g. the momentum shards) back into that

@@ -108,27 +108,20 @@ class EmulatedWorkers:
 
     def iteration(self, lr: float, momentum: float, per_bucket: bool = True, stream=None,
                   fused_update: bool = False, fused_gather: bool = False) -> None:
-        """One pass of the whole path on one stream: reduce-scatter the buckets in the order
-        their gradients become ready, update the owned shards, all-gather in forward order.
-        fused_update: reduce-scatter and update of a bucket in one kernel.
-        fused_gather: update and all-gather of a bucket in one kernel."""
-        buckets = list(range(self.plan.n_buckets)) if per_bucket else [-1]
+        """One pass of the whole path on one stream: reduce-scatter, update of the owned shards,
+        all-gather.  The library chooses how buckets share launches (dear_iteration).
+        fused_update: the averaged gradients are not wanted, shard_grad is not written.
+        fused_gather: reduce-scatters first, then update and all-gather of a bucket in one call;
+        per_bucket False: all buckets in one of these calls."""
         if fused_gather:
+            buckets = list(range(self.plan.n_buckets)) if per_bucket else [-1]
             for b in buckets:
                 self.reduce_scatter(b, stream)
             for b in reversed(buckets):
                 self.update_all_gather(b, lr, momentum, stream)
             return
-        if fused_update:
-            for b in buckets:
-                self.reduce_scatter_update(b, lr, momentum, stream)
-        else:
-            for b in buckets:
-                self.reduce_scatter(b, stream)
-            for b in buckets:
-                self.shard_update(b, lr, momentum, stream)
-        for b in reversed(buckets):
-            self.all_gather(b, stream)
+        B.dear_iteration(self.ctx, -1, None if fused_update else self.shard_grad.data_ptr(),
+                         self.shard_param.data_ptr(), self.shard_mom.data_ptr(), lr, momentum, _stream_handle(stream))
 
     def replan(self, threshold_bytes: Optional[int] = None, plan: Optional[B.Plan] = None, stream=None) -> None:
         """Switch to another bucket plan over the same tensors, carrying the optimizer state
@@ -163,8 +156,7 @@ class EmulatedWorkers:
     def capture_iteration(self, lr: float, momentum: float, per_bucket: bool = True,
                           fused_update: bool = False) -> "torch.cuda.CUDAGraph":
         """Record one iteration (all its launches) into a HIP graph and return it; replay()
-        then runs the iteration with one submission, which matters when the step is
-        launch-bound (many small buckets).  Nothing is executed by the capture itself.  The
+        then runs the iteration with one submission.  Nothing is executed by the capture itself.  The
         library's launches contain no memset nodes and allocate nothing, so they are safe to
         capture; the graph is bound to this context's tensors and launch width."""
         graph = torch.cuda.CUDAGraph()

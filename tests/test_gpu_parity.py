@@ -415,3 +415,32 @@ def test_all_gather_whole_and_short_chunks(n):
         oracle.all_gather(pair.op, -1, to_numpy(em.shard_param), pair.params, workers=range(first, first + count))
         pair.compare_params("workers %d..%d" % (first, first + count - 1))
     pair.close()
+
+
+@pytest.mark.parametrize("dtype,keep,width", [("f32", True, 0), ("f32", False, 0), ("bf16", True, 0),
+                                              ("bf16", False, 5), ("f32", True, 7)])
+def test_iteration_call_of_one_bucket_and_of_several_groups(dtype, keep, width):
+    """dear_iteration on one bucket touches nothing else, and on a plan whose buckets do not all fit
+    one pair of launches (8192 tiles of 4096 elements) equals the three calls."""
+    from paper_2302_12445_amd import dear_iteration
+    say("case: iteration call, %s, keep %s, width %d" % (dtype, keep, width))
+    for sizes, P, bucket in ((RAGGED, 5, 3), ([12_000_003, 12_000_001, 12_000_000, 70], 2, -1)):
+        pair = Pair(small_workload(sizes, P, 0, dtype))
+        em, op, w = pair.em, pair.op, pair.w
+        em.set_max_workgroups(width)
+        pair.seed_shards()
+        pair.load_grads(0)
+        pair.sg[...] = -3.0
+        em.shard_grad.fill_(-3.0)
+        dear_iteration(em.ctx, bucket, em.shard_grad.data_ptr() if keep else None, em.shard_param.data_ptr(),
+                       em.shard_mom.data_ptr(), w.lr, w.momentum)
+        torch.cuda.synchronize()
+        kept = pair.sg.copy()
+        oracle.reduce_scatter(op, bucket, pair.grads, pair.sg)
+        oracle.shard_update(op, bucket, pair.sg, pair.sp, pair.sm, w.lr, w.momentum)
+        oracle.all_gather(op, bucket, pair.sp, pair.params)
+        pair.compare_buffer("shard_grad", em.shard_grad, pair.sg if keep else kept)
+        pair.compare_buffer("shard_mom", em.shard_mom, pair.sm)
+        pair.compare_buffer("shard_param", em.shard_param, pair.sp)
+        pair.compare_params("params")
+        pair.close()
