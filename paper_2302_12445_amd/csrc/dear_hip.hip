@@ -603,7 +603,8 @@ __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_bounded_kernel(
 // shard_update_kernel), stores the new w and v to the shard buffers and the new w to all
 // receiving replicas' layer tensors.  The updated value has to reach every replica from the
 // workgroup that computed it, so the stores go to all replicas at once (P interleaved write
-// streams) instead of replica by replica as in all_gather_kernel.
+// streams) instead of replica by replica as in all_gather_kernel: for few replicas, short
+// launches and bounded grids.
 template <bool ALL_FULL>
 __device__ __forceinline__ void update_gather_tile(const dear_tile &t, float *const *__restrict__ param_tab, int L,
                                                    int P, const float *__restrict__ g, float *__restrict__ w,
@@ -1001,6 +1002,16 @@ extern "C" int dear_shard_update(dear_ctx_t *c, int32_t bucket, const float *sha
                          static_cast<hipStream_t>(hip_stream));
 }
 
+// dear_update_all_gather writes all P replicas from the workgroup that updated: P write streams at once, which
+// HBM sustains worse the more there are (5.4 TB/s at P = 8, against 6.5 replica by replica).  From
+// UAG_SPLIT_P replicas on the 4 bytes per element that one kernel saves are worth less than that, if the
+// launch is long enough to pay for a second one: UAG_SPLIT_TILES tile copies are about 25 us.  us per iteration
+// of reduce-scatters and these calls, one kernel / update, then all-gather: 100 M elements in 64 MB buckets
+// P = 2 710 / 757, P = 3 857 / 878, P = 4 1016 / 1011; 25 M elements in 25 MB buckets P = 8 430 / 400;
+// BERT-Base-shaped P = 16 3173 / 2826; 5 M elements in 4 MB buckets P = 8 115 / 131.
+constexpr int32_t UAG_SPLIT_P = 5;
+constexpr int64_t UAG_SPLIT_TILES = 8192;
+
 extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float *shard_grad,
                                       float *shard_param, float *shard_mom, float lr, float momentum,
                                       void *hip_stream)
@@ -1014,6 +1025,11 @@ extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float
     const dear_tile *tiles = c->d_tiles + c->tile_begin[r.begin];
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const unsigned width = grid_width(c->max_workgroups, count);
+    if (width == count && c->P >= UAG_SPLIT_P && count * c->P >= UAG_SPLIT_TILES &&
+        count * AG_SPLIT * c->P <= 0x3fffffff) {
+        rc = launch_update(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
+        return rc == DEAR_OK ? launch_all_gather(c, r, shard_param, 0, c->P, st) : rc;
+    }
     if (width < count)
         update_all_gather_kernel<true><<<dim3(width), dim3(DEAR_BLOCK), 0, st>>>(
             tiles, c->d_param, c->L, c->P, shard_grad, shard_param, shard_mom, lr, momentum,

@@ -444,3 +444,12 @@ def test_iteration_call_of_one_bucket_and_of_several_groups(dtype, keep, width):
         pair.compare_buffer("shard_param", em.shard_param, pair.sp)
         pair.compare_params("params")
         pair.close()
+
+
+@pytest.mark.parametrize("P,n", [(5, 1639 * 4096), (5, 1638 * 4096), (4, 2048 * 4096), (9, 911 * 4096 + 5)])
+def test_update_all_gather_on_both_sides_of_its_split(P, n):
+    """5 replicas and 8192 tile copies: from there on the call launches the update and the all-gather."""
+    say("case: update + all-gather, P=%d, %d elements" % (P, n))
+    pair = Pair(small_workload([n, 33], P, 0))
+    pair.run(iterations=1, fused_gather=True)
+    pair.close()
