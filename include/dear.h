@@ -323,8 +323,7 @@ int dear_iteration(dear_ctx_t *ctx, int32_t bucket, float *shard_grad, float *sh
 /* dear_all_gather_workers -- dear_all_gather restricted to the workers
  * first_worker .. first_worker+n_workers-1 (only their parameter tensors are written).
  * With one worker it turns any shard buffer (e.g. the momentum shards) back into that
- * worker's per-layer layout, which is what a caller needs to re-shard optimizer state
- * when the bucket plan changes (run-time tuning of the buffer size, paper Section IV-B).
+ * worker's per-layer layout.
  * Errors as dear_all_gather; DEAR_ERANGE also for a worker range outside 0 .. P-1. */
 int dear_all_gather_workers(dear_ctx_t *ctx, int32_t bucket, const float *shard_param,
                             int32_t first_worker, int32_t n_workers, void *hip_stream);
@@ -337,6 +336,17 @@ int dear_all_gather_workers(dear_ctx_t *ctx, int32_t bucket, const float *shard_
  * Errors: DEAR_EINVAL, DEAR_ERANGE (worker), DEAR_EALIGN, DEAR_EHIP.
  */
 int dear_scatter_params(dear_ctx_t *ctx, int32_t worker, float *shard_param, void *hip_stream);
+
+/* ---------------------------------------------------------------------------------
+ * dear_reshard -- move a shard buffer from the layout of one plan to that of another over
+ * the same layers and workers (change of the buffer size at run time, paper Section IV-B):
+ * every layer element goes from its slot under `from` to its slot under `to`; the padding
+ * slots of `to` become +0.0f.  Only the contexts' tables are used, not their tensors.
+ *   shard_from  device, read, laid out for `from`;  shard_to  device, written, for `to`
+ * Errors: DEAR_EINVAL (also for different layer sizes or workers, or one buffer twice),
+ * DEAR_EALIGN, DEAR_EHIP.
+ */
+int dear_reshard(dear_ctx_t *from, dear_ctx_t *to, const float *shard_from, float *shard_to, void *hip_stream);
 
 /* Static, NUL-terminated description of a status code. */
 const char *dear_strerror(int status);

@@ -24,7 +24,7 @@ EXPORTS = [
     "dear_plan", "dear_plan_fixed_layers", "dear_plan_free", "dear_plan_view", "dear_plan_tiles",
     "dear_ctx_create", "dear_ctx_destroy", "dear_ctx_set_max_workgroups", "dear_ctx_set_wave_priority",
     "dear_reduce_scatter", "dear_reduce_scatter_static", "dear_reduce_scatter_update", "dear_shard_update", "dear_all_gather",
-    "dear_all_gather_workers", "dear_update_all_gather", "dear_iteration", "dear_scatter_params", "dear_strerror", "dear_version",
+    "dear_all_gather_workers", "dear_update_all_gather", "dear_iteration", "dear_scatter_params", "dear_reshard", "dear_strerror", "dear_version",
 ]
 
 
@@ -92,12 +92,13 @@ def load_library() -> C.CDLL:
     lib.dear_iteration.argtypes = [vp, i32, vp, vp, vp, f32, f32, vp]
     lib.dear_all_gather_workers.argtypes = [vp, i32, vp, i32, i32, vp]
     lib.dear_scatter_params.argtypes = [vp, i32, vp, vp]
+    lib.dear_reshard.argtypes = [vp, vp, vp, vp, vp]
     lib.dear_strerror.argtypes = [C.c_int]
     lib.dear_strerror.restype = C.c_char_p
     lib.dear_version.restype = C.c_int
     for name in ("dear_plan", "dear_plan_fixed_layers", "dear_plan_view", "dear_plan_tiles", "dear_ctx_create",
                  "dear_reduce_scatter", "dear_reduce_scatter_static", "dear_reduce_scatter_update", "dear_shard_update", "dear_all_gather",
-                 "dear_all_gather_workers", "dear_update_all_gather", "dear_iteration", "dear_scatter_params"):
+                 "dear_all_gather_workers", "dear_update_all_gather", "dear_iteration", "dear_scatter_params", "dear_reshard"):
         getattr(lib, name).restype = C.c_int
     _lib = lib
     return lib
@@ -292,6 +293,11 @@ def dear_all_gather_workers(ctx: Context, bucket: int, shard_param: int, first_w
 def dear_scatter_params(ctx: Context, worker: int, shard_param: int, stream: Optional[int] = None) -> None:
     _check(load_library().dear_scatter_params(ctx.handle, worker, C.c_void_p(shard_param), _stream(stream)),
            "dear_scatter_params")
+
+
+def dear_reshard(src: Context, dst: Context, shard_from: int, shard_to: int, stream: Optional[int] = None) -> None:
+    _check(load_library().dear_reshard(src.handle, dst.handle, C.c_void_p(shard_from), C.c_void_p(shard_to),
+                                       _stream(stream)), "dear_reshard")
 
 
 def dear_version() -> int:

@@ -19,6 +19,7 @@
 // operation, no contraction (file compiled with -ffp-contract=off, and see the pragma).
 #include <hip/hip_runtime.h>
 
+#include <cstring>
 #include <memory>
 #include <new>
 #include <vector>
@@ -41,9 +42,19 @@ struct dear_ctx_impl {
     int64_t row_len = 0;
     std::vector<int64_t> bucket_shard_len, bucket_shard_base;
     std::vector<int64_t> tile_begin;  // [B+1] range of bucket b's tiles in the tile table
+    std::vector<int64_t> layer_sizes;
+    void *d_tables = nullptr;         // one allocation: the four tables below
     dear_tile *d_tiles = nullptr;
+    struct layer_place *d_places = nullptr;  // [L]
     const void **d_grad = nullptr;    // [P*L] device pointers
     float **d_param = nullptr;        // [P*L] device pointers
+};
+
+// Where a layer lies in the shard buffers: element i is position e = offset + i of its bucket, slot
+// e % shard_len of shard e / shard_len, whose slots start at shard_base of the worker's row.
+struct layer_place {
+    int64_t offset, shard_len, shard_base;
+    double inv_shard_len;
 };
 
 // ------------------------------------------------------------------------------- kernels
@@ -706,18 +717,69 @@ __global__ __launch_bounds__(DEAR_BLOCK) void scatter_params_kernel(
     const DEAR_GLOBAL float *in = (const DEAR_GLOBAL float *)param_tab[(size_t)worker * L + t.layer];
     const int64_t a = t.src_begin, c = a + t.count;
     const int64_t v_first = a / VE;
+    u4 val[U];
+    bool full[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {  // all loads first, so they are in flight together
+        const int64_t v = v_first + u * DEAR_BLOCK + tid;
+        full[u] = v * VE >= a && v * VE + VE <= c;
+        if (full[u]) val[u] = load_vec<true>((global_u4_in)in + v);
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int64_t v = v_first + u * DEAR_BLOCK + tid;
-        const int64_t e0 = v * VE;
-        if (e0 >= a && e0 + VE <= c) {
-            *(global_f4u_out)(dst + (e0 - a)) = ((const DEAR_GLOBAL f4 *)in)[v];
+        const int64_t e0 = (v_first + u * DEAR_BLOCK + tid) * VE;
+        if (full[u]) {
+            store_f4_dword_aligned<true>(dst + (e0 - a), __builtin_bit_cast(f4, val[u]));
         } else if (e0 < c) {
             for (int j = 0; j < VE; ++j) {
                 const int64_t e = e0 + j;
                 if (e >= a && e < c) dst[e - a] = in[e];
             }
         }
+    }
+}
+
+// Shard buffer of one plan -> shard buffer of another over the same layers and workers: a workgroup
+// takes one tile of the new plan, finds where its first element lies in the old one and copies up to
+// each old shard's end in turn.  Bound by HBM (4 bytes read, 4 written per element); both sides are only 4-byte
+// aligned against each other, so vectors are counted from the piece's start.
+// Going through a replica's tensors instead (gather, scatter, and gather again to give the tensors back)
+// moves three times the bytes: re-planning BERT-Base-shaped at P = 8 took 1311 us that way and takes 831.
+__global__ __launch_bounds__(DEAR_BLOCK) void reshard_kernel(
+    const dear_tile *__restrict__ tiles, const layer_place *__restrict__ places, int64_t from_row_len,
+    const float *__restrict__ from, float *__restrict__ to)
+{
+    constexpr int U = DEAR_TILE_ELEMS / (4 * DEAR_BLOCK);
+    const dear_tile t = tiles[blockIdx.x];
+    const int tid = threadIdx.x;
+    float *__restrict__ dst = to + t.dst_begin;
+    if (t.layer < 0) {
+        for (int i = tid; i < t.count; i += DEAR_BLOCK) dst[i] = 0.0f;
+        return;
+    }
+    const layer_place at = places[t.layer];
+    const int64_t e = at.offset + t.src_begin;
+    int64_t shard = (int64_t)((double)e * at.inv_shard_len);  // off by one at most
+    if (shard * at.shard_len > e) --shard;
+    if ((shard + 1) * at.shard_len <= e) ++shard;
+    int64_t slot = e - shard * at.shard_len;
+    for (int done = 0; done < t.count; ++shard, slot = 0) {
+        const int64_t room = at.shard_len - slot;
+        const int n = room < t.count - done ? (int)room : t.count - done;
+        const float *__restrict__ src = from + shard * from_row_len + at.shard_base + slot;
+        f4 val[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = 4 * (u * DEAR_BLOCK + tid);
+            if (i + 4 <= n) val[u] = load_f4_dword_aligned<true>(src + i);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = 4 * (u * DEAR_BLOCK + tid);
+            if (i + 4 <= n) store_f4_dword_aligned<true>(dst + done + i, val[u]);
+        }
+        if (tid < n % 4) dst[done + n - n % 4 + tid] = src[n - n % 4 + tid];
+        done += n;
     }
 }
 
@@ -815,6 +877,8 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
     }
     std::unique_ptr<dear_ctx_s> c;
     std::vector<dear_tile> tiles;
+    std::vector<unsigned char> image;  // of the device tables: tiles, layer places, gradient and parameter pointers
+    size_t places_at = 0, grad_at = 0, param_at = 0;
     try {
         c.reset(new dear_ctx_s);
         c->L = plan->L;
@@ -824,31 +888,44 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
         c->row_len = plan->row_len;
         c->bucket_shard_len = plan->bucket_shard_len;
         c->bucket_shard_base = plan->bucket_shard_base;
+        c->layer_sizes = plan->layer_sizes;
         dear_build_tiles(*plan, tiles, c->tile_begin);
+        places_at = tiles.size() * sizeof(dear_tile);
+        grad_at = places_at + plan->L * sizeof(layer_place);
+        param_at = grad_at + n_ptr * sizeof(void *);
+        image.resize(param_at + n_ptr * sizeof(void *));
     } catch (const std::bad_alloc &) {
         return DEAR_ENOMEM;
     }
     if (tiles.size() > 0x7fffffffu / 16) return DEAR_EINVAL;  // grid.x limit, up to 16 workgroups a tile
     if (hipGetDevice(&c->device) != hipSuccess) return DEAR_EHIP;
+    std::memcpy(image.data(), tiles.data(), places_at);
+    for (int32_t l = 0; l < plan->L; ++l) {
+        const int32_t b = plan->layer_bucket[l];
+        const int64_t S = plan->bucket_shard_len[b];
+        const layer_place at{plan->layer_offset[l], S, plan->bucket_shard_base[b], 1.0 / static_cast<double>(S)};
+        std::memcpy(image.data() + places_at + l * sizeof at, &at, sizeof at);
+    }
+    std::memcpy(image.data() + grad_at, grad_ptrs, n_ptr * sizeof(void *));
+    std::memcpy(image.data() + param_at, param_ptrs, n_ptr * sizeof(void *));
 
-    const size_t tile_bytes = tiles.size() * sizeof(dear_tile), ptr_bytes = n_ptr * sizeof(void *);
-    bool ok = hipMalloc(reinterpret_cast<void **>(&c->d_tiles), tile_bytes) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void **>(&c->d_grad), ptr_bytes) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void **>(&c->d_param), ptr_bytes) == hipSuccess;
     int rc = DEAR_OK;
-    if (!ok) {
+    if (hipMalloc(&c->d_tables, image.size()) != hipSuccess) {
+        c->d_tables = nullptr;
         rc = DEAR_ENOMEM;
-        (void)hipGetLastError();
-    } else if (hipMemcpy(c->d_tiles, tiles.data(), tile_bytes, hipMemcpyHostToDevice) != hipSuccess ||
-               hipMemcpy(c->d_grad, grad_ptrs, ptr_bytes, hipMemcpyHostToDevice) != hipSuccess ||
-               hipMemcpy(c->d_param, param_ptrs, ptr_bytes, hipMemcpyHostToDevice) != hipSuccess) {
+    } else if (hipMemcpy(c->d_tables, image.data(), image.size(), hipMemcpyHostToDevice) != hipSuccess) {
         rc = DEAR_EHIP;
-        (void)hipGetLastError();
     }
     if (rc != DEAR_OK) {
+        (void)hipGetLastError();
         dear_ctx_destroy(c.release());
         return rc;
     }
+    unsigned char *base = static_cast<unsigned char *>(c->d_tables);
+    c->d_tiles = reinterpret_cast<dear_tile *>(base);
+    c->d_places = reinterpret_cast<layer_place *>(base + places_at);
+    c->d_grad = reinterpret_cast<const void **>(base + grad_at);
+    c->d_param = reinterpret_cast<float **>(base + param_at);
     *out = c.release();
     return DEAR_OK;
 }
@@ -871,9 +948,7 @@ extern "C" void dear_ctx_destroy(dear_ctx_t *c)
 {
     if (!c) return;
     (void)hipDeviceSynchronize();
-    if (c->d_tiles) (void)hipFree(c->d_tiles);
-    if (c->d_grad) (void)hipFree(c->d_grad);
-    if (c->d_param) (void)hipFree(c->d_param);
+    if (c->d_tables) (void)hipFree(c->d_tables);
     delete c;
 }
 
@@ -1111,6 +1186,21 @@ extern "C" int dear_scatter_params(dear_ctx_t *c, int32_t worker, float *shard_p
     scatter_params_kernel<<<dim3(static_cast<unsigned>(count)), dim3(DEAR_BLOCK), 0,
                             static_cast<hipStream_t>(hip_stream)>>>(c->d_tiles, c->d_param, c->L, worker,
                                                                     shard_param);
+    return launch_status();
+}
+
+extern "C" int dear_reshard(dear_ctx_t *from, dear_ctx_t *to, const float *shard_from, float *shard_to, void *hip_stream)
+{
+    int rc = check_call(from, -1);
+    if (rc == DEAR_OK) rc = check_call(to, -1);
+    if (rc == DEAR_OK) rc = check_shard_buffer(shard_from);
+    if (rc == DEAR_OK) rc = check_shard_buffer(shard_to);
+    if (rc != DEAR_OK) return rc;
+    if (shard_from == shard_to || from->P != to->P || from->layer_sizes != to->layer_sizes) return DEAR_EINVAL;
+    const int64_t count = to->tile_begin[to->B];
+    if (count == 0) return DEAR_OK;
+    reshard_kernel<<<dim3(static_cast<unsigned>(count)), dim3(DEAR_BLOCK), 0, static_cast<hipStream_t>(hip_stream)>>>(
+        to->d_tiles, from->d_places, from->row_len, shard_from, shard_to);
     return launch_status();
 }
 

@@ -134,18 +134,15 @@ class EmulatedWorkers:
         with torch.cuda.device(self.device):
             new_ctx = B.dear_ctx_create(new_plan, B.DEAR_F32 if g == 4 else B.DEAR_BF16, gp, wp)
         row = new_plan.total_shard_len
-        new_param = torch.zeros(self.P, row, dtype=torch.float32, device=self.device)
-        new_mom = torch.zeros(self.P, row, dtype=torch.float32, device=self.device)
+        # the library writes every slot of these two, the padding included
+        new_param = torch.empty(self.P, row, dtype=torch.float32, device=self.device)
+        new_mom = torch.empty(self.P, row, dtype=torch.float32, device=self.device)
         new_grad = torch.zeros(self.P, row, dtype=torch.float32, device=self.device)
-        h = _stream_handle(stream)
-        # w: worker 0's tensors -> new shards
-        B.dear_scatter_params(new_ctx, 0, new_param.data_ptr(), h)
-        # v: old shards -> worker 0's tensors (borrowed) -> new shards
-        B.dear_all_gather_workers(self.ctx, -1, self.shard_mom.data_ptr(), 0, 1, h)
-        B.dear_scatter_params(new_ctx, 0, new_mom.data_ptr(), h)
-        # give worker 0 its parameters back
-        B.dear_all_gather_workers(new_ctx, -1, new_param.data_ptr(), 0, 1, h)
         s = stream if stream is not None else torch.cuda.current_stream()
+        s.wait_stream(torch.cuda.current_stream())  # where the new buffers come from
+        h = s.cuda_stream
+        B.dear_scatter_params(new_ctx, 0, new_param.data_ptr(), h)     # w: worker 0's tensors -> new shards
+        B.dear_reshard(self.ctx, new_ctx, self.shard_mom.data_ptr(), new_mom.data_ptr(), h)  # v: old shards -> new
         s.synchronize()  # the old context and buffers are released below
         self.ctx.destroy()
         self.ctx, self.plan = new_ctx, new_plan

@@ -192,3 +192,39 @@ def test_graph_replays_match_eager_oracle(fused):
             assert np.array_equal(got.view(np.uint32), np.concatenate(params[p]).view(np.uint32)), (it, p)
     del graph
     em.close()
+
+
+@pytest.mark.parametrize("sizes,P,a,b", [
+    ([4097, 3, 8191, 4096, 1, 12289, 7, 30001, 64, 513], 7, 0, 1 << 40),
+    ([4097, 3, 8191, 4096, 1, 12289, 7, 30001, 64, 513], 3, 50_000, 5_000),
+    ([1, 2, 3, 5, 40, 5000], 16, 1 << 40, 0),       # shards of 32 slots, tiles over many of them
+    ([300_007, 123_456], 64, 0, 1 << 40),
+    ([70_001], 1, 0, 1 << 40),
+])
+def test_reshard_between_plans(sizes, P, a, b):
+    """dear_reshard from one plan's layout to another's and back: against the oracle's gather and
+    scatter; every slot is written, padding with +0."""
+    import paper_2302_12445_amd as dear
+    from paper_2302_12445_amd.emulation import EmulatedWorkers
+    print("case: reshard", sizes, P, a, b, flush=True)
+    em = [EmulatedWorkers(sizes, P, "f32", t, DEV) for t in (a, b)]
+    op = [oracle.plan(sizes, P, t, 4) for t in (a, b)]
+    layers = [torch.randn(n, generator=torch.Generator().manual_seed(n)).numpy() for n in sizes]
+    want = []
+    for o in op:
+        rows = np.zeros((P, o.total_shard_len), np.float32)
+        oracle.scatter_params(o, [layers] * P, 0, rows)
+        want.append(rows)
+    em[0].shard_mom.copy_(torch.from_numpy(want[0]))
+    em[1].shard_mom.fill_(float("nan"))
+    dear.dear_reshard(em[0].ctx, em[1].ctx, em[0].shard_mom.data_ptr(), em[1].shard_mom.data_ptr())
+    em[0].shard_grad.fill_(float("nan"))
+    dear.dear_reshard(em[1].ctx, em[0].ctx, em[1].shard_mom.data_ptr(), em[0].shard_grad.data_ptr())
+    torch.cuda.synchronize()
+    assert np.array_equal(em[1].shard_mom.cpu().numpy().view(np.uint32), want[1].view(np.uint32))
+    assert np.array_equal(em[0].shard_grad.cpu().numpy().view(np.uint32), want[0].view(np.uint32))
+    other = EmulatedWorkers(sizes[:-1] + [sizes[-1] + 1], P, "f32", a, DEV)
+    with pytest.raises(dear.DearError):
+        dear.dear_reshard(em[0].ctx, other.ctx, em[0].shard_mom.data_ptr(), other.shard_mom.data_ptr())
+    for x in (*em, other):
+        x.close()

@@ -236,6 +236,7 @@ def test_recorded_counter_traffic_belongs_to_the_kernel_sources_in_the_tree():
             assert 0.95 < got / (alg[phase] / nb) < 1.10, (wl, phase)   # HBM traffic ~ algorithmic bytes
 
 
-def test_iteration_call_rejects_a_null_context():
+def test_iteration_and_reshard_reject_a_null_context():
     lib = dear.load_library()
     assert lib.dear_iteration(None, -1, None, None, None, 0.1, 0.9, None) == binding.DEAR_EINVAL
+    assert lib.dear_reshard(None, None, None, None, None) == binding.DEAR_EINVAL
