@@ -155,6 +155,28 @@ __device__ __forceinline__ float grad_elem(const void *base, int64_t i)
     return ((const DEAR_GLOBAL float *)base)[i];
 }
 
+// The first and last 16-byte vector of a run [a, c) may be partial.  Lanes 0 .. VE-1 take an element each
+// of the first and the next VE lanes of the last, if that vector is among [v_first, v_first + vecs); returns
+// the lane's element, or -1.  (One lane that walks over its elements, and over the replicas for each, is a
+// chain of up to (VE-1) * P loads, some 50 us at P = 8 with bf16: longer than a launch over a small bucket.
+// us per iteration with such lanes -> with a lane per element: 2.9 M elements in 313 tensors P = 64 454 -> 369,
+// 20 M elements in 604 tensors P = 7 bf16 234 -> 225, ResNet-50-shaped P = 8 367 -> 362.)
+template <int VE>
+__device__ __forceinline__ int64_t edge_element(int64_t a, int64_t c, int64_t v_first, int vecs)
+{
+    const int tid = threadIdx.x;
+    const int64_t head = a / VE, tail = c / VE;
+    const int64_t head_end = (a + VE - 1) / VE * VE < c ? (a + VE - 1) / VE * VE : c;
+    if (tid < VE) {
+        const int64_t e = head * VE + tid;
+        if (head >= v_first && head < v_first + vecs && e >= a && e < head_end) return e;
+    } else if (tid < 2 * VE) {
+        const int64_t e = tail * VE + tid - VE;
+        if (tail >= v_first && tail < v_first + vecs && e >= head_end && e < c) return e;
+    }
+    return -1;
+}
+
 // acc += the VE gradient elements held in one 16-byte vector (bf16 widens exactly).
 template <bool BF16, int VE>
 __device__ __forceinline__ void add_vector(float (&acc)[VE], const u4 r)
@@ -362,8 +384,7 @@ __device__ __forceinline__ void reduce_scatter_tile(const dear_tile &t, int part
     }
 
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int64_t e0 = vi[u] * VE;
+    for (int u = 0; u < U; ++u)
         if (full[u]) {
 #pragma unroll
             for (int h = 0; h < PIECES; ++h) {
@@ -372,15 +393,24 @@ __device__ __forceinline__ void reduce_scatter_tile(const dear_tile &t, int part
                 for (int j = 0; j < 4; ++j) r[j] = acc[u][4 * h + j] * inv_P;
                 emit_piece<MODE>(o, piece_idx[u][h], r, w_old[u][h], v_old[u][h]);
             }
-        } else if (e0 < c) {  // edge vector of the run: element by element
-            for (int j = 0; j < VE; ++j) {
-                const int64_t e = e0 + j;
-                if (e < a || e >= c) continue;
-                float s = -0.0f;
-                for (int k = 0; k < P; ++k)
-                    s = s + grad_elem<BF16>(grad_tab[(size_t)ring_worker(start, k, P) * L + t.layer], e);
-                emit_elem<MODE>(o, t.dst_begin + (e - a), s * inv_P);
+        }
+
+    if (!ALL_FULL) {
+        const int64_t e = edge_element<VE>(a, c, v_first, U * DEAR_BLOCK);  // CH replicas loaded together as above
+        if (e >= 0) {
+            float s = -0.0f;
+            for (int k0 = 0; k0 < P; k0 += CH) {
+                float x[CH];
+#pragma unroll
+                for (int kk = 0; kk < CH; ++kk) {
+                    const int k = (!TAIL || k0 + kk < P) ? k0 + kk : 0;
+                    x[kk] = grad_elem<BF16>(grad_tab[(size_t)ring_worker(start, k, P) * L + t.layer], e);
+                }
+#pragma unroll
+                for (int kk = 0; kk < CH; ++kk)
+                    if (!TAIL || k0 + kk < P) s = s + x[kk];
             }
+            emit_elem<MODE>(o, t.dst_begin + (e - a), s * inv_P);
         }
     }
 }
@@ -493,16 +523,11 @@ __device__ __forceinline__ void all_gather_tile(const dear_tile &t, int part, fl
     __builtin_amdgcn_sched_barrier(0);
     DEAR_GLOBAL float *out = (DEAR_GLOBAL float *)*out_entry;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int64_t e0 = vi[u] * VE;
-        if (full[u]) {
-            store_vec<DEAR_AG_NT_STORE>((global_f4_out)out + vi[u], val[u]);
-        } else if (e0 < c) {
-            for (int j = 0; j < VE; ++j) {
-                const int64_t e = e0 + j;
-                if (e >= a && e < c) out[e] = src[e - a];
-            }
-        }
+    for (int u = 0; u < U; ++u)
+        if (full[u]) store_vec<DEAR_AG_NT_STORE>((global_f4_out)out + vi[u], val[u]);
+    if (!ALL_FULL) {
+        const int64_t e = edge_element<VE>(a, c, v_first, U * DEAR_BLOCK);
+        if (e >= 0) out[e] = src[e - a];
     }
 }
 
@@ -577,20 +602,14 @@ __device__ __forceinline__ void all_gather_tile_all_replicas(const dear_tile &t,
         full[u] = ALL_FULL || (e0 >= a && e0 + VE <= c);
         if (full[u]) val[u] = load_f4_dword_aligned<DEAR_AG_NT_LOAD>(src + (e0 - a));
     }
+    const int64_t e = ALL_FULL ? -1 : edge_element<VE>(a, c, v_first, U * DEAR_BLOCK);
+    const float edge = e >= 0 ? src[e - a] : 0.0f;
     for (int q = 0; q < n_p; ++q) {
         DEAR_GLOBAL float *out = (DEAR_GLOBAL float *)param_tab[(size_t)(p_first + q) * L + t.layer];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t e0 = vi[u] * VE;
-            if (full[u]) {
-                store_vec<DEAR_AG_NT_STORE>((global_f4_out)out + vi[u], val[u]);
-            } else if (e0 < c) {
-                for (int j = 0; j < VE; ++j) {
-                    const int64_t e = e0 + j;
-                    if (e >= a && e < c) out[e] = src[e - a];
-                }
-            }
-        }
+        for (int u = 0; u < U; ++u)
+            if (full[u]) store_vec<DEAR_AG_NT_STORE>((global_f4_out)out + vi[u], val[u]);
+        if (e >= 0) out[e] = edge;
     }
 }
 
@@ -654,25 +673,24 @@ __device__ __forceinline__ void update_gather_tile(const dear_tile &t, float *co
             const int64_t slot = t.dst_begin + (e0 - a);
             store_f4_dword_aligned<DEAR_UPD_NT_STORE>(v + slot, vv[u]);
             store_f4_dword_aligned<DEAR_UPD_NT_STORE>(w + slot, ww[u]);
-        } else if (e0 < c) {  // edge vector of the run: element by element, all replicas
-            for (int j = 0; j < VE; ++j) {
-                const int64_t e = e0 + j;
-                if (e < a || e >= c) continue;
-                const int64_t slot = t.dst_begin + (e - a);
-                float wj = w[slot], vj = v[slot];
-                sgd_momentum(g[slot], wj, vj, lr, mu);
-                v[slot] = vj;
-                w[slot] = wj;
-                for (int q = 0; q < P; ++q)
-                    ((DEAR_GLOBAL float *)param_tab[(size_t)q * L + t.layer])[e] = wj;
-            }
         }
+    }
+    const int64_t e = ALL_FULL ? -1 : edge_element<VE>(a, c, v_first, U * DEAR_BLOCK);
+    float edge = 0.0f;
+    if (e >= 0) {
+        const int64_t slot = t.dst_begin + (e - a);
+        float vj = v[slot];
+        edge = w[slot];
+        sgd_momentum(g[slot], edge, vj, lr, mu);
+        v[slot] = vj;
+        w[slot] = edge;
     }
     for (int q = 0; q < P; ++q) {
         DEAR_GLOBAL float *out = (DEAR_GLOBAL float *)param_tab[(size_t)q * L + t.layer];
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (full[u]) store_vec<DEAR_AG_NT_STORE>((global_f4_out)out + vi[u], ww[u]);
+        if (e >= 0) out[e] = edge;
     }
 }
 
@@ -728,15 +746,10 @@ __global__ __launch_bounds__(DEAR_BLOCK) void scatter_params_kernel(
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int64_t e0 = (v_first + u * DEAR_BLOCK + tid) * VE;
-        if (full[u]) {
-            store_f4_dword_aligned<true>(dst + (e0 - a), __builtin_bit_cast(f4, val[u]));
-        } else if (e0 < c) {
-            for (int j = 0; j < VE; ++j) {
-                const int64_t e = e0 + j;
-                if (e >= a && e < c) dst[e - a] = in[e];
-            }
-        }
+        if (full[u]) store_f4_dword_aligned<true>(dst + (e0 - a), __builtin_bit_cast(f4, val[u]));
     }
+    const int64_t e = edge_element<VE>(a, c, v_first, U * DEAR_BLOCK);
+    if (e >= 0) dst[e - a] = in[e];
 }
 
 // Shard buffer of one plan -> shard buffer of another over the same layers and workers: a workgroup

@@ -453,3 +453,15 @@ def test_update_all_gather_on_both_sides_of_its_split(P, n):
     pair = Pair(small_workload([n, 33], P, 0))
     pair.run(iterations=1, fused_gather=True)
     pair.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("P,width,gather", [(1, 0, False), (3, 0, True), (9, 0, False), (9, 2, False), (17, 2, True)])
+def test_every_alignment_of_a_runs_ends(P, width, gather, dtype):
+    """Runs that begin and end at every element of a 16-byte vector, within one vector, in the
+    first, middle and last part of a tile: edge elements have lanes of their own in every kernel."""
+    say("case: run ends, P=%d, width %d, gather %s, %s" % (P, width, gather, dtype))
+    sizes = list(range(1, 19)) + [4096 + k for k in range(9)] + [1024 * k + k for k in range(1, 8)] + [2047, 2049, 3]
+    pair = Pair(small_workload(sizes, P, 40_000, dtype))
+    pair.run(iterations=2, width=width, fused_gather=gather)
+    pair.close()
