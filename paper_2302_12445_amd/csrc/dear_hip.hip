@@ -837,6 +837,28 @@ unsigned grid_width(int32_t max_workgroups, int64_t n_items)
     return static_cast<unsigned>(n_items);
 }
 
+// How many workgroups of a launch are resident on a CU is set by the LDS that the launch reserves for each
+// (nothing uses it): 160 KiB / reservation.  HBM serves many streams at once better the fewer loads compete, as
+// long as some 64 KiB per CU are in flight; too few workgroups cost the more the shorter the launch is.
+constexpr unsigned LDS_FOR_1 = 96 << 10, LDS_FOR_2 = 64 << 10, LDS_FOR_5 = 27 << 10;
+
+// Reduce-scatter: a workgroup has min(P, 8) * U loads of 4 KiB in flight, 32 KiB in fp32 and 64 KiB in bf16
+// from P = 8 on.  us per iteration, as many workgroups as fit / 2 per CU / 1 per CU:
+//   fp32, 30 M elements: P = 4 256 / 249 / 297, P = 6 335 / 322 / 377, P = 12 584 / 551 / 634;
+//         6 M in the largest of 5 launches P = 8 369 / 360 / 384; 4 M: P = 4 35 / 39 / 46, P = 12 78 / 80 / 94;
+//         P = 3, 24 M 165 / 176 / -;
+//   bf16, 60 M elements: P = 4 428 / 428 / 432, P = 8 652 / 646 / 636, P = 32 2078 / 2070 / 2041;
+//         33 M: P = 8 367 / 364 / 361, P = 16 639 / 635 / 618; 20 M: P = 8 207 / 206 / 216; 13 M and 7 M: P = 7
+//         226 / 221 / 234; 4 M: P = 6 40 / 41 / 44; P = 3, 24 M 139 / 144 / -.
+// An item is 1024 elements in fp32 and 4096 in bf16.
+template <bool BF16>
+unsigned reduce_scatter_lds(int P, unsigned n_items)
+{
+    if (!BF16) return P >= 4 && n_items >= 6144 ? LDS_FOR_2 : 0;
+    if (P >= 8 && n_items >= 7680) return LDS_FOR_1;
+    return P >= 5 && n_items >= 3072 ? LDS_FOR_2 : 0;
+}
+
 // tiles, grad_tab: device tables (a context's, or the static scratch's).
 template <bool BF16, rs_mode MODE>
 void rs_launch(int P, int L, const void *const *grad_tab, int32_t max_workgroups, int prio, int64_t n_tiles,
@@ -847,6 +869,7 @@ void rs_launch(int P, int L, const void *const *grad_tab, int32_t max_workgroups
     const unsigned n_items = static_cast<unsigned>(n_tiles * SPLIT);
     const dim3 grid(grid_width(max_workgroups, n_items)), block(DEAR_BLOCK);
     const bool bounded = grid.x < n_items;
+    const unsigned lds = bounded ? 0 : reduce_scatter_lds<BF16>(P, n_items);
     const float inv_P = 1.0f / static_cast<float>(P);
 #define RS_LAUNCH(CH, TAIL)                                                                              \
     do {                                                                                                 \
@@ -854,7 +877,7 @@ void rs_launch(int P, int L, const void *const *grad_tab, int32_t max_workgroups
             reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, true><<<grid, block, 0, st>>>(              \
                 tiles, grad_tab, L, P, inv_P, o, n_items, prio);                                         \
         else                                                                                             \
-            reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, false><<<grid, block, 0, st>>>(             \
+            reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, false><<<grid, block, lds, st>>>(           \
                 tiles, grad_tab, L, P, inv_P, o, n_items, 0);                                            \
     } while (0)
     // replicas per load batch: the largest of 8/4/2/1 that divides P without a tail when
@@ -1035,7 +1058,11 @@ int launch_all_gather(const dear_ctx_impl *c, bucket_range r, const float *shard
         constexpr unsigned chunk = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK * AG_U);
         const unsigned n_parts = static_cast<unsigned>(count * AG_SPLIT), n_p = static_cast<unsigned>(n_workers);
         const unsigned len = n_parts % chunk ? n_parts % chunk : 1;
-        all_gather_kernel<AG_U><<<dim3(n_parts * n_p), dim3(DEAR_BLOCK), 0, st>>>(
+        // With very many replicas five workgroups per CU are enough (see reduce_scatter_lds): us per iteration,
+        // as many as fit / 5: P = 64, 25.6 M elements 2418 / 2332, P = 32, 54 M 2186 / 2100; but P = 16, 110 M 2815 / 2945
+        // and P = 64 in launches over 1.5 M 457 / 492.
+        const unsigned lds = n_p >= 32 && n_parts >= 8192 ? LDS_FOR_5 : 0;
+        all_gather_kernel<AG_U><<<dim3(n_parts * n_p), dim3(DEAR_BLOCK), lds, st>>>(
             tiles, c->d_param, c->L, first_worker, n_p, shard_param, n_parts, 0xffffffffu / n_p, 0xffffffffu / len);
     }
     return launch_status();
@@ -1222,8 +1249,9 @@ extern "C" int dear_reshard(dear_ctx_t *from, dear_ctx_t *to, const float *shard
 // dear_reduce_scatter needs a context, and creating one allocates device memory for the tile
 // table and the pointer table its kernel reads.  For callers that cannot allocate, the same
 // kernel reads both tables from this file-scope device array instead.  Layout: gradient
-// pointer table first, tile table behind it.  Every GPU the library runs on holds its own copy
-// of the array until the process ends.
+// pointer table first, tile table on the next 256-byte boundary behind it, so that one copy of the
+// bytes in use brings both up: while it runs the GPU has nothing else to do.  Every GPU the library
+// runs on holds its own copy of the array until the process ends.
 namespace {
 
 constexpr size_t STATIC_MAX_PTRS = DEAR_STATIC_MAX_POINTERS;
@@ -1277,7 +1305,8 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
         if (!grad_ptrs[i]) return DEAR_EINVAL;
         if (misaligned(grad_ptrs[i], 16)) return DEAR_EALIGN;
     }
-    dear_tile *host_tiles = reinterpret_cast<dear_tile *>(host_stage + STATIC_PTR_BYTES);
+    const size_t tiles_at = (n_ptr * sizeof(void *) + 255) & ~size_t(255);  // <= STATIC_PTR_BYTES
+    dear_tile *host_tiles = reinterpret_cast<dear_tile *>(host_stage + tiles_at);
     const int64_t n_tiles = dear_emit_tiles(*plan, b_first, b_last, host_tiles, STATIC_MAX_TILES, nullptr);
     if (n_tiles > static_cast<int64_t>(STATIC_MAX_TILES)) return DEAR_ETOOBIG;
     if (n_tiles == 0) return DEAR_OK;
@@ -1290,18 +1319,17 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     for (size_t i = 0; i < n_ptr; ++i) reinterpret_cast<const void **>(host_stage)[i] = grad_ptrs[i];
-    // Stream-ordered uploads: earlier kernels of this stream that still read the scratch finish
+    // Stream-ordered upload: earlier kernels of this stream that still read the scratch finish
     // first.  The staging memory is pageable and is reused by the next call, so the stream is
-    // drained before returning to the point where the copies have been taken.
-    if (hipMemcpyAsync(dev, host_stage, n_ptr * sizeof(void *), hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(dev + STATIC_PTR_BYTES, host_tiles, static_cast<size_t>(n_tiles) * sizeof(dear_tile),
+    // drained before returning to the point where the copy has been taken.
+    if (hipMemcpyAsync(dev, host_stage, tiles_at + static_cast<size_t>(n_tiles) * sizeof(dear_tile),
                        hipMemcpyHostToDevice, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess) {
         (void)hipGetLastError();
         return DEAR_EHIP;
     }
     const void *const *grad_tab = reinterpret_cast<const void *const *>(dev);
-    const dear_tile *tiles = reinterpret_cast<const dear_tile *>(dev + STATIC_PTR_BYTES);
+    const dear_tile *tiles = reinterpret_cast<const dear_tile *>(dev + tiles_at);
     const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f};
     if (plan->g == 2)
         rs_launch<true, RS_GBAR>(plan->P, plan->L, grad_tab, 0, 0, n_tiles, st, tiles, o);

@@ -465,3 +465,14 @@ def test_every_alignment_of_a_runs_ends(P, width, gather, dtype):
     pair = Pair(small_workload(sizes, P, 40_000, dtype))
     pair.run(iterations=2, width=width, fused_gather=gather)
     pair.close()
+
+
+@pytest.mark.parametrize("dtype,P,n", [("f32", 4, 6145 * 1024), ("f32", 3, 6145 * 1024), ("bf16", 5, 3073 * 4096),
+                                       ("bf16", 8, 7681 * 4096), ("f32", 32, 8193 * 1024)])
+def test_launches_with_few_resident_workgroups(dtype, P, n):
+    """Sizes from which launches reserve LDS to bound the workgroups per CU (fp32 6144 items from P = 4, bf16
+    3072 from P = 5 and 7680 from P = 8, all-gather 8192 parts from 32 replicas)."""
+    say("case: few resident workgroups, %s, P=%d, %d elements" % (dtype, P, n))
+    pair = Pair(small_workload([n - 77, 77], P, W.NO_LIMIT, dtype))
+    pair.run(iterations=1)
+    pair.close()
