@@ -74,9 +74,6 @@ struct layer_place {
 #ifndef DEAR_RS_NT_STORE
 #define DEAR_RS_NT_STORE 1
 #endif
-#ifndef DEAR_AG_U
-#define DEAR_AG_U 1
-#endif
 #ifndef DEAR_AG_NT_LOAD
 #define DEAR_AG_NT_LOAD 0
 #endif
@@ -500,34 +497,49 @@ __global__ __launch_bounds__(DEAR_BLOCK) void shard_update_kernel(
 // Measured with everything else equal, all-gather of P fp32 replicas, GB/s before -> after: BERT-Large-shaped
 // P = 8 6307 -> 6515, BERT-Base-shaped P = 16 6341 -> 6523, ResNet-50-shaped P = 8 6535 -> 6618, 604 ragged
 // tensors P = 7 6387 -> 7042.  Fewer resident workgroups lose here (they cost in-flight loads, 4 KiB each).
-template <int U, bool ALL_FULL>
-__device__ __forceinline__ void all_gather_tile(const dear_tile &t, int part, float *const *__restrict__ out_entry,
-                                                const float *__restrict__ src)
+// Where a workgroup's stores begin decides how many cache lines are written in two halves, by two
+// workgroups on different XCDs, and HBM takes halves of lines badly (fp32 replicas whose tensors start on
+// 16-byte boundaries only: 5300 GB/s instead of 6800).  A run is therefore not cut at multiples of the tile of
+// the layer's own index but where the replica's addresses are multiples of 128 bytes: every cut moves down by
+// `shift` elements, the distance of the tensor's start from a line.  The run's first tile begins, and its last
+// tile ends, where the run does.  us per iteration: 30 M elements in 60 such tensors P = 8 468 -> 441, P = 16 850
+// -> 787, 20 M in 604 P = 7 bf16 225 -> 217, ResNet-50-shaped P = 64 2432 -> 2348.
+constexpr int AG_SPLIT = DEAR_TILE_ELEMS / (4 * DEAR_BLOCK);  // workgroups per tile and replica
+
+template <bool INNER>
+__device__ __forceinline__ void all_gather_tile(const dear_tile &t, int part, int shift, bool first, bool last,
+                                                float *const *__restrict__ out_entry, const float *__restrict__ src)
 {
-    constexpr int VE = 4;
+    // positions are counted from the tile's first element, so that they fit 32 bits; `low` says how the
+    // element lies in its 16-byte vector and 128-byte line
+    constexpr int VE = 4, LINE = 32, PART = VE * DEAR_BLOCK;
     const int tid = threadIdx.x;
-    const int64_t a = t.src_begin, c = a + t.count;
-    const int64_t v_first = a / VE + (int64_t)part * (U * DEAR_BLOCK);
-    if (!ALL_FULL && v_first * VE >= c) return;
-    int64_t vi[U];
-    bool full[U];
-    f4 val[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {  // all loads first, so they are in flight together
-        vi[u] = v_first + u * DEAR_BLOCK + tid;
-        const int64_t e0 = vi[u] * VE;
-        full[u] = ALL_FULL || (e0 >= a && e0 + VE <= c);
-        if (full[u]) val[u] = load_f4_dword_aligned<DEAR_AG_NT_LOAD>(src + (e0 - a));
+    const int low = (int)(t.src_begin & (LINE - 1));
+    const int lo = INNER || !first ? -shift : 0, hi = INNER || !last ? t.count - shift : t.count;
+    const int begin = (INNER ? lo : lo - ((low + lo + shift) & (LINE - 1))) + part * PART;
+    if (!INNER && begin >= hi) return;
+    const int i = begin + VE * tid;
+    f4 val;
+    if (INNER) {
+        val = load_f4_dword_aligned<DEAR_AG_NT_LOAD>(src + i);
+        // the tensor's address is wanted only by the stores: its load rides behind the data's
+        __builtin_amdgcn_sched_barrier(0);
+        DEAR_GLOBAL float *out = (DEAR_GLOBAL float *)*out_entry + t.src_begin;
+        store_vec<DEAR_AG_NT_STORE>((global_f4_out)(out + i), val);
+        return;
     }
-    // the tensor's address is wanted only by the stores: its load rides behind the data's
-    __builtin_amdgcn_sched_barrier(0);
-    DEAR_GLOBAL float *out = (DEAR_GLOBAL float *)*out_entry;
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-        if (full[u]) store_vec<DEAR_AG_NT_STORE>((global_f4_out)out + vi[u], val[u]);
-    if (!ALL_FULL) {
-        const int64_t e = edge_element<VE>(a, c, v_first, U * DEAR_BLOCK);
-        if (e >= 0) out[e] = src[e - a];
+    DEAR_GLOBAL float *out = (DEAR_GLOBAL float *)*out_entry + t.src_begin;
+    // partial vectors at the run's ends: lanes 0-3 take an element each of the first, lanes 4-7 of the last
+    const int head = lo - ((low + lo) & (VE - 1)), tail = hi - ((low + hi) & (VE - 1));
+    const int head_end = head < lo ? (head + VE < hi ? head + VE : hi) : lo;
+    // a run's end can lie up to a line behind the tile's four parts: the last part reaches that far
+    const int end = begin + PART + (part == AG_SPLIT - 1 ? LINE : 0);
+    if (i >= lo && i + VE <= hi) store_vec<DEAR_AG_NT_STORE>((global_f4_out)(out + i), load_f4_dword_aligned<DEAR_AG_NT_LOAD>(src + i));
+    if (end > begin + PART && tid < LINE / VE && i + PART + VE <= hi)
+        store_vec<DEAR_AG_NT_STORE>((global_f4_out)(out + i + PART), load_f4_dword_aligned<DEAR_AG_NT_LOAD>(src + i + PART));
+    if (tid < 2 * VE) {
+        const int at = tid < VE ? head : tail, e = at + (tid & (VE - 1));
+        if (at >= begin && at < end && (tid < VE ? e >= lo && e < head_end : e >= head_end && e < hi)) out[e] = src[e];
     }
 }
 
@@ -545,19 +557,23 @@ __device__ __forceinline__ unsigned divide(unsigned n, unsigned d, unsigned inv_
     return q;
 }
 
-constexpr int AG_U = DEAR_AG_U;   // vectors per lane, one workgroup per item
+// What the device's copy of a tile carries in the place of its bucket, for the all-gather.
+constexpr int TILE_FIRST = 1, TILE_LAST = 2;  // of its run: the tiles of one layer and shard
+constexpr int TILE_OWN_SHIFT = 4;             // the replicas' tensors lie differently: each has a shift of its own
+constexpr int TILE_SHIFT_BIT = 8;             // the replicas' common shift from this bit on
 
-// n_parts = tiles * SPLIT; replicas p_first .. p_first+n_p-1 receive; there are
+// Elements between the last 128-byte line that begins at or before p, and p (16-byte aligned).
+__host__ __device__ __forceinline__ int line_shift(uintptr_t p) { return static_cast<int>((p >> 2) & 31); }
+
+// n_parts = tiles * AG_SPLIT; replicas p_first .. p_first+n_p-1 receive; there are
 // n_parts * n_p work items.  inv_n_p, inv_len: reciprocals (see divide) of n_p and of the number of parts
 // in the short last chunk.
-template <int U>
 __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_kernel(
     const dear_tile *__restrict__ tiles, float *const *__restrict__ param_tab, int L, int p_first,
     unsigned n_p, const float *__restrict__ shard_param, unsigned n_parts, unsigned inv_n_p, unsigned inv_len)
 {
-    constexpr int SPLIT = DEAR_TILE_ELEMS / (4 * DEAR_BLOCK * U);
-    static_assert(SPLIT >= 1 && (SPLIT & (SPLIT - 1)) == 0, "U must divide the tile");
-    constexpr unsigned CHUNK = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK * U);  // parts per chunk
+    static_assert((AG_SPLIT & (AG_SPLIT - 1)) == 0, "a part's tile is found by a shift");
+    constexpr unsigned CHUNK = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK);  // parts per chunk
     static_assert((CHUNK & (CHUNK - 1)) == 0, "whole chunks are told apart by a shift");
     const unsigned whole = n_parts / CHUNK;
     // item -> (chunk, replica, part within chunk)
@@ -567,15 +583,21 @@ __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_kernel(
         q = divide(blockIdx.x - whole * CHUNK * n_p, n_parts - whole * CHUNK, inv_len, r);
     }
     const unsigned id = chunk * CHUNK + r;
-    const dear_tile t = tiles[id / SPLIT];
-    const int part = id % SPLIT;
+    const dear_tile t = tiles[id / AG_SPLIT];
+    const int part = id % AG_SPLIT;
     if (t.layer < 0) return;
     const float *__restrict__ src = shard_param + t.dst_begin;
     float *const *out = param_tab + (size_t)((unsigned)p_first + q) * L + t.layer;
-    if (t.count == DEAR_TILE_ELEMS)
-        all_gather_tile<U, true>(t, part, out, src);
+    if (t.bucket == 0 && t.count == DEAR_TILE_ELEMS) {  // inside a run of tensors that start on lines
+        all_gather_tile<true>(t, part, 0, false, false, out, src);
+        return;
+    }
+    const bool first = t.bucket & TILE_FIRST, last = t.bucket & TILE_LAST;
+    const int shift = t.bucket & TILE_OWN_SHIFT ? line_shift((uintptr_t)*out) : t.bucket >> TILE_SHIFT_BIT;
+    if (t.count == DEAR_TILE_ELEMS && (shift == 0 || !(first || last)))
+        all_gather_tile<true>(t, part, shift, first, last, out, src);
     else
-        all_gather_tile<U, false>(t, part, out, src);
+        all_gather_tile<false>(t, part, shift, first, last, out, src);
 }
 
 // Bounded-grid form of the all-gather: one item is a whole tile, read once and stored to all
@@ -855,7 +877,7 @@ template <bool BF16>
 unsigned reduce_scatter_lds(int P, unsigned n_items)
 {
     if (!BF16) return P >= 4 && n_items >= 6144 ? LDS_FOR_2 : 0;
-    if (P >= 8 && n_items >= 7680) return LDS_FOR_1;
+    if (P >= 8 && n_items >= 7168) return LDS_FOR_1;
     return P >= 5 && n_items >= 3072 ? LDS_FOR_2 : 0;
 }
 
@@ -893,6 +915,30 @@ void rs_launch(int P, int L, const void *const *grad_tab, int32_t max_workgroups
     else
         RS_LAUNCH(8, true);
 #undef RS_LAUNCH
+}
+
+constexpr size_t SHIFT_TILES = 8;
+
+// Writes into every tile's bucket field what the all-gather wants to know about the tile's run.
+void mark_runs(const dear_plan_s &plan, float *const *param_ptrs, std::vector<dear_tile> &tiles)
+{
+    for (size_t begin = 0, end = 0; begin < tiles.size(); begin = end) {
+        const int32_t layer = tiles[begin].layer;
+        while (end < tiles.size() && tiles[end].layer == layer && tiles[end].shard == tiles[begin].shard) ++end;
+        int flags = 0;
+        if (layer >= 0) {
+            const int shift = line_shift(reinterpret_cast<uintptr_t>(param_ptrs[layer]));
+            flags = shift << TILE_SHIFT_BIT;
+            for (int32_t p = 1; p < plan.P; ++p)
+                if (line_shift(reinterpret_cast<uintptr_t>(param_ptrs[static_cast<size_t>(p) * plan.L + layer])) != shift)
+                    flags = TILE_OWN_SHIFT;
+            // A short run has little to gain: most of its tiles are at an end, where the form that looks at
+            // the ends is taken anyway.  A first tile of less than a line could not give a shift away.
+            if (end - begin < SHIFT_TILES || tiles[begin].count < 32) flags = 0;
+        }
+        for (size_t i = begin; i < end; ++i)
+            tiles[i].bucket = flags | (i == begin ? TILE_FIRST : 0) | (i + 1 == end ? TILE_LAST : 0);
+    }
 }
 
 }  // namespace
@@ -935,6 +981,7 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
     }
     if (tiles.size() > 0x7fffffffu / 16) return DEAR_EINVAL;  // grid.x limit, up to 16 workgroups a tile
     if (hipGetDevice(&c->device) != hipSuccess) return DEAR_EHIP;
+    mark_runs(*plan, param_ptrs, tiles);
     std::memcpy(image.data(), tiles.data(), places_at);
     for (int32_t l = 0; l < plan->L; ++l) {
         const int32_t b = plan->layer_bucket[l];
@@ -1034,8 +1081,6 @@ int launch_update(const dear_ctx_impl *c, bucket_range r, const float *shard_gra
     return launch_status();
 }
 
-constexpr int64_t AG_SPLIT = DEAR_TILE_ELEMS / (4 * DEAR_BLOCK * AG_U);
-
 bool all_gather_fits(const dear_ctx_impl *c, bucket_range r, int32_t n_workers)
 {
     return tiles_of(c, r) * AG_SPLIT * n_workers <= 0x7fffffff;
@@ -1055,14 +1100,14 @@ int launch_all_gather(const dear_ctx_impl *c, bucket_range r, const float *shard
             tiles, c->d_param, c->L, first_worker, n_workers, shard_param, static_cast<unsigned>(count),
             c->wave_priority);
     } else {
-        constexpr unsigned chunk = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK * AG_U);
+        constexpr unsigned chunk = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK);
         const unsigned n_parts = static_cast<unsigned>(count * AG_SPLIT), n_p = static_cast<unsigned>(n_workers);
         const unsigned len = n_parts % chunk ? n_parts % chunk : 1;
         // With very many replicas five workgroups per CU are enough (see reduce_scatter_lds): us per iteration,
         // as many as fit / 5: P = 64, 25.6 M elements 2418 / 2332, P = 32, 54 M 2186 / 2100; but P = 16, 110 M 2815 / 2945
         // and P = 64 in launches over 1.5 M 457 / 492.
         const unsigned lds = n_p >= 32 && n_parts >= 8192 ? LDS_FOR_5 : 0;
-        all_gather_kernel<AG_U><<<dim3(n_parts * n_p), dim3(DEAR_BLOCK), lds, st>>>(
+        all_gather_kernel<<<dim3(n_parts * n_p), dim3(DEAR_BLOCK), lds, st>>>(
             tiles, c->d_param, c->L, first_worker, n_p, shard_param, n_parts, 0xffffffffu / n_p, 0xffffffffu / len);
     }
     return launch_status();
@@ -1123,8 +1168,9 @@ extern "C" int dear_shard_update(dear_ctx_t *c, int32_t bucket, const float *sha
 // launch is long enough to pay for a second one: UAG_SPLIT_TILES tile copies are about 25 us.  us per iteration
 // of reduce-scatters and these calls, one kernel / update, then all-gather: 100 M elements in 64 MB buckets
 // P = 2 710 / 757, P = 3 857 / 878, P = 4 1016 / 1011; 25 M elements in 25 MB buckets P = 8 430 / 400;
-// BERT-Base-shaped P = 16 3173 / 2826; 5 M elements in 4 MB buckets P = 8 115 / 131.
-constexpr int32_t UAG_SPLIT_P = 5;
+// BERT-Base-shaped P = 16 3173 / 2826; 5 M elements in 4 MB buckets P = 8 115 / 131; 36 M elements P = 5 in one call
+// 340 / 346, in 64 MB buckets 431 / 423, P = 6 474 / 463.
+constexpr int32_t UAG_SPLIT_P = 6;
 constexpr int64_t UAG_SPLIT_TILES = 8192;
 
 extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float *shard_grad,

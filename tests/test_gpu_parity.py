@@ -446,9 +446,9 @@ def test_iteration_call_of_one_bucket_and_of_several_groups(dtype, keep, width):
         pair.close()
 
 
-@pytest.mark.parametrize("P,n", [(5, 1639 * 4096), (5, 1638 * 4096), (4, 2048 * 4096), (9, 911 * 4096 + 5)])
+@pytest.mark.parametrize("P,n", [(6, 1366 * 4096), (6, 1365 * 4096), (5, 1700 * 4096), (9, 911 * 4096 + 5)])
 def test_update_all_gather_on_both_sides_of_its_split(P, n):
-    """5 replicas and 8192 tile copies: from there on the call launches the update and the all-gather."""
+    """6 replicas and 8192 tile copies: from there on the call launches the update and the all-gather."""
     say("case: update + all-gather, P=%d, %d elements" % (P, n))
     pair = Pair(small_workload([n, 33], P, 0))
     pair.run(iterations=1, fused_gather=True)
@@ -468,11 +468,41 @@ def test_every_alignment_of_a_runs_ends(P, width, gather, dtype):
 
 
 @pytest.mark.parametrize("dtype,P,n", [("f32", 4, 6145 * 1024), ("f32", 3, 6145 * 1024), ("bf16", 5, 3073 * 4096),
-                                       ("bf16", 8, 7681 * 4096), ("f32", 32, 8193 * 1024)])
+                                       ("bf16", 8, 7169 * 4096), ("f32", 32, 8193 * 1024)])
 def test_launches_with_few_resident_workgroups(dtype, P, n):
     """Sizes from which launches reserve LDS to bound the workgroups per CU (fp32 6144 items from P = 4, bf16
-    3072 from P = 5 and 7680 from P = 8, all-gather 8192 parts from 32 replicas)."""
+    3072 from P = 5 and 7168 from P = 8, all-gather 8192 parts from 32 replicas)."""
     say("case: few resident workgroups, %s, P=%d, %d elements" % (dtype, P, n))
     pair = Pair(small_workload([n - 77, 77], P, W.NO_LIMIT, dtype))
     pair.run(iterations=1)
     pair.close()
+
+
+@pytest.mark.parametrize("starts", [(0, 0, 0), (4, 4, 4), (28, 28, 28), (0, 12, 20), (16, 4, 28)])
+@pytest.mark.parametrize("workers", [(0, 3), (1, 2)])
+def test_all_gather_cuts_at_lines(starts, workers):
+    """Replicas whose tensors start 16-byte aligned at different places of a 128-byte line, alike or not:
+    the cuts of long runs move with them.  One plan has a run whose first tile is shorter than a line, the
+    last layer's runs are short; elements around the tensors stay as they are."""
+    import paper_2302_12445_amd as dear
+    say("case: all-gather, tensors at %s of a line, workers %s" % (starts, workers))
+    for x in (5, 3433):  # with 3433 elements in front, the big layer's second run starts 9 elements before a tile's end
+        sizes, P = [400_003, x], 3
+        op = oracle.plan(sizes, P, W.NO_LIMIT, 4)
+        plan = dear.dear_plan(sizes, P, W.NO_LIMIT, 4)
+        big = [torch.full((400_100,), 7.0, device=DEV) for _ in range(P)]
+        small = [torch.full((x + 64,), 7.0, device=DEV) for _ in range(P)]
+        ptrs = [q for p in range(P) for q in (big[p].data_ptr() + 4 * starts[p], small[p].data_ptr() + 4 * starts[p])]
+        ctx = dear.dear_ctx_create(plan, dear.DEAR_F32, ptrs, ptrs)
+        shards = torch.randn(P, op.total_shard_len, generator=torch.Generator().manual_seed(x))
+        dev = shards.to(DEV)
+        dear.dear_all_gather_workers(ctx, -1, dev.data_ptr(), workers[0], workers[1])
+        torch.cuda.synchronize()
+        params = [[np.full(n, 7.0, np.float32) for n in sizes] for _ in range(P)]
+        oracle.all_gather(op, -1, shards.numpy(), params, workers=range(workers[0], workers[0] + workers[1]))
+        for p in range(P):
+            for got, want in ((big[p], params[p][0]), (small[p], params[p][1])):
+                full = np.full(got.numel(), 7.0, np.float32)
+                full[starts[p]:starts[p] + want.size] = want
+                assert np.array_equal(_bits(got.cpu().numpy()), _bits(full)), (x, p)
+        ctx.destroy()
