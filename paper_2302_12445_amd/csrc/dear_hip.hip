@@ -862,7 +862,7 @@ unsigned grid_width(int32_t max_workgroups, int64_t n_items)
 // How many workgroups of a launch are resident on a CU is set by the LDS that the launch reserves for each
 // (nothing uses it): 160 KiB / reservation.  HBM serves many streams at once better the fewer loads compete, as
 // long as some 64 KiB per CU are in flight; too few workgroups cost the more the shorter the launch is.
-constexpr unsigned LDS_FOR_1 = 96 << 10, LDS_FOR_2 = 64 << 10, LDS_FOR_5 = 27 << 10;
+constexpr unsigned LDS_FOR_1 = 96 << 10, LDS_FOR_2 = 64 << 10;
 
 // Reduce-scatter: a workgroup has min(P, 8) * U loads of 4 KiB in flight, 32 KiB in fp32 and 64 KiB in bf16
 // from P = 8 on.  us per iteration, as many workgroups as fit / 2 per CU / 1 per CU:
@@ -872,12 +872,14 @@ constexpr unsigned LDS_FOR_1 = 96 << 10, LDS_FOR_2 = 64 << 10, LDS_FOR_5 = 27 <<
 //   bf16, 60 M elements: P = 4 428 / 428 / 432, P = 8 652 / 646 / 636, P = 32 2078 / 2070 / 2041;
 //         33 M: P = 8 367 / 364 / 361, P = 16 639 / 635 / 618; 20 M: P = 8 207 / 206 / 216; 13 M and 7 M: P = 7
 //         226 / 221 / 234; 4 M: P = 6 40 / 41 / 44; P = 3, 24 M 139 / 144 / -.
-// An item is 1024 elements in fp32 and 4096 in bf16.
-template <bool BF16>
+// An item is 1024 elements in fp32 and 4096 in bf16.  Without the update (no w and v in flight beside the
+// gradients) one per CU is too few at P = 8: reduce-scatter, update and all-gather of 200 M bf16 elements, as many
+// as fit / 1 per CU, P = 8 2485 / 2509, but 60 M P = 32 2173 / 2118; fp32 110 M P = 16 2930 / 2875 with 2.
+template <bool BF16, rs_mode MODE>
 unsigned reduce_scatter_lds(int P, unsigned n_items)
 {
     if (!BF16) return P >= 4 && n_items >= 6144 ? LDS_FOR_2 : 0;
-    if (P >= 8 && n_items >= 7168) return LDS_FOR_1;
+    if (P >= (MODE & RS_UPDATE ? 8 : 16) && n_items >= 7168) return LDS_FOR_1;
     return P >= 5 && n_items >= 3072 ? LDS_FOR_2 : 0;
 }
 
@@ -891,7 +893,7 @@ void rs_launch(int P, int L, const void *const *grad_tab, int32_t max_workgroups
     const unsigned n_items = static_cast<unsigned>(n_tiles * SPLIT);
     const dim3 grid(grid_width(max_workgroups, n_items)), block(DEAR_BLOCK);
     const bool bounded = grid.x < n_items;
-    const unsigned lds = bounded ? 0 : reduce_scatter_lds<BF16>(P, n_items);
+    const unsigned lds = bounded ? 0 : reduce_scatter_lds<BF16, MODE>(P, n_items);
     const float inv_P = 1.0f / static_cast<float>(P);
 #define RS_LAUNCH(CH, TAIL)                                                                              \
     do {                                                                                                 \
@@ -1103,11 +1105,7 @@ int launch_all_gather(const dear_ctx_impl *c, bucket_range r, const float *shard
         constexpr unsigned chunk = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK);
         const unsigned n_parts = static_cast<unsigned>(count * AG_SPLIT), n_p = static_cast<unsigned>(n_workers);
         const unsigned len = n_parts % chunk ? n_parts % chunk : 1;
-        // With very many replicas five workgroups per CU are enough (see reduce_scatter_lds): us per iteration,
-        // as many as fit / 5: P = 64, 25.6 M elements 2418 / 2332, P = 32, 54 M 2186 / 2100; but P = 16, 110 M 2815 / 2945
-        // and P = 64 in launches over 1.5 M 457 / 492.
-        const unsigned lds = n_p >= 32 && n_parts >= 8192 ? LDS_FOR_5 : 0;
-        all_gather_kernel<<<dim3(n_parts * n_p), dim3(DEAR_BLOCK), lds, st>>>(
+        all_gather_kernel<<<dim3(n_parts * n_p), dim3(DEAR_BLOCK), 0, st>>>(
             tiles, c->d_param, c->L, first_worker, n_p, shard_param, n_parts, 0xffffffffu / n_p, 0xffffffffu / len);
     }
     return launch_status();

@@ -471,7 +471,7 @@ def test_every_alignment_of_a_runs_ends(P, width, gather, dtype):
                                        ("bf16", 8, 7169 * 4096), ("f32", 32, 8193 * 1024)])
 def test_launches_with_few_resident_workgroups(dtype, P, n):
     """Sizes from which launches reserve LDS to bound the workgroups per CU (fp32 6144 items from P = 4, bf16
-    3072 from P = 5 and 7168 from P = 8, all-gather 8192 parts from 32 replicas)."""
+    3072 from P = 5 and 7168 from P = 8)."""
     say("case: few resident workgroups, %s, P=%d, %d elements" % (dtype, P, n))
     pair = Pair(small_workload([n - 77, 77], P, W.NO_LIMIT, dtype))
     pair.run(iterations=1)
