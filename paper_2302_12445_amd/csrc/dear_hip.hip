@@ -504,8 +504,6 @@ __global__ __launch_bounds__(DEAR_BLOCK) void shard_update_kernel(
 // `shift` elements, the distance of the tensor's start from a line.  The run's first tile begins, and its last
 // tile ends, where the run does.  us per iteration: 30 M elements in 60 such tensors P = 8 468 -> 441, P = 16 850
 // -> 787, 20 M in 604 P = 7 bf16 225 -> 217, ResNet-50-shaped P = 64 2432 -> 2348.
-constexpr int AG_SPLIT = DEAR_TILE_ELEMS / (4 * DEAR_BLOCK);  // workgroups per tile and replica
-
 template <bool INNER>
 __device__ __forceinline__ void all_gather_tile(const dear_tile &t, int part, int shift, bool first, bool last,
                                                 float *const *__restrict__ out_entry, const float *__restrict__ src)
@@ -1071,7 +1069,7 @@ int launch_update(const dear_ctx_impl *c, bucket_range r, const float *shard_gra
     const int64_t per_block = static_cast<int64_t>(bounded ? UPD_U_BOUNDED : UPD_U) * DEAR_BLOCK;
     const int64_t blocks = (vecs + per_block - 1) / per_block;
     const int64_t n_items = blocks * rows;
-    if (n_items > 0x7fffffff) return DEAR_EINVAL;
+    if (n_items > (bounded ? 0x7fffffff : MAX_GRID)) return DEAR_EINVAL;
     if (bounded)
         shard_update_kernel<UPD_U_BOUNDED, true><<<dim3(c->max_workgroups), dim3(DEAR_BLOCK), 0, st>>>(
             shard_grad, shard_param, shard_mom, c->row_len, base, vecs, lr, momentum,
@@ -1083,20 +1081,14 @@ int launch_update(const dear_ctx_impl *c, bucket_range r, const float *shard_gra
     return launch_status();
 }
 
-bool all_gather_fits(const dear_ctx_impl *c, bucket_range r, int32_t n_workers)
-{
-    return tiles_of(c, r) * AG_SPLIT * n_workers <= 0x7fffffff;
-}
-
 int launch_all_gather(const dear_ctx_impl *c, bucket_range r, const float *shard_param, int32_t first_worker,
                       int32_t n_workers, hipStream_t st)
 {
     const int64_t count = tiles_of(c, r);
     if (count == 0) return DEAR_OK;
-    if (!all_gather_fits(c, r, n_workers)) return DEAR_EINVAL;
+    if (!all_gather_fits(count, n_workers, c->max_workgroups)) return DEAR_EINVAL;
     const dear_tile *tiles = c->d_tiles + c->tile_begin[r.begin];
-    if (c->max_workgroups > 0 && count * AG_SPLIT * n_workers > c->max_workgroups) {
-        // the bounded form strides over whole tiles, so its grid is at most the tile count
+    if (all_gather_bounded(count, n_workers, c->max_workgroups)) {
         const unsigned width = grid_width(c->max_workgroups, count);
         all_gather_bounded_kernel<<<dim3(width), dim3(DEAR_BLOCK), 0, st>>>(
             tiles, c->d_param, c->L, first_worker, n_workers, shard_param, static_cast<unsigned>(count),
@@ -1160,17 +1152,6 @@ extern "C" int dear_shard_update(dear_ctx_t *c, int32_t bucket, const float *sha
                          static_cast<hipStream_t>(hip_stream));
 }
 
-// dear_update_all_gather writes all P replicas from the workgroup that updated: P write streams at once, which
-// HBM sustains worse the more there are (5.4 TB/s at P = 8, against 6.5 replica by replica).  From
-// UAG_SPLIT_P replicas on the 4 bytes per element that one kernel saves are worth less than that, if the
-// launch is long enough to pay for a second one: UAG_SPLIT_TILES tile copies are about 25 us.  us per iteration
-// of reduce-scatters and these calls, one kernel / update, then all-gather: 100 M elements in 64 MB buckets
-// P = 2 710 / 757, P = 3 857 / 878, P = 4 1016 / 1011; 25 M elements in 25 MB buckets P = 8 430 / 400;
-// BERT-Base-shaped P = 16 3173 / 2826; 5 M elements in 4 MB buckets P = 8 115 / 131; 36 M elements P = 5 in one call
-// 340 / 346, in 64 MB buckets 431 / 423, P = 6 474 / 463.
-constexpr int32_t UAG_SPLIT_P = 6;
-constexpr int64_t UAG_SPLIT_TILES = 8192;
-
 extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float *shard_grad,
                                       float *shard_param, float *shard_mom, float lr, float momentum,
                                       void *hip_stream)
@@ -1184,8 +1165,7 @@ extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float
     const dear_tile *tiles = c->d_tiles + c->tile_begin[r.begin];
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const unsigned width = grid_width(c->max_workgroups, count);
-    if (width == count && c->P >= UAG_SPLIT_P && count * c->P >= UAG_SPLIT_TILES &&
-        count * AG_SPLIT * c->P <= 0x3fffffff) {
+    if (update_all_gather_splits(count, c->P, c->max_workgroups)) {
         rc = launch_update(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
         return rc == DEAR_OK ? launch_all_gather(c, r, shard_param, 0, c->P, st) : rc;
     }
@@ -1241,7 +1221,7 @@ extern "C" int dear_iteration(dear_ctx_t *c, int32_t bucket, float *shard_grad, 
     };
     for (bucket_range r{0, all.begin}; r.end < all.end;) {  // nothing is launched unless everything can be
         r = group_from(r.end);
-        if (!all_gather_fits(c, r, c->P)) return DEAR_EINVAL;
+        if (!all_gather_fits(tiles_of(c, r), c->P, c->max_workgroups)) return DEAR_EINVAL;
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     for (bucket_range r{0, all.begin}; rc == DEAR_OK && r.end < all.end;) {

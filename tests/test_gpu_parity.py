@@ -506,3 +506,45 @@ def test_all_gather_cuts_at_lines(starts, workers):
                 full[starts[p]:starts[p] + want.size] = want
                 assert np.array_equal(_bits(got.cpu().numpy()), _bits(full)), (x, p)
         ctx.destroy()
+
+
+def test_calls_beyond_the_largest_all_gather():
+    """From 2^24 workgroups on an all-gather cannot be launched: dear_all_gather and dear_iteration refuse it and
+    leave everything as it was, dear_update_all_gather takes such a call in its one kernel, a bounded grid
+    takes it anyway.  1024 replicas that share their tensors stand for a card full of them."""
+    import paper_2302_12445_amd as dear
+    from paper_2302_12445_amd import binding
+    n, P = 4104 * 4096, 1024
+    say("case: 2^24 workgroups, %d elements, P=%d in one set of tensors" % (n, P))
+    plan, op = dear.dear_plan([n], P, W.NO_LIMIT, 4), oracle.plan([n], P, W.NO_LIMIT, 4)
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    grad, param = torch.zeros(n, device=DEV), torch.full((n,), 7.0, device=DEV)
+    ctx = dear.dear_ctx_create(plan, dear.DEAR_F32, [grad.data_ptr()] * P, [param.data_ptr()] * P)
+    assert 4 * P * len(dear.dear_plan_tiles(plan)[0]) >= 1 << 24
+    g, w, v = (torch.empty(P, op.total_shard_len, device=DEV).normal_(0.0, 1.0, generator=gen) for _ in range(3))
+    ref = [t.cpu().numpy().copy() for t in (g, w, v)]
+    with pytest.raises(dear.DearError) as e:
+        dear.dear_all_gather(ctx, -1, w.data_ptr())
+    assert e.value.status == binding.DEAR_EINVAL
+    with pytest.raises(dear.DearError) as e:
+        dear.dear_iteration(ctx, -1, g.data_ptr(), w.data_ptr(), v.data_ptr(), 0.1, 0.9)
+    assert e.value.status == binding.DEAR_EINVAL
+    torch.cuda.synchronize()
+    for t, r in zip((g, w, v), ref):
+        assert np.array_equal(_bits(t.cpu().numpy()), _bits(r))
+    assert bool((param == 7.0).all())
+
+    dear.dear_update_all_gather(ctx, -1, g.data_ptr(), w.data_ptr(), v.data_ptr(), 0.1, 0.9)
+    torch.cuda.synchronize()
+    oracle.shard_update(op, -1, ref[0], ref[1], ref[2], 0.1, 0.9)
+    host = [[np.zeros(n, np.float32)]] * P
+    oracle.all_gather(op, -1, ref[1], host, workers=range(0, 1))
+    assert np.array_equal(_bits(w.cpu().numpy()), _bits(ref[1])) and np.array_equal(_bits(v.cpu().numpy()), _bits(ref[2]))
+    assert np.array_equal(_bits(param.cpu().numpy()), _bits(host[0][0]))
+
+    param.fill_(7.0)
+    dear.dear_ctx_set_max_workgroups(ctx, 256)
+    dear.dear_all_gather(ctx, -1, w.data_ptr())
+    torch.cuda.synchronize()
+    assert np.array_equal(_bits(param.cpu().numpy()), _bits(host[0][0]))
+    ctx.destroy()

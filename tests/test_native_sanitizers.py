@@ -43,3 +43,14 @@ def test_oracle_under_sanitizers(tmp_path):
           os.path.join(ROOT, "oracle", "dear_oracle.c"), "-o", exe])
     out = _run([exe], env=ENV)
     assert "ok" in out.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_launch_rules(tmp_path):
+    """The functions that choose a call's launches by its sizes, at their limits: no rule chooses a grid that
+    HIP does not take."""
+    exe = str(tmp_path / "launch_rules")
+    _run(["g++", "-std=c++17", *SAN, "-I", os.path.join(ROOT, "include"),
+          "-I", os.path.join(ROOT, "paper_2302_12445_amd", "csrc"),
+          os.path.join(ROOT, "tests", "native", "launch_rules.cpp"), "-o", exe])
+    assert "launch_rules: ok" in _run([exe], env=ENV).stdout
