@@ -22,7 +22,8 @@ Extra objects on the line:
   iteration_call  the whole pass in one library call
   cpu_baseline  the CPU oracle as it stands, timed on this host on the same workload (one
                 iteration, all buckets unless --sample-buckets says fewer; a baseline, not a
-                target); its output is also compared bit for bit with the GPU's first iteration
+                target); its output is also compared bit for bit with the GPU's first iteration,
+                which makes the launches that are timed
 
 --launch: per_bucket (default, the DeAR launch granularity), all_buckets (one launch per
 phase), graph (the per-bucket launches recorded once into a HIP graph and replayed).
@@ -104,8 +105,8 @@ def fill_inputs(em, w, device):
 
 class CpuBaseline:
     """The oracle on a bounded sample of the workload (the first n_buckets buckets, all P
-    replicas): snapshot() copies the sample's inputs to the host and runs the GPU's first
-    iteration, keeping its results; run() times the oracle (single thread, as it stands, and
+    replicas): snapshot(step) copies the sample's inputs to the host and runs the GPU's first
+    iteration with the benchmark's own step, keeping its results; run() times the oracle (single thread, as it stands, and
     split over host threads) after the GPU timing is done and compares the two."""
 
     def __init__(self, em, w, n_buckets):
@@ -124,7 +125,7 @@ class CpuBaseline:
         t = t.cpu().contiguous()
         return t.view(torch.int16).numpy().view(np.uint16) if t.dtype == torch.bfloat16 else t.numpy()
 
-    def snapshot(self):
+    def snapshot(self, step):
         em, w, op = self.em, self.w, self.op
         self.grads = [[None] * w.n_layers for _ in range(w.P)]
         self.params = [[None] * w.n_layers for _ in range(w.P)]
@@ -133,7 +134,7 @@ class CpuBaseline:
                 self.grads[p][l] = self.host(em.grads[p][l])
                 self.params[p][l] = self.host(em.params[p][l]).copy()
         # GPU: first iteration from the same state; keep what will be compared
-        em.iteration(w.lr, w.momentum, per_bucket=True)
+        step()
         torch.cuda.synchronize()
         self.gpu_shards = {}
         for b in self.buckets:
@@ -236,19 +237,6 @@ def main():
     mode = args.launch
     per_bucket = mode != "all_buckets"
 
-    baseline = None
-    if not args.no_cpu_baseline:
-        baseline = CpuBaseline(em, w, args.sample_buckets)
-        baseline.snapshot()
-
-    if args.pmc_calibration:
-        src = torch.ones(1 << 28, dtype=torch.float32, device=device)
-        dst = torch.empty_like(src)
-        for _ in range(3):
-            dst.copy_(src)
-        torch.cuda.synchronize()
-        del src, dst
-
     graph = None
     if mode == "graph":
         graph = torch.cuda.CUDAGraph()
@@ -288,6 +276,19 @@ def main():
             em.all_gather(-1)
         if marks:
             marks[3].record()
+
+    baseline = None
+    if not args.no_cpu_baseline:
+        baseline = CpuBaseline(em, w, args.sample_buckets)
+        baseline.snapshot(step)
+
+    if args.pmc_calibration:
+        src = torch.ones(1 << 28, dtype=torch.float32, device=device)
+        dst = torch.empty_like(src)
+        for _ in range(3):
+            dst.copy_(src)
+        torch.cuda.synchronize()
+        del src, dst
 
     for _ in range(args.warmup):
         step()

@@ -54,3 +54,24 @@ def bf16_ulp(x: np.ndarray) -> np.ndarray:
     ax = np.abs(x.astype(np.float64))
     ax = np.maximum(ax, 2.0 ** -126)
     return 2.0 ** (np.floor(np.log2(ax)) - 7)
+
+
+def separate_calls(em, lr: float, momentum: float, per_bucket: bool = True, fused: bool = False,
+                   fused_gather: bool = False, stream=None) -> None:
+    """One pass with the library's calls of a phase each: reduce-scatters, updates, all-gathers, bucket by bucket
+    or (per_bucket False) one call over all buckets; fused: reduce-scatter and update in one call;
+    fused_gather: update and all-gather in one call.  (EmulatedWorkers.iteration is one library call.)"""
+    buckets = list(range(em.plan.n_buckets)) if per_bucket else [-1]
+    for b in buckets:
+        if fused:
+            em.reduce_scatter_update(b, lr, momentum, stream)
+        else:
+            em.reduce_scatter(b, stream)
+    if not fused and not fused_gather:
+        for b in buckets:
+            em.shard_update(b, lr, momentum, stream)
+    for b in reversed(buckets):
+        if fused_gather:
+            em.update_all_gather(b, lr, momentum, stream)
+        else:
+            em.all_gather(b, stream)

@@ -1,7 +1,7 @@
-"""GPU parity at the benchmark's full sizes, in the launch configuration bench.py times
-(one launch per bucket and phase): whole sampled buckets / shards are recomputed by the
-oracle and compared bit for bit, and properties that hold at any size are checked over
-everything (all replicas identical after the all-gather, padding slots +0)."""
+"""GPU parity at the benchmark's full sizes, in the launch configurations bench.py times (one launch
+per bucket and phase, one per phase, the whole pass in one call): whole sampled buckets / shards are
+recomputed by the oracle and compared bit for bit, and properties that hold at any size are checked
+over everything (all replicas identical after the all-gather, padding slots +0)."""
 from __future__ import annotations
 
 import numpy as np
@@ -10,6 +10,7 @@ import torch
 
 import oracle
 import workloads as W
+from helpers import separate_calls
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -30,6 +31,15 @@ def _fill(em, w):
     torch.cuda.synchronize()
 
 
+def _pass(em, w, route):
+    """route: "per_bucket" and "all_buckets" as bench.py's --launch, "iteration" its iteration_call."""
+    if route == "iteration":
+        em.iteration(w.lr, w.momentum)
+    else:
+        separate_calls(em, w.lr, w.momentum, per_bucket=(route == "per_bucket"))
+    torch.cuda.synchronize()
+
+
 def _bucket_layers(op, b):
     first = int(op.bucket_first_layer[b])
     return list(range(first, first + int(op.bucket_n_layers[b])))
@@ -46,15 +56,16 @@ def _check_replicas_and_pads(em, op, w):
         assert bool((flat.view(torch.int32) == 0).all())
 
 
-@pytest.mark.parametrize("name,n_buckets,sample,per_bucket", [
-    ("bert_large", 11, [0, 5, 10], True),   # P = 8, bf16 gradients, 64 MB; bucket 10 = word embedding alone
-    ("bert_base", 7, [0, 3, 6], True),      # P = 16, fp32 gradients, 64 MB; bucket 6 = the oversized embedding
-    ("bert_large", 11, [1, 9], False),      # one launch per phase over all buckets (bench.py --launch all_buckets)
+@pytest.mark.parametrize("name,n_buckets,sample,route", [
+    ("bert_large", 11, [0, 5, 10], "per_bucket"),   # P = 8, bf16 gradients, 64 MB; bucket 10 = word embedding alone
+    ("bert_base", 7, [0, 3, 6], "per_bucket"),      # P = 16, fp32 gradients, 64 MB; bucket 6 = the oversized embedding
+    ("bert_large", 11, [1, 9], "all_buckets"),      # one launch per phase over all buckets
+    ("bert_large", 11, [2, 8, 10], "iteration"),
+    ("bert_base", 7, [1, 5, 6], "iteration"),
 ])
-def test_full_size_sampled_buckets(name, n_buckets, sample, per_bucket):
+def test_full_size_sampled_buckets(name, n_buckets, sample, route):
     from paper_2302_12445_amd.emulation import EmulatedWorkers
-    print("case: %s full size, buckets %s recomputed by the oracle, %s" % (
-        name, sample, "one launch per bucket" if per_bucket else "one launch per phase"), flush=True)
+    print("case: %s full size, buckets %s recomputed by the oracle, %s" % (name, sample, route), flush=True)
     w = W.get_workload(name)
     em = EmulatedWorkers(w.sizes, w.P, w.grad_dtype, w.threshold_bytes, DEV)
     op = oracle.plan(w.sizes, w.P, w.threshold_bytes, w.grad_elem_bytes)
@@ -77,8 +88,7 @@ def test_full_size_sampled_buckets(name, n_buckets, sample, per_bucket):
         oracle.scatter_params(op, params, 0, sp, bucket=b)
 
     em.shard_grad.fill_(float("nan"))
-    em.iteration(w.lr, w.momentum, per_bucket=per_bucket)
-    torch.cuda.synchronize()
+    _pass(em, w, route)
 
     for b in sample:
         oracle.reduce_scatter(op, b, grads, sg)
@@ -96,12 +106,13 @@ def test_full_size_sampled_buckets(name, n_buckets, sample, per_bucket):
     em.close()
 
 
+@pytest.mark.parametrize("route", ["per_bucket", "iteration"])
 @pytest.mark.parametrize("name,buckets", [("stress_16mb", [0, 24, 25]), ("stress_single", [0])])
-def test_scale_stress_sampled_shards(name, buckets):
+def test_scale_stress_sampled_shards(name, buckets, route):
     """P = 64 replicas at BERT-Base shape (28 GB of gradients resident).  The oracle recomputes
     single shards (first, a middle one, last) of the sampled buckets."""
     from paper_2302_12445_amd.emulation import EmulatedWorkers
-    print("case:", name, "sampled shards", flush=True)
+    print("case:", name, "sampled shards", route, flush=True)
     w = W.get_workload(name)
     em = EmulatedWorkers(w.sizes, w.P, w.grad_dtype, w.threshold_bytes, DEV)
     op = oracle.plan(w.sizes, w.P, w.threshold_bytes, w.grad_elem_bytes)
@@ -125,8 +136,7 @@ def test_scale_stress_sampled_shards(name, buckets):
             samples.append((b, s, lo, hi, need))
 
     em.shard_grad.fill_(float("nan"))
-    em.iteration(w.lr, w.momentum, per_bucket=True)
-    torch.cuda.synchronize()
+    _pass(em, w, route)
 
     sg = np.zeros((w.P, row), np.float32)
     sm = np.zeros_like(sg)
@@ -181,8 +191,7 @@ def test_scale_stress_one_bucket_every_shard_and_full_replicas():
     for p in (0, w.P - 1):
         for l in layers:
             em.params[p][l].fill_(float("nan"))
-    em.iteration(w.lr, w.momentum, per_bucket=True)
-    torch.cuda.synchronize()
+    _pass(em, w, "per_bucket")
 
     oracle.reduce_scatter(op, b, grads, sg)
     oracle.shard_update(op, b, sg, sp, sm, w.lr, w.momentum)

@@ -14,7 +14,7 @@ import torch
 
 import oracle
 import workloads as W
-from helpers import bf16_ulp, small_workload, split_np, to_numpy
+from helpers import bf16_ulp, separate_calls, small_workload, split_np, to_numpy
 
 pytestmark = pytest.mark.gpu
 
@@ -92,7 +92,10 @@ class Pair:
         oracle.all_gather(self.op, -1, self.sp, self.params)
 
     def run(self, iterations=3, per_bucket=True, poison=True, stream=None, fused=False, width=0, priority=0,
-            fused_gather=False):
+            fused_gather=False, route="calls"):
+        """route "calls": the library's separate calls, as per_bucket, fused and fused_gather say;
+        "iteration": EmulatedWorkers.iteration, one library call that chooses its own launches."""
+        assert route in ("calls", "iteration")
         w, em = self.w, self.em
         em.set_max_workgroups(width)
         em.set_wave_priority(priority)
@@ -105,8 +108,11 @@ class Pair:
                     for t in em.params[p]:
                         t.fill_(float("nan"))
             torch.cuda.synchronize()
-            em.iteration(w.lr, w.momentum, per_bucket=per_bucket, stream=stream, fused_update=fused,
-                         fused_gather=fused_gather)
+            if route == "calls":
+                separate_calls(em, w.lr, w.momentum, per_bucket, fused, fused_gather, stream)
+            else:
+                em.iteration(w.lr, w.momentum, per_bucket=per_bucket, stream=stream, fused_update=fused,
+                             fused_gather=fused_gather)
             torch.cuda.synchronize()
             self.oracle_iteration()
             if not fused:  # the fused kernel never writes the averaged gradient
@@ -122,11 +128,12 @@ class Pair:
 RAGGED = [4097, 3, 8191, 4096, 1, 12289, 7, 30001, 64, 513]
 
 
-def test_tiny_config_three_iterations():
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_tiny_config_three_iterations(route):
     say("case: tiny config, per-bucket launches")
     pr = Pair(W.get_workload("tiny"))
     assert pr.em.plan.n_buckets == 5
-    pr.run(3, per_bucket=True)
+    pr.run(3, per_bucket=True, route=route)
     pr.close()
 
 
@@ -139,80 +146,87 @@ def test_tiny_config_all_buckets_in_one_launch():
 
 @pytest.mark.parametrize("P", [1, 2, 3, 4, 5, 8, 9, 12, 16, 24, 64])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_ragged_layers_all_worker_counts(P, dtype):
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_ragged_layers_all_worker_counts(P, dtype, route):
     say("case: ragged layers P=%d %s" % (P, dtype))
     g = 4 if dtype == "f32" else 2
     w = small_workload(RAGGED, P, 21000 * g, dtype, index=10 + P)
     pr = Pair(w)
     assert pr.em.plan.n_buckets >= 3
-    pr.run(2 if P > 16 else 3, per_bucket=(P % 2 == 0))
+    pr.run(2 if P > 16 else 3, per_bucket=(P % 2 == 0), route=route)
     pr.close()
 
 
 @pytest.mark.parametrize("P", [1, 2, 3, 4, 8, 9, 12, 64])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_fused_reduce_scatter_update(P, dtype):
-    """dear_reduce_scatter_update must leave the same bits in the parameter and momentum
-    shards as dear_reduce_scatter followed by dear_shard_update (both compared with the oracle)."""
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_fused_reduce_scatter_update(P, dtype, route):
+    """dear_reduce_scatter_update, and dear_iteration without a gradient buffer, must leave the same bits in the
+    parameter and momentum shards as dear_reduce_scatter followed by dear_shard_update (both compared with the oracle)."""
     say("case: fused RS+update P=%d %s" % (P, dtype))
     g = 4 if dtype == "f32" else 2
     w = small_workload(RAGGED + [70001, 2], P, 36000 * g, dtype, index=110 + P)
     pr = Pair(w)
-    pr.run(3, per_bucket=(P % 2 == 1), fused=True)
+    pr.run(3, per_bucket=(P % 2 == 1), fused=True, route=route)
     pr.close()
 
 
 @pytest.mark.parametrize("width", [1, 3, 64, 256])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_bounded_grid_gives_the_same_bits(width, dtype):
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_bounded_grid_gives_the_same_bits(width, dtype, route):
     """A bounded grid (workgroups striding over the work items) is only a launch shape."""
     say("case: bounded grid width=%d %s" % (width, dtype))
     g = 4 if dtype == "f32" else 2
     w = small_workload(RAGGED + [300_001], 4, 40000 * g, dtype, index=120 + width)
     pr = Pair(w)
-    pr.run(2, per_bucket=(width != 3), fused=(width == 64), width=width, priority=width % 4)
+    pr.run(2, per_bucket=(width != 3), fused=(width == 64), width=width, priority=width % 4, route=route)
     pr.close()
 
 
-def test_fused_tiny_and_many_tiles():
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_fused_tiny_and_many_tiles(route):
     say("case: fused RS+update, tiny config and many tiles")
     pr = Pair(W.get_workload("tiny"))
-    pr.run(3, fused=True)
+    pr.run(3, fused=True, route=route)
     pr.close()
     w = small_workload([1_000_003, 5, 65_537, 250_001, 2], 8, 1_100_000 * 2, "bf16", index=42, std=1e-3)
     pr = Pair(w)
-    pr.run(2, fused=True)
+    pr.run(2, fused=True, route=route)
     pr.close()
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_single_bucket_and_no_fusion(dtype):
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_single_bucket_and_no_fusion(dtype, route):
     g = 4 if dtype == "f32" else 2
     for thr in (W.NO_LIMIT, 0):
         say("case: threshold %d %s" % (thr, dtype))
         w = small_workload(RAGGED, 4, thr, dtype, index=31)
         pr = Pair(w)
         assert pr.em.plan.n_buckets == (1 if thr else len(RAGGED))
-        pr.run(2)
+        pr.run(2, route=route)
         pr.close()
     del g
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_many_tiles_per_shard(dtype):
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_many_tiles_per_shard(dtype, route):
     """Several hundred tiles per shard, layer starts that are odd in the bucket, a layer
     spanning several shards."""
     say("case: many tiles %s" % dtype)
     g = 4 if dtype == "f32" else 2
     w = small_workload([1_000_003, 5, 65_537, 250_001, 2], 8, 1_100_000 * g, dtype, index=41, std=1e-3)
     pr = Pair(w)
-    pr.run(2)
+    pr.run(2, route=route)
     pr.close()
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("layers_per_bucket", [4, 3])
-def test_fixed_layers_plan(dtype, layers_per_bucket):
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_fixed_layers_plan(dtype, layers_per_bucket, route):
     """The fixed-number-of-layers grouping of the tensor-fusion study (Section VI-G) drives the
     same kernels: the library's plan and the oracle's own fixed-layers plan, bit for bit over
     the shards of every worker and the parameters of every replica, three iterations."""
@@ -224,8 +238,8 @@ def test_fixed_layers_plan(dtype, layers_per_bucket):
     op = oracle.plan_fixed_layers(w.sizes, w.P, layers_per_bucket, g)
     assert plan.n_buckets == op.n_buckets == -(-len(RAGGED) // layers_per_bucket)
     pr = Pair(w, plan=plan, oracle_plan=op)
-    pr.run(3)
-    pr.run(1, fused=True)
+    pr.run(3, route=route)
+    pr.run(1, fused=True, route=route)
     pr.close()
 
 
@@ -326,6 +340,7 @@ def test_side_stream_and_argument_errors():
     pr = Pair(w)
     side = torch.cuda.Stream()
     pr.run(2, stream=side)
+    pr.run(1, stream=side, route="iteration")
     em = pr.em
     lib = dear.load_library()
     h = em.ctx.handle
@@ -347,22 +362,24 @@ def test_side_stream_and_argument_errors():
     pr.close()
 
 
-def test_resnet50_config_one_iteration():
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_resnet50_config_one_iteration(route):
     """Config 2 at full size: 161 tensors, 5 buckets of up to 76 small tensors, P = 8."""
     say("case: resnet50 full size")
     pr = Pair(W.get_workload("resnet50"))
     assert pr.em.plan.n_buckets == 5
-    pr.run(1)
+    pr.run(1, route=route)
     pr.close()
 
 
 @pytest.mark.parametrize("name", ["densenet201", "inception_v4"])
-def test_many_small_tensors_full_size(name):
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_many_small_tensors_full_size(name, route):
     """The paper's other two CNNs at full size: 604 / 449 tensors, hundreds of them a few
     hundred elements long, so most tiles are short runs and edge vectors."""
     say("case: %s full size" % name)
     pr = Pair(W.get_workload(name))
-    pr.run(1, fused=(name == "inception_v4"))
+    pr.run(1, fused=(name == "inception_v4"), route=route)
     pr.close()
 
 
@@ -385,10 +402,11 @@ def test_random_configurations():
         fused = bool(rng.random() < 0.5)
         per_bucket = bool(rng.random() < 0.5)
         layout = str(rng.choice(["flat", "separate"]))
-        say("case: random %d sizes=%s P=%d %s thr=%d width=%d fused=%d per_bucket=%d %s" % (
-            case, sizes, P, dtype, thr, width, fused, per_bucket, layout))
+        route = ["calls", "iteration"][case % 2]
+        say("case: random %d sizes=%s P=%d %s thr=%d width=%d fused=%d per_bucket=%d %s %s" % (
+            case, sizes, P, dtype, thr, width, fused, per_bucket, layout, route))
         pr = Pair(small_workload(sizes, P, thr, dtype, index=1000 + case), layout=layout)
-        pr.run(2, per_bucket=per_bucket, fused=fused, width=width, priority=case % 4)
+        pr.run(2, per_bucket=per_bucket, fused=fused, width=width, priority=case // 2 % 4, route=route)
         pr.close()
 
 
@@ -464,17 +482,21 @@ def test_every_alignment_of_a_runs_ends(P, width, gather, dtype):
     sizes = list(range(1, 19)) + [4096 + k for k in range(9)] + [1024 * k + k for k in range(1, 8)] + [2047, 2049, 3]
     pair = Pair(small_workload(sizes, P, 40_000, dtype))
     pair.run(iterations=2, width=width, fused_gather=gather)
+    if not gather:
+        pair.run(iterations=1, width=width, fused=True)
+        pair.run(iterations=1, width=width, route="iteration")
     pair.close()
 
 
 @pytest.mark.parametrize("dtype,P,n", [("f32", 4, 6145 * 1024), ("f32", 3, 6145 * 1024), ("bf16", 5, 3073 * 4096),
                                        ("bf16", 8, 7169 * 4096), ("f32", 32, 8193 * 1024)])
-def test_launches_with_few_resident_workgroups(dtype, P, n):
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_launches_with_few_resident_workgroups(dtype, P, n, route):
     """Sizes from which launches reserve LDS to bound the workgroups per CU (fp32 6144 items from P = 4, bf16
     3072 from P = 5 and 7168 from P = 8)."""
     say("case: few resident workgroups, %s, P=%d, %d elements" % (dtype, P, n))
     pair = Pair(small_workload([n - 77, 77], P, W.NO_LIMIT, dtype))
-    pair.run(iterations=1)
+    pair.run(iterations=1, route=route)
     pair.close()
 
 

@@ -9,7 +9,7 @@ import torch
 
 import oracle
 import workloads as W
-from helpers import small_workload, split_np, to_numpy
+from helpers import separate_calls, small_workload, split_np, to_numpy
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -154,11 +154,13 @@ def test_all_gather_workers_range_errors_and_subset():
 
 
 @pytest.mark.parametrize("fused", [False, True])
-def test_graph_replays_match_eager_oracle(fused):
-    """One iteration captured into a HIP graph: every replay, with eager work (fresh
-    gradients, a synchronisation) between replays, must equal the oracle's iteration."""
+@pytest.mark.parametrize("route", ["calls", "iteration"])
+def test_graph_replays_match_eager_oracle(fused, route):
+    """One iteration captured into a HIP graph, as the separate calls or as capture_iteration does it: every
+    replay, with eager work (fresh gradients, a synchronisation) between replays, must equal the oracle's
+    iteration."""
     from paper_2302_12445_amd.emulation import EmulatedWorkers
-    print("case: graph capture, fused =", fused, flush=True)
+    print("case: graph capture, fused =", fused, route, flush=True)
     w = W.get_workload("tiny")
     em = EmulatedWorkers(w.sizes, w.P, w.grad_dtype, w.threshold_bytes, DEV)
     op = oracle.plan(w.sizes, w.P, w.threshold_bytes, 4)
@@ -171,7 +173,12 @@ def test_graph_replays_match_eager_oracle(fused):
     sp, sm = np.zeros_like(sg), np.zeros_like(sg)
     oracle.scatter_params(op, params, 0, sp)
     torch.cuda.synchronize()
-    graph = em.capture_iteration(w.lr, w.momentum, fused_update=fused)
+    if route == "iteration":
+        graph = em.capture_iteration(w.lr, w.momentum, fused_update=fused)
+    else:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            separate_calls(em, w.lr, w.momentum, fused=fused)
     # the capture must not have executed anything
     assert np.array_equal(em.shard_param.cpu().numpy().view(np.uint32), sp.view(np.uint32))
     for it in range(4):
