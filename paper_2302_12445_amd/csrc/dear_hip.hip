@@ -22,6 +22,7 @@
 #include <cstring>
 #include <memory>
 #include <new>
+#include <numeric>
 #include <vector>
 
 #include "dear_internal.h"
@@ -40,7 +41,7 @@ struct dear_ctx_impl {
     int32_t max_workgroups = 0;  // 0: one workgroup per work item
     int32_t wave_priority = 0;   // wave priority (0..3) of bounded-grid kernels
     int64_t row_len = 0;
-    std::vector<int64_t> bucket_shard_len, bucket_shard_base;
+    std::vector<int64_t> bucket_len, bucket_shard_len, bucket_shard_base;
     std::vector<int64_t> tile_begin;  // [B+1] range of bucket b's tiles in the tile table
     std::vector<int64_t> layer_sizes;
     void *d_tables = nullptr;         // one allocation: the four tables below
@@ -849,6 +850,11 @@ bucket_range buckets_of(const dear_ctx_impl *c, int32_t bucket)
 
 int64_t tiles_of(const dear_ctx_impl *c, bucket_range r) { return c->tile_begin[r.end] - c->tile_begin[r.begin]; }
 
+int64_t elements_of(const std::vector<int64_t> &bucket_len, bucket_range r)
+{
+    return std::accumulate(bucket_len.begin() + r.begin, bucket_len.begin() + r.end, int64_t{0});
+}
+
 int launch_status() { return hipGetLastError() == hipSuccess ? DEAR_OK : DEAR_EHIP; }
 
 unsigned grid_width(int32_t max_workgroups, int64_t n_items)
@@ -857,41 +863,21 @@ unsigned grid_width(int32_t max_workgroups, int64_t n_items)
     return static_cast<unsigned>(n_items);
 }
 
-// How many workgroups of a launch are resident on a CU is set by the LDS that the launch reserves for each
-// (nothing uses it): 160 KiB / reservation.  HBM serves many streams at once better the fewer loads compete, as
-// long as some 64 KiB per CU are in flight; too few workgroups cost the more the shorter the launch is.
-constexpr unsigned LDS_FOR_1 = 96 << 10, LDS_FOR_2 = 64 << 10;
+// LDS that a launch reserves for each workgroup, and nothing uses, so that `residency` of them share a CU's 160 KiB.
+unsigned residency_lds(int residency) { return residency == 1 ? 96 << 10 : residency == 2 ? 64 << 10 : 0; }
 
-// Reduce-scatter: a workgroup has min(P, 8) * U loads of 4 KiB in flight, 32 KiB in fp32 and 64 KiB in bf16
-// from P = 8 on.  us per iteration, as many workgroups as fit / 2 per CU / 1 per CU:
-//   fp32, 30 M elements: P = 4 256 / 249 / 297, P = 6 335 / 322 / 377, P = 12 584 / 551 / 634;
-//         6 M in the largest of 5 launches P = 8 369 / 360 / 384; 4 M: P = 4 35 / 39 / 46, P = 12 78 / 80 / 94;
-//         P = 3, 24 M 165 / 176 / -;
-//   bf16, 60 M elements: P = 4 428 / 428 / 432, P = 8 652 / 646 / 636, P = 32 2078 / 2070 / 2041;
-//         33 M: P = 8 367 / 364 / 361, P = 16 639 / 635 / 618; 20 M: P = 8 207 / 206 / 216; 13 M and 7 M: P = 7
-//         226 / 221 / 234; 4 M: P = 6 40 / 41 / 44; P = 3, 24 M 139 / 144 / -.
-// An item is 1024 elements in fp32 and 4096 in bf16.  Without the update (no w and v in flight beside the
-// gradients) one per CU is too few at P = 8: reduce-scatter, update and all-gather of 200 M bf16 elements, as many
-// as fit / 1 per CU, P = 8 2485 / 2509, but 60 M P = 32 2173 / 2118; fp32 110 M P = 16 2930 / 2875 with 2.
-template <bool BF16, rs_mode MODE>
-unsigned reduce_scatter_lds(int P, unsigned n_items)
-{
-    if (!BF16) return P >= 4 && n_items >= 6144 ? LDS_FOR_2 : 0;
-    if (P >= (MODE & RS_UPDATE ? 8 : 16) && n_items >= 7168) return LDS_FOR_1;
-    return P >= 5 && n_items >= 3072 ? LDS_FOR_2 : 0;
-}
-
-// tiles, grad_tab: device tables (a context's, or the static scratch's).
+// tiles, grad_tab: device tables (a context's, or the static scratch's); the tiles hold n_elems elements.
 template <bool BF16, rs_mode MODE>
 void rs_launch(int P, int L, const void *const *grad_tab, int32_t max_workgroups, int prio, int64_t n_tiles,
-               hipStream_t st, const dear_tile *tiles, const rs_sink<MODE> &o)
+               int64_t n_elems, hipStream_t st, const dear_tile *tiles, const rs_sink<MODE> &o)
 {
     constexpr int U = BF16 ? DEAR_RS_U_BF16 : DEAR_RS_U_F32;
     constexpr int SPLIT = DEAR_TILE_ELEMS / ((BF16 ? 8 : 4) * DEAR_BLOCK * U);
     const unsigned n_items = static_cast<unsigned>(n_tiles * SPLIT);
     const dim3 grid(grid_width(max_workgroups, n_items)), block(DEAR_BLOCK);
     const bool bounded = grid.x < n_items;
-    const unsigned lds = bounded ? 0 : reduce_scatter_lds<BF16, MODE>(P, n_items);
+    const unsigned lds =
+        bounded ? 0 : residency_lds(reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, P, n_elems, n_tiles));
     const float inv_P = 1.0f / static_cast<float>(P);
 #define RS_LAUNCH(CH, TAIL)                                                                              \
     do {                                                                                                 \
@@ -968,6 +954,7 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
         c->P = plan->P;
         c->g = plan->g;
         c->row_len = plan->row_len;
+        c->bucket_len = plan->bucket_len;
         c->bucket_shard_len = plan->bucket_shard_len;
         c->bucket_shard_base = plan->bucket_shard_base;
         c->layer_sizes = plan->layer_sizes;
@@ -1043,11 +1030,12 @@ int launch_reduce_scatter(const dear_ctx_impl *c, bucket_range r, const rs_sink<
 {
     const int64_t count = tiles_of(c, r);
     if (count == 0) return DEAR_OK;
+    const int64_t elems = elements_of(c->bucket_len, r);
     const dear_tile *tiles = c->d_tiles + c->tile_begin[r.begin];
     if (c->g == 2)
-        rs_launch<true, MODE>(c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, count, st, tiles, o);
+        rs_launch<true, MODE>(c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, count, elems, st, tiles, o);
     else
-        rs_launch<false, MODE>(c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, count, st, tiles, o);
+        rs_launch<false, MODE>(c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, count, elems, st, tiles, o);
     return launch_status();
 }
 
@@ -1355,9 +1343,10 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
     const void *const *grad_tab = reinterpret_cast<const void *const *>(dev);
     const dear_tile *tiles = reinterpret_cast<const dear_tile *>(dev + tiles_at);
     const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f};
+    const int64_t elems = elements_of(plan->bucket_len, bucket_range{b_first, b_last});
     if (plan->g == 2)
-        rs_launch<true, RS_GBAR>(plan->P, plan->L, grad_tab, 0, 0, n_tiles, st, tiles, o);
+        rs_launch<true, RS_GBAR>(plan->P, plan->L, grad_tab, 0, 0, n_tiles, elems, st, tiles, o);
     else
-        rs_launch<false, RS_GBAR>(plan->P, plan->L, grad_tab, 0, 0, n_tiles, st, tiles, o);
+        rs_launch<false, RS_GBAR>(plan->P, plan->L, grad_tab, 0, 0, n_tiles, elems, st, tiles, o);
     return launch_status();
 }

@@ -488,15 +488,27 @@ def test_every_alignment_of_a_runs_ends(P, width, gather, dtype):
     pair.close()
 
 
-@pytest.mark.parametrize("dtype,P,n", [("f32", 4, 6145 * 1024), ("f32", 3, 6145 * 1024), ("bf16", 5, 3073 * 4096),
-                                       ("bf16", 8, 7169 * 4096), ("f32", 32, 8193 * 1024)])
-@pytest.mark.parametrize("route", ["calls", "iteration"])
-def test_launches_with_few_resident_workgroups(dtype, P, n, route):
-    """Sizes from which launches reserve LDS to bound the workgroups per CU (fp32 6144 items from P = 4, bf16
-    3072 from P = 5 and 7168 from P = 8)."""
+@pytest.mark.parametrize("dtype,P,n", [("f32", 4, 25_100_000), ("f32", 13, 7_800_000), ("f32", 32, 3_200_000),
+                                       ("bf16", 5, 16_100_000), ("bf16", 8, 31_300_000), ("bf16", 12, 20_900_000),
+                                       ("bf16", 17, 14_800_000)])
+def test_launches_with_few_resident_workgroups(dtype, P, n):
+    """Sizes just above those from which launches bound the workgroups per CU (reduce_scatter_residency), in each
+    form of the reduce-scatter."""
     say("case: few resident workgroups, %s, P=%d, %d elements" % (dtype, P, n))
     pair = Pair(small_workload([n - 77, 77], P, W.NO_LIMIT, dtype))
-    pair.run(iterations=1, route=route)
+    for route in ("calls", "iteration"):
+        for fused in (False, True):
+            pair.run(iterations=1, route=route, fused=fused)
+    pair.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_many_short_runs(dtype):
+    """Thousands of tensors far shorter than a tile in one launch: as many workgroups as fit."""
+    say("case: 6000 short tensors, %s" % dtype)
+    pair = Pair(small_workload([64, 200, 701] * 2000, 12, W.NO_LIMIT, dtype))
+    pair.run(iterations=1)
+    pair.run(iterations=1, fused=True)
     pair.close()
 
 
