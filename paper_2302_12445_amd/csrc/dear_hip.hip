@@ -542,6 +542,28 @@ __device__ __forceinline__ void all_gather_tile(const dear_tile &t, int part, in
     }
 }
 
+// A part of a tile that is not whole, in a run whose cuts stay at multiples of the tile: short runs, and the ends
+// of runs of tensors that start on lines.  Thousands of short tensors make a launch of mostly such parts, some of
+// them empty, and what bounds it is the number of instructions in front of a part's load: the form above
+// took 69 us for 3000 tensors of 512 elements at P = 8 where this one takes 53, 220 / 171 for 20000 of 300 at P = 4,
+// 182 / 145 for 4000 of 701 at P = 16.  Elements of a partial vector go one after another in that vector's lane
+// for the same reason (a lane for each: 56, 179, 156).
+__device__ __forceinline__ void all_gather_short_tile(const dear_tile &t, int part, float *out_base,
+                                                      const float *__restrict__ src)
+{
+    constexpr int VE = 4, PART = VE * DEAR_BLOCK;
+    const int tid = threadIdx.x;
+    const int mis = (int)t.src_begin & (VE - 1), begin = part * PART - mis;
+    if (begin >= t.count) return;
+    DEAR_GLOBAL float *out = (DEAR_GLOBAL float *)out_base + t.src_begin;
+    const int i = begin + VE * tid;
+    if (i >= 0 && i + VE <= t.count)
+        store_vec<DEAR_AG_NT_STORE>((global_f4_out)(out + i), load_f4_dword_aligned<DEAR_AG_NT_LOAD>(src + i));
+    else if (i < t.count)
+        for (int j = 0; j < VE; ++j)
+            if (i + j >= 0 && i + j < t.count) out[i + j] = src[i + j];
+}
+
 // Quotient and remainder of n < 2^31 by a divisor d whose inv_d = floor((2^32 - 1) / d) the host supplies:
 // n * inv_d / 2^32 is above n / d - 1, so the estimate is at most one too small.  A division proper is a
 // long serial chain of scalar and vector instructions at the head of every workgroup.
@@ -589,6 +611,13 @@ __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_kernel(
     float *const *out = param_tab + (size_t)((unsigned)p_first + q) * L + t.layer;
     if (t.bucket == 0 && t.count == DEAR_TILE_ELEMS) {  // inside a run of tensors that start on lines
         all_gather_tile<true>(t, part, 0, false, false, out, src);
+        return;
+    }
+    if (t.bucket <= (TILE_FIRST | TILE_LAST)) {
+        if (t.count == DEAR_TILE_ELEMS)
+            all_gather_tile<true>(t, part, 0, false, false, out, src);
+        else
+            all_gather_short_tile(t, part, *out, src);
         return;
     }
     const bool first = t.bucket & TILE_FIRST, last = t.bucket & TILE_LAST;
