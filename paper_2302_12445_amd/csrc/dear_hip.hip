@@ -233,10 +233,8 @@ __device__ __forceinline__ void wave_lds_sync()
 //              same four separately rounded operations as shard_update_kernel) while gbar is in registers.
 //              Without RS_GBAR gbar is never written, which saves its 4-byte write and 4-byte re-read per
 //              element; with it only the re-read is saved;
-//   RS_W_NEXT  the next launch reads w: it is stored with the ordinary cache policy, so that the all-gather
-//              behind it finds it in the 256 MB last-level cache.  BERT-Large-shaped iteration, non-temporal ->
-//              ordinary: 3954 -> 3804 us with the all-gather of a bucket directly behind its
-//              reduce-scatter, but 3943 -> 4074 us with all reduce-scatters before all all-gathers.
+//   RS_W_NEXT  the next launch reads w, and finds it in the 256 MB last-level cache (iteration_caches_w): w is stored
+//              with the ordinary cache policy.
 typedef int rs_mode;
 constexpr rs_mode RS_GBAR = 1, RS_UPDATE = 2, RS_W_NEXT = 4;
 
@@ -1214,13 +1212,22 @@ extern "C" int dear_all_gather(dear_ctx_t *c, int32_t bucket, const float *shard
     return dear_all_gather_workers(c, bucket, shard_param, 0, c->P, hip_stream);
 }
 
-// dear_iteration handles consecutive buckets together until they hold this many tiles (32 Mi elements, 128 MiB
-// of w).  A launch costs about 2 us of ramp and drain, which shows up to some hundred microseconds, and the
-// w that a reduce-scatter leaves for the all-gather behind it has to fit the last-level cache.  us per
-// iteration with one launch pair per bucket / 2000 / 4000 / 8192 / 16000 / 32000 tiles: ResNet-50-shaped P = 8
-// 389 / 375 / 376 / 367 / 370 / 366, BERT-Large-shaped P = 8 bf16 3804 / - / 3846 / 3858 / 3892 / 4036, 58
-// tensors in 0.3 MB buckets P = 24 2279 / 1775 / 1697 / 1691 / 1683 / 1729, tiny (5 buckets) 36 / 11 / 11 / 11 / 11 / 11.
-constexpr int64_t ITERATION_TILES = 8192;
+namespace {
+
+// Reduce-scatter and update of a group in one kernel, gbar stored only where it is wanted.
+template <rs_mode W_NEXT>
+int launch_reduce_scatter_update(const dear_ctx_impl *c, bucket_range r, float *shard_grad, float *shard_param,
+                                 float *shard_mom, float lr, float momentum, hipStream_t st)
+{
+    if (shard_grad) {
+        const rs_sink<RS_GBAR | RS_UPDATE | W_NEXT> o{shard_grad, shard_param, shard_mom, lr, momentum};
+        return launch_reduce_scatter(c, r, o, st);
+    }
+    const rs_sink<RS_UPDATE | W_NEXT> o{nullptr, shard_param, shard_mom, lr, momentum};
+    return launch_reduce_scatter(c, r, o, st);
+}
+
+}  // namespace
 
 extern "C" int dear_iteration(dear_ctx_t *c, int32_t bucket, float *shard_grad, float *shard_param,
                               float *shard_mom, float lr, float momentum, void *hip_stream)
@@ -1243,12 +1250,15 @@ extern "C" int dear_iteration(dear_ctx_t *c, int32_t bucket, float *shard_grad, 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     for (bucket_range r{0, all.begin}; rc == DEAR_OK && r.end < all.end;) {
         r = group_from(r.end);
-        if (shard_grad) {
-            const rs_sink<RS_GBAR | RS_UPDATE | RS_W_NEXT> o{shard_grad, shard_param, shard_mom, lr, momentum};
+        const int64_t tiles = tiles_of(c, r);
+        if (shard_grad && iteration_updates_apart(c->g, c->P, tiles)) {
+            const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f};
             rc = launch_reduce_scatter(c, r, o, st);
+            if (rc == DEAR_OK) rc = launch_update(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
+        } else if (iteration_caches_w(c->g, c->P, tiles, c->tile_begin[c->B])) {
+            rc = launch_reduce_scatter_update<RS_W_NEXT>(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
         } else {
-            const rs_sink<RS_UPDATE | RS_W_NEXT> o{nullptr, shard_param, shard_mom, lr, momentum};
-            rc = launch_reduce_scatter(c, r, o, st);
+            rc = launch_reduce_scatter_update<0>(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
         }
         if (rc == DEAR_OK) rc = launch_all_gather(c, r, shard_param, 0, c->P, st);
     }

@@ -103,3 +103,43 @@ inline int reduce_scatter_residency(bool bf16, bool updates, int64_t P, int64_t 
     if (P >= 16 && P % 8 != 4 && bytes >= 500 * MB) return 1;
     return P >= 8 && bytes >= 500 * MB ? 2 : 0;
 }
+
+// dear_iteration handles consecutive buckets together until they hold this many tiles (32 Mi elements, 128 MiB of w).
+// A launch costs about 2 us of ramp and drain, which shows up to some hundred microseconds; a longer group has more
+// w for the last-level cache and a longer way back to it.  us per iteration with gbar, one launch pair per bucket / 2048 /
+// 4096 / 8192 / 16384 / 32768 tiles (spread 0.1-1.4 %): ResNet-50-shaped P = 8 386 / 386 / 365 / 354 / 353 / 353, 58 tensors in
+// 0.3 MB buckets P = 24 1198 / 955 / 969 / 964 / 964 / 961, BERT-Base-shaped in 16 MB P = 8 1867 / 1630 / 1575 / 1579 / 1566
+// / 1578, P = 64 10016 / 10254 / 9642 / 9599 / 9532 / 9726, in 25 MB P = 16 2798 / 2799 / 2773 / 2760 / 2789 / 2825,
+// BERT-Large-shaped bf16 in 25 MB P = 2 2077 / 2076 / 2070 / 2033 / 2044 / 2068, in 64 MB (a bucket each up to 8192) P = 8
+// 3810 / 3852 / 3860.
+constexpr int64_t ITERATION_TILES = 8192;
+
+// Whether a group's reduce-scatter stores w with the ordinary cache policy, for the all-gather behind it: where w is
+// still in the 256 MB last-level cache by then.  That takes a w which fits (a larger bucket is a group of its own),
+// and little gradient traffic beside it, grad_bytes * P per element, or a w of all buckets that stays in the cache.
+// us per iteration without gbar, non-temporal w / ordinary w (spread 0.1-0.3 %), P:
+//   several groups, fp32  2 659 / 665   4 926 / 916  6 1175 / 1187  8 1447 / 1483  16 2593 / 2677  64 9483 / 9666
+//                         (BERT-Base-shaped, 64 MB buckets);  Inception-v4-shaped 8 595 / 619
+//   several groups, bf16  2 1807 / 1772  4 2460 / 2393  8 3671 / 3601  12 4910 / 4877  16 6109 / 6184
+//                         (BERT-Large-shaped, 64 MB);  BERT-Base-shaped 24 2849 / 2919
+//   one group, fp32       DenseNet-201-shaped 8 274 / 267, 16 488 / 487;  ResNet-50-shaped 8 346 / 347, 32 1173 / 1181
+//   one group, bf16       ResNet-50-shaped 16 493 / 488, 32 941 / 921;  604 ragged tensors 7 203 / 190
+//   one bucket beyond ITERATION_TILES, 110 M  fp32 2 686 / 683  8 1492 / 1529  64 9396 / 9706; bf16 8 1213 / 1215
+inline bool iteration_caches_w(int grad_bytes, int64_t P, int64_t group_tiles, int64_t all_tiles)
+{
+    constexpr int64_t ALL_CACHED_TILES = 7168;  // 112 MiB of w
+    if (group_tiles > ITERATION_TILES) return false;
+    if (grad_bytes * P <= (grad_bytes == 2 ? 24 : 16)) return true;
+    return grad_bytes * P <= 64 && all_tiles <= ALL_CACHED_TILES;
+}
+
+// Whether a group whose gbar is wanted takes three launches, the update behind the reduce-scatter: the more replicas
+// are read, the less it costs to read gbar once more, and the better the reduce-scatter runs with one output instead
+// of three.  us per iteration, one kernel / two (spread 0.2-2 %), fp32 P: BERT-Base-shaped, 64 MB buckets 8 1549 / 1638,
+// 16 2715 / 2695, 24 3888 / 3820, 32 5097 / 4980, 64 9649 / 9504; one bucket of 110 M 64 9807 / 9517; ResNet-50-shaped
+// 16 644 / 644, 32 1209 / 1184, 64 2340 / 2277; 2 M elements 24 73.4 / 75.7, 64 192 / 192; bf16: BERT-Base-shaped
+// 24 2949 / 2955, 32 3841 / 3817, 64 7542 / 7346; 8 M elements 64 555 / 545.
+inline bool iteration_updates_apart(int grad_bytes, int64_t P, int64_t group_tiles)
+{
+    return grad_bytes * P >= 96 && group_tiles >= 2048;
+}

@@ -76,10 +76,27 @@ static void residency()
         CHECK(reduce_scatter_residency(c.bf16, c.updates, c.P, c.elems, c.elems / DEAR_TILE_ELEMS + c.P) == c.want);
 }
 
+// dear_iteration: w is left in the cache only where it fits; gbar is read again only where many replicas are read.
+static void iteration()
+{
+    for (int g = 2; g <= 4; g += 2)
+        for (int64_t P = 1; P <= 80; ++P)
+            for (int64_t tiles : {int64_t(1), int64_t(2047), int64_t(2048), ITERATION_TILES, ITERATION_TILES + 1, int64_t(100000)})
+                for (int64_t all : {tiles, tiles + 1, 2 * tiles + 7168}) {
+                    const bool cached = iteration_caches_w(g, P, tiles, all), apart = iteration_updates_apart(g, P, tiles);
+                    CHECK(!cached || tiles <= ITERATION_TILES);
+                    CHECK(!cached || g * P <= (g == 2 ? 24 : 16) || (g * P <= 64 && all <= 7168));
+                    CHECK(cached || tiles > ITERATION_TILES || g * P > (g == 2 ? 24 : 16));
+                    CHECK(apart == (g * P >= 96 && tiles >= 2048));
+                    CHECK(!(apart && cached));
+                }
+}
+
 int main()
 {
     grids();
     residency();
+    iteration();
     std::printf("launch_rules: ok\n");
     return 0;
 }

@@ -464,6 +464,17 @@ def test_iteration_call_of_one_bucket_and_of_several_groups(dtype, keep, width):
         pair.close()
 
 
+@pytest.mark.parametrize("dtype,P,n", [("f32", 25, 2048 * 4096), ("f32", 24, 2000 * 4096), ("bf16", 48, 2048 * 4096)])
+def test_iteration_call_with_many_replicas(dtype, P, n):
+    """From 96 gradient bytes per element and 2048 tiles on dear_iteration updates in a launch of its own if the
+    averaged gradients are wanted; below, and without them, inside the reduce-scatter."""
+    say("case: iteration call, P=%d, %d elements, %s" % (P, n, dtype))
+    pair = Pair(small_workload([n - 33, 33], P, W.NO_LIMIT, dtype))
+    pair.run(iterations=1, route="iteration")
+    pair.run(iterations=1, route="iteration", width=300)
+    pair.close()
+
+
 @pytest.mark.parametrize("P,n", [(6, 1366 * 4096), (6, 1365 * 4096), (5, 1700 * 4096), (9, 911 * 4096 + 5)])
 def test_update_all_gather_on_both_sides_of_its_split(P, n):
     """6 replicas and 8192 tile copies: from there on the call launches the update and the all-gather."""
