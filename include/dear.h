@@ -13,7 +13,9 @@
  *
  * Conventions
  *   - Every function returns a status (DEAR_OK = 0, errors < 0); nothing is printed,
- *     nothing aborts.  On error nothing is launched and outputs are untouched.
+ *     nothing aborts.  On error nothing is launched and outputs are untouched; DEAR_EHIP
+ *     from a call that makes several launches (dear_update_all_gather, dear_iteration) can
+ *     also mean that a later one failed.
  *   - "host" / "device" is stated for every pointer.  All large device memory is owned
  *     by the caller; the library owns only its plan/context objects and their small
  *     tables (host and device), released by dear_plan_free / dear_ctx_destroy.
@@ -131,7 +133,8 @@ typedef struct {
     int32_t bucket;
 } dear_tile_t;
 
-/* dear_plan_tiles -- the tile table dear_ctx_create uploads, for inspection and tests.
+/* dear_plan_tiles -- the plan's tile table, for inspection and tests.  (The device copy that
+ * dear_ctx_create makes of it carries notes for the all-gather in the place of `bucket`.)
  *   out       host, capacity entries (may be NULL when capacity = 0)
  *   n_tiles   host, receives the number of tiles of the plan (always)
  *   bucket_tile_begin  host, n_buckets+1 entries or NULL: tiles of bucket b are
@@ -153,8 +156,8 @@ int dear_plan_tiles(const dear_plan_t *plan, dear_tile_t *out, int64_t capacity,
  * Every tensor base pointer must be 16-byte aligned (DEAR_EALIGN otherwise).  The two
  * pointer arrays are copied; the tensors themselves stay owned by the caller and must
  * outlive the context.  The context copies what it needs from the plan, so the plan
- * may be freed first.  Allocates device memory for its tables (pointer tables and a
- * tile table of 32 bytes per DEAR_TILE_ELEMS elements).  Uses the current HIP device;
+ * may be freed first.  Allocates device memory for its tables (pointer tables, a
+ * table of 32 bytes per layer and a tile table of 32 bytes per DEAR_TILE_ELEMS elements).  Uses the current HIP device;
  * every later call on the context must be made with that device current (DEAR_EINVAL
  * otherwise).
  * Errors: DEAR_EINVAL, DEAR_EALIGN, DEAR_ENOMEM, DEAR_EHIP.
@@ -237,7 +240,8 @@ int dear_reduce_scatter(dear_ctx_t *ctx, int32_t bucket, float *shard_grad, void
  * GPU's array, which keeps the last call's tables: nothing in it needs clearing (every
  * entry the kernel reads is rewritten by the call), but calls that overlap on one GPU --
  * different host threads, or a second call on another stream while the first call's
- * kernel still runs -- race and must be serialised by the caller.
+ * kernel still runs -- race and must be serialised by the caller; so must calls from different
+ * host threads on different GPUs, which share the host staging area.
  * Errors: DEAR_EINVAL, DEAR_ERANGE, DEAR_EALIGN, DEAR_ETOOBIG, DEAR_EHIP.
  */
 #define DEAR_STATIC_MAX_POINTERS 131072
@@ -285,7 +289,8 @@ int dear_reduce_scatter_update(dear_ctx_t *ctx, int32_t bucket, float *shard_par
  * For every worker p, every layer l of the bucket and element i:
  *     param[p][l][i] = shard_param[s][shard_base_b + e % S_b],  e = layer_offset[l] + i
  *   shard_param  device, read
- * Errors: DEAR_EINVAL, DEAR_ERANGE, DEAR_EALIGN, DEAR_EHIP.
+ * Errors: DEAR_EINVAL (also, without a bounded grid, for 2^24 workgroups or more: 4 per tile
+ * and replica), DEAR_ERANGE, DEAR_EALIGN, DEAR_EHIP.
  */
 int dear_all_gather(dear_ctx_t *ctx, int32_t bucket, const float *shard_param, void *hip_stream);
 
@@ -308,14 +313,15 @@ int dear_update_all_gather(dear_ctx_t *ctx, int32_t bucket, const float *shard_g
 /* ---------------------------------------------------------------------------------
  * dear_iteration -- the whole pass over a bucket (or all of them) on one stream, for callers
  * whose gradients are all in place: reduce-scatter, update and all-gather.  Results are
- * bit-identical to dear_reduce_scatter, dear_shard_update and dear_all_gather in a row.  The
- * update is applied in the reduce-scatter's kernel, small buckets share a launch, and the
- * all-gather of a group of buckets follows its reduce-scatter directly, while the parameter
- * shards are in the last-level cache.  (The decoupled schedule, paper Section III-B, issues
- * the halves separately with the calls above.)
+ * bit-identical to dear_reduce_scatter, dear_shard_update and dear_all_gather in a row.  Small
+ * buckets share a launch; the update is applied in the reduce-scatter's kernel, or behind it
+ * where many replicas are read and shard_grad is wanted; the all-gather of a group of buckets
+ * follows directly, while the parameter shards are in the last-level cache if they fit it.
+ * (The decoupled schedule, paper Section III-B, issues the halves separately with the calls
+ * above.)
  *   shard_grad   device, written; NULL if the averaged gradients are not wanted
  *   shard_param, shard_mom  device, updated in place
- * Errors: DEAR_EINVAL, DEAR_ERANGE, DEAR_EALIGN, DEAR_EHIP.
+ * Errors as dear_all_gather.
  */
 int dear_iteration(dear_ctx_t *ctx, int32_t bucket, float *shard_grad, float *shard_param, float *shard_mom,
                    float lr, float momentum, void *hip_stream);

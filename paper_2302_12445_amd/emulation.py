@@ -109,10 +109,12 @@ class EmulatedWorkers:
     def iteration(self, lr: float, momentum: float, per_bucket: bool = True, stream=None,
                   fused_update: bool = False, fused_gather: bool = False) -> None:
         """One pass of the whole path on one stream: reduce-scatter, update of the owned shards,
-        all-gather.  The library chooses how buckets share launches (dear_iteration).
+        all-gather.  One library call (dear_iteration), which chooses how buckets share launches and
+        gathers a group of buckets before it reduces the next.
         fused_update: the averaged gradients are not wanted, shard_grad is not written.
-        fused_gather: reduce-scatters first, then update and all-gather of a bucket in one call;
-        per_bucket False: all buckets in one of these calls."""
+        fused_gather: instead, reduce-scatters first, then update and all-gather in one call each.
+        per_bucket: with fused_gather, a call per bucket or (False) one for all of them; it shapes
+        nothing otherwise.  For launches of one's own choice there are the calls above."""
         if fused_gather:
             buckets = list(range(self.plan.n_buckets)) if per_bucket else [-1]
             for b in buckets:
@@ -152,7 +154,8 @@ class EmulatedWorkers:
 
     def capture_iteration(self, lr: float, momentum: float, per_bucket: bool = True,
                           fused_update: bool = False) -> "torch.cuda.CUDAGraph":
-        """Record one iteration (all its launches) into a HIP graph and return it; replay()
+        """Record one iteration (all its launches, which `iteration` chooses whatever per_bucket says)
+        into a HIP graph and return it; replay()
         then runs the iteration with one submission.  Nothing is executed by the capture itself.  The
         library's launches contain no memset nodes and allocate nothing, so they are safe to
         capture; the graph is bound to this context's tensors and launch width."""
