@@ -74,7 +74,7 @@ void dear_build_tiles(const dear_plan_s &pl, std::vector<dear_tile> &tiles, std:
 //       fp32 without  P = 4  33 M  528  +4/+23   110 M 1760   +4/+24 | P = 8  13 M 416 +0.2/+12  33 M 1056 -0.6/+11
 //                     P = 12  6 M  312  +1/+19    13 M  624 -1.3/+18 | P = 16  4 M 256 -0.4/+7    6 M  416 -1.4/+6
 //                     P = 64  2 M  512 -0.6/+5     4 M 1024 -1.5/+6
-//       fp32 with     P = 4  13 M  208  +3/+20    33 M  528   -3/+13 | P = 8   6 M 208 +0.8/+11  13 M  416 -1.0/+9
+//       fp32 with     P = 4  26 M  416  +3/+19    33 M  528   -3/+13 | P = 8   6 M 208 +0.8/+11  13 M  416 -1.0/+9
 //                     P = 16  2 M  128  +1/+10     4 M  256 -1.2/+5  | P = 64  2 M 512 -0.4/+6    4 M 1024 -1.6/+6
 //       bf16 without  P = 5 110 M 1100 +0.3/+6  | P = 8  26 M  416 +0.2/+1.4  110 M 1760 -0.8/-0.2
 //                     P = 12 13 M  312 -0.5/+6    26 M  624 -1.2/+4  | P = 16 13 M 416 -0.1/-0.6 26 M  832 -1.0/-1.9
@@ -93,7 +93,7 @@ inline int reduce_scatter_residency(bool bf16, bool updates, int64_t P, int64_t 
     const int64_t bytes = elems * P * (bf16 ? 2 : 4);
     if (elems * 5 < tiles * (4 * DEAR_TILE_ELEMS)) return 0;
     if (!bf16) {
-        if (updates) return P >= 4 && bytes >= 400 * MB ? 2 : 0;
+        if (updates) return P >= 4 && bytes >= (P >= 8 ? 400 : 500) * MB ? 2 : 0;
         return P >= 8 && bytes >= (P >= 12 ? 400 : 800) * MB ? 2 : 0;
     }
     if (updates) {

@@ -65,7 +65,8 @@ static void residency()
                 }
             }
     struct { bool bf16, updates; int64_t P, elems; int want; } const at[] = {
-        {false, true, 4, 24900000, 0},   {false, true, 4, 25100000, 2},   {false, true, 3, 110000000, 0},
+        {false, true, 4, 31200000, 0},   {false, true, 4, 31300000, 2},   {false, true, 3, 110000000, 0},
+        {false, true, 8, 12400000, 0},   {false, true, 8, 12600000, 2},
         {false, false, 4, 110000000, 0}, {false, false, 8, 24900000, 0},  {false, false, 8, 25100000, 2},
         {false, false, 16, 6200000, 0},  {false, false, 16, 6300000, 2},  {true, true, 5, 15900000, 0},
         {true, true, 5, 110000000, 2},   {true, true, 8, 28700000, 2},    {true, true, 8, 28800000, 1},

@@ -499,7 +499,7 @@ def test_every_alignment_of_a_runs_ends(P, width, gather, dtype):
     pair.close()
 
 
-@pytest.mark.parametrize("dtype,P,n", [("f32", 4, 25_100_000), ("f32", 13, 7_800_000), ("f32", 32, 3_200_000),
+@pytest.mark.parametrize("dtype,P,n", [("f32", 4, 31_300_000), ("f32", 13, 7_800_000), ("f32", 32, 3_200_000),
                                        ("bf16", 5, 16_100_000), ("bf16", 8, 31_300_000), ("bf16", 12, 20_900_000),
                                        ("bf16", 17, 14_800_000)])
 def test_launches_with_few_resident_workgroups(dtype, P, n):
