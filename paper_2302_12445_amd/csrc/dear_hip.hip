@@ -63,12 +63,6 @@ struct layer_place {
 // Launch-shape and cache-hint choices, fixed at build time (measured on MI355X; the
 // defaults are the fastest found).  *_U = 16-byte vectors per lane; a tile of
 // DEAR_TILE_ELEMS is shared by TILE_VECS / (U * DEAR_BLOCK) workgroups.
-#ifndef DEAR_RS_U_F32
-#define DEAR_RS_U_F32 1
-#endif
-#ifndef DEAR_RS_U_BF16
-#define DEAR_RS_U_BF16 2
-#endif
 #ifndef DEAR_RS_NT_LOAD
 #define DEAR_RS_NT_LOAD 1
 #endif
@@ -97,6 +91,7 @@ struct layer_place {
 // Pointers read from the pointer tables are generic; every tensor lives in global
 // memory, and saying so lets the compiler use global_load / global_store.
 #define DEAR_GLOBAL __attribute__((address_space(1)))
+#define DEAR_CONSTANT __attribute__((address_space(4)))  // tables, which no kernel writes: scalar loads
 typedef const DEAR_GLOBAL u4 *global_u4_in;
 typedef DEAR_GLOBAL f4 *global_f4_out;
 typedef const DEAR_GLOBAL f4_dword_aligned *global_f4u_in;
@@ -505,7 +500,7 @@ __global__ __launch_bounds__(DEAR_BLOCK) void shard_update_kernel(
 // -> 787, 20 M in 604 P = 7 bf16 225 -> 217, ResNet-50-shaped P = 64 2432 -> 2348.
 template <bool INNER>
 __device__ __forceinline__ void all_gather_tile(const dear_tile &t, int part, int shift, bool first, bool last,
-                                                float *const *__restrict__ out_entry, const float *__restrict__ src)
+                                                float *const DEAR_CONSTANT *out_entry, const float *__restrict__ src)
 {
     // positions are counted from the tile's first element, so that they fit 32 bits; `low` says how the
     // element lies in its 16-byte vector and 128-byte line
@@ -584,12 +579,21 @@ constexpr int TILE_SHIFT_BIT = 8;             // the replicas' common shift from
 // Elements between the last 128-byte line that begins at or before p, and p (16-byte aligned).
 __host__ __device__ __forceinline__ int line_shift(uintptr_t p) { return static_cast<int>((p >> 2) & 31); }
 
-// n_parts = tiles * AG_SPLIT; replicas p_first .. p_first+n_p-1 receive; there are
-// n_parts * n_p work items.  inv_n_p, inv_len: reciprocals (see divide) of n_p and of the number of parts
-// in the short last chunk.
+// n_parts = tiles * AG_SPLIT; replicas p_first .. p_first+n_p-1 receive.  inv_n_p, inv_len: reciprocals (see divide)
+// of n_p and of len, the number of workgroups per replica in the short last chunk.
+// Workgroups go to the eight XCDs in turn, and a part of a chunk belongs on one XCD for all replicas, whose L2 then
+// holds the shard values: len is a multiple of 8 (workgroups behind the last part have nothing to do).  In a short launch
+// the values are still in the L2 of the XCD whose reduce-scatter + update wrote them, so they are read there: `run` is
+// the logarithm of the number of parts that one workgroup of that kernel had (fp32 0; bf16 1).
+// One launch of each, us per iteration without gbar, 1 M elements (an odd number of tiles) len as it falls / rounded:
+// fp32 P = 4 13.7 / 11.5, P = 8 18.3 / 16.1, P = 16 29.6 / 27.6; 8 M fp32 P = 8 108.6 / 103.1, P = 16 195 / 187.  bf16, run 0 / 1:
+// P = 4 1 M 12.1 / 10.7, 2 M 19.1 / 17.2, P = 8 1 M 16.1 / 14.7, 2 M 26.4 / 24.5, 3 M 36.0 / 34.6, P = 16 2 M 40.8 / 39.0;
+// beyond, the values have left L2, and writes in this order cost: P = 8 10 M 100.9 / 101.6, P = 16 6 M 109 / 111, 20 M 355 / 368.
+template <unsigned RUN>
 __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_kernel(
     const dear_tile *__restrict__ tiles, float *const *__restrict__ param_tab, int L, int p_first,
-    unsigned n_p, const float *__restrict__ shard_param, unsigned n_parts, unsigned inv_n_p, unsigned inv_len)
+    unsigned n_p, const float *__restrict__ shard_param, unsigned n_parts, unsigned inv_n_p, unsigned len,
+    unsigned inv_len)
 {
     static_assert((AG_SPLIT & (AG_SPLIT - 1)) == 0, "a part's tile is found by a shift");
     constexpr unsigned CHUNK = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK);  // parts per chunk
@@ -599,14 +603,16 @@ __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_kernel(
     unsigned q, chunk = divide(blockIdx.x / CHUNK, n_p, inv_n_p, q), r = blockIdx.x % CHUNK;
     if (chunk >= whole) {
         chunk = whole;
-        q = divide(blockIdx.x - whole * CHUNK * n_p, n_parts - whole * CHUNK, inv_len, r);
+        q = divide(blockIdx.x - whole * CHUNK * n_p, len, inv_len, r);
+        if (chunk * CHUNK + all_gather_part(r, RUN) >= n_parts) return;
     }
-    const unsigned id = chunk * CHUNK + r;
+    const unsigned id = chunk * CHUNK + all_gather_part(r, RUN);
     const dear_tile t = tiles[id / AG_SPLIT];
     const int part = id % AG_SPLIT;
     if (t.layer < 0) return;
     const float *__restrict__ src = shard_param + t.dst_begin;
-    float *const *out = param_tab + (size_t)((unsigned)p_first + q) * L + t.layer;
+    float *const DEAR_CONSTANT *out =
+        (float *const DEAR_CONSTANT *)param_tab + ((size_t)((unsigned)p_first + q) * (unsigned)L + (unsigned)t.layer);
     if (t.bucket == 0 && t.count == DEAR_TILE_ELEMS) {  // inside a run of tensors that start on lines
         all_gather_tile<true>(t, part, 0, false, false, out, src);
         return;
@@ -893,41 +899,61 @@ unsigned grid_width(int32_t max_workgroups, int64_t n_items)
 // LDS that a launch reserves for each workgroup, and nothing uses, so that `residency` of them share a CU's 160 KiB.
 unsigned residency_lds(int residency) { return residency == 1 ? 96 << 10 : residency == 2 ? 64 << 10 : 0; }
 
-// tiles, grad_tab: device tables (a context's, or the static scratch's); the tiles hold n_elems elements.
-template <bool BF16, rs_mode MODE>
-void rs_launch(int P, int L, const void *const *grad_tab, int32_t max_workgroups, int prio, int64_t n_tiles,
-               int64_t n_elems, hipStream_t st, const dear_tile *tiles, const rs_sink<MODE> &o)
+// What a reduce-scatter launch is made from.  tiles, grads: device tables (a context's, or the static scratch's); the
+// tiles hold n_elems elements.
+struct rs_call {
+    int P, L;
+    const void *const *grads;
+    int32_t max_workgroups;
+    int prio;
+    const dear_tile *tiles;
+    int64_t n_tiles, n_elems;
+    hipStream_t st;
+};
+
+template <bool BF16, rs_mode MODE, int U, int CH, bool TAIL>
+void rs_launch_as(const rs_call &c, const rs_sink<MODE> &o)
 {
-    constexpr int U = BF16 ? DEAR_RS_U_BF16 : DEAR_RS_U_F32;
     constexpr int SPLIT = DEAR_TILE_ELEMS / ((BF16 ? 8 : 4) * DEAR_BLOCK * U);
-    const unsigned n_items = static_cast<unsigned>(n_tiles * SPLIT);
-    const dim3 grid(grid_width(max_workgroups, n_items)), block(DEAR_BLOCK);
-    const bool bounded = grid.x < n_items;
-    const unsigned lds =
-        bounded ? 0 : residency_lds(reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, P, n_elems, n_tiles));
-    const float inv_P = 1.0f / static_cast<float>(P);
-#define RS_LAUNCH(CH, TAIL)                                                                              \
-    do {                                                                                                 \
-        if (bounded)                                                                                     \
-            reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, true><<<grid, block, 0, st>>>(              \
-                tiles, grad_tab, L, P, inv_P, o, n_items, prio);                                         \
-        else                                                                                             \
-            reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, false><<<grid, block, lds, st>>>(           \
-                tiles, grad_tab, L, P, inv_P, o, n_items, 0);                                            \
-    } while (0)
-    // replicas per load batch: the largest of 8/4/2/1 that divides P without a tail when
-    // P is small or a multiple of 4; otherwise batches of 8 with a predicated tail
-    if (P % 8 == 0)
-        RS_LAUNCH(8, false);
-    else if (P % 4 == 0)
-        RS_LAUNCH(4, false);
-    else if (P == 2)
-        RS_LAUNCH(2, false);
-    else if (P == 1)
-        RS_LAUNCH(1, false);
+    const unsigned n_items = static_cast<unsigned>(c.n_tiles * SPLIT);
+    const dim3 grid(grid_width(c.max_workgroups, n_items)), block(DEAR_BLOCK);
+    const float inv_P = 1.0f / static_cast<float>(c.P);
+    if (grid.x < n_items) {
+        reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, true>
+            <<<grid, block, 0, c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, c.prio);
+        return;
+    }
+    const unsigned lds = residency_lds(reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, c.P, c.n_elems, c.n_tiles));
+    reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, false>
+        <<<grid, block, lds, c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, 0);
+}
+
+// Replicas per load batch: the largest of 8/4/2/1 that divides P without a tail when
+// P is small or a multiple of 4; otherwise batches of 8 with a predicated tail.
+template <bool BF16, rs_mode MODE, int U>
+void rs_launch_batched(const rs_call &c, const rs_sink<MODE> &o)
+{
+    if (c.P % 8 == 0)
+        rs_launch_as<BF16, MODE, U, 8, false>(c, o);
+    else if (c.P % 4 == 0)
+        rs_launch_as<BF16, MODE, U, 4, false>(c, o);
+    else if (c.P == 2)
+        rs_launch_as<BF16, MODE, U, 2, false>(c, o);
+    else if (c.P == 1)
+        rs_launch_as<BF16, MODE, U, 1, false>(c, o);
     else
-        RS_LAUNCH(8, true);
-#undef RS_LAUNCH
+        rs_launch_as<BF16, MODE, U, 8, true>(c, o);
+}
+
+template <rs_mode MODE>
+void rs_launch(bool bf16, const rs_call &c, const rs_sink<MODE> &o)
+{
+    if (!bf16)
+        rs_launch_batched<false, MODE, 1>(c, o);
+    else if (reduce_scatter_half_tiles((MODE & RS_UPDATE) != 0, c.max_workgroups, c.n_tiles))
+        rs_launch_batched<true, MODE, 1>(c, o);
+    else
+        rs_launch_batched<true, MODE, 2>(c, o);
 }
 
 constexpr size_t SHIFT_TILES = 8;
@@ -1062,10 +1088,7 @@ int launch_reduce_scatter(const dear_ctx_impl *c, bucket_range r, const rs_sink<
     if (count == 0) return DEAR_OK;
     const int64_t elems = elements_of(c->bucket_len, r);
     const dear_tile *tiles = c->d_tiles + c->tile_begin[r.begin];
-    if (c->g == 2)
-        rs_launch<true, MODE>(c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, count, elems, st, tiles, o);
-    else
-        rs_launch<false, MODE>(c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, count, elems, st, tiles, o);
+    rs_launch<MODE>(c->g == 2, rs_call{c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, tiles, count, elems, st}, o);
     return launch_status();
 }
 
@@ -1114,9 +1137,12 @@ int launch_all_gather(const dear_ctx_impl *c, bucket_range r, const float *shard
     } else {
         constexpr unsigned chunk = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK);
         const unsigned n_parts = static_cast<unsigned>(count * AG_SPLIT), n_p = static_cast<unsigned>(n_workers);
-        const unsigned len = n_parts % chunk ? n_parts % chunk : 1;
-        all_gather_kernel<<<dim3(n_parts * n_p), dim3(DEAR_BLOCK), 0, st>>>(
-            tiles, c->d_param, c->L, first_worker, n_p, shard_param, n_parts, 0xffffffffu / n_p, 0xffffffffu / len);
+        const unsigned whole = n_parts / chunk * chunk;
+        const all_gather_order o = all_gather_numbering(c->g, c->max_workgroups, whole, n_parts, n_workers);
+        const auto kernel = o.run ? all_gather_kernel<1> : all_gather_kernel<0>;
+        kernel<<<dim3((whole + o.len) * n_p), dim3(DEAR_BLOCK), 0, st>>>(
+            tiles, c->d_param, c->L, first_worker, n_p, shard_param, n_parts, 0xffffffffu / n_p, o.len,
+            0xffffffffu / (o.len ? o.len : 1));
     }
     return launch_status();
 }
@@ -1386,9 +1412,6 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
     const dear_tile *tiles = reinterpret_cast<const dear_tile *>(dev + tiles_at);
     const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f};
     const int64_t elems = elements_of(plan->bucket_len, bucket_range{b_first, b_last});
-    if (plan->g == 2)
-        rs_launch<true, RS_GBAR>(plan->P, plan->L, grad_tab, 0, 0, n_tiles, elems, st, tiles, o);
-    else
-        rs_launch<false, RS_GBAR>(plan->P, plan->L, grad_tab, 0, 0, n_tiles, elems, st, tiles, o);
+    rs_launch<RS_GBAR>(plan->g == 2, rs_call{plan->P, plan->L, grad_tab, 0, 0, tiles, n_tiles, elems, st}, o);
     return launch_status();
 }

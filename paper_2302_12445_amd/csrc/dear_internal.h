@@ -6,6 +6,12 @@
 
 #include "dear.h"
 
+#ifdef __HIPCC__
+#define DEAR_HOST_DEVICE __host__ __device__
+#else
+#define DEAR_HOST_DEVICE
+#endif
+
 struct dear_plan_s {
     int32_t L = 0, B = 0, P = 0, g = 0;
     int64_t threshold_bytes = 0;
@@ -40,6 +46,38 @@ inline bool all_gather_fits(int64_t tiles, int64_t n_workers, int64_t max_workgr
     const int64_t items = tiles * AG_SPLIT * n_workers;
     if (!all_gather_bounded(tiles, n_workers, max_workgroups)) return items <= MAX_GRID;
     return items <= 0x7fffffff && (max_workgroups <= MAX_GRID || tiles <= MAX_GRID);
+}
+
+// A bf16 reduce-scatter takes half a tile a workgroup (one 16-byte vector a lane instead of two) where a launch is so
+// short that whole tiles leave CUs idle, and, with the update, as long as the all-gather behind it finds w in L2, which
+// it does better in halves (see all_gather_kernel).  GPU time, us, whole tiles / halves: reduce-scatter alone P = 8 0.2 M
+// elements 4.47 / 4.06, 0.4 M 4.83 / 4.38, 0.8 M 5.39 / 5.41, 1.6 M 7.32 / 7.71; P = 32 0.4 M 11.9 / 10.8, 1.6 M 21.6 / 22.5;
+// iteration P = 4 0.3 M 8.10 / 7.44, 2 M 17.8 / 17.2, 6 M 41.8 / 41.6; P = 8 0.3 M 10.3 / 8.9, 1 M 15.6 / 14.7, 3 M 34.7 / 34.6,
+// 10 M 101.1 / 101.6; P = 16 0.3 M 14.6 / 12.5, 1 M 24.3 / 23.3, 3 M 56.2 / 55.7, 6 M 108.5 / 110.9.
+inline bool reduce_scatter_half_tiles(bool updates, int64_t max_workgroups, int64_t tiles)
+{
+    return max_workgroups <= 0 && tiles <= (updates ? 1024 : 160);
+}
+
+// How the unbounded all-gather numbers its workgroups (see all_gather_kernel).  Where HIP would not take a launch with a
+// rounded last chunk, that chunk stays as it falls.
+struct all_gather_order {
+    unsigned len, run;
+};
+
+// Part of a chunk that a replica's r-th workgroup takes: XCD r % 8 takes 2^run parts in a row out of every 8 * 2^run.
+DEAR_HOST_DEVICE inline unsigned all_gather_part(unsigned r, unsigned run)
+{
+    return (r & ~((8u << run) - 1)) | (r & 7) << run | (r >> 3 & ((1u << run) - 1));
+}
+
+inline all_gather_order all_gather_numbering(int grad_bytes, int64_t max_workgroups, unsigned whole, unsigned parts, int64_t n_workers)
+{
+    const unsigned last = parts - whole;
+    const unsigned run = grad_bytes == 2 && reduce_scatter_half_tiles(true, max_workgroups, parts / AG_SPLIT) ? 1 : 0;
+    const unsigned rounded = (last + (8u << run) - 1) & ~((8u << run) - 1);
+    if ((static_cast<int64_t>(whole) + rounded) * n_workers > MAX_GRID) return {last, 0};
+    return {rounded, run};
 }
 
 // dear_update_all_gather as one kernel writes all P replicas from the workgroup that updated: P write streams at

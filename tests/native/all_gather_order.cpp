@@ -1,0 +1,36 @@
+// Host-only check of the all-gather's numbering (dear_internal.h): for every replica, each part of a launch belongs to
+// exactly one workgroup, in chunks and behind them, whatever the part count.  Exits non-zero on the first mistake.
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+
+#include "dear_internal.h"
+
+int main()
+{
+    const unsigned chunk = 4096;
+    for (int g = 2; g <= 4; g += 2)
+        for (int64_t width : {0, 256})
+            for (int64_t P : {int64_t(1), int64_t(7), int64_t(64), int64_t(4095), int64_t(4096), int64_t(5000), MAX_GRID / 4})
+                for (unsigned tiles : {1u, 2u, 3u, 4u, 5u, 511u, 1021u, 1023u, 1024u, 1025u, 1026u, 2047u, 2048u, 2049u}) {
+                    const unsigned parts = tiles * AG_SPLIT;
+                    if (!all_gather_fits(tiles, P, 0)) continue;
+                    const unsigned whole = parts / chunk * chunk;
+                    const all_gather_order o = all_gather_numbering(g, width, whole, parts, P);
+                    std::vector<int> seen(parts, 0);
+                    for (unsigned r = 0; r < whole + o.len; ++r) {
+                        const unsigned first = r < whole ? r / chunk * chunk : whole;
+                        const unsigned id = first + all_gather_part(r - first, o.run);
+                        if (id < parts) ++seen[id];
+                    }
+                    bool ok = (whole + int64_t(o.len)) * P <= MAX_GRID;
+                    for (int n : seen) ok = ok && n == 1;
+                    if (!ok) {
+                        std::fprintf(stderr, "FAILED g=%d width=%d P=%lld tiles=%u\n", g, int(width), (long long)P, tiles);
+                        std::exit(1);
+                    }
+                }
+    std::printf("all_gather_order: ok\n");
+    return 0;
+}
