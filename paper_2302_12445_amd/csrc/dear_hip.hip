@@ -230,8 +230,10 @@ __device__ __forceinline__ void wave_lds_sync()
 //              element; with it only the re-read is saved;
 //   RS_W_NEXT  the next launch reads w, and finds it in the 256 MB last-level cache (iteration_caches_w): w is stored
 //              with the ordinary cache policy.
+//   RS_GATHER  (with RS_UPDATE) the new w goes to every replica's layer tensor from the registers it was computed in: the
+//              whole iteration in one launch, and no launch reads w again (iteration_gathers_at_once).
 typedef int rs_mode;
-constexpr rs_mode RS_GBAR = 1, RS_UPDATE = 2, RS_W_NEXT = 4;
+constexpr rs_mode RS_GBAR = 1, RS_UPDATE = 2, RS_W_NEXT = 4, RS_GATHER = 8;
 
 template <rs_mode MODE>
 struct rs_sink {
@@ -239,6 +241,7 @@ struct rs_sink {
     float *__restrict__ w;  // RS_UPDATE: parameter shards
     float *__restrict__ v;  // RS_UPDATE: momentum shards
     float lr, mu;
+    float *const *__restrict__ params;  // RS_GATHER: [P*L] layer tensors
 };
 
 __device__ __forceinline__ void sgd_momentum(float gbar, float &w, float &v, float lr, float mu)
@@ -250,9 +253,9 @@ __device__ __forceinline__ void sgd_momentum(float gbar, float &w, float &v, flo
 }
 
 // One 16-byte piece of results at shard-buffer element index `idx` (4-byte aligned).  Callers
-// that update pass the slot's w and v, loaded early so the loads overlap the gradient loads.
+// that update pass the slot's w and v, loaded early so the loads overlap the gradient loads; returns the new w.
 template <rs_mode MODE>
-__device__ __forceinline__ void emit_piece(const rs_sink<MODE> &o, int64_t idx, f4 gbar, f4 w, f4 v)
+__device__ __forceinline__ f4 emit_piece(const rs_sink<MODE> &o, int64_t idx, f4 gbar, f4 w, f4 v)
 {
     if (MODE & RS_GBAR) store_f4_dword_aligned<DEAR_RS_NT_STORE>(o.g + idx, gbar);
     if (MODE & RS_UPDATE) {
@@ -266,18 +269,22 @@ __device__ __forceinline__ void emit_piece(const rs_sink<MODE> &o, int64_t idx, 
         store_f4_dword_aligned<DEAR_RS_NT_STORE>(o.v + idx, v);
         store_f4_dword_aligned<DEAR_RS_NT_STORE && !(MODE & RS_W_NEXT)>(o.w + idx, w);
     }
+    return w;
 }
 
 template <rs_mode MODE>
-__device__ __forceinline__ void emit_elem(const rs_sink<MODE> &o, int64_t idx, float gbar)
+__device__ __forceinline__ float emit_elem(const rs_sink<MODE> &o, int64_t idx, float gbar)
 {
+    float w = 0.0f;
     if (MODE & RS_GBAR) o.g[idx] = gbar;
     if (MODE & RS_UPDATE) {
-        float w = o.w[idx], v = o.v[idx];
+        float v = o.v[idx];
+        w = o.w[idx];
         sgd_momentum(gbar, w, v, o.lr, o.mu);
         o.v[idx] = v;
         o.w[idx] = w;
     }
+    return w;
 }
 
 // Body of the reduce-scatter for one workgroup's part of a tile.  ALL_FULL: the tile is a
@@ -305,6 +312,9 @@ __device__ __forceinline__ void reduce_scatter_tile(const dear_tile &t, int part
     int64_t vi[U];
     bool full[U];
     int64_t piece_idx[U][PIECES];  // shard-buffer element index of each result piece
+    f4 w_new[U][PIECES];           // only RS_GATHER reads these three: new w of the pieces,
+    float edge_w = 0.0f;           // of the lane's element of a partial vector,
+    int64_t edge = -1;             // and that element, if the lane has one
     float acc[U][VE];
     f4 w_old[U][PIECES] = {}, v_old[U][PIECES] = {};  // only the updating sinks read them
 #pragma unroll
@@ -368,40 +378,56 @@ __device__ __forceinline__ void reduce_scatter_tile(const dear_tile &t, int part
             const f4 o0 = *reinterpret_cast<const f4 *>(sw + 4 * lane);
             const f4 o1 = *reinterpret_cast<const f4 *>(sw + 256 + 4 * lane);
             wave_lds_sync();
-            emit_piece<MODE>(o, piece_idx[u][0], o0, w_old[u][0], v_old[u][0]);
-            emit_piece<MODE>(o, piece_idx[u][PIECES - 1], o1, w_old[u][PIECES - 1], v_old[u][PIECES - 1]);
+            w_new[u][0] = emit_piece<MODE>(o, piece_idx[u][0], o0, w_old[u][0], v_old[u][0]);
+            w_new[u][PIECES - 1] =
+                emit_piece<MODE>(o, piece_idx[u][PIECES - 1], o1, w_old[u][PIECES - 1], v_old[u][PIECES - 1]);
         }
-        return;
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (full[u]) {
+#pragma unroll
+                for (int h = 0; h < PIECES; ++h) {
+                    f4 r;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) r[j] = acc[u][4 * h + j] * inv_P;
+                    w_new[u][h] = emit_piece<MODE>(o, piece_idx[u][h], r, w_old[u][h], v_old[u][h]);
+                }
+            }
     }
 
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-        if (full[u]) {
-#pragma unroll
-            for (int h = 0; h < PIECES; ++h) {
-                f4 r;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) r[j] = acc[u][4 * h + j] * inv_P;
-                emit_piece<MODE>(o, piece_idx[u][h], r, w_old[u][h], v_old[u][h]);
-            }
-        }
-
     if (!ALL_FULL) {
-        const int64_t e = edge_element<VE>(a, c, v_first, U * DEAR_BLOCK);  // CH replicas loaded together as above
-        if (e >= 0) {
+        edge = edge_element<VE>(a, c, v_first, U * DEAR_BLOCK);  // CH replicas loaded together as above
+        if (edge >= 0) {
             float s = -0.0f;
             for (int k0 = 0; k0 < P; k0 += CH) {
                 float x[CH];
 #pragma unroll
                 for (int kk = 0; kk < CH; ++kk) {
                     const int k = (!TAIL || k0 + kk < P) ? k0 + kk : 0;
-                    x[kk] = grad_elem<BF16>(grad_tab[(size_t)ring_worker(start, k, P) * L + t.layer], e);
+                    x[kk] = grad_elem<BF16>(grad_tab[(size_t)ring_worker(start, k, P) * L + t.layer], edge);
                 }
 #pragma unroll
                 for (int kk = 0; kk < CH; ++kk)
                     if (!TAIL || k0 + kk < P) s = s + x[kk];
             }
-            emit_elem<MODE>(o, t.dst_begin + (e - a), s * inv_P);
+            edge_w = emit_elem<MODE>(o, t.dst_begin + (edge - a), s * inv_P);
+        }
+    }
+
+    if constexpr ((MODE & RS_GATHER) != 0) {
+        const int64_t to_layer = a - t.dst_begin;  // from a slot's index to that of its element in the layer
+#pragma unroll 4
+        for (int q = 0; q < P; ++q) {
+            DEAR_GLOBAL float *out = (DEAR_GLOBAL float *)o.params[(size_t)q * L + t.layer];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (full[u]) {
+#pragma unroll
+                    for (int h = 0; h < PIECES; ++h)
+                        store_vec<DEAR_AG_NT_STORE>((global_f4_out)(out + (to_layer + piece_idx[u][h])), w_new[u][h]);
+                }
+            if (!ALL_FULL && edge >= 0) out[edge] = edge_w;
         }
     }
 }
@@ -918,14 +944,19 @@ void rs_launch_as(const rs_call &c, const rs_sink<MODE> &o)
     const unsigned n_items = static_cast<unsigned>(c.n_tiles * SPLIT);
     const dim3 grid(grid_width(c.max_workgroups, n_items)), block(DEAR_BLOCK);
     const float inv_P = 1.0f / static_cast<float>(c.P);
-    if (grid.x < n_items) {
-        reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, true>
-            <<<grid, block, 0, c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, c.prio);
-        return;
+    int residency = 0;
+    if constexpr ((MODE & RS_GATHER) != 0) {  // never bounded
+        residency = iteration_at_once_residency(BF16, c.n_elems, c.n_tiles);
+    } else {
+        if (grid.x < n_items) {
+            reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, true>
+                <<<grid, block, 0, c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, c.prio);
+            return;
+        }
+        residency = reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, c.P, c.n_elems, c.n_tiles);
     }
-    const unsigned lds = residency_lds(reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, c.P, c.n_elems, c.n_tiles));
     reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, false>
-        <<<grid, block, lds, c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, 0);
+        <<<grid, block, residency_lds(residency), c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, 0);
 }
 
 // Replicas per load batch: the largest of 8/4/2/1 that divides P without a tail when
@@ -950,7 +981,8 @@ void rs_launch(bool bf16, const rs_call &c, const rs_sink<MODE> &o)
 {
     if (!bf16)
         rs_launch_batched<false, MODE, 1>(c, o);
-    else if (reduce_scatter_half_tiles((MODE & RS_UPDATE) != 0, c.max_workgroups, c.n_tiles))
+    else if ((MODE & RS_GATHER) ? iteration_at_once_half_tiles(c.n_elems, c.n_tiles)
+                                : reduce_scatter_half_tiles((MODE & RS_UPDATE) != 0, c.max_workgroups, c.n_tiles))
         rs_launch_batched<true, MODE, 1>(c, o);
     else
         rs_launch_batched<true, MODE, 2>(c, o);
@@ -1171,7 +1203,7 @@ extern "C" int dear_reduce_scatter(dear_ctx_t *c, int32_t bucket, float *shard_g
     int rc = check_call(c, bucket);
     if (rc == DEAR_OK) rc = check_shard_buffer(shard_grad);
     if (rc != DEAR_OK) return rc;
-    const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f};
+    const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f, nullptr};
     return launch_reduce_scatter(c, buckets_of(c, bucket), o, static_cast<hipStream_t>(hip_stream));
 }
 
@@ -1181,7 +1213,7 @@ extern "C" int dear_reduce_scatter_update(dear_ctx_t *c, int32_t bucket, float *
     int rc = check_call(c, bucket);
     if (rc == DEAR_OK) rc = check_update_buffers(shard_param, shard_mom);
     if (rc != DEAR_OK) return rc;
-    const rs_sink<RS_UPDATE> o{nullptr, shard_param, shard_mom, lr, momentum};
+    const rs_sink<RS_UPDATE> o{nullptr, shard_param, shard_mom, lr, momentum, nullptr};
     return launch_reduce_scatter(c, buckets_of(c, bucket), o, static_cast<hipStream_t>(hip_stream));
 }
 
@@ -1243,16 +1275,16 @@ extern "C" int dear_all_gather(dear_ctx_t *c, int32_t bucket, const float *shard
 
 namespace {
 
-// Reduce-scatter and update of a group in one kernel, gbar stored only where it is wanted.
-template <rs_mode W_NEXT>
+// Reduce-scatter and update of a group in one kernel, gbar stored only where it is wanted; MORE: RS_W_NEXT or RS_GATHER.
+template <rs_mode MORE>
 int launch_reduce_scatter_update(const dear_ctx_impl *c, bucket_range r, float *shard_grad, float *shard_param,
                                  float *shard_mom, float lr, float momentum, hipStream_t st)
 {
     if (shard_grad) {
-        const rs_sink<RS_GBAR | RS_UPDATE | W_NEXT> o{shard_grad, shard_param, shard_mom, lr, momentum};
+        const rs_sink<RS_GBAR | RS_UPDATE | MORE> o{shard_grad, shard_param, shard_mom, lr, momentum, c->d_param};
         return launch_reduce_scatter(c, r, o, st);
     }
-    const rs_sink<RS_UPDATE | W_NEXT> o{nullptr, shard_param, shard_mom, lr, momentum};
+    const rs_sink<RS_UPDATE | MORE> o{nullptr, shard_param, shard_mom, lr, momentum, c->d_param};
     return launch_reduce_scatter(c, r, o, st);
 }
 
@@ -1277,11 +1309,13 @@ extern "C" int dear_iteration(dear_ctx_t *c, int32_t bucket, float *shard_grad, 
         if (!all_gather_fits(tiles_of(c, r), c->P, c->max_workgroups)) return DEAR_EINVAL;
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (iteration_gathers_at_once(c->g, c->P, elements_of(c->bucket_len, all), tiles_of(c, all), shard_grad != nullptr, c->max_workgroups))
+        return launch_reduce_scatter_update<RS_GATHER>(c, all, shard_grad, shard_param, shard_mom, lr, momentum, st);
     for (bucket_range r{0, all.begin}; rc == DEAR_OK && r.end < all.end;) {
         r = group_from(r.end);
         const int64_t tiles = tiles_of(c, r);
         if (shard_grad && iteration_updates_apart(c->g, c->P, tiles)) {
-            const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f};
+            const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f, nullptr};
             rc = launch_reduce_scatter(c, r, o, st);
             if (rc == DEAR_OK) rc = launch_update(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
         } else if (iteration_caches_w(c->g, c->P, tiles, c->tile_begin[c->B])) {
@@ -1410,7 +1444,7 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
     }
     const void *const *grad_tab = reinterpret_cast<const void *const *>(dev);
     const dear_tile *tiles = reinterpret_cast<const dear_tile *>(dev + tiles_at);
-    const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f};
+    const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f, nullptr};
     const int64_t elems = elements_of(plan->bucket_len, bucket_range{b_first, b_last});
     rs_launch<RS_GBAR>(plan->g == 2, rs_call{plan->P, plan->L, grad_tab, 0, 0, tiles, n_tiles, elems, st}, o);
     return launch_status();

@@ -181,3 +181,49 @@ inline bool iteration_updates_apart(int grad_bytes, int64_t P, int64_t group_til
 {
     return grad_bytes * P >= 96 && group_tiles >= 2048;
 }
+
+// Whether dear_iteration takes everything in ONE launch, each workgroup storing the new w of its elements to all replicas.
+// That saves a launch (2 us of GPU time, 3 of the host's), the 4-byte re-read of w, and the all-gather's empty workgroups
+// for the parts of tiles that short tensors leave open (`open` elements); but the replicas are written as P interleaved
+// streams.  As long as the writes go to the 256 MB last-level cache that does not matter; HBM takes it the worse the more
+// streams there are, and from large calls with few replicas the re-read costs more.  GPU time, us, without gbar, two launches / one
+// (three sets of buffers in turn, spread 1 %):
+//   fp32  P = 2 0.2 M elements 5.7 / 4.1  1 M 8.9 / 6.9  4 M 25.7 / 22.9  10 M 55.6 / 53.2  40 M 237 / 207  100 M 607 / 512
+//         P = 3 1 M 10.0 / 8.3  4 M 30.0 / 28.6  6 M 41.2 / 41.7  20 M 129 / 129  30 M 208 / 194  100 M 720 / 639
+//         P = 4 1 M 11.3 / 9.8  3 M 26.8 / 26.8  6 M 48.1 / 50.0  20 M 155 / 160  50 M 402 / 383 (with gbar 429 / 430)
+//         P = 8 0.2 M 7.5 / 6.7  1 M 15.9 / 15.2  1.5 M 22.2 / 22.8  6 M 78.8 / 85.5  P = 12 0.5 M 13.4 / 13.2  1 M 22.6 / 23.8
+//         P = 16 0.2 M 11.3 / 11.8  1 M 27.1 / 30.8
+//         open tiles: P = 8 1 M in 500 tensors 27.3 / 22.4, 2 M in 200 34.2 / 34.1, 3 M in 500 50.2 / 50.7;
+//         P = 16 1 M in 500 47.8 / 39.7, in 60 29.0 / 32.0, 3 M in 500 86.3 / 93.2
+//   bf16  P = 2 1 M 8.9 / 6.6  6 M 33.4 / 31.0  20 M 92.2 / 97.1  30 M 150 / 145  100 M 514 / 481
+//         P = 4 1 M 10.7 / 8.7  3 M 24.1 / 22.8  6 M 42.8 / 43.9  P = 8 0.5 M 10.3 / 9.2  1.5 M 19.3 / 18.5  3 M 34.3 / 35.2
+//         P = 12 0.5 M 13.2 / 12.8  1 M 18.6 / 19.2  P = 16 0.2 M 11.2 / 11.9  1 M 22.9 / 25.3, in 500 tensors 46.2 / 37.7
+inline bool iteration_gathers_at_once(int grad_bytes, int64_t P, int64_t elems, int64_t tiles, bool with_gbar, int64_t max_workgroups)
+{
+    constexpr int64_t M = 1000000;
+    if (max_workgroups > 0 || tiles * AG_SPLIT > MAX_GRID) return false;
+    const bool bf16 = grad_bytes == 2;
+    const int64_t open = tiles * DEAR_TILE_ELEMS - elems;
+    const int64_t cached = P > 12 ? 0 : P > 8 ? (bf16 ? 7 : 6) * M : (bf16 ? 12 : 9) * M;
+    if (P * (elems - open) <= cached) return true;
+    if (bf16) return P <= 2 && elems >= 25 * M;
+    return P <= 2 || (P == 3 && elems >= 25 * M) || (P == 4 && elems >= (with_gbar ? 64 : 40) * M);
+}
+
+// Workgroups per CU of such a launch (see reduce_scatter_residency), 0 for as many as fit: us at as many / 2 / 1, fp32
+// with gbar P = 2 5 M 32.8 / 31.6 / 38.9, 100 M 640 / 579 / 703, P = 3 100 M 788 / 722 / 878, without P = 4 100 M 854 / 776 / 876;
+// bf16 with gbar, half tiles, P = 2 30 M - / 180 / 161, 100 M 596 / 594 / 525.
+inline int iteration_at_once_residency(bool bf16, int64_t elems, int64_t tiles)
+{
+    if (elems * 5 < tiles * (4 * DEAR_TILE_ELEMS)) return 0;
+    if (bf16) return elems >= 25000000 ? 1 : 0;
+    return elems >= 4000000 ? 2 : 0;
+}
+
+// bf16, half tiles a workgroup in such a launch: where whole ones would leave the 256 CUs unevenly filled (P = 4 0.5 M
+// 7.2 / 6.3, 1.5 M 13.4 / 12.3, 2 M 15.0 / 15.7, P = 8 0.5 M 10.1 / 9.2, 1.5 M 19.9 / 18.5, 2 M 24.3 / 24.7), and in large ones (P = 2
+// 100 M 599 / 525 with one workgroup per CU or as many as fit, which is what each likes best).
+inline bool iteration_at_once_half_tiles(int64_t elems, int64_t tiles)
+{
+    return tiles <= 400 || elems >= 25000000;
+}

@@ -1,5 +1,6 @@
-// Host-only check of the all-gather's numbering (dear_internal.h): for every replica, each part of a launch belongs to
-// exactly one workgroup, in chunks and behind them, whatever the part count.  Exits non-zero on the first mistake.
+// Host-only check (dear_internal.h) of the all-gather's numbering -- for every replica, each part of a launch belongs to
+// exactly one workgroup, in chunks and behind them, whatever the part count -- and of the rule that takes a whole iteration in
+// one launch: none that HIP would not take, none with a bounded grid.  Exits non-zero on the first mistake.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -31,6 +32,21 @@ int main()
                         std::exit(1);
                     }
                 }
-    std::printf("all_gather_order: ok\n");
+    for (int g = 2; g <= 4; g += 2)
+        for (int64_t P = 1; P <= 70; ++P)
+            for (int64_t elems = 1; elems < int64_t(1) << 38; elems *= 3)
+                for (int64_t tiles : {elems / DEAR_TILE_ELEMS + P, elems / 700 + P, MAX_GRID / AG_SPLIT, MAX_GRID / AG_SPLIT + 1}) {
+                    bool ok = true;
+                    for (bool gbar : {false, true}) {
+                        const bool once = iteration_gathers_at_once(g, P, elems, tiles, gbar, 0);
+                        ok = ok && !iteration_gathers_at_once(g, P, elems, tiles, gbar, 256) && (!once || tiles * AG_SPLIT <= MAX_GRID);
+                        if (once && P > 4) ok = ok && P * (2 * elems - tiles * DEAR_TILE_ELEMS) <= 12000000;
+                    }
+                    if (!ok) {
+                        std::fprintf(stderr, "FAILED at once g=%d P=%lld elems=%lld tiles=%lld\n", g, (long long)P, (long long)elems, (long long)tiles);
+                        std::exit(1);
+                    }
+                }
+    std::printf("launch_order: ok\n");
     return 0;
 }

@@ -1,5 +1,5 @@
-"""Which workgroup takes what: the all-gather's numbering on the host, and launches at the sizes where it and the form
-of the bf16 reduce-scatter change, against the oracle."""
+"""Which workgroup takes what: the rules on the host, and launches at the sizes where the all-gather's numbering, the form of
+the bf16 reduce-scatter and the number of an iteration's launches change, against the oracle."""
 from __future__ import annotations
 
 import os
@@ -12,11 +12,11 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
-def test_all_gather_order(tmp_path):
-    exe = str(tmp_path / "all_gather_order")
+def test_order_and_rules_on_the_host(tmp_path):
+    exe = str(tmp_path / "launch_order")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2302_12445_amd", "csrc"),
-                    os.path.join(ROOT, "tests", "native", "all_gather_order.cpp"), "-o", exe], check=True)
-    assert "all_gather_order: ok" in subprocess.run([exe], check=True, capture_output=True, text=True).stdout
+                    os.path.join(ROOT, "tests", "native", "launch_order.cpp"), "-o", exe], check=True)
+    assert "launch_order: ok" in subprocess.run([exe], check=True, capture_output=True, text=True).stdout
 
 
 def list_of_tiles(tiles, P, g):
@@ -41,4 +41,24 @@ def test_launches_around_the_limits(dtype, tiles):
     pair = Pair(small_workload(list_of_tiles(tiles, 3, 2 if dtype == "bf16" else 4), 3, W.NO_LIMIT, dtype))
     for route, fused in (("calls", False), ("calls", True), ("iteration", False), ("iteration", True)):
         pair.run(iterations=1, route=route, fused=fused)
+    pair.close()
+
+
+# one launch / several: below and above the limit for the replica count, few-replica calls with one and two workgroups per
+# CU, thousands of open tiles, run ends of every alignment
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,P,sizes", [
+    ("f32", 1, [1]), ("f32", 1, [4_100_003, 5]), ("f32", 2, [4_000_000, 300_001]), ("f32", 3, [25_000_001, 77]), ("f32", 5, [1_790_000]),
+    ("f32", 5, [1_810_001]), ("f32", 8, [1_125_000 - 4096]), ("f32", 11, [530_003]), ("f32", 16, [701] * 900), ("f32", 33, [77, 200] * 40),
+    ("bf16", 1, [9, 4096, 3]), ("bf16", 2, [1_650_000, 9]), ("bf16", 2, [25_000_100]), ("bf16", 7, [1_600_003, 33]), ("bf16", 8, [1_500_000 + 4096]),
+    ("bf16", 12, [577_777, 3]), ("bf16", 24, [1000, 64, 33] * 300), ("bf16", 6, list(range(1, 19)) + [4096 + k for k in range(9)] + [2047, 2049]),
+])
+def test_iteration_in_one_launch(dtype, P, sizes):
+    from test_gpu_parity import Pair, say, small_workload
+    import workloads as W
+    say("case: iteration, %s, P=%d, %d tensors, %d elements" % (dtype, P, len(sizes), sum(sizes)))
+    pair = Pair(small_workload(sizes, P, W.NO_LIMIT, dtype))
+    pair.run(iterations=2 if sum(sizes) * P < 20_000_000 else 1, route="iteration")
+    pair.run(iterations=1, route="iteration", fused=True)
+    pair.run(iterations=1, route="iteration", width=64)
     pair.close()
