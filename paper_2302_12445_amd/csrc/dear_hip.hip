@@ -630,12 +630,11 @@ __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_kernel(
     if (chunk >= whole) {
         chunk = whole;
         q = divide(blockIdx.x - whole * CHUNK * n_p, len, inv_len, r);
-        if (chunk * CHUNK + all_gather_part(r, RUN) >= n_parts) return;
     }
     const unsigned id = chunk * CHUNK + all_gather_part(r, RUN);
     const dear_tile t = tiles[id / AG_SPLIT];
     const int part = id % AG_SPLIT;
-    if (t.layer < 0) return;
+    if (t.layer < 0 || id >= n_parts) return;  // behind the last part: a tile beyond the launch's, or the table's room
     const float *__restrict__ src = shard_param + t.dst_begin;
     float *const DEAR_CONSTANT *out =
         (float *const DEAR_CONSTANT *)param_tab + ((size_t)((unsigned)p_first + q) * (unsigned)L + (unsigned)t.layer);
@@ -925,15 +924,15 @@ unsigned grid_width(int32_t max_workgroups, int64_t n_items)
 // LDS that a launch reserves for each workgroup, and nothing uses, so that `residency` of them share a CU's 160 KiB.
 unsigned residency_lds(int residency) { return residency == 1 ? 96 << 10 : residency == 2 ? 64 << 10 : 0; }
 
-// What a reduce-scatter launch is made from.  tiles, grads: device tables (a context's, or the static scratch's); the
-// tiles hold n_elems elements.
+// What a reduce-scatter launch is made from.  tiles, grads: device tables (a context's, or the static scratch's).  The
+// launch may be one of several over all_tiles tiles, which hold all_elems elements.
 struct rs_call {
     int P, L;
     const void *const *grads;
     int32_t max_workgroups;
     int prio;
     const dear_tile *tiles;
-    int64_t n_tiles, n_elems;
+    int64_t n_tiles, all_tiles, all_elems;
     hipStream_t st;
 };
 
@@ -946,14 +945,14 @@ void rs_launch_as(const rs_call &c, const rs_sink<MODE> &o)
     const float inv_P = 1.0f / static_cast<float>(c.P);
     int residency = 0;
     if constexpr ((MODE & RS_GATHER) != 0) {  // never bounded
-        residency = iteration_at_once_residency(BF16, c.n_elems, c.n_tiles);
+        residency = iteration_at_once_residency(BF16, c.all_elems, c.all_tiles);
     } else {
         if (grid.x < n_items) {
             reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, true>
                 <<<grid, block, 0, c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, c.prio);
             return;
         }
-        residency = reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, c.P, c.n_elems, c.n_tiles);
+        residency = reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, c.P, c.all_elems, c.all_tiles);
     }
     reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, false>
         <<<grid, block, residency_lds(residency), c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, 0);
@@ -981,7 +980,7 @@ void rs_launch(bool bf16, const rs_call &c, const rs_sink<MODE> &o)
 {
     if (!bf16)
         rs_launch_batched<false, MODE, 1>(c, o);
-    else if ((MODE & RS_GATHER) ? iteration_at_once_half_tiles(c.n_elems, c.n_tiles)
+    else if ((MODE & RS_GATHER) ? iteration_at_once_half_tiles(c.all_elems, c.n_tiles)
                                 : reduce_scatter_half_tiles((MODE & RS_UPDATE) != 0, c.max_workgroups, c.n_tiles))
         rs_launch_batched<true, MODE, 1>(c, o);
     else
@@ -1047,7 +1046,7 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
         c->bucket_shard_base = plan->bucket_shard_base;
         c->layer_sizes = plan->layer_sizes;
         dear_build_tiles(*plan, tiles, c->tile_begin);
-        places_at = tiles.size() * sizeof(dear_tile);
+        places_at = (tiles.size() + TILES_BEHIND) * sizeof(dear_tile);
         grad_at = places_at + plan->L * sizeof(layer_place);
         param_at = grad_at + n_ptr * sizeof(void *);
         image.resize(param_at + n_ptr * sizeof(void *));
@@ -1057,7 +1056,7 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
     if (tiles.size() > 0x7fffffffu / 16) return DEAR_EINVAL;  // item counts fit 31 bits, up to 16 a tile
     if (hipGetDevice(&c->device) != hipSuccess) return DEAR_EHIP;
     mark_runs(*plan, param_ptrs, tiles);
-    std::memcpy(image.data(), tiles.data(), places_at);
+    std::memcpy(image.data(), tiles.data(), tiles.size() * sizeof(dear_tile));
     for (int32_t l = 0; l < plan->L; ++l) {
         const int32_t b = plan->layer_bucket[l];
         const int64_t S = plan->bucket_shard_len[b];
@@ -1112,15 +1111,23 @@ extern "C" void dear_ctx_destroy(dear_ctx_t *c)
 
 namespace {
 
-// One launch over the tiles of a range of buckets.
-template <rs_mode MODE>
-int launch_reduce_scatter(const dear_ctx_impl *c, bucket_range r, const rs_sink<MODE> &o, hipStream_t st)
+// What a launch goes over: tiles begin .. begin+count-1 of the table, part of a call's `all_tiles` with `all_elems`.
+struct tile_range {
+    int64_t begin, count, all_tiles, all_elems;
+};
+
+tile_range range_of(const dear_ctx_impl *c, bucket_range r)
 {
-    const int64_t count = tiles_of(c, r);
-    if (count == 0) return DEAR_OK;
-    const int64_t elems = elements_of(c->bucket_len, r);
-    const dear_tile *tiles = c->d_tiles + c->tile_begin[r.begin];
-    rs_launch<MODE>(c->g == 2, rs_call{c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, tiles, count, elems, st}, o);
+    return {c->tile_begin[r.begin], tiles_of(c, r), tiles_of(c, r), elements_of(c->bucket_len, r)};
+}
+
+template <rs_mode MODE>
+int launch_reduce_scatter(const dear_ctx_impl *c, tile_range t, const rs_sink<MODE> &o, hipStream_t st)
+{
+    if (t.count == 0) return DEAR_OK;
+    const rs_call call{c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, c->d_tiles + t.begin, t.count,
+                       t.all_tiles, t.all_elems, st};
+    rs_launch<MODE>(c->g == 2, call, o);
     return launch_status();
 }
 
@@ -1154,13 +1161,13 @@ int launch_update(const dear_ctx_impl *c, bucket_range r, const float *shard_gra
     return launch_status();
 }
 
-int launch_all_gather(const dear_ctx_impl *c, bucket_range r, const float *shard_param, int32_t first_worker,
+int launch_all_gather(const dear_ctx_impl *c, tile_range t, const float *shard_param, int32_t first_worker,
                       int32_t n_workers, hipStream_t st)
 {
-    const int64_t count = tiles_of(c, r);
+    const int64_t count = t.count;
     if (count == 0) return DEAR_OK;
     if (!all_gather_fits(count, n_workers, c->max_workgroups)) return DEAR_EINVAL;
-    const dear_tile *tiles = c->d_tiles + c->tile_begin[r.begin];
+    const dear_tile *tiles = c->d_tiles + t.begin;
     if (all_gather_bounded(count, n_workers, c->max_workgroups)) {
         const unsigned width = grid_width(c->max_workgroups, count);
         all_gather_bounded_kernel<<<dim3(width), dim3(DEAR_BLOCK), 0, st>>>(
@@ -1204,7 +1211,7 @@ extern "C" int dear_reduce_scatter(dear_ctx_t *c, int32_t bucket, float *shard_g
     if (rc == DEAR_OK) rc = check_shard_buffer(shard_grad);
     if (rc != DEAR_OK) return rc;
     const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f, nullptr};
-    return launch_reduce_scatter(c, buckets_of(c, bucket), o, static_cast<hipStream_t>(hip_stream));
+    return launch_reduce_scatter(c, range_of(c, buckets_of(c, bucket)), o, static_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int dear_reduce_scatter_update(dear_ctx_t *c, int32_t bucket, float *shard_param,
@@ -1214,7 +1221,7 @@ extern "C" int dear_reduce_scatter_update(dear_ctx_t *c, int32_t bucket, float *
     if (rc == DEAR_OK) rc = check_update_buffers(shard_param, shard_mom);
     if (rc != DEAR_OK) return rc;
     const rs_sink<RS_UPDATE> o{nullptr, shard_param, shard_mom, lr, momentum, nullptr};
-    return launch_reduce_scatter(c, buckets_of(c, bucket), o, static_cast<hipStream_t>(hip_stream));
+    return launch_reduce_scatter(c, range_of(c, buckets_of(c, bucket)), o, static_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int dear_shard_update(dear_ctx_t *c, int32_t bucket, const float *shard_grad,
@@ -1243,7 +1250,7 @@ extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float
     const unsigned width = grid_width(c->max_workgroups, count);
     if (update_all_gather_splits(count, c->P, c->max_workgroups)) {
         rc = launch_update(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
-        return rc == DEAR_OK ? launch_all_gather(c, r, shard_param, 0, c->P, st) : rc;
+        return rc == DEAR_OK ? launch_all_gather(c, range_of(c, r), shard_param, 0, c->P, st) : rc;
     }
     if (width < count)
         update_all_gather_kernel<true><<<dim3(width), dim3(DEAR_BLOCK), 0, st>>>(
@@ -1263,7 +1270,7 @@ extern "C" int dear_all_gather_workers(dear_ctx_t *c, int32_t bucket, const floa
     if (rc == DEAR_OK) rc = check_shard_buffer(shard_param);
     if (rc != DEAR_OK) return rc;
     if (first_worker < 0 || n_workers < 1 || first_worker > c->P - n_workers) return DEAR_ERANGE;
-    return launch_all_gather(c, buckets_of(c, bucket), shard_param, first_worker, n_workers,
+    return launch_all_gather(c, range_of(c, buckets_of(c, bucket)), shard_param, first_worker, n_workers,
                              static_cast<hipStream_t>(hip_stream));
 }
 
@@ -1275,17 +1282,17 @@ extern "C" int dear_all_gather(dear_ctx_t *c, int32_t bucket, const float *shard
 
 namespace {
 
-// Reduce-scatter and update of a group in one kernel, gbar stored only where it is wanted; MORE: RS_W_NEXT or RS_GATHER.
+// Reduce-scatter and update in one kernel, gbar stored only where it is wanted; MORE: RS_W_NEXT or RS_GATHER.
 template <rs_mode MORE>
-int launch_reduce_scatter_update(const dear_ctx_impl *c, bucket_range r, float *shard_grad, float *shard_param,
+int launch_reduce_scatter_update(const dear_ctx_impl *c, tile_range t, float *shard_grad, float *shard_param,
                                  float *shard_mom, float lr, float momentum, hipStream_t st)
 {
     if (shard_grad) {
         const rs_sink<RS_GBAR | RS_UPDATE | MORE> o{shard_grad, shard_param, shard_mom, lr, momentum, c->d_param};
-        return launch_reduce_scatter(c, r, o, st);
+        return launch_reduce_scatter(c, t, o, st);
     }
     const rs_sink<RS_UPDATE | MORE> o{nullptr, shard_param, shard_mom, lr, momentum, c->d_param};
-    return launch_reduce_scatter(c, r, o, st);
+    return launch_reduce_scatter(c, t, o, st);
 }
 
 }  // namespace
@@ -1309,21 +1316,30 @@ extern "C" int dear_iteration(dear_ctx_t *c, int32_t bucket, float *shard_grad, 
         if (!all_gather_fits(tiles_of(c, r), c->P, c->max_workgroups)) return DEAR_EINVAL;
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    if (iteration_gathers_at_once(c->g, c->P, elements_of(c->bucket_len, all), tiles_of(c, all), shard_grad != nullptr, c->max_workgroups))
-        return launch_reduce_scatter_update<RS_GATHER>(c, all, shard_grad, shard_param, shard_mom, lr, momentum, st);
+    const tile_range whole = range_of(c, all);
+    if (iteration_gathers_at_once(c->g, c->P, whole.all_elems, whole.count, shard_grad != nullptr, c->max_workgroups))
+        return launch_reduce_scatter_update<RS_GATHER>(c, whole, shard_grad, shard_param, shard_mom, lr, momentum, st);
     for (bucket_range r{0, all.begin}; rc == DEAR_OK && r.end < all.end;) {
         r = group_from(r.end);
-        const int64_t tiles = tiles_of(c, r);
-        if (shard_grad && iteration_updates_apart(c->g, c->P, tiles)) {
+        const tile_range group = range_of(c, r);
+        if (shard_grad && iteration_updates_apart(c->g, c->P, group.count)) {
             const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f, nullptr};
-            rc = launch_reduce_scatter(c, r, o, st);
+            rc = launch_reduce_scatter(c, group, o, st);
             if (rc == DEAR_OK) rc = launch_update(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
-        } else if (iteration_caches_w(c->g, c->P, tiles, c->tile_begin[c->B])) {
-            rc = launch_reduce_scatter_update<RS_W_NEXT>(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
-        } else {
-            rc = launch_reduce_scatter_update<0>(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
+            if (rc == DEAR_OK) rc = launch_all_gather(c, group, shard_param, 0, c->P, st);
+            continue;
         }
-        if (rc == DEAR_OK) rc = launch_all_gather(c, r, shard_param, 0, c->P, st);
+        const int64_t pieces = iteration_pieces(c->g, c->P, group.count, c->tile_begin[c->B]);
+        for (int64_t i = 0; rc == DEAR_OK && i < pieces; ++i) {
+            tile_range t = group;
+            t.begin += group.count * i / pieces;
+            t.count = group.begin + group.count * (i + 1) / pieces - t.begin;
+            if (iteration_caches_w(c->g, c->P, t.count, c->tile_begin[c->B]))
+                rc = launch_reduce_scatter_update<RS_W_NEXT>(c, t, shard_grad, shard_param, shard_mom, lr, momentum, st);
+            else
+                rc = launch_reduce_scatter_update<0>(c, t, shard_grad, shard_param, shard_mom, lr, momentum, st);
+            if (rc == DEAR_OK) rc = launch_all_gather(c, t, shard_param, 0, c->P, st);
+        }
     }
     return rc;
 }
@@ -1446,6 +1462,6 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
     const dear_tile *tiles = reinterpret_cast<const dear_tile *>(dev + tiles_at);
     const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f, nullptr};
     const int64_t elems = elements_of(plan->bucket_len, bucket_range{b_first, b_last});
-    rs_launch<RS_GBAR>(plan->g == 2, rs_call{plan->P, plan->L, grad_tab, 0, 0, tiles, n_tiles, elems, st}, o);
+    rs_launch<RS_GBAR>(plan->g == 2, rs_call{plan->P, plan->L, grad_tab, 0, 0, tiles, n_tiles, n_tiles, elems, st}, o);
     return launch_status();
 }

@@ -65,6 +65,9 @@ struct all_gather_order {
     unsigned len, run;
 };
 
+// Room behind a context's tile table: the workgroups of a rounded last chunk read up to 15 parts beyond the last.
+constexpr int TILES_BEHIND = 4;
+
 // Part of a chunk that a replica's r-th workgroup takes: XCD r % 8 takes 2^run parts in a row out of every 8 * 2^run.
 DEAR_HOST_DEVICE inline unsigned all_gather_part(unsigned r, unsigned run)
 {
@@ -169,6 +172,17 @@ inline bool iteration_caches_w(int grad_bytes, int64_t P, int64_t group_tiles, i
     if (group_tiles > ITERATION_TILES) return false;
     if (grad_bytes * P <= (grad_bytes == 2 ? 24 : 16)) return true;
     return grad_bytes * P <= 64 && all_tiles <= ALL_CACHED_TILES;
+}
+
+// A bucket beyond ITERATION_TILES is handled in pieces of its tiles, whatever layers and shards they belong to, if that
+// leaves each piece's w in the last-level cache for its all-gather.  us per iteration without and with gbar, one launch pair /
+// pieces, one bucket: bf16 P = 3 50 M 312 / 292 and 359 / 329, P = 5 36 M 286 / 284 and 324 / 313, P = 8 110 M 1149 / 1132 and 1252 / 1205,
+// 300 M 3137 / 3038 and 3351 / 3229; not where w is stored non-temporally anyway: bf16 P = 16 100 M 1766 / 1768 and 1868 / 1848, fp32
+// P = 5 36 M 336 / 344 and 359 / 366, P = 8 100 M 1284 / 1312 and 1370 / 1388.  Pieces of 4096 and 12288 tiles are level to 1 %.
+inline int64_t iteration_pieces(int grad_bytes, int64_t P, int64_t group_tiles, int64_t all_tiles)
+{
+    if (!iteration_caches_w(grad_bytes, P, ITERATION_TILES, all_tiles) || grad_bytes != 2) return 1;
+    return (group_tiles + ITERATION_TILES - 1) / ITERATION_TILES;
 }
 
 // Whether a group whose gbar is wanted takes three launches, the update behind the reduce-scatter: the more replicas

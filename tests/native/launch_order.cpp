@@ -24,6 +24,7 @@ int main()
                         const unsigned first = r < whole ? r / chunk * chunk : whole;
                         const unsigned id = first + all_gather_part(r - first, o.run);
                         if (id < parts) ++seen[id];
+                        if (id / AG_SPLIT >= tiles + TILES_BEHIND) seen[0] = 2;  // reads a tile that is not there
                     }
                     bool ok = (whole + int64_t(o.len)) * P <= MAX_GRID;
                     for (int n : seen) ok = ok && n == 1;

@@ -62,3 +62,16 @@ def test_iteration_in_one_launch(dtype, P, sizes):
     pair.run(iterations=1, route="iteration", fused=True)
     pair.run(iterations=1, route="iteration", width=64)
     pair.close()
+
+
+# one bucket beyond 8192 tiles: pieces that begin inside a layer and a shard
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,P,thr", [("f32", 5, None), ("bf16", 3, None), ("bf16", 5, 40_000_000)])
+def test_iteration_over_a_bucket_in_pieces(dtype, P, thr):
+    from test_gpu_parity import Pair, say, small_workload
+    import workloads as W
+    say("case: one bucket in pieces, %s, P=%d" % (dtype, P))
+    pair = Pair(small_workload([17_000_001, 3, 20_100_077], P, thr or W.NO_LIMIT, dtype))
+    pair.run(iterations=1, route="iteration")
+    pair.run(iterations=1, route="iteration", fused=True)
+    pair.close()
