@@ -218,10 +218,11 @@ int dear_reduce_scatter(dear_ctx_t *ctx, int32_t bucket, float *shard_grad, void
  * device memory: tight serving or training loops and harnesses that forbid hipMalloc
  * once running, where creating a context (which allocates its tile and pointer tables)
  * is not possible.  It needs no context and calls neither hipMalloc nor hipFree nor any
- * other allocating routine, on the device or the host: the two tables its kernel reads
- * are built in a fixed host staging area and uploaded into a fixed device array that
+ * other allocating routine, on the device or the host (the first call on a GPU looks the array
+ * up and makes the event that calls wait with): what its kernel reads
+ * is built in a fixed host staging area and uploaded into a fixed device array that
  * the library holds on every GPU it runs on until the process ends
- * (DEAR_STATIC_MAX_POINTERS * 8 + DEAR_STATIC_MAX_TILES * 32 bytes = 4 MiB).
+ * (DEAR_STATIC_MAX_POINTERS * 8 + DEAR_STATIC_MAX_TILES * 80 bytes = 8.5 MiB).
  *
  *   plan        host, as for dear_ctx_create
  *   grad_dtype  DEAR_F32 or DEAR_BF16, must agree with the plan
@@ -234,9 +235,9 @@ int dear_reduce_scatter(dear_ctx_t *ctx, int32_t bucket, float *shard_grad, void
  * at most DEAR_STATIC_MAX_TILES tiles (one tile per DEAR_TILE_ELEMS elements of a layer
  * within a shard, plus ragged ends: about 400 M elements); beyond that DEAR_ETOOBIG is
  * returned and nothing is launched.
- * The call uploads the tables on hip_stream, waits for that stream (so work queued on it
- * earlier has finished when the call returns), then enqueues the kernel and returns
- * without waiting for it.  Uses the current HIP device.  All calls on one GPU share that
+ * The call uploads the tables on hip_stream, enqueues the kernel behind them and returns when the upload
+ * is done (so work queued on the stream earlier has finished), without waiting for the kernel.  On a
+ * stream that is being captured it returns DEAR_EHIP.  Uses the current HIP device.  All calls on one GPU share that
  * GPU's array, which keeps the last call's tables: nothing in it needs clearing (every
  * entry the kernel reads is rewritten by the call), but calls that overlap on one GPU --
  * different host threads, or a second call on another stream while the first call's

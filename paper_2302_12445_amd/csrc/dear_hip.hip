@@ -875,6 +875,23 @@ __global__ __launch_bounds__(DEAR_BLOCK) void reshard_kernel(
     }
 }
 
+__host__ __device__ __forceinline__ dear_tile marked_tile(const dear_run &r, int64_t k, int64_t n)
+{
+    dear_tile t = tile_of_run(r, k);
+    t.bucket |= (k == 0 ? TILE_FIRST : 0) | (k + 1 == n ? TILE_LAST : 0);
+    return t;
+}
+
+// Tile table from runs, a workgroup a run.  The kernel takes some 3 us; what it saves is the host's time, which wrote and
+// uploaded 32 bytes a tile and now 48 a run (BERT-Base-shaped, P = 8: 27000 tiles, 317 runs; making a context 190 us -> 89).
+// A run's `bucket` goes into all its tiles, with notes on which of them are its first and its last.
+__global__ __launch_bounds__(DEAR_BLOCK) void expand_runs_kernel(const dear_run *__restrict__ runs, dear_tile *__restrict__ tiles)
+{
+    const dear_run r = runs[blockIdx.x];
+    const int64_t n = tiles_of_run(r);
+    for (int64_t k = threadIdx.x; k < n; k += DEAR_BLOCK) tiles[r.first_tile + k] = marked_tile(r, k, n);
+}
+
 // ------------------------------------------------------------------------------- host side
 
 inline bool misaligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; }
@@ -911,6 +928,28 @@ int64_t tiles_of(const dear_ctx_impl *c, bucket_range r) { return c->tile_begin[
 int64_t elements_of(const std::vector<int64_t> &bucket_len, bucket_range r)
 {
     return std::accumulate(bucket_len.begin() + r.begin, bucket_len.begin() + r.end, int64_t{0});
+}
+
+// Whether the launch was taken; says nothing of errors that other calls left behind.
+bool expand_runs(const dear_run *runs, int64_t n_runs, dear_tile *tiles, hipStream_t st)
+{
+    void *args[] = {&runs, &tiles};
+    return hipLaunchKernel(reinterpret_cast<const void *>(expand_runs_kernel), dim3(static_cast<unsigned>(n_runs)), dim3(DEAR_BLOCK),
+                           args, 0, st) == hipSuccess;
+}
+
+// Host memory that is not pinned -> device memory, stream-ordered.  The runtime takes copies of up to 16 KiB without waiting;
+// behind queued work longer ones cost 7-10 us more of the GPU's time, so a table of a few such pieces goes in pieces
+// (reduce-scatters with their tables back to back, us, one copy / pieces: 22 KB 177 / 167, 45 KB 152 / 143, 28 KB 43.6 / 35.0;
+// 180 KB 150 / 163).
+bool upload(unsigned char *to, const unsigned char *from, size_t bytes, hipStream_t st)
+{
+    constexpr size_t PIECE = 16 << 10, MOST = 64 << 10;
+    const size_t step = bytes <= MOST ? PIECE : bytes;
+    for (size_t at = 0; at < bytes; at += step)
+        if (hipMemcpyAsync(to + at, from + at, bytes - at < step ? bytes - at : step, hipMemcpyHostToDevice, st) != hipSuccess)
+            return false;
+    return true;
 }
 
 int launch_status() { return hipGetLastError() == hipSuccess ? DEAR_OK : DEAR_EHIP; }
@@ -987,30 +1026,30 @@ void rs_launch(bool bf16, const rs_call &c, const rs_sink<MODE> &o)
         rs_launch_batched<true, MODE, 2>(c, o);
 }
 
-constexpr size_t SHIFT_TILES = 8;
+// Up to this many tiles a context's table is cut on the host: 13 us for 85 tiles, 17 with the kernel and the wait for it.
+constexpr int64_t HOST_TILES = 1024;
 
-// Writes into every tile's bucket field what the all-gather wants to know about the tile's run.
-void mark_runs(const dear_plan_s &plan, float *const *param_ptrs, std::vector<dear_tile> &tiles)
+constexpr int64_t SHIFT_TILES = 8;
+
+// Writes into every run's bucket field what the all-gather wants to know about its tiles.
+void mark_runs(const dear_plan_s &plan, float *const *param_ptrs, dear_run *runs, int64_t n_runs)
 {
-    for (size_t begin = 0, end = 0; begin < tiles.size(); begin = end) {
-        const int32_t layer = tiles[begin].layer;
-        while (end < tiles.size() && tiles[end].layer == layer && tiles[end].shard == tiles[begin].shard) ++end;
+    for (dear_run *r = runs; r < runs + n_runs; ++r) {
         int flags = 0;
-        if (layer >= 0) {
-            const int shift = line_shift(reinterpret_cast<uintptr_t>(param_ptrs[layer]));
+        if (r->layer >= 0) {
+            const int shift = line_shift(reinterpret_cast<uintptr_t>(param_ptrs[r->layer]));
             flags = shift << TILE_SHIFT_BIT;
             for (int32_t p = 1; p < plan.P; ++p)
-                if (line_shift(reinterpret_cast<uintptr_t>(param_ptrs[static_cast<size_t>(p) * plan.L + layer])) != shift)
+                if (line_shift(reinterpret_cast<uintptr_t>(param_ptrs[static_cast<size_t>(p) * plan.L + r->layer])) != shift)
                     flags = TILE_OWN_SHIFT;
             // A short run has little to gain: most of its tiles are at an end, and moved ends take the long form.
             // All-gather of 20 M elements in tensors of n tiles that start on 16-byte boundaries, P = 8, us, cuts
             // moved / not (not resolved better than 10 % around 6 tiles): 4 tiles 143 / 117, 5 121 / 107, 6 114 / 112
             // and 126, 8 118 / 124, 10 100 / 123, 21 97 / 117; P = 32: 8 tiles 408 / 501.
             // A first tile of less than a line could not give a shift away.
-            if (end - begin < SHIFT_TILES || tiles[begin].count < 32) flags = 0;
+            if (tiles_of_run(*r) < SHIFT_TILES || tile_of_run(*r, 0).count < 32) flags = 0;
         }
-        for (size_t i = begin; i < end; ++i)
-            tiles[i].bucket = flags | (i == begin ? TILE_FIRST : 0) | (i + 1 == end ? TILE_LAST : 0);
+        r->bucket = flags;
     }
 }
 
@@ -1031,8 +1070,9 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
         if (misaligned(grad_ptrs[i], 16) || misaligned(param_ptrs[i], 16)) return DEAR_EALIGN;
     }
     std::unique_ptr<dear_ctx_s> c;
-    std::vector<dear_tile> tiles;
-    std::vector<unsigned char> image;  // of the device tables: tiles, layer places, gradient and parameter pointers
+    std::vector<dear_run> runs;
+    std::vector<unsigned char> image;  // what is uploaded: tiles or runs, layer places, gradient and parameter pointers
+    int64_t n_runs = 0, n_tiles = 0;
     size_t places_at = 0, grad_at = 0, param_at = 0;
     try {
         c.reset(new dear_ctx_s);
@@ -1045,18 +1085,28 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
         c->bucket_shard_len = plan->bucket_shard_len;
         c->bucket_shard_base = plan->bucket_shard_base;
         c->layer_sizes = plan->layer_sizes;
-        dear_build_tiles(*plan, tiles, c->tile_begin);
-        places_at = (tiles.size() + TILES_BEHIND) * sizeof(dear_tile);
+        c->tile_begin.assign(plan->B + 1, 0);
+        n_runs = dear_emit_runs(*plan, 0, plan->B, nullptr, 0, &n_tiles, c->tile_begin.data());
+        runs.resize(n_runs);
+        places_at = n_tiles <= HOST_TILES ? (n_tiles + TILES_BEHIND) * sizeof(dear_tile) : n_runs * sizeof(dear_run);
         grad_at = places_at + plan->L * sizeof(layer_place);
         param_at = grad_at + n_ptr * sizeof(void *);
         image.resize(param_at + n_ptr * sizeof(void *));
     } catch (const std::bad_alloc &) {
         return DEAR_ENOMEM;
     }
-    if (tiles.size() > 0x7fffffffu / 16) return DEAR_EINVAL;  // item counts fit 31 bits, up to 16 a tile
+    if (n_tiles > 0x7fffffff / 16) return DEAR_EINVAL;  // item counts fit 31 bits, up to 16 a tile
     if (hipGetDevice(&c->device) != hipSuccess) return DEAR_EHIP;
-    mark_runs(*plan, param_ptrs, tiles);
-    std::memcpy(image.data(), tiles.data(), tiles.size() * sizeof(dear_tile));
+    dear_emit_runs(*plan, 0, plan->B, runs.data(), n_runs, &n_tiles, nullptr);
+    mark_runs(*plan, param_ptrs, runs.data(), n_runs);
+    const bool on_host = n_tiles <= HOST_TILES;
+    if (on_host) {
+        dear_tile *tiles = reinterpret_cast<dear_tile *>(image.data());
+        for (const dear_run &r : runs)
+            for (int64_t k = 0, n = tiles_of_run(r); k < n; ++k) tiles[r.first_tile + k] = marked_tile(r, k, n);
+    } else {
+        std::memcpy(image.data(), runs.data(), places_at);
+    }
     for (int32_t l = 0; l < plan->L; ++l) {
         const int32_t b = plan->layer_bucket[l];
         const int64_t S = plan->bucket_shard_len[b];
@@ -1067,19 +1117,24 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
     std::memcpy(image.data() + param_at, param_ptrs, n_ptr * sizeof(void *));
 
     int rc = DEAR_OK;
-    if (hipMalloc(&c->d_tables, image.size()) != hipSuccess) {
+    const size_t in_front = on_host ? 0 : (n_tiles + TILES_BEHIND) * sizeof(dear_tile);  // room for the tiles
+    unsigned char *base = nullptr;
+    if (hipMalloc(&c->d_tables, in_front + image.size()) != hipSuccess) {
         c->d_tables = nullptr;
         rc = DEAR_ENOMEM;
-    } else if (hipMemcpy(c->d_tables, image.data(), image.size(), hipMemcpyHostToDevice) != hipSuccess) {
-        rc = DEAR_EHIP;
+    } else {
+        c->d_tiles = static_cast<dear_tile *>(c->d_tables);
+        base = static_cast<unsigned char *>(c->d_tables) + in_front;
+        if (hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice) != hipSuccess ||
+            (!on_host && (!expand_runs(reinterpret_cast<const dear_run *>(base), n_runs, c->d_tiles, nullptr) ||
+                          hipStreamSynchronize(nullptr) != hipSuccess)))
+            rc = DEAR_EHIP;
     }
     if (rc != DEAR_OK) {
         (void)hipGetLastError();
         dear_ctx_destroy(c.release());
         return rc;
     }
-    unsigned char *base = static_cast<unsigned char *>(c->d_tables);
-    c->d_tiles = reinterpret_cast<dear_tile *>(base);
     c->d_places = reinterpret_cast<layer_place *>(base + places_at);
     c->d_grad = reinterpret_cast<const void **>(base + grad_at);
     c->d_param = reinterpret_cast<float **>(base + param_at);
@@ -1379,30 +1434,40 @@ extern "C" int dear_reshard(dear_ctx_t *from, dear_ctx_t *to, const float *shard
 // dear_reduce_scatter needs a context, and creating one allocates device memory for the tile
 // table and the pointer table its kernel reads.  For callers that cannot allocate, the same
 // kernel reads both tables from this file-scope device array instead.  Layout: gradient
-// pointer table first, tile table on the next 256-byte boundary behind it, so that one copy of the
-// bytes in use brings both up: while it runs the GPU has nothing else to do.  Every GPU the library
+// pointer table first, the runs on the next 256-byte boundary behind it, so that one copy of the
+// bytes in use brings both up, then the tiles that expand_runs_kernel makes of them.  Every GPU the library
 // runs on holds its own copy of the array until the process ends.
 namespace {
 
 constexpr size_t STATIC_MAX_PTRS = DEAR_STATIC_MAX_POINTERS;
-constexpr size_t STATIC_MAX_TILES = DEAR_STATIC_MAX_TILES;
+constexpr size_t STATIC_MAX_TILES = DEAR_STATIC_MAX_TILES;  // and runs: each has a tile at least
 constexpr size_t STATIC_PTR_BYTES = STATIC_MAX_PTRS * sizeof(void *);
+constexpr size_t STATIC_RUN_BYTES = STATIC_MAX_TILES * sizeof(dear_run);
 constexpr size_t STATIC_TILE_BYTES = STATIC_MAX_TILES * sizeof(dear_tile);
-static_assert(STATIC_PTR_BYTES % 256 == 0, "the tile table must start aligned");
+static_assert(STATIC_PTR_BYTES % 256 == 0 && STATIC_RUN_BYTES % 256 == 0, "the tables must start aligned");
 
-__device__ __align__(256) unsigned char scratch[STATIC_PTR_BYTES + STATIC_TILE_BYTES];
+__device__ __align__(256) unsigned char scratch[STATIC_PTR_BYTES + STATIC_RUN_BYTES + STATIC_TILE_BYTES];
 
-// Host staging of the two tables (pageable, file scope: no heap use on this path).
-unsigned char host_stage[STATIC_PTR_BYTES + STATIC_TILE_BYTES];
+// Host staging of pointers and runs (pageable, file scope: no heap use on this path).
+alignas(256) unsigned char host_stage[STATIC_PTR_BYTES + STATIC_RUN_BYTES];
 
 constexpr int MAX_DEVICES = 64;
 unsigned char *scratch_of_device[MAX_DEVICES];  // device address of `scratch`, per GPU
+hipEvent_t uploaded_on_device[MAX_DEVICES];     // behind the upload of the tables, per GPU
 
-// `scratch` names a host-side stand-in in host code; the device address has to be asked for,
-// once per device, with that device current.
+// `scratch` names a host-side stand-in in host code; the device address has to be asked for, and an event
+// made, once per device, with that device current.
 int static_scratch(int device, unsigned char **out)
 {
     if (device < 0 || device >= MAX_DEVICES) return DEAR_EINVAL;
+    if (!uploaded_on_device[device]) {
+        hipEvent_t event = nullptr;
+        if (hipEventCreateWithFlags(&event, hipEventDisableTiming) != hipSuccess || !event) {
+            (void)hipGetLastError();
+            return DEAR_EHIP;
+        }
+        uploaded_on_device[device] = event;
+    }
     if (!scratch_of_device[device]) {
         void *p = nullptr;
         if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) {
@@ -1435,9 +1500,11 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
         if (!grad_ptrs[i]) return DEAR_EINVAL;
         if (misaligned(grad_ptrs[i], 16)) return DEAR_EALIGN;
     }
-    const size_t tiles_at = (n_ptr * sizeof(void *) + 255) & ~size_t(255);  // <= STATIC_PTR_BYTES
-    dear_tile *host_tiles = reinterpret_cast<dear_tile *>(host_stage + tiles_at);
-    const int64_t n_tiles = dear_emit_tiles(*plan, b_first, b_last, host_tiles, STATIC_MAX_TILES, nullptr);
+    auto aligned = [](size_t n) { return (n + 255) & ~size_t(255); };
+    const size_t runs_at = aligned(n_ptr * sizeof(void *));  // <= STATIC_PTR_BYTES
+    int64_t n_tiles = 0;
+    const int64_t n_runs = dear_emit_runs(*plan, b_first, b_last, reinterpret_cast<dear_run *>(host_stage + runs_at),
+                                          STATIC_MAX_TILES, &n_tiles, nullptr);
     if (n_tiles > static_cast<int64_t>(STATIC_MAX_TILES)) return DEAR_ETOOBIG;
     if (n_tiles == 0) return DEAR_OK;
 
@@ -1448,20 +1515,34 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
     if (rc != DEAR_OK) return rc;
 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {  // it cannot be waited for
+        (void)hipGetLastError();
+        return DEAR_EHIP;
+    }
     for (size_t i = 0; i < n_ptr; ++i) reinterpret_cast<const void **>(host_stage)[i] = grad_ptrs[i];
     // Stream-ordered upload: earlier kernels of this stream that still read the scratch finish
-    // first.  The staging memory is pageable and is reused by the next call, so the stream is
-    // drained before returning to the point where the copy has been taken.
-    if (hipMemcpyAsync(dev, host_stage, tiles_at + static_cast<size_t>(n_tiles) * sizeof(dear_tile),
-                       hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess) {
+    // first.  The staging memory is pageable and is reused by the next call, so the call waits for the
+    // upload before it returns, but with the kernel behind it in the queue already: the GPU idles for the copy of the pointers
+    // and runs and the making of the tiles, and not for the host's wake-up and launch.  Calls back to back, us, before (tiles
+    // uploaded, stream drained, kernel launched) / now: 161 tensors P = 8 fp32 25 M elements 177 / 167, 11 tensors P = 8 bf16
+    // 6 M 43.6 / 30.2, 30 tensors P = 6 bf16 60 M 193 / 168, 400 tensors P = 8 fp32 20 M 155 / 143, 600 P = 12 2 M 43.7 / 44.0.
+    const size_t bytes = runs_at + static_cast<size_t>(n_runs) * sizeof(dear_run);
+    const dear_run *runs = reinterpret_cast<const dear_run *>(dev + runs_at);
+    dear_tile *tiles = reinterpret_cast<dear_tile *>(dev + aligned(bytes));
+    if (!upload(dev, host_stage, bytes, st) || !expand_runs(runs, n_runs, tiles, st) || hipEventRecord(uploaded_on_device[device], st) != hipSuccess) {
+        (void)hipStreamSynchronize(st);
         (void)hipGetLastError();
         return DEAR_EHIP;
     }
     const void *const *grad_tab = reinterpret_cast<const void *const *>(dev);
-    const dear_tile *tiles = reinterpret_cast<const dear_tile *>(dev + tiles_at);
     const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f, nullptr};
     const int64_t elems = elements_of(plan->bucket_len, bucket_range{b_first, b_last});
     rs_launch<RS_GBAR>(plan->g == 2, rs_call{plan->P, plan->L, grad_tab, 0, 0, tiles, n_tiles, n_tiles, elems, st}, o);
-    return launch_status();
+    rc = launch_status();
+    if (hipEventSynchronize(uploaded_on_device[device]) != hipSuccess) {
+        (void)hipGetLastError();
+        return DEAR_EHIP;
+    }
+    return rc;
 }

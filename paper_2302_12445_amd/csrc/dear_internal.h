@@ -26,6 +26,27 @@ struct dear_plan_s {
 typedef dear_tile_t dear_tile;
 static_assert(sizeof(dear_tile) == 32, "tile descriptors are read as two 16-byte loads");
 
+// A run: `count` elements of one layer within one shard, or padding slots of one shard (layer -1, src_begin 0).  The tile
+// table follows from the runs, which are a few hundred where the tiles are thousands, so it is the runs that are uploaded,
+// and a kernel cuts them (expand_runs_kernel).
+struct dear_run {
+    int64_t src_begin, dst_begin, count;
+    int64_t first_tile;  // its tiles' place in the table
+    int32_t layer, shard, bucket, reserved;
+};
+
+DEAR_HOST_DEVICE inline int64_t tiles_of_run(const dear_run &r)
+{
+    return (r.src_begin + r.count + DEAR_TILE_ELEMS - 1) / DEAR_TILE_ELEMS - r.src_begin / DEAR_TILE_ELEMS;
+}
+
+DEAR_HOST_DEVICE inline dear_tile tile_of_run(const dear_run &r, int64_t k)
+{
+    const int64_t cut = (r.src_begin / DEAR_TILE_ELEMS + k) * DEAR_TILE_ELEMS, end = r.src_begin + r.count;
+    const int64_t lo = k == 0 ? r.src_begin : cut, hi = cut + DEAR_TILE_ELEMS < end ? cut + DEAR_TILE_ELEMS : end;
+    return {r.layer < 0 ? 0 : lo, r.dst_begin + (lo - r.src_begin), static_cast<int32_t>(hi - lo), r.layer, r.shard, r.bucket};
+}
+
 constexpr int DEAR_BLOCK = 256;  // threads per workgroup = 4 wavefronts
 
 // ------------------------------------------------ which launches a call makes, by its sizes alone
@@ -100,7 +121,9 @@ inline bool update_all_gather_splits(int64_t tiles, int64_t P, int64_t max_workg
     return !bounded && P >= UAG_SPLIT_P && tiles * P >= UAG_SPLIT_TILES && all_gather_fits(tiles, P, max_workgroups);
 }
 
-// Cuts every bucket of the plan into tiles (plan.cpp).
+// Cuts every bucket of the plan into runs and tiles (plan.cpp).
+int64_t dear_emit_runs(const dear_plan_s &pl, int32_t b_first, int32_t b_last, dear_run *out, int64_t capacity,
+                       int64_t *n_tiles, int64_t *tile_begin);
 int64_t dear_emit_tiles(const dear_plan_s &pl, int32_t b_first, int32_t b_last, dear_tile *out,
                         int64_t capacity, int64_t *tile_begin);
 void dear_build_tiles(const dear_plan_s &pl, std::vector<dear_tile> &tiles, std::vector<int64_t> &tile_begin);

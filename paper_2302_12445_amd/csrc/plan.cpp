@@ -120,64 +120,56 @@ extern "C" int dear_plan_fixed_layers(const int64_t *layer_sizes, int32_t n_laye
     return DEAR_OK;
 }
 
-// Cut the buckets b_first .. b_last-1 into tiles: runs of one layer within one shard, split
-// at multiples of DEAR_TILE_ELEMS of the layer's own element index so that tile-interior
-// vectors stay aligned; then the padding slots behind the last real element.  Tiles are
-// written to out[0 .. capacity) as far as they fit; the return value is the number of tiles
-// the buckets have (so a first call with capacity 0 sizes the table).  tile_begin, if given,
-// receives b_last - b_first + 1 range starts relative to the first tile written.
-int64_t dear_emit_tiles(const dear_plan_s &pl, int32_t b_first, int32_t b_last, dear_tile *out,
-                        int64_t capacity, int64_t *tile_begin)
+// The runs of the buckets b_first .. b_last-1 in bucket-position order: the elements of one layer within one shard; then
+// the padding slots behind the last real element, shard by shard.  Runs are written to out[0 .. capacity) as far as they
+// fit; the return value is the number of runs the buckets have.  n_tiles receives the number of their tiles, tile_begin,
+// if given, b_last - b_first + 1 range starts relative to the first tile.
+int64_t dear_emit_runs(const dear_plan_s &pl, int32_t b_first, int32_t b_last, dear_run *out, int64_t capacity,
+                       int64_t *n_tiles, int64_t *tile_begin)
 {
-    int64_t n_out = 0;
-    auto emit = [&](const dear_tile &t) {
-        if (n_out < capacity) out[n_out] = t;
+    int64_t n_out = 0, tiles = 0;
+    auto emit = [&](dear_run r) {
+        r.first_tile = tiles;
+        if (n_out < capacity) out[n_out] = r;
         ++n_out;
+        tiles += tiles_of_run(r);
     };
     for (int32_t b = b_first; b < b_last; ++b) {
-        if (tile_begin) tile_begin[b - b_first] = n_out;
+        if (tile_begin) tile_begin[b - b_first] = tiles;
         const int64_t S = pl.bucket_shard_len[b], base = pl.bucket_shard_base[b];
         const int32_t lo = pl.bucket_first_layer[b], hi = lo + pl.bucket_n_layers[b];
         for (int32_t l = hi - 1; l >= lo; --l) {
             const int64_t off = pl.layer_offset[l], n = pl.layer_sizes[l];
-            int64_t i = 0;
-            while (i < n) {
+            for (int64_t i = 0; i < n;) {
                 const int64_t s = (off + i) / S;
-                const int64_t run_end = (s + 1) * S - off < n ? (s + 1) * S - off : n;
-                while (i < run_end) {
-                    const int64_t next_cut = (i / DEAR_TILE_ELEMS + 1) * DEAR_TILE_ELEMS;
-                    const int64_t end = next_cut < run_end ? next_cut : run_end;
-                    dear_tile t;
-                    t.src_begin = i;
-                    t.dst_begin = s * pl.row_len + base + (off + i - s * S);
-                    t.count = static_cast<int32_t>(end - i);
-                    t.layer = l;
-                    t.shard = static_cast<int32_t>(s);
-                    t.bucket = b;
-                    emit(t);
-                    i = end;
-                }
+                const int64_t end = (s + 1) * S - off < n ? (s + 1) * S - off : n;
+                emit({i, s * pl.row_len + base + (off + i - s * S), end - i, 0, l, static_cast<int32_t>(s), b, 0});
+                i = end;
             }
         }
-        int64_t e = pl.bucket_len[b];
         const int64_t total = S * pl.P;
-        while (e < total) {
-            const int64_t s = e / S;
-            int64_t end = (s + 1) * S;
-            if (end - e > DEAR_TILE_ELEMS) end = e + DEAR_TILE_ELEMS;
-            dear_tile t;
-            t.src_begin = 0;
-            t.dst_begin = s * pl.row_len + base + (e - s * S);
-            t.count = static_cast<int32_t>(end - e);
-            t.layer = -1;
-            t.shard = static_cast<int32_t>(s);
-            t.bucket = b;
-            emit(t);
+        for (int64_t e = pl.bucket_len[b]; e < total;) {
+            const int64_t s = e / S, end = (s + 1) * S;
+            emit({0, s * pl.row_len + base + (e - s * S), end - e, 0, -1, static_cast<int32_t>(s), b, 0});
             e = end;
         }
     }
-    if (tile_begin) tile_begin[b_last - b_first] = n_out;
+    if (tile_begin) tile_begin[b_last - b_first] = tiles;
+    *n_tiles = tiles;
     return n_out;
+}
+
+// Cut the buckets b_first .. b_last-1 into tiles: their runs, split at multiples of DEAR_TILE_ELEMS of the layer's own
+// element index so that tile-interior vectors stay aligned.  Arguments and result as above, in tiles.
+int64_t dear_emit_tiles(const dear_plan_s &pl, int32_t b_first, int32_t b_last, dear_tile *out,
+                        int64_t capacity, int64_t *tile_begin)
+{
+    int64_t n_tiles = 0;
+    std::vector<dear_run> runs(static_cast<size_t>(dear_emit_runs(pl, b_first, b_last, nullptr, 0, &n_tiles, nullptr)));
+    dear_emit_runs(pl, b_first, b_last, runs.data(), static_cast<int64_t>(runs.size()), &n_tiles, tile_begin);
+    for (const dear_run &r : runs)
+        for (int64_t k = 0, n = tiles_of_run(r); k < n && r.first_tile + k < capacity; ++k) out[r.first_tile + k] = tile_of_run(r, k);
+    return n_tiles;
 }
 
 void dear_build_tiles(const dear_plan_s &pl, std::vector<dear_tile> &tiles, std::vector<int64_t> &tile_begin)

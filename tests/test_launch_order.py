@@ -8,6 +8,7 @@ import subprocess
 
 import pytest
 
+W_NO_LIMIT = (1 << 63) - 1
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -75,3 +76,53 @@ def test_iteration_over_a_bucket_in_pieces(dtype, P, thr):
     pair.run(iterations=1, route="iteration")
     pair.run(iterations=1, route="iteration", fused=True)
     pair.close()
+
+
+# tables of one upload piece, of several and of more than go in pieces (about 2, 30, 64 and 200 KB), nothing waited for between calls
+@pytest.mark.gpu
+def test_static_calls_back_to_back():
+    import torch
+    import paper_2302_12445_amd as dear
+    from paper_2302_12445_amd import binding as B
+    from paper_2302_12445_amd.emulation import EmulatedWorkers
+    ems = [EmulatedWorkers([1000 + 7 * l for l in range(L)], P, dtype, thr, "cuda:0")
+           for L, P, dtype, thr in ((5, 4, "f32", 9000), (300, 8, "bf16", 40_000), (1, 3, "f32", 0), (500, 9, "f32", W_NO_LIMIT), (700, 16, "f32", 60_000))]
+    side = torch.cuda.Stream()
+    outs = []
+    for em in ems:
+        for rep in em.grads:
+            rep[0]._base.normal_(generator=torch.Generator("cuda:0").manual_seed(len(outs)))
+        em.reduce_scatter()
+        outs.append(torch.full_like(em.shard_grad, 7.0))
+    side.wait_stream(torch.cuda.current_stream())
+    for em, out in zip(ems, outs):
+        print("case: static reduce-scatter, %d layers, P=%d" % (len(em.sizes), em.P), flush=True)
+        dear.dear_reduce_scatter_static(em.plan, B.DEAR_F32 if em.grad_dtype == "f32" else B.DEAR_BF16,
+                                        [t.data_ptr() for rep in em.grads for t in rep], -1, out.data_ptr(), side.cuda_stream)
+    side.synchronize()
+    for em, out in zip(ems, outs):
+        assert torch.equal(out.view(torch.int32), em.shard_grad.view(torch.int32))
+
+
+@pytest.mark.gpu
+def test_static_call_refuses_a_captured_stream():
+    import torch
+    import paper_2302_12445_amd as dear
+    from paper_2302_12445_amd import binding as B
+    from paper_2302_12445_amd.emulation import EmulatedWorkers
+    em = EmulatedWorkers([5000, 77], 3, "f32", W_NO_LIMIT, "cuda:0")
+    ptrs = [t.data_ptr() for rep in em.grads for t in rep]
+    side, x = torch.cuda.Stream(), torch.zeros(4, device="cuda:0")
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        x.add_(1)
+        with pytest.raises(dear.DearError) as e:
+            dear.dear_reduce_scatter_static(em.plan, B.DEAR_F32, ptrs, -1, em.shard_grad.data_ptr(), side.cuda_stream)
+        assert e.value.status == B.DEAR_EHIP
+    for n in range(1, 4):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert x.tolist() == [n] * 4
+    dear.dear_reduce_scatter_static(em.plan, B.DEAR_F32, ptrs, -1, em.shard_grad.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
