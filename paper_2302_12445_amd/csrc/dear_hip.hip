@@ -797,79 +797,65 @@ __global__ __launch_bounds__(DEAR_BLOCK) void update_all_gather_kernel(
     });
 }
 
+// The two copies below take a quarter of a tile a workgroup, one 16-byte vector a lane: short workgroups in dispatch order, as
+// in the all-gather.  BERT-Base-shaped at P = 8 (881 MB moved), us, whole tiles / halves / quarters: scatter 155 / 149 / 136,
+// reshard 154 / 143 / 136 (6.5 TB/s, a plain copy reaches 6.65); 20 M ragged elements P = 7 31.0 / 29.5 / 28.7 and 32.0 / 30.0 / 30.0.
+// Fewer resident workgroups cost: four per CU 139 and 153.
+constexpr int COPY_PART = 4 * DEAR_BLOCK, COPY_SPLIT = DEAR_TILE_ELEMS / COPY_PART;
+
 // Inverse of the all-gather for one worker: layer tensors -> owned shard slots.
 __global__ __launch_bounds__(DEAR_BLOCK) void scatter_params_kernel(
     const dear_tile *__restrict__ tiles, float *const *__restrict__ param_tab, int L, int worker,
     float *__restrict__ shard_param)
 {
     constexpr int VE = 4;
-    constexpr int U = DEAR_TILE_ELEMS / (VE * DEAR_BLOCK);
-    const dear_tile t = tiles[blockIdx.x];
-    const int tid = threadIdx.x;
+    const dear_tile t = tiles[blockIdx.x / COPY_SPLIT];
+    const int tid = threadIdx.x, part = blockIdx.x % COPY_SPLIT;
     float *__restrict__ dst = shard_param + t.dst_begin;
     if (t.layer < 0) {
-        for (int i = tid; i < t.count; i += DEAR_BLOCK) dst[i] = 0.0f;
+        for (int i = part * DEAR_BLOCK + tid; i < t.count; i += COPY_SPLIT * DEAR_BLOCK) dst[i] = 0.0f;
         return;
     }
-    const DEAR_GLOBAL float *in = (const DEAR_GLOBAL float *)param_tab[(size_t)worker * L + t.layer];
     const int64_t a = t.src_begin, c = a + t.count;
-    const int64_t v_first = a / VE;
-    u4 val[U];
-    bool full[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {  // all loads first, so they are in flight together
-        const int64_t v = v_first + u * DEAR_BLOCK + tid;
-        full[u] = v * VE >= a && v * VE + VE <= c;
-        if (full[u]) val[u] = load_vec<true>((global_u4_in)in + v);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int64_t e0 = (v_first + u * DEAR_BLOCK + tid) * VE;
-        if (full[u]) store_f4_dword_aligned<true>(dst + (e0 - a), __builtin_bit_cast(f4, val[u]));
-    }
-    const int64_t e = edge_element<VE>(a, c, v_first, U * DEAR_BLOCK);
+    const int64_t v_first = a / VE + part * DEAR_BLOCK, e0 = (v_first + tid) * VE;
+    if (v_first * VE >= c) return;
+    const DEAR_GLOBAL float *in = (const DEAR_GLOBAL float *)param_tab[(size_t)worker * L + t.layer];
+    if (e0 >= a && e0 + VE <= c)
+        store_f4_dword_aligned<true>(dst + (e0 - a), __builtin_bit_cast(f4, load_vec<true>((global_u4_in)(in + e0))));
+    const int64_t e = edge_element<VE>(a, c, v_first, DEAR_BLOCK);
     if (e >= 0) dst[e - a] = in[e];
 }
 
 // Shard buffer of one plan -> shard buffer of another over the same layers and workers: a workgroup
-// takes one tile of the new plan, finds where its first element lies in the old one and copies up to
+// takes a part of a tile of the new plan, finds where its first element lies in the old one and copies up to
 // each old shard's end in turn.  Bound by HBM (4 bytes read, 4 written per element); both sides are only 4-byte
 // aligned against each other, so vectors are counted from the piece's start.
 // Going through a replica's tensors instead (gather, scatter, and gather again to give the tensors back)
-// moves three times the bytes: re-planning BERT-Base-shaped at P = 8 took 1311 us that way and takes 831.
+// moves three times the bytes: re-planning BERT-Base-shaped at P = 8 took 1311 us that way and 831 this way.
 __global__ __launch_bounds__(DEAR_BLOCK) void reshard_kernel(
     const dear_tile *__restrict__ tiles, const layer_place *__restrict__ places, int64_t from_row_len,
     const float *__restrict__ from, float *__restrict__ to)
 {
-    constexpr int U = DEAR_TILE_ELEMS / (4 * DEAR_BLOCK);
-    const dear_tile t = tiles[blockIdx.x];
-    const int tid = threadIdx.x;
-    float *__restrict__ dst = to + t.dst_begin;
+    const dear_tile t = tiles[blockIdx.x / COPY_SPLIT];
+    const int tid = threadIdx.x, skip = blockIdx.x % COPY_SPLIT * COPY_PART;
+    const int count = t.count - skip < COPY_PART ? t.count - skip : COPY_PART;
+    if (count <= 0) return;
+    float *__restrict__ dst = to + t.dst_begin + skip;
     if (t.layer < 0) {
-        for (int i = tid; i < t.count; i += DEAR_BLOCK) dst[i] = 0.0f;
+        for (int i = tid; i < count; i += DEAR_BLOCK) dst[i] = 0.0f;
         return;
     }
     const layer_place at = places[t.layer];
-    const int64_t e = at.offset + t.src_begin;
+    const int64_t e = at.offset + t.src_begin + skip;
     int64_t shard = (int64_t)((double)e * at.inv_shard_len);  // off by one at most
     if (shard * at.shard_len > e) --shard;
     if ((shard + 1) * at.shard_len <= e) ++shard;
     int64_t slot = e - shard * at.shard_len;
-    for (int done = 0; done < t.count; ++shard, slot = 0) {
+    for (int done = 0; done < count; ++shard, slot = 0) {
         const int64_t room = at.shard_len - slot;
-        const int n = room < t.count - done ? (int)room : t.count - done;
+        const int n = room < count - done ? (int)room : count - done, i = 4 * tid;
         const float *__restrict__ src = from + shard * from_row_len + at.shard_base + slot;
-        f4 val[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = 4 * (u * DEAR_BLOCK + tid);
-            if (i + 4 <= n) val[u] = load_f4_dword_aligned<true>(src + i);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = 4 * (u * DEAR_BLOCK + tid);
-            if (i + 4 <= n) store_f4_dword_aligned<true>(dst + done + i, val[u]);
-        }
+        if (i + 4 <= n) store_f4_dword_aligned<true>(dst + done + i, load_f4_dword_aligned<true>(src + i));
         if (tid < n % 4) dst[done + n - n % 4 + tid] = src[n - n % 4 + tid];
         done += n;
     }
@@ -1399,6 +1385,24 @@ extern "C" int dear_iteration(dear_ctx_t *c, int32_t bucket, float *shard_grad, 
     return rc;
 }
 
+namespace {
+
+// Workgroups for all parts of n_tiles tiles, in as many launches as HIP wants for them.
+template <class Launch>
+int launch_copies(int64_t n_tiles, Launch launch)
+{
+    constexpr int64_t MOST = MAX_GRID / COPY_SPLIT;
+    int rc = DEAR_OK;
+    for (int64_t first = 0; rc == DEAR_OK && first < n_tiles; first += MOST) {
+        const int64_t n = n_tiles - first < MOST ? n_tiles - first : MOST;
+        launch(first, dim3(static_cast<unsigned>(n * COPY_SPLIT)));
+        rc = launch_status();
+    }
+    return rc;
+}
+
+}  // namespace
+
 extern "C" int dear_scatter_params(dear_ctx_t *c, int32_t worker, float *shard_param, void *hip_stream)
 {
     int rc = check_call(c, -1);
@@ -1406,12 +1410,10 @@ extern "C" int dear_scatter_params(dear_ctx_t *c, int32_t worker, float *shard_p
     if (worker < 0 || worker >= c->P) return DEAR_ERANGE;
     rc = check_shard_buffer(shard_param);
     if (rc != DEAR_OK) return rc;
-    const int64_t count = c->tile_begin[c->B];
-    if (count == 0) return DEAR_OK;
-    scatter_params_kernel<<<dim3(static_cast<unsigned>(count)), dim3(DEAR_BLOCK), 0,
-                            static_cast<hipStream_t>(hip_stream)>>>(c->d_tiles, c->d_param, c->L, worker,
-                                                                    shard_param);
-    return launch_status();
+    return launch_copies(c->tile_begin[c->B], [&](int64_t first, dim3 grid) {
+        scatter_params_kernel<<<grid, dim3(DEAR_BLOCK), 0, static_cast<hipStream_t>(hip_stream)>>>(
+            c->d_tiles + first, c->d_param, c->L, worker, shard_param);
+    });
 }
 
 extern "C" int dear_reshard(dear_ctx_t *from, dear_ctx_t *to, const float *shard_from, float *shard_to, void *hip_stream)
@@ -1422,11 +1424,10 @@ extern "C" int dear_reshard(dear_ctx_t *from, dear_ctx_t *to, const float *shard
     if (rc == DEAR_OK) rc = check_shard_buffer(shard_to);
     if (rc != DEAR_OK) return rc;
     if (shard_from == shard_to || from->P != to->P || from->layer_sizes != to->layer_sizes) return DEAR_EINVAL;
-    const int64_t count = to->tile_begin[to->B];
-    if (count == 0) return DEAR_OK;
-    reshard_kernel<<<dim3(static_cast<unsigned>(count)), dim3(DEAR_BLOCK), 0, static_cast<hipStream_t>(hip_stream)>>>(
-        to->d_tiles, from->d_places, from->row_len, shard_from, shard_to);
-    return launch_status();
+    return launch_copies(to->tile_begin[to->B], [&](int64_t first, dim3 grid) {
+        reshard_kernel<<<grid, dim3(DEAR_BLOCK), 0, static_cast<hipStream_t>(hip_stream)>>>(
+            to->d_tiles + first, from->d_places, from->row_len, shard_from, shard_to);
+    });
 }
 
 // ------------------------------------------------------------- entry point without allocation

@@ -126,3 +126,32 @@ def test_static_call_refuses_a_captured_stream():
         assert x.tolist() == [n] * 4
     dear.dear_reduce_scatter_static(em.plan, B.DEAR_F32, ptrs, -1, em.shard_grad.data_ptr(), torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
+
+
+# quarters of tiles: runs that begin and end at every element of a vector, at a part's ends, within old shards of other lengths
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,thr_from,thr_to", [(1, W_NO_LIMIT, 0), (3, 0, 30_000), (7, 9000, W_NO_LIMIT), (5, W_NO_LIMIT, 60_001)])
+def test_copies_between_layouts(P, thr_from, thr_to):
+    import torch
+    import paper_2302_12445_amd as dear
+    from paper_2302_12445_amd.emulation import EmulatedWorkers
+    print("case: copies between layouts, P=%d" % P, flush=True)
+    sizes = list(range(1, 12)) + [1024 * k + j for k in (1, 2, 3, 4) for j in (-1, 0, 1, 2, 3)] + [30_001, 5, 12_289]
+    gen = torch.Generator("cuda:0").manual_seed(P)
+    old = EmulatedWorkers(sizes, P, "f32", thr_from, "cuda:0")
+    new = EmulatedWorkers(sizes, P, "f32", thr_to, "cuda:0")
+    for em in (old, new):
+        em.params[P - 1][0]._base.normal_(generator=gen.manual_seed(P))
+        em.shard_param.fill_(float("nan"))
+        em.scatter_params(P - 1)
+        for layer, t in enumerate(em.params[P - 1]):      # slot of every element, by the plan's own numbers
+            b = em.plan.layer_bucket[layer]
+            S, base = em.plan.bucket_shard_len[b], em.plan.bucket_shard_base[b]
+            e = em.plan.layer_offset[layer] + torch.arange(t.numel(), device="cuda:0")
+            assert torch.equal(em.shard_param[e // S, base + e % S], t)
+        assert int(em.shard_param.isnan().sum()) == 0 and float(em.shard_param.double().abs().sum()) > 0
+        assert int((em.shard_param != 0).sum()) <= sum(sizes)     # padding slots are +0
+    out = torch.full_like(new.shard_param, float("nan"))
+    dear.dear_reshard(old.ctx, new.ctx, old.shard_param.data_ptr(), out.data_ptr())
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int32), new.shard_param.view(torch.int32))
