@@ -14,8 +14,11 @@ from . import binding as B
 
 
 def _stream_handle(stream: Optional["torch.cuda.Stream"]) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+    """hipStream_t of `stream`, or of the current device's current stream.  The handle alone: 0.2 us, where
+    torch.cuda.current_stream() makes a Stream object in 2.7, half of what a small iteration takes."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 class EmulatedWorkers:
@@ -131,15 +134,16 @@ class EmulatedWorkers:
         Expects the state after an all-gather (every replica holds the current parameters)."""
         g = self.plan.grad_elem_bytes
         new_plan = plan if plan is not None else B.dear_plan(self.sizes, self.P, threshold_bytes, g)
+        row = new_plan.total_shard_len
+        # filled while the host gathers the tensors' addresses (as long as the fill, some 80 us, in 1600 tensors)
+        new_grad = torch.zeros(self.P, row, dtype=torch.float32, device=self.device)
         gp = [t.data_ptr() for rep in self.grads for t in rep]
         wp = [t.data_ptr() for rep in self.params for t in rep]
         with torch.cuda.device(self.device):
             new_ctx = B.dear_ctx_create(new_plan, B.DEAR_F32 if g == 4 else B.DEAR_BF16, gp, wp)
-        row = new_plan.total_shard_len
         # the library writes every slot of these two, the padding included
         new_param = torch.empty(self.P, row, dtype=torch.float32, device=self.device)
         new_mom = torch.empty(self.P, row, dtype=torch.float32, device=self.device)
-        new_grad = torch.zeros(self.P, row, dtype=torch.float32, device=self.device)
         s = stream if stream is not None else torch.cuda.current_stream()
         s.wait_stream(torch.cuda.current_stream())  # where the new buffers come from
         h = s.cuda_stream

@@ -20,6 +20,18 @@ def test_order_and_rules_on_the_host(tmp_path):
     assert "launch_order: ok" in subprocess.run([exe], check=True, capture_output=True, text=True).stdout
 
 
+def test_pointer_arrays_are_what_ctypes_makes_of_the_addresses():
+    import ctypes as C
+    import numpy as np
+    from paper_2302_12445_amd import binding as B
+    far = (1 << 64) - 256
+    for a in ([], [0], [far, 16], (1 << 40, 32), [None, 48], [-16], [True], np.array([64, 1 << 45], np.int64), np.array([far], np.uint64), b"ab"):
+        assert list(B._pointers(a)) == list((C.c_void_p * len(a))(*[int(x) if isinstance(x, np.integer) else x for x in a]))
+    for a in (["x"], [1.5]):
+        with pytest.raises(TypeError):
+            B._pointers(a)
+
+
 def list_of_tiles(tiles, P, g):
     """Two tensors whose plan has that many tiles in all."""
     import paper_2302_12445_amd as dear
