@@ -714,15 +714,16 @@ __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_bounded_kernel(
 // workgroup that computed it, so the stores go to all replicas at once (P interleaved write
 // streams) instead of replica by replica as in all_gather_kernel: for few replicas, short
 // launches and bounded grids.
-template <bool ALL_FULL>
-__device__ __forceinline__ void update_gather_tile(const dear_tile &t, float *const *__restrict__ param_tab, int L,
+template <int U, bool ALL_FULL>
+__device__ __forceinline__ void update_gather_tile(const dear_tile &t, int part, float *const *__restrict__ param_tab, int L,
                                                    int P, const float *__restrict__ g, float *__restrict__ w,
                                                    float *__restrict__ v, float lr, float mu)
 {
-    constexpr int VE = 4, U = DEAR_TILE_ELEMS / (VE * DEAR_BLOCK);
+    constexpr int VE = 4;
     const int tid = threadIdx.x;
     const int64_t a = t.src_begin, c = a + t.count;
-    const int64_t v_first = a / VE;
+    const int64_t v_first = a / VE + part * (U * DEAR_BLOCK);
+    if (!ALL_FULL && v_first * VE >= c) return;
     int64_t vi[U];
     bool full[U];
     f4 gg[U], ww[U], vv[U];
@@ -773,16 +774,18 @@ __device__ __forceinline__ void update_gather_tile(const dear_tile &t, float *co
     }
 }
 
-template <bool BOUNDED>
+template <int U, bool BOUNDED>
 __global__ __launch_bounds__(DEAR_BLOCK) void update_all_gather_kernel(
     const dear_tile *__restrict__ tiles, float *const *__restrict__ param_tab, int L, int P,
     const float *__restrict__ g, float *__restrict__ w, float *__restrict__ v, float lr, float mu,
-    unsigned n_tiles, int prio)
+    unsigned n_items, int prio)
 {
-    for_each_item<BOUNDED>(n_tiles, prio, [&](unsigned item) {
-        const dear_tile t = tiles[item];
+    constexpr int SPLIT = DEAR_TILE_ELEMS / (4 * DEAR_BLOCK * U);
+    for_each_item<BOUNDED>(n_items, prio, [&](unsigned item) {
+        const dear_tile t = tiles[item / SPLIT];
+        const int part = item % SPLIT;
         if (t.layer < 0) {  // padding slots are updated like any other (their averaged gradient is +0)
-            for (int i = threadIdx.x; i < t.count; i += DEAR_BLOCK) {
+            for (int i = part * DEAR_BLOCK + threadIdx.x; i < t.count; i += SPLIT * DEAR_BLOCK) {
                 const int64_t slot = t.dst_begin + i;
                 float wj = w[slot], vj = v[slot];
                 sgd_momentum(g[slot], wj, vj, lr, mu);
@@ -790,9 +793,9 @@ __global__ __launch_bounds__(DEAR_BLOCK) void update_all_gather_kernel(
                 w[slot] = wj;
             }
         } else if (t.count == DEAR_TILE_ELEMS) {
-            update_gather_tile<true>(t, param_tab, L, P, g, w, v, lr, mu);
+            update_gather_tile<U, true>(t, part, param_tab, L, P, g, w, v, lr, mu);
         } else {
-            update_gather_tile<false>(t, param_tab, L, P, g, w, v, lr, mu);
+            update_gather_tile<U, false>(t, part, param_tab, L, P, g, w, v, lr, mu);
         }
     });
 }
@@ -1289,18 +1292,21 @@ extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float
     const dear_tile *tiles = c->d_tiles + c->tile_begin[r.begin];
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const unsigned width = grid_width(c->max_workgroups, count);
-    if (update_all_gather_splits(count, c->P, c->max_workgroups)) {
+    if (update_all_gather_pays_apart(elements_of(c->bucket_len, r), count, c->P) &&
+        update_all_gather_splits(count, c->P, c->max_workgroups)) {
         rc = launch_update(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
         return rc == DEAR_OK ? launch_all_gather(c, range_of(c, r), shard_param, 0, c->P, st) : rc;
     }
+    auto launch = [&](auto kernel, int64_t items, unsigned grid, int prio) {
+        kernel<<<dim3(grid), dim3(DEAR_BLOCK), 0, st>>>(tiles, c->d_param, c->L, c->P, shard_grad, shard_param, shard_mom, lr,
+                                                        momentum, static_cast<unsigned>(items), prio);
+    };
     if (width < count)
-        update_all_gather_kernel<true><<<dim3(width), dim3(DEAR_BLOCK), 0, st>>>(
-            tiles, c->d_param, c->L, c->P, shard_grad, shard_param, shard_mom, lr, momentum,
-            static_cast<unsigned>(count), c->wave_priority);
+        launch(update_all_gather_kernel<4, true>, count, width, c->wave_priority);
+    else if (update_all_gather_quarters(elements_of(c->bucket_len, r), count))
+        launch(update_all_gather_kernel<1, false>, count * 4, width * 4, 0);
     else
-        update_all_gather_kernel<false><<<dim3(width), dim3(DEAR_BLOCK), 0, st>>>(
-            tiles, c->d_param, c->L, c->P, shard_grad, shard_param, shard_mom, lr, momentum,
-            static_cast<unsigned>(count), 0);
+        launch(update_all_gather_kernel<4, false>, count, width, 0);
     return launch_status();
 }
 

@@ -107,18 +107,36 @@ inline all_gather_order all_gather_numbering(int grad_bytes, int64_t max_workgro
 // dear_update_all_gather as one kernel writes all P replicas from the workgroup that updated: P write streams at
 // once, which HBM sustains worse the more there are (5.4 TB/s at P = 8, against 6.5 replica by replica).  From
 // UAG_SPLIT_P replicas on the 4 bytes per element that one kernel saves are worth less than that, if the
-// launch is long enough to pay for a second one: UAG_SPLIT_TILES tile copies are about 25 us.  us per iteration
+// launch is long enough to pay for a second one: UAG_SPLIT_TILES tile copies are about 15 us.  us per iteration
 // of reduce-scatters and these calls, one kernel / update, then all-gather: 100 M elements in 64 MB buckets
 // P = 2 710 / 757, P = 3 857 / 878, P = 4 1016 / 1011; 25 M elements in 25 MB buckets P = 8 430 / 400;
 // BERT-Base-shaped P = 16 3173 / 2826; 5 M elements in 4 MB buckets P = 8 115 / 131; 36 M elements P = 5 in one call
-// 340 / 346, in 64 MB buckets 431 / 423, P = 6 474 / 463.  Beyond the largest all-gather the one kernel, whose
+// 340 / 346, in 64 MB buckets 431 / 423, P = 6 474 / 463.  GPU time of this call alone, us: P = 4 20 M 128 / 120, 60 M 383 / 384,
+// P = 6 2 M 16.2 / 17.8, 4 M 33.3 / 31.5, 20 M 159 / 147, P = 8 1 M 9.6 / 11.8, 2 M 19.7 / 20.3, 4 M 40.7 / 36.6, P = 12 1 M 14.9 / 14.4, 2 M
+// 25.8 / 24.9, P = 16 0.3 M 8.1 / 8.8, 1 M 18.2 / 16.6, P = 32 0.3 M 11.0 / 14.1, 1 M 31.7 / 27.4.  Beyond the largest all-gather the one kernel, whose
 // grid is the tile count alone, still takes the call.
-constexpr int64_t UAG_SPLIT_P = 6, UAG_SPLIT_TILES = 8192;
+constexpr int64_t UAG_SPLIT_P = 5, UAG_SPLIT_TILES = 4096;
 
 inline bool update_all_gather_splits(int64_t tiles, int64_t P, int64_t max_workgroups)
 {
     const bool bounded = max_workgroups > 0 && tiles > max_workgroups;
     return !bounded && P >= UAG_SPLIT_P && tiles * P >= UAG_SPLIT_TILES && all_gather_fits(tiles, P, max_workgroups);
+}
+
+// It pays by what the tiles hold: the all-gather's workgroups for the parts of tiles that short tensors leave open cost as much as
+// others (1 M elements in 500 tensors, one kernel / two: P = 8 16.5 / 20.1, P = 16 24.8 / 32.9; 3 M in 300 P = 8 35.3 / 32.5).
+inline bool update_all_gather_pays_apart(int64_t elems, int64_t tiles, int64_t P)
+{
+    const int64_t open = tiles * DEAR_TILE_ELEMS - elems;
+    return (elems - open) * P >= 14000000;
+}
+
+// The one kernel in quarters of tiles: where whole ones leave most CUs idle, or are mostly open.  GPU time, us, whole tiles /
+// quarters: 0.1 M elements P = 2 4.0 / 3.2, P = 8 5.1 / 3.8, P = 32 9.8 / 7.1, 0.3 M P = 2 4.6 / 3.7, P = 8 6.1 / 5.1, 1 M in 500 tensors P = 8
+// 16.5 / 14.7; 1 M P = 2 6.0 / 6.3, P = 8 9.6 / 10.1, 2 M P = 4 13.3 / 15.2, 20 M P = 2 97.6 / 103.
+inline bool update_all_gather_quarters(int64_t elems, int64_t tiles)
+{
+    return tiles <= 160 || (tiles <= 1024 && elems < tiles * (DEAR_TILE_ELEMS / 2));
 }
 
 // Cuts every bucket of the plan into runs and tiles (plan.cpp).

@@ -167,3 +167,17 @@ def test_copies_between_layouts(P, thr_from, thr_to):
     dear.dear_reshard(old.ctx, new.ctx, old.shard_param.data_ptr(), out.data_ptr())
     torch.cuda.synchronize()
     assert torch.equal(out.view(torch.int32), new.shard_param.view(torch.int32))
+
+
+# update and all-gather in one call: quarters of tiles and whole ones, open tiles, one kernel and two
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,sizes", [(1, [5]), (2, [150 * 4096, 77]), (2, [158 * 4096 + 1]), (7, [171 * 4096, 9]), (3, [300, 701, 64] * 150), (4, [2100] * 400),
+                                     (5, [2_000_003]), (5, [3_900_001, 33]), (8, [900] * 700), (12, [1_300_000])])
+def test_update_all_gather_forms(P, sizes):
+    from test_gpu_parity import Pair, say, small_workload
+    import workloads as W
+    say("case: update + all-gather, P=%d, %d tensors, %d elements" % (P, len(sizes), sum(sizes)))
+    pair = Pair(small_workload(sizes, P, W.NO_LIMIT))
+    pair.run(iterations=1, fused_gather=True)
+    pair.run(iterations=1, fused_gather=True, width=50)
+    pair.close()
