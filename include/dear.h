@@ -157,7 +157,8 @@ int dear_plan_tiles(const dear_plan_t *plan, dear_tile_t *out, int64_t capacity,
  * pointer arrays are copied; the tensors themselves stay owned by the caller and must
  * outlive the context.  The context copies what it needs from the plan, so the plan
  * may be freed first.  Allocates device memory for its tables (pointer tables, a
- * table of 32 bytes per layer and a tile table of 32 bytes per DEAR_TILE_ELEMS elements).  Uses the current HIP device;
+ * table of 32 bytes per layer, one of 48 bytes per run of a layer within a shard, and a tile table of 32
+ * bytes per DEAR_TILE_ELEMS elements).  Uses the current HIP device;
  * every later call on the context must be made with that device current (DEAR_EINVAL
  * otherwise).
  * Errors: DEAR_EINVAL, DEAR_EALIGN, DEAR_ENOMEM, DEAR_EHIP.
@@ -315,9 +316,11 @@ int dear_update_all_gather(dear_ctx_t *ctx, int32_t bucket, const float *shard_g
  * dear_iteration -- the whole pass over a bucket (or all of them) on one stream, for callers
  * whose gradients are all in place: reduce-scatter, update and all-gather.  Results are
  * bit-identical to dear_reduce_scatter, dear_shard_update and dear_all_gather in a row.  Small
- * buckets share a launch; the update is applied in the reduce-scatter's kernel, or behind it
- * where many replicas are read and shard_grad is wanted; the all-gather of a group of buckets
- * follows directly, while the parameter shards are in the last-level cache if they fit it.
+ * calls, and large ones with few replicas, are one launch, which stores the updated parameters to
+ * all replicas as it computes them.  Otherwise small buckets share launches; the update is applied
+ * in the reduce-scatter's kernel, or behind it where many replicas are read and shard_grad is
+ * wanted; the all-gather of a group of buckets, or of a piece of a large one, follows directly,
+ * while the parameter shards are in the last-level cache if they fit it.
  * (The decoupled schedule, paper Section III-B, issues the halves separately with the calls
  * above.)
  *   shard_grad   device, written; NULL if the averaged gradients are not wanted

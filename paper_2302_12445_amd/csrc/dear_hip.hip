@@ -5,7 +5,7 @@
 // layer/shard run, many independent loads in flight per lane, no matrix cores.
 //
 // Packing (copy into the fusion buffer, paper Sec. IV-A / V-A) is never materialised:
-// a host-built tile table maps every run of bucket positions to (layer, element range,
+// a tile table maps every run of bucket positions to (layer, element range,
 // owning shard, shard-buffer offset), and the reduce-scatter reads the per-layer tensors
 // directly while the all-gather writes them directly.
 //
@@ -707,7 +707,7 @@ __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_bounded_kernel(
     });
 }
 
-// Update and all-gather of a bucket in one kernel: a workgroup takes one tile, applies the
+// Update and all-gather of a bucket in one kernel: a workgroup takes one tile (U = 4; a quarter with U = 1), applies the
 // SGD-momentum update to the tile's slots (the same four separately rounded operations as
 // shard_update_kernel), stores the new w and v to the shard buffers and the new w to all
 // receiving replicas' layer tensors.  The updated value has to reach every replica from the
