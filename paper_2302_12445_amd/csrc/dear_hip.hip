@@ -872,7 +872,7 @@ __host__ __device__ __forceinline__ dear_tile marked_tile(const dear_run &r, int
 }
 
 // Tile table from runs, a workgroup a run.  The kernel takes some 3 us; what it saves is the host's time, which wrote and
-// uploaded 32 bytes a tile and now 48 a run (BERT-Base-shaped, P = 8: 27000 tiles, 317 runs; making a context 190 us -> 89).
+// uploaded 32 bytes a tile and now 48 a run (BERT-Base-shaped, P = 8: 27000 tiles, 317 runs; making a context 150 us -> 45).
 // A run's `bucket` goes into all its tiles, with notes on which of them are its first and its last.
 __global__ __launch_bounds__(DEAR_BLOCK) void expand_runs_kernel(const dear_run *__restrict__ runs, dear_tile *__restrict__ tiles)
 {
@@ -919,12 +919,17 @@ int64_t elements_of(const std::vector<int64_t> &bucket_len, bucket_range r)
     return std::accumulate(bucket_len.begin() + r.begin, bucket_len.begin() + r.end, int64_t{0});
 }
 
-// Whether the launch was taken; says nothing of errors that other calls left behind.
+// Whether the launches were taken; says nothing of errors that other calls left behind.
 bool expand_runs(const dear_run *runs, int64_t n_runs, dear_tile *tiles, hipStream_t st)
 {
-    void *args[] = {&runs, &tiles};
-    return hipLaunchKernel(reinterpret_cast<const void *>(expand_runs_kernel), dim3(static_cast<unsigned>(n_runs)), dim3(DEAR_BLOCK),
-                           args, 0, st) == hipSuccess;
+    for (; n_runs > 0; runs += MAX_GRID, n_runs -= MAX_GRID) {
+        const int64_t n = n_runs < MAX_GRID ? n_runs : MAX_GRID;
+        void *args[] = {&runs, &tiles};
+        if (hipLaunchKernel(reinterpret_cast<const void *>(expand_runs_kernel), dim3(static_cast<unsigned>(n)), dim3(DEAR_BLOCK), args,
+                            0, st) != hipSuccess)
+            return false;
+    }
+    return true;
 }
 
 // Host memory that is not pinned -> device memory, stream-ordered.  The runtime takes copies of up to 16 KiB without waiting;
@@ -1015,8 +1020,9 @@ void rs_launch(bool bf16, const rs_call &c, const rs_sink<MODE> &o)
         rs_launch_batched<true, MODE, 2>(c, o);
 }
 
-// Up to this many tiles a context's table is cut on the host: 13 us for 85 tiles, 17 with the kernel and the wait for it.
-constexpr int64_t HOST_TILES = 1024;
+// Up to this many tiles a context's table is cut on the host.  Making a context, us, on the host / with the kernel and the wait
+// for it: 93 tiles 12.9 / 17, 2700 tiles 28 / 31, 5100 (300 tensors) 38 / 29, 5000 (100 tensors) 34 / 21, 27000 150 / 45.
+constexpr int64_t HOST_TILES = 3072;
 
 constexpr int64_t SHIFT_TILES = 8;
 
@@ -1114,10 +1120,13 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
     } else {
         c->d_tiles = static_cast<dear_tile *>(c->d_tables);
         base = static_cast<unsigned char *>(c->d_tables) + in_front;
-        if (hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice) != hipSuccess ||
-            (!on_host && (!expand_runs(reinterpret_cast<const dear_run *>(base), n_runs, c->d_tiles, nullptr) ||
-                          hipStreamSynchronize(nullptr) != hipSuccess)))
-            rc = DEAR_EHIP;
+        if (on_host) {
+            if (hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice) != hipSuccess) rc = DEAR_EHIP;
+        } else {
+            const bool sent = upload(base, image.data(), image.size(), nullptr) &&
+                              expand_runs(reinterpret_cast<const dear_run *>(base), n_runs, c->d_tiles, nullptr);
+            if (hipStreamSynchronize(nullptr) != hipSuccess || !sent) rc = DEAR_EHIP;
+        }
     }
     if (rc != DEAR_OK) {
         (void)hipGetLastError();
