@@ -1312,7 +1312,7 @@ extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float
     };
     if (width < count)
         launch(update_all_gather_kernel<4, true>, count, width, c->wave_priority);
-    else if (update_all_gather_quarters(elements_of(c->bucket_len, r), count))
+    else if (update_all_gather_quarters(elements_of(c->bucket_len, r), count, c->max_workgroups))
         launch(update_all_gather_kernel<1, false>, count * 4, width * 4, 0);
     else
         launch(update_all_gather_kernel<4, false>, count, width, 0);

@@ -131,11 +131,13 @@ inline bool update_all_gather_pays_apart(int64_t elems, int64_t tiles, int64_t P
     return (elems - open) * P >= 14000000;
 }
 
-// The one kernel in quarters of tiles: where whole ones leave most CUs idle, or are mostly open.  GPU time, us, whole tiles /
+// The one kernel in quarters of tiles: where whole ones leave most CUs idle, or are mostly open, and a bound on the grid
+// leaves room for four workgroups a tile.  GPU time, us, whole tiles /
 // quarters: 0.1 M elements P = 2 4.0 / 3.2, P = 8 5.1 / 3.8, P = 32 9.8 / 7.1, 0.3 M P = 2 4.6 / 3.7, P = 8 6.1 / 5.1, 1 M in 500 tensors P = 8
 // 16.5 / 14.7; 1 M P = 2 6.0 / 6.3, P = 8 9.6 / 10.1, 2 M P = 4 13.3 / 15.2, 20 M P = 2 97.6 / 103.
-inline bool update_all_gather_quarters(int64_t elems, int64_t tiles)
+inline bool update_all_gather_quarters(int64_t elems, int64_t tiles, int64_t max_workgroups)
 {
+    if (max_workgroups > 0 && tiles * 4 > max_workgroups) return false;
     return tiles <= 160 || (tiles <= 1024 && elems < tiles * (DEAR_TILE_ELEMS / 2));
 }
 

@@ -48,6 +48,17 @@ int main()
                         std::exit(1);
                     }
                 }
+    // a bound holds for the grid that dear_update_all_gather's one kernel gets
+    for (int64_t width : {1, 5, 50, 64, 160, 256, 640, 641, 1000, 5000})
+        for (int64_t tiles = 1; tiles < 1100; ++tiles)
+            for (int64_t elems : {tiles, tiles * 700, tiles * 2100, tiles * DEAR_TILE_ELEMS}) {
+                const bool bounded = tiles > width;
+                const int64_t grid = bounded ? width : update_all_gather_quarters(elems, tiles, width) ? tiles * 4 : tiles;
+                if (grid > width) {
+                    std::fprintf(stderr, "FAILED update + all-gather: %lld workgroups, bound %lld\n", (long long)grid, (long long)width);
+                    std::exit(1);
+                }
+            }
     std::printf("launch_order: ok\n");
     return 0;
 }
