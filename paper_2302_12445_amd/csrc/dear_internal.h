@@ -81,7 +81,7 @@ inline bool reduce_scatter_half_tiles(bool updates, int64_t max_workgroups, int6
 }
 
 // How the unbounded all-gather numbers its workgroups (see all_gather_kernel).  Where HIP would not take a launch with a
-// rounded last chunk, that chunk stays as it falls.
+// rounded last chunk, or a bound on the grid would not allow it, that chunk stays as it falls.
 struct all_gather_order {
     unsigned len, run;
 };
@@ -100,7 +100,8 @@ inline all_gather_order all_gather_numbering(int grad_bytes, int64_t max_workgro
     const unsigned last = parts - whole;
     const unsigned run = grad_bytes == 2 && reduce_scatter_half_tiles(true, max_workgroups, parts / AG_SPLIT) ? 1 : 0;
     const unsigned rounded = (last + (8u << run) - 1) & ~((8u << run) - 1);
-    if ((static_cast<int64_t>(whole) + rounded) * n_workers > MAX_GRID) return {last, 0};
+    const int64_t most = max_workgroups > 0 && max_workgroups < MAX_GRID ? max_workgroups : MAX_GRID;
+    if ((static_cast<int64_t>(whole) + rounded) * n_workers > most) return {last, 0};
     return {rounded, run};
 }
 

@@ -1,6 +1,6 @@
 // Host-only check (dear_internal.h) of the all-gather's numbering -- for every replica, each part of a launch belongs to
-// exactly one workgroup, in chunks and behind them, whatever the part count -- and of the rule that takes a whole iteration in
-// one launch: none that HIP would not take, none with a bounded grid.  Exits non-zero on the first mistake.
+// exactly one workgroup, in chunks and behind them, whatever the part count, in a grid that HIP and a bound allow -- and of the
+// rule that takes a whole iteration in one launch: none that HIP would not take, none with a bounded grid.  Exits non-zero on the first mistake.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -12,11 +12,11 @@ int main()
 {
     const unsigned chunk = 4096;
     for (int g = 2; g <= 4; g += 2)
-        for (int64_t width : {0, 256})
+        for (int64_t width : {0, 8, 28, 56, 256, 1000, 100000})
             for (int64_t P : {int64_t(1), int64_t(7), int64_t(64), int64_t(4095), int64_t(4096), int64_t(5000), MAX_GRID / 4})
                 for (unsigned tiles : {1u, 2u, 3u, 4u, 5u, 511u, 1021u, 1023u, 1024u, 1025u, 1026u, 2047u, 2048u, 2049u}) {
                     const unsigned parts = tiles * AG_SPLIT;
-                    if (!all_gather_fits(tiles, P, 0)) continue;
+                    if (!all_gather_fits(tiles, P, 0) || all_gather_bounded(tiles, P, width)) continue;
                     const unsigned whole = parts / chunk * chunk;
                     const all_gather_order o = all_gather_numbering(g, width, whole, parts, P);
                     std::vector<int> seen(parts, 0);
@@ -26,7 +26,8 @@ int main()
                         if (id < parts) ++seen[id];
                         if (id / AG_SPLIT >= tiles + TILES_BEHIND) seen[0] = 2;  // reads a tile that is not there
                     }
-                    bool ok = (whole + int64_t(o.len)) * P <= MAX_GRID;
+                    const int64_t grid = (whole + int64_t(o.len)) * P;
+                    bool ok = grid <= MAX_GRID && (width == 0 || grid <= width);
                     for (int n : seen) ok = ok && n == 1;
                     if (!ok) {
                         std::fprintf(stderr, "FAILED g=%d width=%d P=%lld tiles=%u\n", g, int(width), (long long)P, tiles);

@@ -31,7 +31,13 @@ static void grids()
                     const bool bounded = all_gather_bounded(tiles, P, width);
                     const bool fits = all_gather_fits(tiles, P, width);
                     // the grid that launch_all_gather asks for
-                    if (fits) CHECK(hip_takes(!bounded ? items : width < tiles ? width : tiles));
+                    int64_t grid = width < tiles ? width : tiles;
+                    if (!bounded && fits) {
+                        const unsigned parts = static_cast<unsigned>(tiles * AG_SPLIT), whole = parts / 4096 * 4096;
+                        grid = (int64_t(whole) + all_gather_numbering(2, width, whole, parts, P).len) * P;
+                        CHECK(grid >= items && (width <= 0 || grid <= width));
+                    }
+                    if (fits) CHECK(hip_takes(grid));
                     if (!bounded) CHECK(fits == hip_takes(items));
                     if (bounded && width <= MAX_GRID) CHECK(fits == (items <= 0x7fffffff));
                     // the update goes first, so the all-gather behind it must be one that can be launched
