@@ -13,12 +13,17 @@ import torch
 from . import binding as B
 
 
+_raw_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # not a name that torch promises to keep
+
+
 def _stream_handle(stream: Optional["torch.cuda.Stream"]) -> int:
     """hipStream_t of `stream`, or of the current device's current stream.  The handle alone: 0.2 us, where
     torch.cuda.current_stream() makes a Stream object in 2.7, half of what a small iteration takes."""
     if stream is not None:
         return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_current_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_current_stream(torch.cuda.current_device())
 
 
 class EmulatedWorkers:

@@ -32,6 +32,16 @@ def test_pointer_arrays_are_what_ctypes_makes_of_the_addresses():
             B._pointers(a)
 
 
+def test_stream_handle_without_torchs_private_name(monkeypatch):
+    import torch
+    from types import SimpleNamespace
+    from paper_2302_12445_amd import emulation
+    monkeypatch.setattr(emulation, "_raw_current_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=4711))
+    assert emulation._stream_handle(None) == 4711
+    assert emulation._stream_handle(SimpleNamespace(cuda_stream=5)) == 5
+
+
 def list_of_tiles(tiles, P, g):
     """Two tensors whose plan has that many tiles in all."""
     import paper_2302_12445_amd as dear
