@@ -43,6 +43,7 @@ struct dear_ctx_impl {
     int64_t row_len = 0;
     std::vector<int64_t> bucket_len, bucket_shard_len, bucket_shard_base;
     std::vector<int64_t> tile_begin;  // [B+1] range of bucket b's tiles in the tile table
+    std::vector<int64_t> whole_begin;  // [B+1] how many of the tiles before bucket b are whole
     std::vector<int64_t> layer_sizes;
     void *d_tables = nullptr;         // one allocation: the four tables below
     dear_tile *d_tiles = nullptr;
@@ -1081,6 +1082,7 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
         c->bucket_shard_base = plan->bucket_shard_base;
         c->layer_sizes = plan->layer_sizes;
         c->tile_begin.assign(plan->B + 1, 0);
+        c->whole_begin.assign(plan->B + 1, 0);
         n_runs = dear_emit_runs(*plan, 0, plan->B, nullptr, 0, &n_tiles, c->tile_begin.data());
         runs.resize(n_runs);
         places_at = n_tiles <= HOST_TILES ? (n_tiles + TILES_BEHIND) * sizeof(dear_tile) : n_runs * sizeof(dear_run);
@@ -1093,6 +1095,8 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
     if (n_tiles > 0x7fffffff / 16) return DEAR_EINVAL;  // item counts fit 31 bits, up to 16 a tile
     if (hipGetDevice(&c->device) != hipSuccess) return DEAR_EHIP;
     dear_emit_runs(*plan, 0, plan->B, runs.data(), n_runs, &n_tiles, nullptr);
+    for (const dear_run &r : runs) c->whole_begin[r.bucket + 1] += whole_tiles_of_run(r);
+    std::partial_sum(c->whole_begin.begin(), c->whole_begin.end(), c->whole_begin.begin());
     mark_runs(*plan, param_ptrs, runs.data(), n_runs);
     const bool on_host = n_tiles <= HOST_TILES;
     if (on_host) {
@@ -1312,7 +1316,7 @@ extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float
     };
     if (width < count)
         launch(update_all_gather_kernel<4, true>, count, width, c->wave_priority);
-    else if (update_all_gather_quarters(elements_of(c->bucket_len, r), count, c->max_workgroups))
+    else if (update_all_gather_quarters(elements_of(c->bucket_len, r), count, c->whole_begin[r.end] - c->whole_begin[r.begin], c->P, c->max_workgroups))
         launch(update_all_gather_kernel<1, false>, count * 4, width * 4, 0);
     else
         launch(update_all_gather_kernel<4, false>, count, width, 0);

@@ -40,6 +40,13 @@ DEAR_HOST_DEVICE inline int64_t tiles_of_run(const dear_run &r)
     return (r.src_begin + r.count + DEAR_TILE_ELEMS - 1) / DEAR_TILE_ELEMS - r.src_begin / DEAR_TILE_ELEMS;
 }
 
+// Those of its tiles that are whole ones of a layer.
+inline int64_t whole_tiles_of_run(const dear_run &r)
+{
+    const int64_t n = (r.src_begin + r.count) / DEAR_TILE_ELEMS - (r.src_begin + DEAR_TILE_ELEMS - 1) / DEAR_TILE_ELEMS;
+    return r.layer < 0 || n < 0 ? 0 : n;
+}
+
 DEAR_HOST_DEVICE inline dear_tile tile_of_run(const dear_run &r, int64_t k)
 {
     const int64_t cut = (r.src_begin / DEAR_TILE_ELEMS + k) * DEAR_TILE_ELEMS, end = r.src_begin + r.count;
@@ -132,14 +139,33 @@ inline bool update_all_gather_pays_apart(int64_t elems, int64_t tiles, int64_t P
     return (elems - open) * P >= 14000000;
 }
 
-// The one kernel in quarters of tiles: where whole ones leave most CUs idle, or are mostly open, and a bound on the grid
-// leaves room for four workgroups a tile.  GPU time, us, whole tiles /
-// quarters: 0.1 M elements P = 2 4.0 / 3.2, P = 8 5.1 / 3.8, P = 32 9.8 / 7.1, 0.3 M P = 2 4.6 / 3.7, P = 8 6.1 / 5.1, 1 M in 500 tensors P = 8
-// 16.5 / 14.7; 1 M P = 2 6.0 / 6.3, P = 8 9.6 / 10.1, 2 M P = 4 13.3 / 15.2, 20 M P = 2 97.6 / 103.
-inline bool update_all_gather_quarters(int64_t elems, int64_t tiles, int64_t max_workgroups)
+// Whether some of a launch's tiles are whole.  Weights between short vectors give whole tiles and nearly empty ones, tensors
+// that are all shorter than a tile none; elements and tiles alone do not tell one from the other.
+inline bool some_whole(int64_t whole, int64_t tiles) { return whole * 64 >= tiles; }
+
+// The one kernel in quarters of tiles, one vector a lane: where whole ones leave CUs idle, or keep them waiting for the few that
+// hold most.  The more workgroups there are already, and the less all tiles hold, the more their number costs; it stays within a
+// bound on the grid.  GPU time, all reduce-scatters, then these calls, us, whole tiles / quarters:
+//   one bucket of weights and short vectors, by tiles a bucket
+//     P = 2  113 7.6 / 6.5  199 8.0 / 7.4  357 10.7 / 8.9  586 11.7 / 11.1   P = 3 sixteen buckets of 166 (90 % full) 162 / 171
+//     P = 8  91 9.7 / 9.0  128 9.8 / 9.0  182 9.9 / 9.4  297 16.2 / 14.5  466 15.6 / 13.9  614 (a tenth full) 11.1 / 12.9
+//     P = 16 125 13.6 / 12.8  165 14.2 / 13.3  288 16.0 / 15.7  440 (60 % full) 36.5 / 37.9   P = 24 322 28.8 / 26.1  660 54.0 / 51.5
+//     P = 32 106 19.9 / 18.2  138 22.5 / 23.6  238 24.1 / 26.3   P = 48 87 (eleven buckets) 283 / 259  132 28.9 / 30.0
+//     P = 64 83 (nearly empty) 20.7 / 19.2  120 (two buckets) 65.8 / 66.7  138 37.4 / 43.1
+//   eight buckets (fewer from P = 32 on) of one tensor  P = 2 24 tiles 47.5 / 39.7  64 51.7 / 50.7  110 59.0 / 57.8  150 63.4 / 65.3   P = 4 24 52.8 / 43.8
+//     110 68.6 / 69.3  150 74.6 / 78.9   P = 8 24 62.6 / 51.5  110 84.0 / 84.8  150 99.0 / 101.1   P = 16 24 85.5 / 68.7  150 155.2 / 157.2
+//     P = 32 24 127 / 103  110 221 / 233   P = 64 24 193 / 189  64 246 / 252  97 109 / 111
+//   of tensors of one length, 3000  P = 4 64 61.1 / 52.1  128 68.9 / 66.3   P = 16 64 96 / 82  128 107 / 106  143 123 / 126;  900  P = 2 32 47.4 / 47.3
+//     64 49.5 / 50.7   P = 8 56 60.8 / 60.0  72 65.4 / 65.7   P = 16 80 93.1 / 93.7  96 100 / 105   P = 24 104 141 / 132;  beyond
+//     P = 2 800 of 1200 13.3 / 17.7   P = 8 400 of 1200 15.6 / 19.3  800 24.9 / 32.8
+inline bool update_all_gather_quarters(int64_t elems, int64_t tiles, int64_t whole, int64_t P, int64_t max_workgroups)
 {
     if (max_workgroups > 0 && tiles * 4 > max_workgroups) return false;
-    return tiles <= 160 || (tiles <= 1024 && elems < tiles * (DEAR_TILE_ELEMS / 2));
+    if (P > 24) return tiles <= 112;
+    const int64_t room = tiles * DEAR_TILE_ELEMS;
+    if (!some_whole(whole, tiles)) return tiles <= (elems * 3 >= room ? 128 : P <= 6 ? 48 : P <= 16 ? 80 : 112);
+    if (elems * 4 >= room * 3) return tiles <= (P <= 2 ? 144 : 112);
+    return tiles <= (elems * 2 < room && elems * 8 >= room ? 1024 : 160);
 }
 
 // Cuts every bucket of the plan into runs and tiles (plan.cpp).

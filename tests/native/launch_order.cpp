@@ -54,7 +54,7 @@ int main()
         for (int64_t tiles = 1; tiles < 1100; ++tiles)
             for (int64_t elems : {tiles, tiles * 700, tiles * 2100, tiles * DEAR_TILE_ELEMS}) {
                 const bool bounded = tiles > width;
-                const int64_t grid = bounded ? width : update_all_gather_quarters(elems, tiles, width) ? tiles * 4 : tiles;
+                const int64_t grid = bounded ? width : update_all_gather_quarters(elems, tiles, elems / DEAR_TILE_ELEMS, 8, width) ? tiles * 4 : tiles;
                 if (grid > width) {
                     std::fprintf(stderr, "FAILED update + all-gather: %lld workgroups, bound %lld\n", (long long)grid, (long long)width);
                     std::exit(1);

@@ -99,11 +99,45 @@ static void iteration()
                 }
 }
 
+// dear_update_all_gather in one kernel: quarters of tiles in small launches, the smaller the more replicas, and in larger ones of
+// few whole tiles among short ones.
+static void update_and_gather()
+{
+    struct { int64_t P, tiles, fill, whole; bool quarters; } const at[] = {
+        {1, 1, 5, 0, true},         {3, 112, 4096, 112, true},  {3, 113, 4096, 113, false}, {2, 144, 4096, 144, true}, {2, 145, 4096, 145, false},
+        {16, 160, 3000, 80, true},  {16, 161, 3000, 80, false}, {16, 113, 3072, 80, false}, {2, 145, 3072, 80, false},
+        {24, 1024, 1500, 16, true}, {24, 1025, 1500, 20, false}, {24, 1024, 1500, 15, false},
+        {8, 400, 2048, 99, false},  {8, 400, 2047, 99, true},   {4, 128, 1366, 0, true},    {4, 129, 1366, 0, false},  {6, 48, 900, 0, true},
+        {6, 49, 900, 0, false},     {7, 80, 900, 0, true},      {7, 81, 900, 1, false},     {7, 81, 900, 2, true},     {25, 112, 4096, 112, true},
+        {8, 614, 511, 20, false},    {8, 614, 512, 20, true},    {8, 160, 300, 20, true},    {25, 113, 900, 30, false},  {17, 112, 900, 0, true},   {17, 113, 900, 0, false},  {64, 112, 900, 0, true},    {64, 113, 2000, 9, false},  {4, 402, 1200, 0, false},  {8, 802, 1500, 0, false},
+    };
+    for (const auto &c : at) {
+        CHECK(update_all_gather_quarters(c.tiles * c.fill, c.tiles, c.whole, c.P, 0) == c.quarters);
+        CHECK(update_all_gather_quarters(c.tiles * c.fill, c.tiles, c.whole, c.P, 4 * c.tiles) == c.quarters);
+        CHECK(!update_all_gather_quarters(c.tiles * c.fill, c.tiles, c.whole, c.P, 4 * c.tiles - 1));
+    }
+}
+
+// Whole tiles of a run against its tiles one by one.
+static void whole_tiles()
+{
+    for (int64_t begin : {0, 1, 5, 4095, 4096, 4097, 8192, 12287})
+        for (int64_t count : {1, 2, 4090, 4095, 4096, 4097, 8191, 8192, 8193, 20000, 20480})
+            for (int32_t layer : {-1, 3}) {
+                const dear_run r{layer < 0 ? 0 : begin, 7, count, 0, layer, 0, 0, 0};
+                int64_t n = 0;
+                for (int64_t k = 0; k < tiles_of_run(r); ++k) n += layer >= 0 && tile_of_run(r, k).count == DEAR_TILE_ELEMS;
+                CHECK(whole_tiles_of_run(r) == n);
+            }
+}
+
 int main()
 {
     grids();
     residency();
     iteration();
+    whole_tiles();
+    update_and_gather();
     std::printf("launch_rules: ok\n");
     return 0;
 }

@@ -179,10 +179,12 @@ def test_copies_between_layouts(P, thr_from, thr_to):
     assert torch.equal(out.view(torch.int32), new.shard_param.view(torch.int32))
 
 
-# update and all-gather in one call: quarters of tiles and whole ones, open tiles, one kernel and two
+# update and all-gather in one call, on both sides of the limits: quarters of tiles and whole ones, full and open ones, one kernel
+# and two (the limits themselves are pinned in native/launch_rules.cpp)
 @pytest.mark.gpu
-@pytest.mark.parametrize("P,sizes", [(1, [5]), (2, [150 * 4096, 77]), (2, [158 * 4096 + 1]), (7, [171 * 4096, 9]), (3, [300, 701, 64] * 150), (4, [2100] * 400),
-                                     (5, [2_000_003]), (5, [3_900_001, 33]), (8, [900] * 700), (12, [1_300_000])])
+@pytest.mark.parametrize("P,sizes", [(1, [5]), (2, [141 * 4096, 77]), (2, [146 * 4096 + 1]), (3, [110 * 4096 - 5]), (7, [171 * 4096, 9]), (16, [9001] * 40),
+                                     (3, [300, 701, 64] * 150), (4, [2100] * 60), (4, [2100] * 400), (8, [30, 5000, 7] * 150), (26, [450_000]), (26, [333] * 90),
+                                     (5, [2_000_003]), (5, [4_010_001, 33]), (8, [900] * 700), (12, [1_700_000])])
 def test_update_all_gather_forms(P, sizes):
     from test_gpu_parity import Pair, say, small_workload
     import workloads as W
