@@ -1300,13 +1300,12 @@ extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float
     if (rc == DEAR_OK) rc = check_update_buffers(shard_grad, shard_param, shard_mom);
     if (rc != DEAR_OK) return rc;
     const bucket_range r = buckets_of(c, bucket);
-    const int64_t count = tiles_of(c, r);
+    const int64_t count = tiles_of(c, r), elems = elements_of(c->bucket_len, r), whole = c->whole_begin[r.end] - c->whole_begin[r.begin];
     if (count == 0) return DEAR_OK;
     const dear_tile *tiles = c->d_tiles + c->tile_begin[r.begin];
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const unsigned width = grid_width(c->max_workgroups, count);
-    if (update_all_gather_pays_apart(elements_of(c->bucket_len, r), count, c->P) &&
-        update_all_gather_splits(count, c->P, c->max_workgroups)) {
+    if (update_all_gather_splits(elems, count, whole, c->P, c->max_workgroups)) {
         rc = launch_update(c, r, shard_grad, shard_param, shard_mom, lr, momentum, st);
         return rc == DEAR_OK ? launch_all_gather(c, range_of(c, r), shard_param, 0, c->P, st) : rc;
     }
@@ -1316,7 +1315,7 @@ extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float
     };
     if (width < count)
         launch(update_all_gather_kernel<4, true>, count, width, c->wave_priority);
-    else if (update_all_gather_quarters(elements_of(c->bucket_len, r), count, c->whole_begin[r.end] - c->whole_begin[r.begin], c->P, c->max_workgroups))
+    else if (update_all_gather_quarters(elems, count, whole, c->P, c->max_workgroups))
         launch(update_all_gather_kernel<1, false>, count * 4, width * 4, 0);
     else
         launch(update_all_gather_kernel<4, false>, count, width, 0);

@@ -112,36 +112,40 @@ inline all_gather_order all_gather_numbering(int grad_bytes, int64_t max_workgro
     return {rounded, run};
 }
 
-// dear_update_all_gather as one kernel writes all P replicas from the workgroup that updated: P write streams at
-// once, which HBM sustains worse the more there are (5.4 TB/s at P = 8, against 6.5 replica by replica).  From
-// UAG_SPLIT_P replicas on the 4 bytes per element that one kernel saves are worth less than that, if the
-// launch is long enough to pay for a second one: UAG_SPLIT_TILES tile copies are about 15 us.  us per iteration
-// of reduce-scatters and these calls, one kernel / update, then all-gather: 100 M elements in 64 MB buckets
-// P = 2 710 / 757, P = 3 857 / 878, P = 4 1016 / 1011; 25 M elements in 25 MB buckets P = 8 430 / 400;
-// BERT-Base-shaped P = 16 3173 / 2826; 5 M elements in 4 MB buckets P = 8 115 / 131; 36 M elements P = 5 in one call
-// 340 / 346, in 64 MB buckets 431 / 423, P = 6 474 / 463.  GPU time of this call alone, us: P = 4 20 M 128 / 120, 60 M 383 / 384,
-// P = 6 2 M 16.2 / 17.8, 4 M 33.3 / 31.5, 20 M 159 / 147, P = 8 1 M 9.6 / 11.8, 2 M 19.7 / 20.3, 4 M 40.7 / 36.6, P = 12 1 M 14.9 / 14.4, 2 M
-// 25.8 / 24.9, P = 16 0.3 M 8.1 / 8.8, 1 M 18.2 / 16.6, P = 32 0.3 M 11.0 / 14.1, 1 M 31.7 / 27.4.  Beyond the largest all-gather the one kernel, whose
-// grid is the tile count alone, still takes the call.
-constexpr int64_t UAG_SPLIT_P = 5, UAG_SPLIT_TILES = 4096;
-
-inline bool update_all_gather_splits(int64_t tiles, int64_t P, int64_t max_workgroups)
-{
-    const bool bounded = max_workgroups > 0 && tiles > max_workgroups;
-    return !bounded && P >= UAG_SPLIT_P && tiles * P >= UAG_SPLIT_TILES && all_gather_fits(tiles, P, max_workgroups);
-}
-
-// It pays by what the tiles hold: the all-gather's workgroups for the parts of tiles that short tensors leave open cost as much as
-// others (1 M elements in 500 tensors, one kernel / two: P = 8 16.5 / 20.1, P = 16 24.8 / 32.9; 3 M in 300 P = 8 35.3 / 32.5).
-inline bool update_all_gather_pays_apart(int64_t elems, int64_t tiles, int64_t P)
-{
-    const int64_t open = tiles * DEAR_TILE_ELEMS - elems;
-    return (elems - open) * P >= 14000000;
-}
-
 // Whether some of a launch's tiles are whole.  Weights between short vectors give whole tiles and nearly empty ones, tensors
 // that are all shorter than a tile none; elements and tiles alone do not tell one from the other.
 inline bool some_whole(int64_t whole, int64_t tiles) { return whole * 64 >= tiles; }
+
+// dear_update_all_gather as one kernel writes all P replicas from the workgroup that updated: P write streams at
+// once, which HBM sustains worse the more there are (5.4 TB/s at P = 8, against 6.5 replica by replica).  From
+// UAG_SPLIT_P replicas on the 4 bytes per element that one kernel saves are worth less than that, if the launch is long enough
+// to pay for a second one and for the all-gather's workgroups for the parts of tiles that short tensors leave open (`open`
+// elements), which cost as much as others.  GPU time of some buckets of one size, all reduce-scatters, then these calls, us, one
+// kernel / two:
+//   one tensor a bucket  P = 4 2.3 M elements 211 / 216  9 M 169 / 168   P = 5 1.8 M 193 / 202  2.8 M 175.7 / 175.9  3.4 M 171 / 164
+//                        7.2 M 160 / 154
+//                        P = 8 1.6 M 171 / 169  1.75 M 152 / 153  2.1 M 149 / 145 (2 of 12 buckets, the others smaller, 251 / 257)  4.5 M 142 / 135
+//                        P = 12 0.9 M 153 / 166  1.3 M 161 / 153  (in 76 tensors 1.6 M 32.8 / 33.9)
+//                        P = 16 0.8 M 140 / 150  1 M 150 / 149  1.1 M 133 / 126  2.3 M 127 / 114   P = 32 0.9 M 89 / 92  1 M 105 / 99   P = 64 0.7 M 63 / 67  0.9 M 79 / 80  1 M 96 / 89
+//   tensors of 3500      P = 5 2.2 M 28.8 / 31.8  5 M 63.1 / 61.8   P = 8 2.2 M 38.6 / 40.7  5 M 86.2 / 82.0   P = 16 1 M 31.8 / 33.6  5 M 149 / 135
+//   tensors of 5000 (61 % full)  P = 8 2.2 M 45.4 / 46.6  5 M 90.5 / 97.8  16 M 294 / 299   P = 16 2.2 M 73 / 78   P = 32 2.2 M 131 / 141
+//   tensors of 3000 (73 %)       P = 5 5 M 62.1 / 64.9   P = 8 2.2 M 37.7 / 43.1  16 M 267 / 261   P = 12 2.2 M 50.8 / 56.3  5 M 117 / 114   P = 32 1 M 56 / 61
+//   tensors of 2400-9400 (74 %)  P = 6 5 M 76.4 / 72.0   P = 8 3.8 M 69.0 / 66.0
+//   weights and short vectors P = 6 3.5 M (78 %) 53.8 / 49.6, P = 8 2.5 M (89 %) 44.6 / 42.2  2.6 M (58 %) 53.0 / 51.9   P = 12 1.9 M (62 %) 50.3 / 52.4   P = 16 1.1 M (59 %) 36.5 / 40.9
+//                        P = 32 2.6 M (58 %) 133 / 125
+//   tensors of 2500 (61 %)       P = 5 16 M 195 / 211   P = 8 16 M 273 / 293   P = 32 2.2 M 129 / 143
+// Beyond the largest all-gather the one kernel, whose grid is the tile count alone, still takes the call.
+constexpr int64_t UAG_SPLIT_P = 5;
+
+inline bool update_all_gather_splits(int64_t elems, int64_t tiles, int64_t whole, int64_t P, int64_t max_workgroups)
+{
+    constexpr int64_t M = 1000000;
+    const bool bounded = max_workgroups > 0 && tiles > max_workgroups;
+    const int64_t open = tiles * DEAR_TILE_ELEMS - elems;
+    if (bounded || P < UAG_SPLIT_P || !all_gather_fits(tiles, P, max_workgroups)) return false;
+    if (elems < (P > 16 ? 920000 : 17 * M / P)) return false;
+    return some_whole(whole, tiles) ? (elems - open) * P >= 15 * M : (2 * elems - 3 * open) * P >= 24 * M;
+}
 
 // The one kernel in quarters of tiles, one vector a lane: where whole ones leave CUs idle, or keep them waiting for the few that
 // hold most.  The more workgroups there are already, and the less all tiles hold, the more their number costs; it stays within a

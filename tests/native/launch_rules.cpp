@@ -23,7 +23,7 @@ static void grids()
     static const int64_t widths[] = {0, 1, 256, 100000, MAX_GRID, MAX_GRID + 1, 0x7fffffff};
     for (int64_t P : workers)
         for (int64_t width : widths) {
-            const int64_t at[] = {1, UAG_SPLIT_TILES / P, MAX_GRID / (AG_SPLIT * P), 0x3fffffff / (AG_SPLIT * P),
+            const int64_t at[] = {1, 4096 / P, MAX_GRID / (AG_SPLIT * P), 0x3fffffff / (AG_SPLIT * P),
                                   0x7fffffff / (AG_SPLIT * P), 300000, 0x7fffffff / 16};
             for (int64_t middle : at)
                 for (int64_t tiles = middle > 2 ? middle - 2 : 1; tiles <= middle + 2; ++tiles) {
@@ -41,14 +41,15 @@ static void grids()
                     if (!bounded) CHECK(fits == hip_takes(items));
                     if (bounded && width <= MAX_GRID) CHECK(fits == (items <= 0x7fffffff));
                     // the update goes first, so the all-gather behind it must be one that can be launched
-                    if (update_all_gather_splits(tiles, P, width)) {
-                        CHECK(fits && P >= UAG_SPLIT_P && tiles * P >= UAG_SPLIT_TILES);
-                        CHECK(width <= 0 || tiles <= width);
-                    }
+                    for (int64_t elems : {tiles * DEAR_TILE_ELEMS, tiles * 3500})
+                        if (update_all_gather_splits(elems, tiles, elems / DEAR_TILE_ELEMS, P, width)) {
+                            CHECK(fits && P >= UAG_SPLIT_P && elems * P >= 15600000 && elems >= 920000);
+                            CHECK(width <= 0 || tiles <= width);
+                        }
                 }
         }
     // 268 M elements in one call for 64 workers: the all-gather's grid is 2^24 workgroups, the one kernel's 65536
-    CHECK(update_all_gather_splits(65535, 64, 0) && !update_all_gather_splits(65536, 64, 0));
+    CHECK(update_all_gather_splits(65535ll << 12, 65535, 65535, 64, 0) && !update_all_gather_splits(65536ll << 12, 65536, 65536, 64, 0));
     CHECK(!all_gather_fits(65536, 64, 0) && all_gather_fits(65536, 64, 256));
 }
 
@@ -99,7 +100,8 @@ static void iteration()
                 }
 }
 
-// dear_update_all_gather in one kernel: quarters of tiles in small launches, the smaller the more replicas, and in larger ones of
+// dear_update_all_gather: two launches from where they pay, by elements, replicas and open tiles.  (The limits of full tiles are
+// those that test_gpu_parity.py's test of both sides takes.)  In one kernel: quarters of tiles in small launches, the smaller the more replicas, and in larger ones of
 // few whole tiles among short ones.
 static void update_and_gather()
 {
@@ -115,6 +117,18 @@ static void update_and_gather()
         CHECK(update_all_gather_quarters(c.tiles * c.fill, c.tiles, c.whole, c.P, 0) == c.quarters);
         CHECK(update_all_gather_quarters(c.tiles * c.fill, c.tiles, c.whole, c.P, 4 * c.tiles) == c.quarters);
         CHECK(!update_all_gather_quarters(c.tiles * c.fill, c.tiles, c.whole, c.P, 4 * c.tiles - 1));
+    }
+    struct { int64_t P, elems, tiles, whole; bool splits; } const apart[] = {
+        {4, 100000000, 24415, 24413, false}, {5, 831 * 4096, 836, 826, true},   {5, 830 * 4096, 835, 825, false},  {8, 519 * 4096, 527, 511, true},
+        {8, 518 * 4096, 526, 510, false},    {16, 260 * 4096, 276, 244, true},  {16, 259 * 4096, 275, 243, false}, {24, 225 * 4096, 249, 201, true},
+        {64, 225 * 4096, 288, 161, true},    {64, 224 * 4096, 287, 160, false}, {8, 5000000, 2008, 1000, false},   {12, 2200000, 745, 0, false},
+        {12, 5000000, 1678, 0, true},        {8, 16000000, 6408, 3200, true},   {5, 5000000, 1505, 1000, true},    {32, 1000000, 365, 0, false},
+        {8, 5000000, 1436, 0, true},         {6, 5000000, 1641, 600, true},     {8, 3750000, 1202, 450, true},     {48, 450000, 144, 80, false},
+        {6, 3513000, 1092, 600, true},       {16, 1060000, 440, 150, false},    {12, 1870000, 741, 250, false},    {32, 2641000, 1108, 400, true},
+    };
+    for (const auto &c : apart) {
+        CHECK(update_all_gather_splits(c.elems, c.tiles, c.whole, c.P, 0) == c.splits);
+        CHECK(!update_all_gather_splits(c.elems, c.tiles, c.whole, c.P, c.tiles - 1));
     }
 }
 

@@ -475,9 +475,11 @@ def test_iteration_call_with_many_replicas(dtype, P, n):
     pair.close()
 
 
-@pytest.mark.parametrize("P,n", [(6, 1366 * 4096), (6, 1365 * 4096), (5, 1700 * 4096), (9, 911 * 4096 + 5)])
+@pytest.mark.parametrize("P,n", [(4, 1100 * 4096), (5, 831 * 4096), (5, 830 * 4096), (8, 519 * 4096), (8, 518 * 4096), (16, 260 * 4096),
+                                 (16, 259 * 4096), (24, 225 * 4096), (24, 224 * 4096), (9, 911 * 4096 + 5)])
 def test_update_all_gather_on_both_sides_of_its_split(P, n):
-    """6 replicas and 8192 tile copies: from there on the call launches the update and the all-gather."""
+    """From 5 replicas and 17 M copied elements on (beyond 16 replicas from 0.92 M elements), in tiles that are mostly full, the
+    call launches the update and the all-gather; native/launch_rules.cpp pins these sizes to their sides."""
     say("case: update + all-gather, P=%d, %d elements" % (P, n))
     pair = Pair(small_workload([n, 33], P, 0))
     pair.run(iterations=1, fused_gather=True)
