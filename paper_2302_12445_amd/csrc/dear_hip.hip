@@ -915,6 +915,8 @@ bucket_range buckets_of(const dear_ctx_impl *c, int32_t bucket)
 
 int64_t tiles_of(const dear_ctx_impl *c, bucket_range r) { return c->tile_begin[r.end] - c->tile_begin[r.begin]; }
 
+int64_t whole_tiles_of(const dear_ctx_impl *c, bucket_range r) { return c->whole_begin[r.end] - c->whole_begin[r.begin]; }
+
 int64_t elements_of(const std::vector<int64_t> &bucket_len, bucket_range r)
 {
     return std::accumulate(bucket_len.begin() + r.begin, bucket_len.begin() + r.end, int64_t{0});
@@ -959,14 +961,14 @@ unsigned grid_width(int32_t max_workgroups, int64_t n_items)
 unsigned residency_lds(int residency) { return residency == 1 ? 96 << 10 : residency == 2 ? 64 << 10 : 0; }
 
 // What a reduce-scatter launch is made from.  tiles, grads: device tables (a context's, or the static scratch's).  The
-// launch may be one of several over all_tiles tiles, which hold all_elems elements.
+// launch may be one of several over all_tiles tiles, which hold all_elems elements and of which all_whole are whole.
 struct rs_call {
     int P, L;
     const void *const *grads;
     int32_t max_workgroups;
     int prio;
     const dear_tile *tiles;
-    int64_t n_tiles, all_tiles, all_elems;
+    int64_t n_tiles, all_tiles, all_elems, all_whole;
     hipStream_t st;
 };
 
@@ -1015,7 +1017,7 @@ void rs_launch(bool bf16, const rs_call &c, const rs_sink<MODE> &o)
     if (!bf16)
         rs_launch_batched<false, MODE, 1>(c, o);
     else if ((MODE & RS_GATHER) ? iteration_at_once_half_tiles(c.all_elems, c.n_tiles)
-                                : reduce_scatter_half_tiles((MODE & RS_UPDATE) != 0, c.max_workgroups, c.n_tiles))
+                                : reduce_scatter_half_tiles((MODE & RS_UPDATE) != 0, c.max_workgroups, c.all_elems, c.n_tiles, c.all_whole))
         rs_launch_batched<true, MODE, 1>(c, o);
     else
         rs_launch_batched<true, MODE, 2>(c, o);
@@ -1170,12 +1172,12 @@ namespace {
 
 // What a launch goes over: tiles begin .. begin+count-1 of the table, part of a call's `all_tiles` with `all_elems`.
 struct tile_range {
-    int64_t begin, count, all_tiles, all_elems;
+    int64_t begin, count, all_tiles, all_elems, all_whole;
 };
 
 tile_range range_of(const dear_ctx_impl *c, bucket_range r)
 {
-    return {c->tile_begin[r.begin], tiles_of(c, r), tiles_of(c, r), elements_of(c->bucket_len, r)};
+    return {c->tile_begin[r.begin], tiles_of(c, r), tiles_of(c, r), elements_of(c->bucket_len, r), whole_tiles_of(c, r)};
 }
 
 template <rs_mode MODE>
@@ -1183,7 +1185,7 @@ int launch_reduce_scatter(const dear_ctx_impl *c, tile_range t, const rs_sink<MO
 {
     if (t.count == 0) return DEAR_OK;
     const rs_call call{c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, c->d_tiles + t.begin, t.count,
-                       t.all_tiles, t.all_elems, st};
+                       t.all_tiles, t.all_elems, t.all_whole, st};
     rs_launch<MODE>(c->g == 2, call, o);
     return launch_status();
 }
@@ -1234,7 +1236,7 @@ int launch_all_gather(const dear_ctx_impl *c, tile_range t, const float *shard_p
         constexpr unsigned chunk = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK);
         const unsigned n_parts = static_cast<unsigned>(count * AG_SPLIT), n_p = static_cast<unsigned>(n_workers);
         const unsigned whole = n_parts / chunk * chunk;
-        const all_gather_order o = all_gather_numbering(c->g, c->max_workgroups, whole, n_parts, n_workers);
+        const all_gather_order o = all_gather_numbering(c->g, c->max_workgroups, t.all_elems, t.all_whole, whole, n_parts, n_workers);
         const auto kernel = o.run ? all_gather_kernel<1> : all_gather_kernel<0>;
         kernel<<<dim3((whole + o.len) * n_p), dim3(DEAR_BLOCK), 0, st>>>(
             tiles, c->d_param, c->L, first_worker, n_p, shard_param, n_parts, 0xffffffffu / n_p, o.len,
@@ -1300,7 +1302,7 @@ extern "C" int dear_update_all_gather(dear_ctx_t *c, int32_t bucket, const float
     if (rc == DEAR_OK) rc = check_update_buffers(shard_grad, shard_param, shard_mom);
     if (rc != DEAR_OK) return rc;
     const bucket_range r = buckets_of(c, bucket);
-    const int64_t count = tiles_of(c, r), elems = elements_of(c->bucket_len, r), whole = c->whole_begin[r.end] - c->whole_begin[r.begin];
+    const int64_t count = tiles_of(c, r), elems = elements_of(c->bucket_len, r), whole = whole_tiles_of(c, r);
     if (count == 0) return DEAR_OK;
     const dear_tile *tiles = c->d_tiles + c->tile_begin[r.begin];
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -1526,6 +1528,8 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
                                           STATIC_MAX_TILES, &n_tiles, nullptr);
     if (n_tiles > static_cast<int64_t>(STATIC_MAX_TILES)) return DEAR_ETOOBIG;
     if (n_tiles == 0) return DEAR_OK;
+    int64_t n_whole = 0;
+    for (int64_t i = 0; i < n_runs; ++i) n_whole += whole_tiles_of_run(reinterpret_cast<const dear_run *>(host_stage + runs_at)[i]);
 
     int device = -1;
     if (hipGetDevice(&device) != hipSuccess) return DEAR_EHIP;
@@ -1557,7 +1561,7 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
     const void *const *grad_tab = reinterpret_cast<const void *const *>(dev);
     const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f, nullptr};
     const int64_t elems = elements_of(plan->bucket_len, bucket_range{b_first, b_last});
-    rs_launch<RS_GBAR>(plan->g == 2, rs_call{plan->P, plan->L, grad_tab, 0, 0, tiles, n_tiles, n_tiles, elems, st}, o);
+    rs_launch<RS_GBAR>(plan->g == 2, rs_call{plan->P, plan->L, grad_tab, 0, 0, tiles, n_tiles, n_tiles, elems, n_whole, st}, o);
     rc = launch_status();
     if (hipEventSynchronize(uploaded_on_device[device]) != hipSuccess) {
         (void)hipGetLastError();

@@ -76,15 +76,26 @@ inline bool all_gather_fits(int64_t tiles, int64_t n_workers, int64_t max_workgr
     return items <= 0x7fffffff && (max_workgroups <= MAX_GRID || tiles <= MAX_GRID);
 }
 
+// Whether some of a launch's tiles are whole.  Weights between short vectors give whole tiles and nearly empty ones, tensors
+// that are all shorter than a tile none; elements and tiles alone do not tell one from the other.
+inline bool some_whole(int64_t whole, int64_t tiles) { return whole * 64 >= tiles; }
+
 // A bf16 reduce-scatter takes half a tile a workgroup (one 16-byte vector a lane instead of two) where a launch is so
-// short that whole tiles leave CUs idle, and, with the update, as long as the all-gather behind it finds w in L2, which
-// it does better in halves (see all_gather_kernel).  GPU time, us, whole tiles / halves: reduce-scatter alone P = 8 0.2 M
-// elements 4.47 / 4.06, 0.4 M 4.83 / 4.38, 0.8 M 5.39 / 5.41, 1.6 M 7.32 / 7.71; P = 32 0.4 M 11.9 / 10.8, 1.6 M 21.6 / 22.5;
-// iteration P = 4 0.3 M 8.10 / 7.44, 2 M 17.8 / 17.2, 6 M 41.8 / 41.6; P = 8 0.3 M 10.3 / 8.9, 1 M 15.6 / 14.7, 3 M 34.7 / 34.6,
-// 10 M 101.1 / 101.6; P = 16 0.3 M 14.6 / 12.5, 1 M 24.3 / 23.3, 3 M 56.2 / 55.7, 6 M 108.5 / 110.9.
-inline bool reduce_scatter_half_tiles(bool updates, int64_t max_workgroups, int64_t tiles)
+// short that whole tiles leave CUs idle, unless its tensors are all so short that most second halves are empty.  GPU time, us,
+// whole tiles / halves: reduce-scatter alone P = 8 0.2 M elements 4.47 / 4.06, 0.4 M 4.83 / 4.38, 0.8 M 5.39 / 5.41,
+// 1.6 M 7.32 / 7.71; P = 32 0.4 M 11.9 / 10.8, 1.6 M 21.6 / 22.5.  With the update the line lies further out, behind an all-gather that
+// follows at once or later: all reduce-scatters + updates, then all all-gathers of up to eight buckets of 150 / 300 / 550 / 850 tiles,
+// change in %: P = 4 -2 / -5 / -5 / -1, P = 8 -5 / -6 / -5 / -3, P = 16 -3 / -6 / -4 / -3, P = 32 -9 / -5 / +1 / -3, P = 48 -7 / -3 / +5 / +2,
+// P = 64 -7 / -7 / +4 / +1; iteration of one bucket P = 4 0 / -5 / -3 / +1, P = 8 -5 / -7 / -7 / -2, P = 32 -12 / -6 / -7 / -2, P = 64 -8 / -4 / -4 / -3;
+// one bucket of weights and short vectors, 15 to 90 % full, P = 3 to 64, 80 to 850 tiles -18 to +1.
+// Short tensors, iteration in two launches: P = 9 60 of 400 elements 8.20 / 8.62, of 1000 8.90 / 9.33, of 1600 9.85 / 9.08;
+// P = 32 of 1000 17.7 / 18.5, of 1600 20.2 / 18.3; P = 64 of 1000 35.2 / 37.5, of 1600 35.6 / 38.4, of 2400 42.9 / 38.5.
+// Reduce-scatter + update P = 10 396 tensors of 1430 9.33 / 10.08; in a dozen tiles empty halves cost nothing (P = 8 2460 elements in 5
+// tensors 5.96 / 5.64).
+inline bool reduce_scatter_half_tiles(bool updates, int64_t max_workgroups, int64_t elems, int64_t tiles, int64_t whole)
 {
-    return max_workgroups <= 0 && tiles <= (updates ? 1024 : 160);
+    if (max_workgroups > 0 || tiles > (updates ? 1024 : 160)) return false;
+    return tiles <= 16 || some_whole(whole, tiles) || elems >= tiles * (tiles <= 200 ? 1024 : 1536);
 }
 
 // How the unbounded all-gather numbers its workgroups (see all_gather_kernel).  Where HIP would not take a launch with a
@@ -102,19 +113,15 @@ DEAR_HOST_DEVICE inline unsigned all_gather_part(unsigned r, unsigned run)
     return (r & ~((8u << run) - 1)) | (r & 7) << run | (r >> 3 & ((1u << run) - 1));
 }
 
-inline all_gather_order all_gather_numbering(int grad_bytes, int64_t max_workgroups, unsigned whole, unsigned parts, int64_t n_workers)
+inline all_gather_order all_gather_numbering(int grad_bytes, int64_t max_workgroups, int64_t elems, int64_t whole_tiles, unsigned whole, unsigned parts, int64_t n_workers)
 {
     const unsigned last = parts - whole;
-    const unsigned run = grad_bytes == 2 && reduce_scatter_half_tiles(true, max_workgroups, parts / AG_SPLIT) ? 1 : 0;
+    const unsigned run = grad_bytes == 2 && reduce_scatter_half_tiles(true, max_workgroups, elems, parts / AG_SPLIT, whole_tiles) ? 1 : 0;
     const unsigned rounded = (last + (8u << run) - 1) & ~((8u << run) - 1);
     const int64_t most = max_workgroups > 0 && max_workgroups < MAX_GRID ? max_workgroups : MAX_GRID;
     if ((static_cast<int64_t>(whole) + rounded) * n_workers > most) return {last, 0};
     return {rounded, run};
 }
-
-// Whether some of a launch's tiles are whole.  Weights between short vectors give whole tiles and nearly empty ones, tensors
-// that are all shorter than a tile none; elements and tiles alone do not tell one from the other.
-inline bool some_whole(int64_t whole, int64_t tiles) { return whole * 64 >= tiles; }
 
 // dear_update_all_gather as one kernel writes all P replicas from the workgroup that updated: P write streams at
 // once, which HBM sustains worse the more there are (5.4 TB/s at P = 8, against 6.5 replica by replica).  From
@@ -199,7 +206,8 @@ void dear_build_tiles(const dear_plan_s &pl, std::vector<dear_tile> &tiles, std:
 //   - tiles that are four fifths full on average.  40 M elements in runs of one length, P = 8, the same passes:
 //     350 elements fp32 without 3319 / 5453 / 7787 us, bf16 with 2918 / 3441 / 4149; 2500 fp32 with 770 / 822 / 1079;
 //     9000 (73 % full) fp32 without 704 / 721 / 847, bf16 with 525 / 511 / 511; 20000 (98 %) fp32 with 610 / 580 / 643.
-// One per CU without the update takes eight replicas in flight at a time, which P = 12, 20, 28 have not.
+// One per CU without the update takes eight replicas in flight at a time, which P = 12, 20, 28 have not.  Half tiles have half
+// the loads in flight and the same line: 960 of them with the update, P = 64, as many / 2 / 1 per CU 100 / 97 / 95, iteration 243 / 238 / 237.
 // Beside compute on another stream it does no harm: the DeAR schedule with unbounded grids, fp32 2048^3 products, us
 // as many as fit / by this rule: BERT-Base-shaped P = 16 12668 / 12414, BERT-Large-shaped P = 8 bf16 11759 / 11498.
 inline int reduce_scatter_residency(bool bf16, bool updates, int64_t P, int64_t elems, int64_t tiles)

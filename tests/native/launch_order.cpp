@@ -18,7 +18,7 @@ int main()
                     const unsigned parts = tiles * AG_SPLIT;
                     if (!all_gather_fits(tiles, P, 0) || all_gather_bounded(tiles, P, width)) continue;
                     const unsigned whole = parts / chunk * chunk;
-                    const all_gather_order o = all_gather_numbering(g, width, whole, parts, P);
+                    const all_gather_order o = all_gather_numbering(g, width, int64_t(tiles) * DEAR_TILE_ELEMS, tiles, whole, parts, P);
                     std::vector<int> seen(parts, 0);
                     for (unsigned r = 0; r < whole + o.len; ++r) {
                         const unsigned first = r < whole ? r / chunk * chunk : whole;

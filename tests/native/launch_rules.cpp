@@ -34,7 +34,7 @@ static void grids()
                     int64_t grid = width < tiles ? width : tiles;
                     if (!bounded && fits) {
                         const unsigned parts = static_cast<unsigned>(tiles * AG_SPLIT), whole = parts / 4096 * 4096;
-                        grid = (int64_t(whole) + all_gather_numbering(2, width, whole, parts, P).len) * P;
+                        grid = (int64_t(whole) + all_gather_numbering(2, width, tiles * DEAR_TILE_ELEMS, tiles, whole, parts, P).len) * P;
                         CHECK(grid >= items && (width <= 0 || grid <= width));
                     }
                     if (fits) CHECK(hip_takes(grid));
@@ -82,6 +82,22 @@ static void residency()
     };
     for (const auto &c : at)
         CHECK(reduce_scatter_residency(c.bf16, c.updates, c.P, c.elems, c.elems / DEAR_TILE_ELEMS + c.P) == c.want);
+}
+
+// bf16 reduce-scatters in half tiles: short launches, some of whose tiles are whole or which are a quarter (many: three eighths) full.
+static void half_tiles()
+{
+    CHECK(reduce_scatter_half_tiles(true, 0, 1024 * 4096, 1024, 1024) && !reduce_scatter_half_tiles(true, 0, 1025 * 4096, 1025, 1025));
+    CHECK(reduce_scatter_half_tiles(false, 0, 160 * 4096, 160, 160) && !reduce_scatter_half_tiles(false, 0, 161 * 4096, 161, 161));
+    for (bool updates : {false, true}) {
+        CHECK(!reduce_scatter_half_tiles(updates, 256, 100 * 4096, 100, 100));
+        CHECK(reduce_scatter_half_tiles(updates, 0, 100 * 1024, 100, 0) && !reduce_scatter_half_tiles(updates, 0, 100 * 1024 - 1, 100, 1));
+        CHECK(reduce_scatter_half_tiles(updates, 0, 100 * 600, 100, 2));
+    }
+    CHECK(reduce_scatter_half_tiles(true, 0, 16, 16, 0) && !reduce_scatter_half_tiles(true, 0, 17, 17, 0));
+    CHECK(reduce_scatter_half_tiles(true, 0, 200 * 1024, 200, 0) && !reduce_scatter_half_tiles(true, 0, 201 * 1536 - 1, 201, 0));
+    CHECK(reduce_scatter_half_tiles(true, 0, 201 * 1536, 201, 0) && !reduce_scatter_half_tiles(true, 0, 406 * 1400, 406, 6));
+    CHECK(reduce_scatter_half_tiles(true, 0, 406 * 1400, 406, 7));
 }
 
 // dear_iteration: w is left in the cache only where it fits; gbar is read again only where many replicas are read.
@@ -149,6 +165,7 @@ int main()
 {
     grids();
     residency();
+    half_tiles();
     iteration();
     whole_tiles();
     update_and_gather();
