@@ -609,9 +609,9 @@ __host__ __device__ __forceinline__ int line_shift(uintptr_t p) { return static_
 // n_parts = tiles * AG_SPLIT; replicas p_first .. p_first+n_p-1 receive.  inv_n_p, inv_len: reciprocals (see divide)
 // of n_p and of len, the number of workgroups per replica in the short last chunk.
 // Workgroups go to the eight XCDs in turn, and a part of a chunk belongs on one XCD for all replicas, whose L2 then
-// holds the shard values: len is a multiple of 8 (workgroups behind the last part have nothing to do).  In a short launch
-// the values are still in the L2 of the XCD whose reduce-scatter + update wrote them, so they are read there: `run` is
-// the logarithm of the number of parts that one workgroup of that kernel had (fp32 0; bf16 1).
+// holds the shard values: len is a multiple of 8 (workgroups behind the last part have nothing to do).  Right behind a short
+// reduce-scatter + update the values are still in the L2 of the XCD that wrote them, so they are read there: `run` is
+// the logarithm of the number of parts that one workgroup of that kernel had (fp32 0; bf16 in half tiles 1; all_gather_run).
 // One launch of each, us per iteration without gbar, 1 M elements (an odd number of tiles) len as it falls / rounded:
 // fp32 P = 4 13.7 / 11.5, P = 8 18.3 / 16.1, P = 16 29.6 / 27.6; 8 M fp32 P = 8 108.6 / 103.1, P = 16 195 / 187.  bf16, run 0 / 1:
 // P = 4 1 M 12.1 / 10.7, 2 M 19.1 / 17.2, P = 8 1 M 16.1 / 14.7, 2 M 26.4 / 24.5, 3 M 36.0 / 34.6, P = 16 2 M 40.8 / 39.0;
@@ -1220,8 +1220,9 @@ int launch_update(const dear_ctx_impl *c, bucket_range r, const float *shard_gra
     return launch_status();
 }
 
+// behind_update: the reduce-scatter + update of the same tiles is the launch before.
 int launch_all_gather(const dear_ctx_impl *c, tile_range t, const float *shard_param, int32_t first_worker,
-                      int32_t n_workers, hipStream_t st)
+                      int32_t n_workers, hipStream_t st, bool behind_update = false)
 {
     const int64_t count = t.count;
     if (count == 0) return DEAR_OK;
@@ -1236,7 +1237,8 @@ int launch_all_gather(const dear_ctx_impl *c, tile_range t, const float *shard_p
         constexpr unsigned chunk = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK);
         const unsigned n_parts = static_cast<unsigned>(count * AG_SPLIT), n_p = static_cast<unsigned>(n_workers);
         const unsigned whole = n_parts / chunk * chunk;
-        const all_gather_order o = all_gather_numbering(c->g, c->max_workgroups, t.all_elems, t.all_whole, whole, n_parts, n_workers);
+        const unsigned run = all_gather_run(c->g, c->max_workgroups, t.all_elems, count, t.all_whole, n_workers, behind_update);
+        const all_gather_order o = all_gather_numbering(run, c->max_workgroups, whole, n_parts, n_workers);
         const auto kernel = o.run ? all_gather_kernel<1> : all_gather_kernel<0>;
         kernel<<<dim3((whole + o.len) * n_p), dim3(DEAR_BLOCK), 0, st>>>(
             tiles, c->d_param, c->L, first_worker, n_p, shard_param, n_parts, 0xffffffffu / n_p, o.len,
@@ -1399,7 +1401,7 @@ extern "C" int dear_iteration(dear_ctx_t *c, int32_t bucket, float *shard_grad, 
                 rc = launch_reduce_scatter_update<RS_W_NEXT>(c, t, shard_grad, shard_param, shard_mom, lr, momentum, st);
             else
                 rc = launch_reduce_scatter_update<0>(c, t, shard_grad, shard_param, shard_mom, lr, momentum, st);
-            if (rc == DEAR_OK) rc = launch_all_gather(c, t, shard_param, 0, c->P, st);
+            if (rc == DEAR_OK) rc = launch_all_gather(c, t, shard_param, 0, c->P, st, true);
         }
     }
     return rc;

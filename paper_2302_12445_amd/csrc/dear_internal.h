@@ -98,6 +98,26 @@ inline bool reduce_scatter_half_tiles(bool updates, int64_t max_workgroups, int6
     return tiles <= 16 || some_whole(whole, tiles) || elems >= tiles * (tiles <= 200 ? 1024 : 1536);
 }
 
+// Whether a replica's workgroups take two parts in a row (1) or each the next one (0) on an XCD (see all_gather_kernel): two are
+// what a workgroup of a bf16 reduce-scatter + update in half tiles wrote, and where that launch comes right before, as in
+// dear_iteration, they are in this XCD's L2.  The more replicas, and the emptier the tiles, the more the rounding to 16 parts costs.
+// One / two in a row:
+//   dear_iteration, us, one bucket of 100 / 200 / 400 / 850 full tiles  P = 8 8.5 / 8.3  12.6 / 12.1  22.1 / 20.1  39.5 / 38.4
+//     P = 24 16.0 / 16.0  24.7 / 24.2  45.9 / 44.4  92.3 / 88.7   P = 40 23.4 / 24.4  36.8 / 37.2  71.6 / 69.5  144 / 145   P = 48 28.5 / 28.9  43.9 / 45.2  82.5 / 83.1
+//     P = 64 38.7 / 39.4  57.4 / 59.0  108 / 109  225 / 221;  weights and short vectors, change in %: P = 3 -7 to 0, P = 8 up to 150 tiles 0, 340 to 430 full
+//     ones -4 to -8, P = 12 and 16 up to 230 tiles +1 to +3, 390 full ones -4, P = 24 +1 to +3, P = 32 +1 to +4, P = 48 and 64 +3 to +5
+//   all reduce-scatters, then all all-gathers, change of the whole pass in %: eight buckets or fewer of 40 / 100 / 200 / 400 / 850 full tiles
+//     P = 4 -7 / -3 / -2 / 0 / 0   P = 8 -9 / -4 / 0 / 0 / -1   P = 16 -3 / -2 / 0 / +1 / -2   P = 24 0 / 0 / +2 / +2 / -1   P = 32 +1 / +1 / +2 / +3 / -1
+//     P = 48 -1 / +1 / +3 / +3 / -1   P = 64 +2 / +3 / +3 / +3 / +3;  weights and short vectors P = 3 and 4 -6 to 0, P = 8 -3 to +2, with an update between
+//     +1 to +2.5, P = 12 and 16 +1 to +3, from P = 24 on +2 to +5
+inline unsigned all_gather_run(int grad_bytes, int64_t max_workgroups, int64_t elems, int64_t tiles, int64_t whole, int64_t n_workers,
+                               bool behind_update)
+{
+    if (grad_bytes != 2 || !reduce_scatter_half_tiles(true, max_workgroups, elems, tiles, whole)) return 0;
+    if (!behind_update) return n_workers <= (tiles <= 160 ? 8 : 4);
+    return n_workers <= 8 || (elems * 4 >= tiles * (3 * DEAR_TILE_ELEMS) && n_workers <= (tiles < 400 ? 32 : 47));
+}
+
 // How the unbounded all-gather numbers its workgroups (see all_gather_kernel).  Where HIP would not take a launch with a
 // rounded last chunk, or a bound on the grid would not allow it, that chunk stays as it falls.
 struct all_gather_order {
@@ -113,10 +133,9 @@ DEAR_HOST_DEVICE inline unsigned all_gather_part(unsigned r, unsigned run)
     return (r & ~((8u << run) - 1)) | (r & 7) << run | (r >> 3 & ((1u << run) - 1));
 }
 
-inline all_gather_order all_gather_numbering(int grad_bytes, int64_t max_workgroups, int64_t elems, int64_t whole_tiles, unsigned whole, unsigned parts, int64_t n_workers)
+inline all_gather_order all_gather_numbering(unsigned run, int64_t max_workgroups, unsigned whole, unsigned parts, int64_t n_workers)
 {
     const unsigned last = parts - whole;
-    const unsigned run = grad_bytes == 2 && reduce_scatter_half_tiles(true, max_workgroups, elems, parts / AG_SPLIT, whole_tiles) ? 1 : 0;
     const unsigned rounded = (last + (8u << run) - 1) & ~((8u << run) - 1);
     const int64_t most = max_workgroups > 0 && max_workgroups < MAX_GRID ? max_workgroups : MAX_GRID;
     if ((static_cast<int64_t>(whole) + rounded) * n_workers > most) return {last, 0};

@@ -11,14 +11,14 @@
 int main()
 {
     const unsigned chunk = 4096;
-    for (int g = 2; g <= 4; g += 2)
+    for (unsigned run : {0u, 1u})
         for (int64_t width : {0, 8, 28, 56, 256, 1000, 100000})
             for (int64_t P : {int64_t(1), int64_t(7), int64_t(64), int64_t(4095), int64_t(4096), int64_t(5000), MAX_GRID / 4})
                 for (unsigned tiles : {1u, 2u, 3u, 4u, 5u, 511u, 1021u, 1023u, 1024u, 1025u, 1026u, 2047u, 2048u, 2049u}) {
                     const unsigned parts = tiles * AG_SPLIT;
                     if (!all_gather_fits(tiles, P, 0) || all_gather_bounded(tiles, P, width)) continue;
                     const unsigned whole = parts / chunk * chunk;
-                    const all_gather_order o = all_gather_numbering(g, width, int64_t(tiles) * DEAR_TILE_ELEMS, tiles, whole, parts, P);
+                    const all_gather_order o = all_gather_numbering(run, width, whole, parts, P);
                     std::vector<int> seen(parts, 0);
                     for (unsigned r = 0; r < whole + o.len; ++r) {
                         const unsigned first = r < whole ? r / chunk * chunk : whole;
@@ -30,7 +30,7 @@ int main()
                     bool ok = grid <= MAX_GRID && (width == 0 || grid <= width);
                     for (int n : seen) ok = ok && n == 1;
                     if (!ok) {
-                        std::fprintf(stderr, "FAILED g=%d width=%d P=%lld tiles=%u\n", g, int(width), (long long)P, tiles);
+                        std::fprintf(stderr, "FAILED run=%u width=%d P=%lld tiles=%u\n", run, int(width), (long long)P, tiles);
                         std::exit(1);
                     }
                 }

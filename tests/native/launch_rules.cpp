@@ -34,7 +34,7 @@ static void grids()
                     int64_t grid = width < tiles ? width : tiles;
                     if (!bounded && fits) {
                         const unsigned parts = static_cast<unsigned>(tiles * AG_SPLIT), whole = parts / 4096 * 4096;
-                        grid = (int64_t(whole) + all_gather_numbering(2, width, tiles * DEAR_TILE_ELEMS, tiles, whole, parts, P).len) * P;
+                        grid = (int64_t(whole) + all_gather_numbering(1, width, whole, parts, P).len) * P;
                         CHECK(grid >= items && (width <= 0 || grid <= width));
                     }
                     if (fits) CHECK(hip_takes(grid));
@@ -98,6 +98,26 @@ static void half_tiles()
     CHECK(reduce_scatter_half_tiles(true, 0, 200 * 1024, 200, 0) && !reduce_scatter_half_tiles(true, 0, 201 * 1536 - 1, 201, 0));
     CHECK(reduce_scatter_half_tiles(true, 0, 201 * 1536, 201, 0) && !reduce_scatter_half_tiles(true, 0, 406 * 1400, 406, 6));
     CHECK(reduce_scatter_half_tiles(true, 0, 406 * 1400, 406, 7));
+}
+
+// All-gathers in pairs of parts: where the bf16 reduce-scatter + update went in half tiles, and then mostly in dear_iteration.
+static void pairs_of_parts()
+{
+    struct { int64_t P, tiles, fill; bool behind, apart; } const at[] = {
+        {1, 40, 4000, true, true},   {8, 160, 2000, true, true},    {9, 160, 4000, true, false},   {9, 160, 3071, false, false}, {9, 160, 3072, true, false},
+        {4, 161, 2000, true, true},  {5, 161, 4000, true, false},   {32, 399, 4000, true, false},  {33, 399, 4000, false, false}, {47, 400, 4000, true, false},
+        {48, 400, 4000, false, false}, {4, 1024, 4000, true, true}, {8, 1024, 3000, true, false},  {8, 1025, 4000, false, false},
+    };
+    for (const auto &c : at) {
+        const int64_t elems = c.tiles * c.fill;
+        CHECK(all_gather_run(2, 0, elems, c.tiles, c.tiles / 2, c.P, true) == c.behind);
+        CHECK(all_gather_run(2, 0, elems, c.tiles, c.tiles / 2, c.P, false) == c.apart);
+        for (bool behind : {false, true}) {
+            CHECK(all_gather_run(4, 0, elems, c.tiles, c.tiles, c.P, behind) == 0);
+            CHECK(all_gather_run(2, 100000, elems, c.tiles, c.tiles, c.P, behind) == 0);
+            CHECK(all_gather_run(2, 0, c.tiles * 1000, c.tiles, 0, c.P, behind) == 0);
+        }
+    }
 }
 
 // dear_iteration: w is left in the cache only where it fits; gbar is read again only where many replicas are read.
@@ -166,6 +186,7 @@ int main()
     grids();
     residency();
     half_tiles();
+    pairs_of_parts();
     iteration();
     whole_tiles();
     update_and_gather();
