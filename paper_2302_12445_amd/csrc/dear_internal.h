@@ -313,14 +313,35 @@ inline bool iteration_updates_apart(int grad_bytes, int64_t P, int64_t group_til
 //   bf16  P = 2 1 M 8.9 / 6.6  6 M 33.4 / 31.0  20 M 92.2 / 97.1  30 M 150 / 145  100 M 514 / 481
 //         P = 4 1 M 10.7 / 8.7  3 M 24.1 / 22.8  6 M 42.8 / 43.9  P = 8 0.5 M 10.3 / 9.2  1.5 M 19.3 / 18.5  3 M 34.3 / 35.2
 //         P = 12 0.5 M 13.2 / 12.8  1 M 18.6 / 19.2  P = 16 0.2 M 11.2 / 11.9  1 M 22.9 / 25.3, in 500 tensors 46.2 / 37.7
+// From 9 (bf16) or 10 replicas on a launch of few tiles is slower so: each of its few workgroups writes them all, one after another.  One
+// launch behind start of the two, GPU time without gbar:
+//   fp32  P = 12 20 tiles 7.5 / 8.1  33 6.8 / 6.2   P = 16 26 tiles 7.7 / 8.6  46 9.0 / 9.3  61 9.8 / 9.6   P = 32 42 tiles 12.2 / 15.3  77 17.3 / 17.8  92 18.4 / 17.8
+//         P = 64 72 tiles 25.1 / 27.8  94 32.9 / 32.4
+//   bf16  P = 8 18 tiles 5.0 / 5.2  39 5.4 / 5.2   P = 10 18 tiles 5.5 / 6.1  40 8.6 / 8.7  76 9.9 / 9.5   P = 16 46 tiles 9.4 / 10.0  76 10.8 / 10.5
+//         P = 32 62 tiles 15.6 / 17.2  92 18.5 / 18.3  112 20.6 / 18.9   P = 64 94 tiles 32.3 / 31.9  124 37.5 / 33.1
+// And bf16 beyond what the last-level cache holds of the pass's elems * (6 P + 20) bytes: tensors of 2000 elements P = 8 2 M without / with
+// gbar 44 / 38 and 48 / 45, 6 M 99.8 / 100 and 112 / 125, P = 32 0.6 M 44 / 40, 2 M 108 / 130, P = 64 0.3 M in 18 47.5 / 49.3, 2 M 212 / 254;
+// of 2600 P = 6 2.6 M 39.9 / 40.7 and 44.7 / 48.5, P = 8 0.8 M 17.0 / 15.4, 2.6 M 46 / 50 and 51 / 58; whole P = 5 2 M (493 tiles) 17.2 / 15.8, 2.1 M (517)
+// 18.2 / 19.7, P = 4 2.3 M (566) 17.6 / 18.9, 3 M (737) 23.1 / 21.0; weights and short
+// vectors P = 5 4 M (71 %) 41.8 / 39.2, P = 8 1.7 M (88 %) 22.5 / 21.4, P = 11 1.3 M (51 %) 34.4 / 31.0 and 35.9 / 33.4.  Of 1500 and less one launch is faster at any size (P = 8 4.5 M
+// 90 / 65, P = 32 1.5 M 102 / 94), as in fp32 (P = 64 1.5 M 272 / 266), where half full tiles cost from 25 replicas on (135 tensors of
+// 3500 in 246 tiles P = 64 75.7 / 78.7, 1 M in 500 160 / 169; weights and short vectors 40 % full P = 64 52.5 / 59.3).
 inline bool iteration_gathers_at_once(int grad_bytes, int64_t P, int64_t elems, int64_t tiles, bool with_gbar, int64_t max_workgroups)
 {
     constexpr int64_t M = 1000000;
     if (max_workgroups > 0 || tiles * AG_SPLIT > MAX_GRID) return false;
     const bool bf16 = grad_bytes == 2;
+    const int64_t few = bf16 ? (P < 31 ? 4 * P : 124) : P <= 12 ? 2 * P : P < 31 ? 3 * P : 92;
+    if (P > (bf16 ? 8 : 9) && tiles < few) return false;
     const int64_t open = tiles * DEAR_TILE_ELEMS - elems;
-    const int64_t cached = P > 12 ? 0 : P > 8 ? (bf16 ? 7 : 6) * M : (bf16 ? 12 : 9) * M;
-    if (P * (elems - open) <= cached) return true;
+    const int64_t cached = P > 12 ? 0 : bf16 ? (P > 8 ? 7 : 12) * M : (P >= 8 ? 6 : 9) * M;
+    if (P * (elems - open) <= cached) {
+        if (elems * 5 < tiles * (2 * DEAR_TILE_ELEMS)) return true;
+        if (!bf16) return P <= 24 || elems * 8 < tiles * (3 * DEAR_TILE_ELEMS);
+        if (P >= 3 && tiles > 512 && tiles <= 680 && elems * 4 >= tiles * (3 * DEAR_TILE_ELEMS)) return false;  // a third whole tile for few of the CUs
+        const int64_t most = elems * 5 >= tiles * (3 * DEAR_TILE_ELEMS) ? 120 : elems > open ? 180 : 256;
+        return P < 6 || (P <= 32 && elems * (6 * P + 20) <= most * M);
+    }
     if (bf16) return P <= 2 && elems >= 25 * M;
     return P <= 2 || (P == 3 && elems >= 25 * M) || (P == 4 && elems >= (with_gbar ? 64 : 40) * M);
 }

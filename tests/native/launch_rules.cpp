@@ -181,6 +181,29 @@ static void whole_tiles()
             }
 }
 
+// dear_iteration in one launch: few replicas, or small calls and open tiles.
+static void at_once()
+{
+    struct { int g; int64_t P, elems, tiles; bool gbar, once; } const at[] = {
+        {4, 1, 1, 1, true, true},             {4, 2, 100000000, 24500, true, true},  {4, 3, 24999999, 6200, false, false}, {4, 3, 25000000, 6200, true, true},
+        {4, 4, 39999999, 9800, false, false}, {4, 4, 40000000, 9800, false, true},   {4, 4, 40000000, 9800, true, false},  {4, 4, 64000000, 15700, true, true},
+        {4, 7, 1200000, 293, false, true},    {4, 8, 740000, 181, true, true},       {4, 8, 875000, 214, false, false},    {4, 12, 80000, 24, false, true},      {4, 12, 70000, 23, true, false},
+        {4, 13, 70000, 38, false, false},     {4, 16, 60000, 47, false, false},      {4, 16, 60000, 48, true, true},       {4, 64, 100000, 92, false, true},
+        {4, 64, 100000, 91, true, false},     {4, 9, 5000, 10, true, true},          {4, 16, 1000000, 516, false, true},   {4, 32, 6000000, 2000, false, false},
+        {4, 64, 468750, 246, false, false},   {4, 24, 468750, 246, false, true},     {4, 64, 300000, 246, false, true},      {4, 64, 1500000, 1064, true, true},
+        {2, 2, 24999999, 6200, true, false},  {2, 2, 25000000, 6200, true, true},    {2, 4, 2900000, 710, false, true},    {2, 5, 1800000, 444, false, true},
+        {2, 5, 2080000, 513, false, false},   {2, 4, 2300000, 566, true, false},     {2, 2, 2300000, 566, false, true},      {2, 6, 1916700, 474, true, true},     {2, 11, 1337000, 640, true, true},     {2, 5, 3950000, 1354, false, true},    {2, 8, 1708768, 473, true, true},     {2, 6, 2600000, 1006, false, false},
+        {2, 5, 2300000, 566, false, false},   {2, 8, 1437500, 359, true, true},      {2, 8, 30000, 18, false, true},       {2, 9, 60000, 36, false, true},
+        {2, 9, 60000, 35, false, false},      {2, 32, 100000, 124, true, true},      {2, 32, 100000, 123, false, false},   {2, 8, 2600000, 1006, true, false},
+        {2, 8, 780000, 306, true, true},      {2, 8, 2000000, 1006, true, true},     {2, 8, 6000000, 3008, true, false},   {2, 8, 4500000, 3008, true, true},
+        {2, 32, 600000, 330, false, true},    {2, 32, 2000000, 1030, false, false},  {2, 32, 1500000, 1030, false, true},  {2, 64, 300000, 330, false, true},    {2, 64, 300000, 152, true, false},
+    };
+    for (const auto &c : at) {
+        CHECK(iteration_gathers_at_once(c.g, c.P, c.elems, c.tiles, c.gbar, 0) == c.once);
+        CHECK(!iteration_gathers_at_once(c.g, c.P, c.elems, c.tiles, c.gbar, 1 << 20));
+    }
+}
+
 int main()
 {
     grids();
@@ -190,6 +213,7 @@ int main()
     iteration();
     whole_tiles();
     update_and_gather();
+    at_once();
     std::printf("launch_rules: ok\n");
     return 0;
 }
