@@ -981,7 +981,7 @@ void rs_launch_as(const rs_call &c, const rs_sink<MODE> &o)
     const float inv_P = 1.0f / static_cast<float>(c.P);
     int residency = 0;
     if constexpr ((MODE & RS_GATHER) != 0) {  // never bounded
-        residency = iteration_at_once_residency(BF16, c.all_elems, c.all_tiles);
+        residency = iteration_at_once_residency(BF16, (MODE & RS_GBAR) != 0, c.P, c.all_elems, c.all_tiles);
     } else {
         if (grid.x < n_items) {
             reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, true>

@@ -348,11 +348,12 @@ inline bool iteration_gathers_at_once(int grad_bytes, int64_t P, int64_t elems, 
 
 // Workgroups per CU of such a launch (see reduce_scatter_residency), 0 for as many as fit: us at as many / 2 / 1, fp32
 // with gbar P = 2 5 M 32.8 / 31.6 / 38.9, 100 M 640 / 579 / 703, P = 3 100 M 788 / 722 / 878, without P = 4 100 M 854 / 776 / 876;
-// bf16 with gbar, half tiles, P = 2 30 M - / 180 / 161, 100 M 596 / 594 / 525.
-inline int iteration_at_once_residency(bool bf16, int64_t elems, int64_t tiles)
+// bf16 with gbar, half tiles, P = 2 30 M - / 180 / 161, 100 M 596 / 594 / 525.  bf16 P = 1 without gbar 26 M 97 / 93 / 106, 100 M 389 / 355 / 395,
+// 250 M - / 923 / 1017, with it 26 M 125 / 114 / 118, 80 M - / 354 / 358, 100 M 499 / 449 / 444, 150 M - / 702 / 683.
+inline int iteration_at_once_residency(bool bf16, bool with_gbar, int64_t P, int64_t elems, int64_t tiles)
 {
     if (elems * 5 < tiles * (4 * DEAR_TILE_ELEMS)) return 0;
-    if (bf16) return elems >= 25000000 ? 1 : 0;
+    if (bf16) return elems < 25000000 ? 0 : P == 1 && !(with_gbar && elems >= 90000000) ? 2 : 1;
     return elems >= 4000000 ? 2 : 0;
 }
 

@@ -198,6 +198,11 @@ static void at_once()
         {2, 8, 780000, 306, true, true},      {2, 8, 2000000, 1006, true, true},     {2, 8, 6000000, 3008, true, false},   {2, 8, 4500000, 3008, true, true},
         {2, 32, 600000, 330, false, true},    {2, 32, 2000000, 1030, false, false},  {2, 32, 1500000, 1030, false, true},  {2, 64, 300000, 330, false, true},    {2, 64, 300000, 152, true, false},
     };
+    CHECK(iteration_at_once_residency(true, false, 1, 25000000, 6104) == 2 && iteration_at_once_residency(true, false, 1, 24999999, 6104) == 0);
+    CHECK(iteration_at_once_residency(true, true, 1, 89000000, 21800) == 2 && iteration_at_once_residency(true, true, 1, 90000000, 22000) == 1);
+    CHECK(iteration_at_once_residency(true, false, 1, 300000000, 73300) == 2 && iteration_at_once_residency(true, false, 2, 25000000, 6104) == 1);
+    CHECK(iteration_at_once_residency(false, true, 1, 4000000, 980) == 2 && iteration_at_once_residency(false, true, 3, 3900000, 960) == 0);
+    CHECK(iteration_at_once_residency(true, true, 2, 30000000, 12000) == 0);
     for (const auto &c : at) {
         CHECK(iteration_gathers_at_once(c.g, c.P, c.elems, c.tiles, c.gbar, 0) == c.once);
         CHECK(!iteration_gathers_at_once(c.g, c.P, c.elems, c.tiles, c.gbar, 1 << 20));
