@@ -102,15 +102,17 @@ def test_iteration_over_a_bucket_in_pieces(dtype, P, thr):
     pair.close()
 
 
-# tables of one upload piece, of several and of more than go in pieces (about 2, 30, 64 and 200 KB), nothing waited for between calls
+# tables of one upload piece, of several and of more than go in pieces, nothing waited for between calls; tiles cut on the host
+# (tensors of about a tile) and on the device (long ones)
 @pytest.mark.gpu
 def test_static_calls_back_to_back():
     import torch
     import paper_2302_12445_amd as dear
     from paper_2302_12445_amd import binding as B
     from paper_2302_12445_amd.emulation import EmulatedWorkers
-    ems = [EmulatedWorkers([1000 + 7 * l for l in range(L)], P, dtype, thr, "cuda:0")
-           for L, P, dtype, thr in ((5, 4, "f32", 9000), (300, 8, "bf16", 40_000), (1, 3, "f32", 0), (500, 9, "f32", W_NO_LIMIT), (700, 16, "f32", 60_000))]
+    ems = [EmulatedWorkers([n + 7 * l for l in range(L)], P, dtype, thr, "cuda:0")
+           for n, L, P, dtype, thr in ((1000, 5, 4, "f32", 9000), (90_000, 3, 2, "bf16", W_NO_LIMIT), (1000, 300, 8, "bf16", 40_000), (1000, 1, 3, "f32", 0),
+                                       (20_000, 130, 4, "f32", 900_000), (1000, 500, 9, "f32", W_NO_LIMIT), (1000, 700, 16, "f32", 60_000))]
     side = torch.cuda.Stream()
     outs = []
     for em in ems:
