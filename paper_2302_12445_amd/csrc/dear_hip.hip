@@ -980,16 +980,17 @@ void rs_launch_as(const rs_call &c, const rs_sink<MODE> &o)
     const dim3 grid(grid_width(c.max_workgroups, n_items)), block(DEAR_BLOCK);
     const float inv_P = 1.0f / static_cast<float>(c.P);
     int residency = 0;
-    if constexpr ((MODE & RS_GATHER) != 0) {  // never bounded
+    if constexpr ((MODE & RS_GATHER) != 0)
         residency = iteration_at_once_residency(BF16, (MODE & RS_GBAR) != 0, c.P, c.all_elems, c.all_tiles);
-    } else {
+    else
+        residency = reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, c.P, c.all_elems, c.all_tiles);
+    // one launch for the iteration, and half tiles, are for unbounded grids only
+    if constexpr ((MODE & RS_GATHER) == 0 && !(BF16 && U == 1))
         if (grid.x < n_items) {
             reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, true>
                 <<<grid, block, 0, c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, c.prio);
             return;
         }
-        residency = reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, c.P, c.all_elems, c.all_tiles);
-    }
     reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, false>
         <<<grid, block, residency_lds(residency), c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, 0);
 }
