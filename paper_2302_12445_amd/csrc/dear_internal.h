@@ -277,9 +277,11 @@ inline bool iteration_caches_w(int grad_bytes, int64_t P, int64_t group_tiles, i
 
 // A bucket beyond ITERATION_TILES is handled in pieces of its tiles, whatever layers and shards they belong to, if that
 // leaves each piece's w in the last-level cache for its all-gather.  us per iteration without and with gbar, one launch pair /
-// pieces, one bucket: bf16 P = 3 50 M 312 / 292 and 359 / 329, P = 5 36 M 286 / 284 and 324 / 313, P = 8 110 M 1149 / 1132 and 1252 / 1205,
-// 300 M 3137 / 3038 and 3351 / 3229; not where w is stored non-temporally anyway: bf16 P = 16 100 M 1766 / 1768 and 1868 / 1848, fp32
-// P = 5 36 M 336 / 344 and 359 / 366, P = 8 100 M 1284 / 1312 and 1370 / 1388.  Pieces of 4096 and 12288 tiles are level to 1 %.
+// pieces, one bucket (two runs of one side differ by up to 5 %): bf16 P = 3 50 M 321 / 295 and 370 / 338, 100 M 640 / 586 and 740 / 674, P = 4 50 M 369 / 344
+// and 419 / 386, P = 5 36 M 295 / 281 and 332 / 312, P = 6 60 M 543 / 511 and 610 / 561, P = 8 50 M 536 / 524 and 577 / 554, 110 M 1155 / 1128 and
+// 1263 / 1197; with a bounded grid of 256 P = 3 50 M 336 / 322 and 385 / 365, P = 8 110 M 1442 / 1328 and 1537 / 1404, of 1024 P = 8 60 M 803 / 724.
+// Not where w is stored non-temporally anyway: bf16 P = 16 100 M 1766 / 1768 and 1868 / 1848, fp32 P = 5 36 M 336 / 344 and 359 / 366, P = 8 100 M 1284 / 1312
+// and 1370 / 1388.  Pieces of 4096 and 12288 tiles are level to 1 %.
 inline int64_t iteration_pieces(int grad_bytes, int64_t P, int64_t group_tiles, int64_t all_tiles)
 {
     if (!iteration_caches_w(grad_bytes, P, ITERATION_TILES, all_tiles) || grad_bytes != 2) return 1;

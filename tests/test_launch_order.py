@@ -91,15 +91,52 @@ def test_iteration_in_one_launch(dtype, P, sizes):
 
 # one bucket beyond 8192 tiles: pieces that begin inside a layer and a shard
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype,P,thr", [("f32", 5, None), ("bf16", 3, None), ("bf16", 5, 40_000_000)])
-def test_iteration_over_a_bucket_in_pieces(dtype, P, thr):
+@pytest.mark.parametrize("dtype,P,thr,width", [("f32", 5, None, 0), ("bf16", 3, None, 0), ("bf16", 5, 40_000_000, 0), ("bf16", 3, None, 300)])
+def test_iteration_over_a_bucket_in_pieces(dtype, P, thr, width):
     from test_gpu_parity import Pair, say, small_workload
     import workloads as W
-    say("case: one bucket in pieces, %s, P=%d" % (dtype, P))
+    say("case: one bucket in pieces, %s, P=%d, width %d" % (dtype, P, width))
     pair = Pair(small_workload([17_000_001, 3, 20_100_077], P, thr or W.NO_LIMIT, dtype))
-    pair.run(iterations=1, route="iteration")
-    pair.run(iterations=1, route="iteration", fused=True)
+    pair.run(iterations=1, route="iteration", width=width)
+    pair.run(iterations=1, route="iteration", fused=True, width=width)
     pair.close()
+
+
+# pieces that begin inside a run whose all-gather's cuts are moved to the replicas' 128-byte lines: every cut is where the one
+# all-gather over the whole bucket has it, and nothing around the tensors is written
+@pytest.mark.gpu
+@pytest.mark.parametrize("starts,width", [((4, 4, 4), 0), ((28, 28, 28), 0), ((0, 12, 20), 0), ((16, 4, 28), 300)])
+def test_pieces_of_runs_with_moved_cuts(starts, width):
+    import torch
+    import paper_2302_12445_amd as dear
+    from paper_2302_12445_amd import binding as B
+    print("case: pieces, tensors at %s of a line, width %d" % (starts, width), flush=True)
+    sizes, P = [17_000_001, 20_100_077], 3
+    plan = dear.dear_plan(sizes, P, W_NO_LIMIT, 2)
+    gen = torch.Generator("cuda:0").manual_seed(sum(starts))
+    grads = [[torch.randn(n, device="cuda:0", generator=gen).to(torch.bfloat16) for n in sizes] for _ in range(P)]
+    w0 = torch.randn(P, plan.total_shard_len, device="cuda:0", generator=gen)
+    got = []
+    for whole in (False, True):
+        params = [[torch.full((n + 96,), 7.0, device="cuda:0") for n in sizes] for _ in range(P)]
+        ctx = dear.dear_ctx_create(plan, B.DEAR_BF16, [t.data_ptr() for rep in grads for t in rep],
+                                   [t.data_ptr() + 4 * (32 + starts[p]) for p, rep in enumerate(params) for t in rep])
+        g, w, v = torch.zeros_like(w0), w0.clone(), w0 * 0.25
+        if whole:  # a launch of each, over all tiles
+            dear.dear_reduce_scatter(ctx, -1, g.data_ptr())
+            dear.dear_shard_update(ctx, -1, g.data_ptr(), w.data_ptr(), v.data_ptr(), 0.1, 0.9)
+            dear.dear_all_gather(ctx, -1, w.data_ptr())
+        else:
+            dear.dear_ctx_set_max_workgroups(ctx, width)
+            dear.dear_iteration(ctx, -1, g.data_ptr(), w.data_ptr(), v.data_ptr(), 0.1, 0.9)
+        torch.cuda.synchronize()
+        got.append([g, w, v] + [t for rep in params for t in rep])
+        ctx.destroy()
+    for a, b in zip(*got):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    for p, t in enumerate(got[0][3::2]):
+        assert bool((t[:32 + starts[p]] == 7.0).all()) and bool((t[32 + starts[p] + sizes[0]:] == 7.0).all())
+        assert int((t[32 + starts[p]:32 + starts[p] + sizes[0]] == 7.0).sum()) < 10
 
 
 # tables of one upload piece, of several and of more than go in pieces, nothing waited for between calls; tiles cut on the host
