@@ -15,7 +15,8 @@
  *   - Every function returns a status (DEAR_OK = 0, errors < 0); nothing is printed,
  *     nothing aborts.  On error nothing is launched and outputs are untouched; DEAR_EHIP
  *     from a call that makes several launches (dear_update_all_gather, dear_iteration) can
- *     also mean that a later one failed.
+ *     also mean that a later one failed, and from dear_reduce_scatter_static that the wait
+ *     behind the launches did.
  *   - "host" / "device" is stated for every pointer.  All large device memory is owned
  *     by the caller; the library owns only its plan/context objects and their small
  *     tables (host and device), released by dear_plan_free / dear_ctx_destroy.
@@ -157,8 +158,8 @@ int dear_plan_tiles(const dear_plan_t *plan, dear_tile_t *out, int64_t capacity,
  * pointer arrays are copied; the tensors themselves stay owned by the caller and must
  * outlive the context.  The context copies what it needs from the plan, so the plan
  * may be freed first.  Allocates device memory for its tables (pointer tables, a
- * table of 32 bytes per layer, one of 48 bytes per run of a layer within a shard, and a tile table of 32
- * bytes per DEAR_TILE_ELEMS elements).  Uses the current HIP device;
+ * table of 32 bytes per layer, a tile table of 32 bytes per DEAR_TILE_ELEMS elements, and beyond 3072
+ * tiles one of 48 bytes per run of a layer within a shard, from which it is cut).  Uses the current HIP device;
  * every later call on the context must be made with that device current (DEAR_EINVAL
  * otherwise).
  * Errors: DEAR_EINVAL, DEAR_EALIGN, DEAR_ENOMEM, DEAR_EHIP.

@@ -27,8 +27,8 @@ typedef dear_tile_t dear_tile;
 static_assert(sizeof(dear_tile) == 32, "tile descriptors are read as two 16-byte loads");
 
 // A run: `count` elements of one layer within one shard, or padding slots of one shard (layer -1, src_begin 0).  The tile
-// table follows from the runs, which are a few hundred where the tiles are thousands, so it is the runs that are uploaded,
-// and a kernel cuts them (expand_runs_kernel).
+// table follows from the runs.  Where they are a few hundred and the tiles thousands, it is the runs that are uploaded, and a kernel
+// cuts them (expand_runs_kernel); small tables are cut on the host and uploaded as they are.
 struct dear_run {
     int64_t src_begin, dst_begin, count;
     int64_t first_tile;  // its tiles' place in the table
