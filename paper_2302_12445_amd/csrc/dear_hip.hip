@@ -1072,7 +1072,7 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
     std::vector<dear_run> runs;
     std::vector<unsigned char> image;  // what is uploaded: tiles or runs, layer places, gradient and parameter pointers
     int64_t n_runs = 0, n_tiles = 0;
-    size_t places_at = 0, grad_at = 0, param_at = 0;
+    table_layout at{};
     try {
         c.reset(new dear_ctx_s);
         c->L = plan->L;
@@ -1088,10 +1088,8 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
         c->whole_begin.assign(plan->B + 1, 0);
         n_runs = dear_emit_runs(*plan, 0, plan->B, nullptr, 0, &n_tiles, c->tile_begin.data());
         runs.resize(n_runs);
-        places_at = n_tiles <= HOST_TILES ? (n_tiles + TILES_BEHIND) * sizeof(dear_tile) : n_runs * sizeof(dear_run);
-        grad_at = places_at + plan->L * sizeof(layer_place);
-        param_at = grad_at + n_ptr * sizeof(void *);
-        image.resize(param_at + n_ptr * sizeof(void *));
+        at = lay_out_tables(n_tiles <= HOST_TILES, n_tiles, n_runs, plan->L * sizeof(layer_place), n_ptr * sizeof(void *));
+        image.resize(at.end - at.uploaded);
     } catch (const std::bad_alloc &) {
         return DEAR_ENOMEM;
     }
@@ -1107,31 +1105,32 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
         for (const dear_run &r : runs)
             for (int64_t k = 0, n = tiles_of_run(r); k < n; ++k) tiles[r.first_tile + k] = marked_tile(r, k, n);
     } else {
-        std::memcpy(image.data(), runs.data(), places_at);
+        std::memcpy(image.data(), runs.data(), n_runs * sizeof(dear_run));
     }
+    auto in_image = [&](size_t device_offset) { return image.data() + (device_offset - at.uploaded); };
     for (int32_t l = 0; l < plan->L; ++l) {
         const int32_t b = plan->layer_bucket[l];
         const int64_t S = plan->bucket_shard_len[b];
-        const layer_place at{plan->layer_offset[l], S, plan->bucket_shard_base[b], 1.0 / static_cast<double>(S)};
-        std::memcpy(image.data() + places_at + l * sizeof at, &at, sizeof at);
+        const layer_place place{plan->layer_offset[l], S, plan->bucket_shard_base[b], 1.0 / static_cast<double>(S)};
+        std::memcpy(in_image(at.places) + l * sizeof place, &place, sizeof place);
     }
-    std::memcpy(image.data() + grad_at, grad_ptrs, n_ptr * sizeof(void *));
-    std::memcpy(image.data() + param_at, param_ptrs, n_ptr * sizeof(void *));
+    std::memcpy(in_image(at.grad), grad_ptrs, n_ptr * sizeof(void *));
+    std::memcpy(in_image(at.param), param_ptrs, n_ptr * sizeof(void *));
 
     int rc = DEAR_OK;
-    const size_t in_front = on_host ? 0 : (n_tiles + TILES_BEHIND) * sizeof(dear_tile);  // room for the tiles
     unsigned char *base = nullptr;
-    if (hipMalloc(&c->d_tables, in_front + image.size()) != hipSuccess) {
+    if (hipMalloc(&c->d_tables, at.end) != hipSuccess) {
         c->d_tables = nullptr;
         rc = DEAR_ENOMEM;
     } else {
         c->d_tiles = static_cast<dear_tile *>(c->d_tables);
-        base = static_cast<unsigned char *>(c->d_tables) + in_front;
+        base = static_cast<unsigned char *>(c->d_tables);
+        unsigned char *const to = base + at.uploaded;
         if (on_host) {
-            if (hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice) != hipSuccess) rc = DEAR_EHIP;
+            if (hipMemcpy(to, image.data(), image.size(), hipMemcpyHostToDevice) != hipSuccess) rc = DEAR_EHIP;
         } else {
-            const bool sent = upload(base, image.data(), image.size(), nullptr) &&
-                              expand_runs(reinterpret_cast<const dear_run *>(base), n_runs, c->d_tiles, nullptr);
+            const bool sent = upload(to, image.data(), image.size(), nullptr) &&
+                              expand_runs(reinterpret_cast<const dear_run *>(to), n_runs, c->d_tiles, nullptr);
             if (hipStreamSynchronize(nullptr) != hipSuccess || !sent) rc = DEAR_EHIP;
         }
     }
@@ -1140,9 +1139,9 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
         dear_ctx_destroy(c.release());
         return rc;
     }
-    c->d_places = reinterpret_cast<layer_place *>(base + places_at);
-    c->d_grad = reinterpret_cast<const void **>(base + grad_at);
-    c->d_param = reinterpret_cast<float **>(base + param_at);
+    c->d_places = reinterpret_cast<layer_place *>(base + at.places);
+    c->d_grad = reinterpret_cast<const void **>(base + at.grad);
+    c->d_param = reinterpret_cast<float **>(base + at.param);
     *out = c.release();
     return DEAR_OK;
 }

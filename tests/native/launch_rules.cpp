@@ -209,8 +209,27 @@ static void at_once()
     }
 }
 
+// Tables of a context: each on 256 bytes, none over another, all within the allocation, whatever lies before them.
+static void tables()
+{
+    for (bool sent : {true, false})
+        for (int64_t runs : {1, 5, 7, 171, 1000})
+            for (int64_t tiles : {runs, runs + 3, 40 * runs})
+                for (int64_t L : {1, 3, 161})
+                    for (int64_t P : {1, 7, 64}) {
+                        const size_t places = L * 32, pointers = L * P * sizeof(void *);
+                        const size_t room = (tiles + TILES_BEHIND) * sizeof(dear_tile);
+                        const table_layout t = lay_out_tables(sent, tiles, runs, places, pointers);
+                        CHECK(t.uploaded % 256 == 0 && t.places % 256 == 0 && t.grad % 256 == 0 && t.param % 256 == 0);
+                        CHECK(sent ? t.uploaded == 0 && t.places >= room
+                                   : t.uploaded >= room && t.places >= t.uploaded + runs * sizeof(dear_run));
+                        CHECK(t.grad >= t.places + places && t.param >= t.grad + pointers && t.end == t.param + pointers);
+                    }
+}
+
 int main()
 {
+    tables();
     grids();
     residency();
     half_tiles();
