@@ -331,6 +331,8 @@ inline bool iteration_updates_apart(int grad_bytes, int64_t P, int64_t group_til
 //         P = 4 1 M 11.3 / 9.8  3 M 26.8 / 26.8  6 M 48.1 / 50.0  20 M 155 / 160  50 M 402 / 383 (with gbar 429 / 430)
 //         P = 8 0.2 M 7.5 / 6.7  1 M 15.9 / 15.2  1.5 M 22.2 / 22.8  6 M 78.8 / 85.5  P = 12 0.5 M 13.4 / 13.2  1 M 22.6 / 23.8
 //         P = 16 0.2 M 11.3 / 11.8  1 M 27.1 / 30.8
+//         P = 8 from 6 to 9 M copied elements, where only 240 to 258 tiles, of four workgroups each, fill the 256 CUs evenly: one tensor 223 tiles 13.1 / 14.1  242 13.7 / 13.3  258 14.9 / 13.8  262 15.8 / 16.1  277 16.0 / 17.2, 23 tensors
+//         230 14.3 / 14.2  248 15.4 / 14.3  257 15.6 / 14.4  267 16.5 / 16.7  281 16.9 / 17.4
 //         open tiles: P = 8 1 M in 500 tensors 27.3 / 22.4, 2 M in 200 34.2 / 34.1, 3 M in 500 50.2 / 50.7;
 //         P = 16 1 M in 500 47.8 / 39.7, in 60 29.0 / 32.0, 3 M in 500 86.3 / 93.2
 //   bf16  P = 2 1 M 8.9 / 6.6  6 M 33.4 / 31.0  20 M 92.2 / 97.1  30 M 150 / 145  100 M 514 / 481
@@ -357,7 +359,8 @@ inline bool iteration_gathers_at_once(int grad_bytes, int64_t P, int64_t elems, 
     const int64_t few = bf16 ? (P < 31 ? 4 * P : 124) : P <= 12 ? 2 * P : P < 31 ? 3 * P : 92;
     if (P > (bf16 ? 8 : 9) && tiles < few) return false;
     const int64_t open = tiles * DEAR_TILE_ELEMS - elems;
-    const int64_t cached = P > 12 ? 0 : bf16 ? (P > 8 ? 7 : 12) * M : (P >= 8 ? 6 : 9) * M;
+    const bool even = P == 8 && tiles >= 240 && tiles <= 258;
+    const int64_t cached = P > 12 ? 0 : bf16 ? (P > 8 ? 7 : 12) * M : (P < 8 || even ? 9 : 6) * M;
     if (P * (elems - open) <= cached) {
         if (elems * 5 < tiles * (2 * DEAR_TILE_ELEMS)) return true;
         if (!bf16) return P <= 24 || elems * 8 < tiles * (3 * DEAR_TILE_ELEMS);

@@ -187,7 +187,9 @@ static void at_once()
     struct { int g; int64_t P, elems, tiles; bool gbar, once; } const at[] = {
         {4, 1, 1, 1, true, true},             {4, 2, 100000000, 24500, true, true},  {4, 3, 24999999, 6200, false, false}, {4, 3, 25000000, 6200, true, true},
         {4, 4, 39999999, 9800, false, false}, {4, 4, 40000000, 9800, false, true},   {4, 4, 40000000, 9800, true, false},  {4, 4, 64000000, 15700, true, true},
-        {4, 7, 1200000, 293, false, true},    {4, 8, 740000, 181, true, true},       {4, 8, 875000, 214, false, false},    {4, 12, 80000, 24, false, true},      {4, 12, 70000, 23, true, false},
+        {4, 7, 1200000, 293, false, true},    {4, 8, 740000, 181, true, true},       {4, 8, 875000, 214, false, false},
+        {4, 8, 960000, 239, false, false},    {4, 8, 960000, 240, false, true},      {4, 8, 1000000, 258, true, true},      {4, 8, 1000000, 259, true, false},
+        {4, 8, 1056000, 258, false, true},    {4, 9, 1000000, 250, false, false},    {4, 12, 80000, 24, false, true},      {4, 12, 70000, 23, true, false},
         {4, 13, 70000, 38, false, false},     {4, 16, 60000, 47, false, false},      {4, 16, 60000, 48, true, true},       {4, 64, 100000, 92, false, true},
         {4, 64, 100000, 91, true, false},     {4, 9, 5000, 10, true, true},          {4, 16, 1000000, 516, false, true},   {4, 32, 6000000, 2000, false, false},
         {4, 64, 468750, 246, false, false},   {4, 24, 468750, 246, false, true},     {4, 64, 300000, 246, false, true},      {4, 64, 1500000, 1064, true, true},
