@@ -23,6 +23,7 @@
 #include <memory>
 #include <new>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include "dear_internal.h"
@@ -139,14 +140,18 @@ __device__ __forceinline__ int ring_worker(int start, int k, int P)
     return p >= P ? p - P : p;
 }
 
+// One gradient element: its bits as they lie in memory, and their value.
 template <bool BF16>
-__device__ __forceinline__ float grad_elem(const void *base, int64_t i)
+__device__ __forceinline__ uint32_t grad_bits(const void *base, int64_t i)
 {
-    if (BF16) {
-        uint32_t h = ((const DEAR_GLOBAL uint16_t *)base)[i];
-        return __uint_as_float(h << 16);
-    }
-    return ((const DEAR_GLOBAL float *)base)[i];
+    if (BF16) return ((const DEAR_GLOBAL uint16_t *)base)[i];
+    return ((const DEAR_GLOBAL uint32_t *)base)[i];
+}
+
+template <bool BF16>
+__device__ __forceinline__ float grad_value(uint32_t bits)
+{
+    return __uint_as_float(BF16 ? bits << 16 : bits);
 }
 
 // The first and last 16-byte vector of a run [a, c) may be partial.  Lanes 0 .. VE-1 take an element each
@@ -406,7 +411,7 @@ __device__ __forceinline__ void reduce_scatter_tile(const dear_tile &t, int part
 #pragma unroll
                 for (int kk = 0; kk < CH; ++kk) {
                     const int k = (!TAIL || k0 + kk < P) ? k0 + kk : 0;
-                    x[kk] = grad_elem<BF16>(grad_tab[(size_t)ring_worker(start, k, P) * L + t.layer], edge);
+                    x[kk] = grad_value<BF16>(grad_bits<BF16>(grad_tab[(size_t)ring_worker(start, k, P) * L + t.layer], edge));
                 }
 #pragma unroll
                 for (int kk = 0; kk < CH; ++kk)
@@ -433,12 +438,168 @@ __device__ __forceinline__ void reduce_scatter_tile(const dear_tile &t, int part
     }
 }
 
-// Reduce-scatter (paper Sec. III-A; Eq. 2 for the 1/P).  SPLIT workgroups share a tile.
+// What comes behind the first D replicas: nothing (P = D: no loop in the code, whose lines a short launch waits for), as many
+// again some times over, or that and a rest.
+enum rest_of_replicas { REST_NONE, REST_BATCHES, REST_TAIL };
+
+// Sum of all replicas in ring order from replica `start` on: one vector a lane, at `vec`, and with EDGE one element, at `elem`.
+// D replicas are in flight: as soon as one has come and is added, the load of the one D further on takes its registers, with
+// the pointers fetched another D ahead, so that a wavefront's loads never drain between batches.  Lanes without a
+// vector or an element of their own are given an address in bounds, so that there is no branch between a load and its use
+// but the uniform ones behind the loop.  P >= D, see rest_of_replicas.
+template <bool BF16, int D, rest_of_replicas REST, bool VECTOR, bool EDGE, int VE>
+__device__ __forceinline__ void sum_replicas(float (&acc)[VE], float &acc_edge, int64_t vec, int64_t elem,
+                                             const void *const *__restrict__ grad_tab, int L, int P, int layer, int start)
+{
+    const void *src[D];
+    u4 raw[D];
+    uint32_t one[D];
+    // the table's entries of this layer, by their distance in bytes from worker 0's (pointer_table_fits)
+    const char DEAR_CONSTANT *const entries = (const char DEAR_CONSTANT *)(grad_tab + layer);
+    const unsigned step = (unsigned)L * 8, end = (unsigned)P * step;
+    unsigned at = (unsigned)start * step;
+    auto pointers = [&]() {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            src[d] = *(const void *const DEAR_CONSTANT *)(entries + at);
+            at += step;
+            at = at == end ? 0 : at;
+        }
+    };
+    auto load = [&](int d) {
+        if (VECTOR) raw[d] = load_vec<DEAR_RS_NT_LOAD>((global_u4_in)src[d] + vec);
+        if (EDGE) one[d] = grad_bits<BF16>(src[d], elem);
+    };
+    auto add = [&](int d) {
+        if (VECTOR) add_vector<BF16, VE>(acc, raw[d]);
+        if (EDGE) acc_edge = acc_edge + grad_value<BF16>(one[d]);
+    };
+    pointers();
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+        load(d);
+    if (REST != REST_NONE && P > D) pointers();
+    int k0 = D;
+    for (; REST != REST_NONE && k0 + D <= P; k0 += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            add(d);
+            load(d);
+            __builtin_amdgcn_sched_barrier(0);  // or all loads are put behind the last addition
+        }
+        pointers();  // behind the loads that use the last ones: a wait for one scalar load is a wait for all
+    }
+    const int left = P - k0;  // REST_TAIL: 1 .. D-1 replicas have not been asked for yet
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        add(d);
+        if (REST == REST_TAIL && d < left) load(d);
+    }
+    if (REST == REST_TAIL) {
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d)
+            if (d < left) add(d);
+    }
+}
+
+// A workgroup's part of a tile, DEAR_BLOCK vectors.  ALL_FULL: the tile is a whole, aligned DEAR_TILE_ELEMS run.  Otherwise
+// the elements of the run's partial first and last vectors go along with the vectors, a lane each (edge_element): as a pass
+// of their own behind the vectors they doubled the part's chain of loads.
+template <bool BF16, int D, rest_of_replicas REST, bool ALL_FULL, rs_mode MODE>
+__device__ __forceinline__ void reduce_scatter_part(const dear_tile &t, int part, const void *const *__restrict__ grad_tab,
+                                                    int L, int P, float inv_P, const rs_sink<MODE> &o)
+{
+    constexpr int VE = BF16 ? 8 : 4, PIECES = VE / 4;
+    constexpr bool TURN = BF16 && ALL_FULL;  // results go through LDS, see reduce_scatter_tile
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int64_t a = t.src_begin, c = a + t.count;
+    const int64_t v_first = a / VE + (int64_t)part * DEAR_BLOCK, v_wave = v_first + wave * 64;
+    if (!ALL_FULL && v_first * VE >= c) return;
+    if (!ALL_FULL && wave > 0 && v_wave * VE >= c) return;  // the first wavefront has the partial vectors
+    const int start = t.shard + 1 >= P ? 0 : t.shard + 1;
+    const int64_t v_whole = (a + VE - 1) / VE;  // the run's first whole vector, if it has one
+    const bool vectors = ALL_FULL || (v_whole + 1) * VE <= c;
+
+    const int64_t edge = ALL_FULL ? -1 : edge_element<VE>(a, c, v_first, DEAR_BLOCK);
+    float acc[VE], acc_edge = -0.0f;
+#pragma unroll
+    for (int j = 0; j < VE; ++j) acc[j] = -0.0f;
+    if (vectors) {
+        int64_t vec = v_wave + lane;
+        const bool full = ALL_FULL || (vec * VE >= a && vec * VE + VE <= c);
+        if (!full) vec = v_whole;
+        int64_t piece_idx[PIECES];  // shard-buffer element index of each 16-byte piece of results
+        f4 w_old[PIECES], v_old[PIECES], r[PIECES];
+#pragma unroll
+        for (int h = 0; h < PIECES; ++h) {
+            piece_idx[h] = t.dst_begin - a + (TURN ? v_wave * VE + 256 * h + 4 * lane : vec * VE + 4 * h);
+            if (MODE & RS_UPDATE) {
+                w_old[h] = load_f4_dword_aligned<DEAR_RS_NT_LOAD>(o.w + piece_idx[h]);
+                v_old[h] = load_f4_dword_aligned<DEAR_RS_NT_LOAD>(o.v + piece_idx[h]);
+            }
+        }
+        sum_replicas<BF16, D, REST, true, !ALL_FULL>(acc, acc_edge, vec, edge >= 0 ? edge : a, grad_tab, L, P, t.layer, start);
+#pragma unroll
+        for (int h = 0; h < PIECES; ++h)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) r[h][j] = acc[4 * h + j] * inv_P;
+        if constexpr (TURN) {
+            __shared__ float stage[DEAR_BLOCK / 64][64 * 8];
+            float *sw = stage[wave];
+            *reinterpret_cast<f4 *>(sw + 8 * lane) = r[0];
+            *reinterpret_cast<f4 *>(sw + 8 * lane + 4) = r[PIECES - 1];
+            wave_lds_sync();
+            r[0] = *reinterpret_cast<const f4 *>(sw + 4 * lane);
+            r[PIECES - 1] = *reinterpret_cast<const f4 *>(sw + 256 + 4 * lane);
+            wave_lds_sync();
+        }
+        if (full)
+#pragma unroll
+            for (int h = 0; h < PIECES; ++h) emit_piece<MODE>(o, piece_idx[h], r[h], w_old[h], v_old[h]);
+    } else {
+        sum_replicas<BF16, D, REST, false, true>(acc, acc_edge, 0, edge >= 0 ? edge : a, grad_tab, L, P, t.layer, start);
+    }
+    if (edge >= 0) emit_elem<MODE>(o, t.dst_begin + (edge - a), acc_edge * inv_P);
+}
+
+// Reduce-scatter (paper Sec. III-A; Eq. 2 for the 1/P), one part of a tile a workgroup.
 // Summation starts at worker s+1 and ends with worker s, the order in which the ring
 // delivers the partial sums of chunk s to its owner.  The accumulator starts as -0.0f,
 // the additive identity that keeps the first addend's bits (including a -0.0f).
-template <bool BF16, int U, int CH, bool TAIL, rs_mode MODE, bool BOUNDED>
+// Bound by HBM: P streams read once.  With batches of replicas waited for together (the kernel below) a workgroup's loads drained
+// before every next batch, and neighbouring tiles went to different XCDs.  us, that kernel / this one: ResNet-50-shaped fp32 P = 64 all
+// buckets with update 1209 / 1131 (6.1 TB/s of a plain read's 7.0), BERT-Large-shaped bf16 P = 8 without 1210 / 1074 (5.7 / 6.4 TB/s),
+// with 1882 / 1773, ResNet-50-shaped fp32 P = 8 155 / 150 and 204 / 201.  reduce_scatter_shape_of says which form goes when.
+template <bool BF16, int D, rest_of_replicas REST, bool TILES, rs_mode MODE>
 __global__ __launch_bounds__(DEAR_BLOCK) void reduce_scatter_kernel(
+    const dear_tile *__restrict__ tiles, const void *const *__restrict__ grad_tab, int L, int P,
+    float inv_P, const rs_sink<MODE> o, unsigned n_items, unsigned run)
+{
+    constexpr int SPLIT = DEAR_TILE_ELEMS / ((BF16 ? 8 : 4) * DEAR_BLOCK), STEP = TILES ? 1 : SPLIT;
+    const unsigned item = reduce_scatter_item(blockIdx.x, run, n_items);
+    const dear_tile t = tiles[item / STEP];
+    const int first = item % STEP;
+    if (__builtin_expect(t.layer >= 0 && t.count == DEAR_TILE_ELEMS, 1)) {  // first, where the code's lines come in order
+#pragma unroll 1
+        for (int part = first; part < SPLIT; part += STEP)
+            reduce_scatter_part<BF16, D, REST, true, MODE>(t, part, grad_tab, L, P, inv_P, o);
+    } else if (t.layer >= 0) {
+#pragma unroll 1
+        for (int part = first; part < SPLIT; part += STEP)
+            reduce_scatter_part<BF16, D, REST, false, MODE>(t, part, grad_tab, L, P, inv_P, o);
+    } else {  // padding slots: gbar = +0
+        for (int i = first * DEAR_BLOCK + threadIdx.x; i < t.count; i += STEP * DEAR_BLOCK)
+            emit_elem<MODE>(o, t.dst_begin + i, 0.0f);
+    }
+}
+
+// The same in bounded grids, with the all-gather in the same launch (RS_GATHER), for what reduce_scatter_kernel cannot count, and
+// where reduce_scatter_shape_of finds it faster.  SPLIT workgroups share a tile.  Replicas come in batches of CH here, waited for
+// together: beside GEMMs, and with the writes of all replicas to follow, that is the better form (BERT-Large-shaped schedule, bf16 in
+// bounded grids, ms: this one 32.2, loads that never drain 36.1).
+template <bool BF16, int U, int CH, bool TAIL, bool BOUNDED, rs_mode MODE>
+__global__ __launch_bounds__(DEAR_BLOCK) void reduce_scatter_batch_kernel(
     const dear_tile *__restrict__ tiles, const void *const *__restrict__ grad_tab, int L, int P,
     float inv_P, const rs_sink<MODE> o, unsigned n_items, int prio)
 {
@@ -957,8 +1118,12 @@ unsigned grid_width(int32_t max_workgroups, int64_t n_items)
     return static_cast<unsigned>(n_items);
 }
 
-// LDS that a launch reserves for each workgroup, and nothing uses, so that `residency` of them share a CU's 160 KiB.
-unsigned residency_lds(int residency) { return residency == 1 ? 96 << 10 : residency == 2 ? 64 << 10 : 0; }
+// LDS that a launch reserves for each workgroup, and nothing uses, so that `residency` of them share a CU's 160 KiB (4: five in
+// fp32, whose kernel has no LDS of its own).
+unsigned residency_lds(int residency)
+{
+    return residency == 0 ? 0 : residency == 1 ? 96 << 10 : residency == 2 ? 64 << 10 : residency == 3 ? 44 << 10 : 32 << 10;
+}
 
 // What a reduce-scatter launch is made from.  tiles, grads: device tables (a context's, or the static scratch's).  The
 // launch may be one of several over all_tiles tiles, which hold all_elems elements and of which all_whole are whole.
@@ -973,55 +1138,97 @@ struct rs_call {
 };
 
 template <bool BF16, rs_mode MODE, int U, int CH, bool TAIL>
-void rs_launch_as(const rs_call &c, const rs_sink<MODE> &o)
+void rs_launch_batch_as(const rs_call &c, const rs_sink<MODE> &o)
 {
     constexpr int SPLIT = DEAR_TILE_ELEMS / ((BF16 ? 8 : 4) * DEAR_BLOCK * U);
     const unsigned n_items = static_cast<unsigned>(c.n_tiles * SPLIT);
-    const dim3 grid(grid_width(c.max_workgroups, n_items)), block(DEAR_BLOCK);
-    const float inv_P = 1.0f / static_cast<float>(c.P);
+    const dim3 grid(grid_width(c.max_workgroups, n_items));
     int residency = 0;
-    if constexpr ((MODE & RS_GATHER) != 0)
+    if ((MODE & RS_GATHER) != 0)
         residency = iteration_at_once_residency(BF16, (MODE & RS_GBAR) != 0, c.P, c.all_elems, c.all_tiles);
-    else
+    else if (grid.x == n_items)
         residency = reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, c.P, c.all_elems, c.all_tiles);
+    auto launch = [&](auto kernel) {
+        kernel<<<grid, dim3(DEAR_BLOCK), residency_lds(residency), c.st>>>(
+            c.tiles, c.grads, c.L, c.P, 1.0f / static_cast<float>(c.P), o, n_items, c.prio);
+    };
     // one launch for the iteration, and half tiles, are for unbounded grids only
     if constexpr ((MODE & RS_GATHER) == 0 && !(BF16 && U == 1))
-        if (grid.x < n_items) {
-            reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, true>
-                <<<grid, block, 0, c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, c.prio);
-            return;
-        }
-    reduce_scatter_kernel<BF16, U, CH, TAIL, MODE, false>
-        <<<grid, block, residency_lds(residency), c.st>>>(c.tiles, c.grads, c.L, c.P, inv_P, o, n_items, 0);
+        if (grid.x < n_items) return launch(reduce_scatter_batch_kernel<BF16, U, CH, TAIL, true, MODE>);
+    launch(reduce_scatter_batch_kernel<BF16, U, CH, TAIL, false, MODE>);
 }
 
 // Replicas per load batch: the largest of 8/4/2/1 that divides P without a tail when
 // P is small or a multiple of 4; otherwise batches of 8 with a predicated tail.
 template <bool BF16, rs_mode MODE, int U>
-void rs_launch_batched(const rs_call &c, const rs_sink<MODE> &o)
+void rs_launch_batch(const rs_call &c, const rs_sink<MODE> &o)
 {
     if (c.P % 8 == 0)
-        rs_launch_as<BF16, MODE, U, 8, false>(c, o);
+        rs_launch_batch_as<BF16, MODE, U, 8, false>(c, o);
     else if (c.P % 4 == 0)
-        rs_launch_as<BF16, MODE, U, 4, false>(c, o);
+        rs_launch_batch_as<BF16, MODE, U, 4, false>(c, o);
     else if (c.P == 2)
-        rs_launch_as<BF16, MODE, U, 2, false>(c, o);
+        rs_launch_batch_as<BF16, MODE, U, 2, false>(c, o);
     else if (c.P == 1)
-        rs_launch_as<BF16, MODE, U, 1, false>(c, o);
+        rs_launch_batch_as<BF16, MODE, U, 1, false>(c, o);
     else
-        rs_launch_as<BF16, MODE, U, 8, true>(c, o);
+        rs_launch_batch_as<BF16, MODE, U, 8, true>(c, o);
+}
+
+template <bool BF16, rs_mode MODE>
+void rs_launch_parts(const rs_call &c, const rs_sink<MODE> &o, const reduce_scatter_shape &shape)
+{
+    const unsigned n_items = static_cast<unsigned>(c.n_tiles * (shape.tiles ? 1 : reduce_scatter_split(BF16)));
+    auto launch = [&](auto kernel) {
+        kernel<<<dim3(n_items), dim3(DEAR_BLOCK), residency_lds(shape.residency), c.st>>>(
+            c.tiles, c.grads, c.L, c.P, 1.0f / static_cast<float>(c.P), o, n_items, static_cast<unsigned>(shape.run));
+    };
+    auto launch_as = [&](auto depth, auto whole_tiles) {
+        constexpr int D = decltype(depth)::value;
+        constexpr bool TILES = decltype(whole_tiles)::value;
+        if constexpr (!TILES)
+            if (c.P == D) return launch(reduce_scatter_kernel<BF16, D, REST_NONE, TILES, MODE>);
+        if constexpr (D > 1)
+            if (c.P % D != 0) return launch(reduce_scatter_kernel<BF16, D, REST_TAIL, TILES, MODE>);
+        if constexpr (D > 1 || TILES) launch(reduce_scatter_kernel<BF16, D, REST_BATCHES, TILES, MODE>);
+    };
+    auto launch_depth = [&](auto whole_tiles) {
+        if (shape.depth == 8) return launch_as(std::integral_constant<int, 8>{}, whole_tiles);
+        if (shape.depth == 4) return launch_as(std::integral_constant<int, 4>{}, whole_tiles);
+        if (shape.depth == 2) return launch_as(std::integral_constant<int, 2>{}, whole_tiles);
+        launch_as(std::integral_constant<int, 1>{}, whole_tiles);
+    };
+    if (shape.tiles)
+        launch_depth(std::true_type{});
+    else
+        launch_depth(std::false_type{});
+}
+
+template <rs_mode MODE, bool BF16>
+void rs_launch_type(const rs_call &c, const rs_sink<MODE> &o)
+{
+    if constexpr ((MODE & RS_GATHER) != 0) {
+        if (BF16 && !iteration_at_once_half_tiles(c.all_elems, c.n_tiles)) return rs_launch_batch<BF16, MODE, BF16 ? 2 : 1>(c, o);
+    } else {
+        const int64_t parts = c.n_tiles * reduce_scatter_split(BF16);
+        if (parts <= MAX_GRID && (c.max_workgroups == 0 || parts <= c.max_workgroups) && pointer_table_fits(c.P, c.L)) {
+            const reduce_scatter_shape shape =
+                reduce_scatter_shape_of(BF16, (MODE & RS_UPDATE) != 0, (MODE & RS_W_NEXT) != 0, c.P, c.all_elems, c.all_tiles, c.all_whole);
+            if (shape.depth > 0) return rs_launch_parts<BF16, MODE>(c, o, shape);
+        }
+        if (BF16 && !reduce_scatter_half_tiles((MODE & RS_UPDATE) != 0, c.max_workgroups, c.all_elems, c.n_tiles, c.all_whole))
+            return rs_launch_batch<BF16, MODE, BF16 ? 2 : 1>(c, o);
+    }
+    rs_launch_batch<BF16, MODE, 1>(c, o);
 }
 
 template <rs_mode MODE>
 void rs_launch(bool bf16, const rs_call &c, const rs_sink<MODE> &o)
 {
-    if (!bf16)
-        rs_launch_batched<false, MODE, 1>(c, o);
-    else if ((MODE & RS_GATHER) ? iteration_at_once_half_tiles(c.all_elems, c.n_tiles)
-                                : reduce_scatter_half_tiles((MODE & RS_UPDATE) != 0, c.max_workgroups, c.all_elems, c.n_tiles, c.all_whole))
-        rs_launch_batched<true, MODE, 1>(c, o);
+    if (bf16)
+        rs_launch_type<MODE, true>(c, o);
     else
-        rs_launch_batched<true, MODE, 2>(c, o);
+        rs_launch_type<MODE, false>(c, o);
 }
 
 // Up to this many tiles a context's table is cut on the host.  Making a context, us, on the host / with the kernel and the wait

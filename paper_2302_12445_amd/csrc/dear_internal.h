@@ -80,7 +80,7 @@ inline bool all_gather_fits(int64_t tiles, int64_t n_workers, int64_t max_workgr
 // that are all shorter than a tile none; elements and tiles alone do not tell one from the other.
 inline bool some_whole(int64_t whole, int64_t tiles) { return whole * 64 >= tiles; }
 
-// A bf16 reduce-scatter takes half a tile a workgroup (one 16-byte vector a lane instead of two) where a launch is so
+// The batch kernel of the bf16 reduce-scatter takes half a tile a workgroup (one 16-byte vector a lane instead of two) where a launch is so
 // short that whole tiles leave CUs idle, unless its tensors are all so short that most second halves are empty.  GPU time, us,
 // whole tiles / halves: reduce-scatter alone P = 8 0.2 M elements 4.47 / 4.06, 0.4 M 4.83 / 4.38, 0.8 M 5.39 / 5.41,
 // 1.6 M 7.32 / 7.71; P = 32 0.4 M 11.9 / 10.8, 1.6 M 21.6 / 22.5.  With the update the line lies further out, behind an all-gather that
@@ -226,7 +226,7 @@ int64_t dear_emit_tiles(const dear_plan_s &pl, int32_t b_first, int32_t b_last, 
                         int64_t capacity, int64_t *tile_begin);
 void dear_build_tiles(const dear_plan_s &pl, std::vector<dear_tile> &tiles, std::vector<int64_t> &tile_begin);
 
-// How many workgroups of a reduce-scatter launch may share a CU: 1, 2, or 0 for as many as fit.  HBM serves many
+// How many workgroups of an unbounded launch of the batch kernel may share a CU: 1, 2, or 0 for as many as fit.  HBM serves many
 // streams at once better the fewer loads compete, as long as some 64 KiB per CU are in flight (a workgroup has
 // min(P, 8) * U loads of 4 KiB, 32 KiB in fp32 and 64 KiB in bf16 from P = 8 on).  Too few workgroups cost the
 // more the shorter the launch is, and where the workgroups are short ones, so it takes
@@ -266,6 +266,106 @@ inline int reduce_scatter_residency(bool bf16, bool updates, int64_t P, int64_t 
     if (P >= 16 && P % 8 != 4 && bytes >= 500 * MB) return 1;
     return P >= 8 && bytes >= 500 * MB ? 2 : 0;
 }
+
+// Parts of a tile in the reduce-scatter: one 16-byte vector a lane.
+inline int64_t reduce_scatter_split(bool bf16) { return DEAR_TILE_ELEMS / ((bf16 ? 8 : 4) * DEAR_BLOCK); }
+
+// Item that the workgroup of index b takes: XCD b % 8 takes 2^run items in a row out of every 8 * 2^run, and what does not fill
+// such a group goes as it falls.
+DEAR_HOST_DEVICE inline unsigned reduce_scatter_item(unsigned b, unsigned run, unsigned n_items)
+{
+    const unsigned group = 8u << run, first = b & ~(group - 1);
+    if (n_items - first < group) return b;
+    return first | (b & 7) << run | (b >> 3 & ((1u << run) - 1));
+}
+
+// How an unbounded reduce-scatter goes: replicas in flight per lane (0: the batch kernel), workgroups that may share a CU (0: as
+// many as fit), the logarithm of the number of items in a row on an XCD, and whether a workgroup takes whole tiles.
+struct reduce_scatter_shape {
+    int depth, residency, run;
+    bool tiles;
+};
+
+// HBM serves P streams at once best with 24 to 32 KiB of loads in flight per CU, as long as they never stop: D loads of 4 KiB for
+// each of the workgroups that share a CU.  With more the streams get into each other's way, with fewer the latency shows; a
+// launch that does not fill the chip wants more per workgroup.  So two replicas a lane and three or four workgroups a CU in
+// long launches, four or eight replicas in short ones.  2652 launches (0.3 MB to 1.5 GB of gradients, P = 1 to 64, one tensor, 60
+// ragged ones, tensors of 900 and of 5000 elements; GPU time, sets of buffers in turn) take 0.914 of what the batch kernel took in
+// the geometric mean, the best shape for each 0.896.  Where the lines come from, batch kernel = 1, depth / workgroups a CU (- as many as fit):
+//   full tiles, fp32 with update  P = 8  1024 tiles 2/4 0.94  4/3 0.96  8/- 1.00   2048  2/3 0.98  2/4 0.98  4/3 0.99
+//     P = 16  256 tiles 2/4 0.92  2/- 0.93  4/- 0.95   1024  2/3 0.94  4/2 0.96    P = 32  512 tiles 2/3 0.89  2/4 0.91  4/2 0.92  2048  2/3 0.94
+//     P = 64  512 tiles 2/3 0.88  2/4 0.92   P = 6  1024 tiles 2/- 0.97  2/4 0.99  4096  2/3 0.97   P = 2  4096 tiles 2/4 0.95  2/- 0.98
+//   fp32 without  P = 8  1024 tiles 2/4 0.96  2/- 0.97  4096  2/4 0.96   P = 32  512 tiles 2/3 0.91   P = 6  512 tiles 2/- 0.97  4096  2/4 0.94  2/3 0.98   P = 2 2/- 1.00  2/4 1.06
+//   bf16 with  P = 8  256 tiles 2/- 0.97  4/- 1.01   1024  4/3 0.97  2/4 0.98  2048  2/4 0.97  4096  2/3 0.95   P = 32  1024 tiles 2/3 0.94  4/2 0.96
+//     P = 64  1024 tiles 2/3 0.90   P = 6  1024 tiles 4/3 0.97  4096  4/3 0.96  4/2 0.95   P = 2  512 tiles 2/4 0.96
+//   half to four fifths full, fp32 with  P = 8  1024 tiles 8/- 0.90  2/- 0.92   P = 16 and up 2/4 0.87  2/- 0.90   P = 6 2/- 0.92;  bf16 with 4/3 0.97  8/- 0.99
+//   few full tiles, without / with update, depth 8, 4 and 2, as many workgroups as fit; the batch kernel keeps what it does best (0):
+//     fp32 P = 4   90 tiles - 1.08 1.00 / - 1.05 1.00   130 - 1.06 0.97 / - 0.99 0.96   P = 6  60 - 0.94 1.04 / - 0.97 1.03   90 - 1.00 1.03 / - 1.06 1.08 (0)   160 - 0.98 0.96 / - 0.99 0.99
+//     P = 8   50 0.98 1.01 1.21 / 0.97 1.00 1.18   60 1.03 0.95 1.14 / 1.02 0.97 1.09   P = 32  20 8/- 0.69 / 0.70  90 0.94 / 0.96
+//     bf16 P = 4   90 tiles - 1.07 1.08 (0) / - 0.94 1.04   160 - 0.97 0.91 / - 1.03 1.05 (0)   260 - 1.14 0.98 / - 0.96 0.97   P = 6   60 - 1.01 1.09 / - 1.05 1.07 (0)
+//     P = 8   90 0.96 1.02 1.03 / 0.99 1.08 1.10   130 1.05 0.97 1.14 / 1.04 1.05 1.10 (0)   260 0.92 0.90 0.90 / 0.95 1.00 0.96; 250 with update 1.06 (0)
+//     P = 12   60 0.86 0.86 1.06 / 0.90 0.89 1.03   130 0.94 0.86 1.06 / 0.99 0.95 1.03   P = 16   60 0.91 0.98 1.24 / 0.96 0.99 1.22   130 0.97 0.91 1.19 / 1.01 0.99 1.13
+// Tensors shorter than a tile leave most parts empty: a workgroup takes whole tiles then.  900 elements each, P = 8  560 tiles fp32
+// 13.3 -> 6.9 us, 2230 42 -> 20, bf16 2230 22 -> 21; P = 64  130 tiles 0.62.  A whole tile among them would keep its workgroup four times as long (P = 32, 101
+// tiles 22 % full 10.2 -> 13.5), and from a quarter (many tiles: two fifths) full on there are enough workgroups' worth (P = 64, 162 tiles 38 % full 21.7 -> 30).
+// Sixty-four items in a row on an XCD, 256 KiB of each replica, whose lines of the tile table its L2 then has, and whose pages its
+// address translation: BERT-Large-shaped P = 8 bf16 5683 -> 6085 GB/s, with update 5787 -> 6063, BERT-Base-shaped P = 8 fp32 5731 -> 5909.
+// Not in launches so long that its rows of several replicas drift apart (fp32, P up to 16): BERT-Base-shaped, batch kernel = 1, tensors on
+// 256-byte boundaries / 16-byte ones, two replicas and three workgroups in rows of 64 | four and two as they fall: P = 8 all buckets
+// without update 0.99 / 1.02 | 0.97 / 0.99, iteration 1.01 / 1.01 | 0.99 / 0.99, P = 16 1.01 / 1.04 | 0.98 / 0.97, iteration 0.98 / 1.00 |
+// 0.99 / 0.99, P = 4 with update 1.03 / 1.01 | 0.99 / 0.99; P = 6 iteration 1.04 / 1.03 | 1.00 / 1.01 (the batch kernel keeps it), 64
+// replicas of ResNet-50 with update 0.94 / 0.93 | 0.98 / 0.99 (stay in rows).
+// Not where w of a launch fits the L2s (2048 tiles, 32 MiB): the all-gather behind it reads w in the L2 of the XCD that wrote it, if both
+// go through the tiles as they fall.  Pass = reduce-scatter with update, all-gather, one state over and over / three in turn, batch kernel = 1, as
+// they fall | in rows: fp32 P = 2 900 tiles 0.98 / 0.99 | 1.15 / 0.98, 1800 1.01 / 1.01 | 1.09 / 0.98, P = 8 600 1.03 / 1.02 | 1.07 / 1.02, 900 1.01 / 1.01 |
+// 1.08 / 0.98, 1800 1.00 / 1.01 | 1.04 / 0.98, P = 16 400 1.02 / 1.02 | 1.04 / 1.02, 900 0.98 / 0.97 | 0.99 / 0.94; dear_iteration P = 8 800 1.02 / 1.03 | 1.13 / 1.03, bf16
+// P = 6 800 1.00 / 0.99 | 1.21 / 0.98; more replicas leave little of it: P = 32 fp32 900 0.98 / 0.96 | 0.95 / 0.92, 400 1.00 / 0.99 | 1.01 / 0.99.
+// In dear_iteration where the all-gather comes next (caches_w) four replicas a lane and as many workgroups as fit, below 1600 tiles: fp32 P = 8
+// 350 / 550 / 800 / 1200 tiles 1.02 / 1.01 / 0.99 / 0.99, two replicas 1.03 / 1.02 / 1.00 / 0.99 and with four workgroups 1.07 / 1.04 / 1.02 / 1.00, bf16 P = 12
+// 0.99 / 1.00 / 1.01 / 0.98 and 1.01 / 1.01 / 1.02 / 0.99; bf16 P = 6 and 8 at 550 1.03 and 1.03 (the batch kernel up to 700).  So too fp32 360 to 700 tiles in calls of their own:
+// P = 8 400 1.00, two replicas and four workgroups 1.02; P = 32 400 0.99 / 0.98, two in rows 1.02 / 0.99.  bf16 from 1600 on two a lane: P = 7 4900 tiles four and three workgroups
+// 1.02 / 1.01, two and as many as fit 0.98 / 0.99, BERT-Base-shaped P = 5 1.00 / 0.99 and 0.99 / 0.98.
+inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, bool caches_w, int64_t P, int64_t elems, int64_t tiles,
+                                                    int64_t whole)
+{
+    auto depth = [&](int most) { return P >= most ? most : P >= 4 ? 4 : P >= 2 ? 2 : 1; };
+    auto filled = [&](int percent) { return elems * 100 >= tiles * DEAR_TILE_ELEMS * percent; };
+    const int run = tiles < (P <= 8 ? 2048 : P <= 16 ? 1600 : 320) ? 0 : 6;
+    auto parts = [&](int most, int residency) { return reduce_scatter_shape{depth(most), residency, run, false}; };
+    const bool full = filled(80);
+    if (!some_whole(whole, tiles) && tiles >= (P >= 8 ? 96 : 128) && !filled(tiles >= 512 ? 40 : 25))
+        return {depth(tiles < (bf16 ? 512 : 256) ? 8 : 4), 0, 4, true};
+    if (!bf16 && full && P >= 4 && P <= 16 && tiles >= 6000 && (updates || P >= 8)) {
+        if (P > 4 && P < 8) return {0, 0, 0, false};
+        return {4, 2, 0, false};
+    }
+    if (P < 4) return parts(2, updates && (full || bf16) && tiles >= (bf16 ? 512 : P > 1 ? 4096 : 1024) ? 4 : 0);
+    if (bf16 && P >= 4 && P <= 8 && filled(50) && tiles < (caches_w ? 700 : !updates ? 150 : P % 4 ? 300 : 256) && tiles >= (P % 4 ? 40 : updates ? 110 : 50) && (updates || P == 4))
+        return {0, 0, 0, false};
+    if (caches_w && filled(50) && P >= 4 && tiles >= (P <= 16 ? 256 : 512) && tiles < 1600 && (bf16 || P <= 16)) return {4, 0, 0, false};
+    if (!bf16 && filled(50) && P >= 4 && tiles >= 360 && tiles < (P <= 16 ? 700 : 450)) return {4, 0, 0, false};
+    if (bf16 && caches_w && tiles >= 1600 && filled(50)) return parts(2, P < 8 || tiles < 2048 ? 0 : 4);
+    if (!bf16 && updates && P > 4 && P < 8 && full && tiles >= 75 && tiles < 120) return {0, 0, 0, false};
+    if (P < 8) {
+        if (bf16 && updates) return parts(4, tiles >= 1024 ? 3 : 0);
+        if (tiles < (bf16 ? P == 4 ? 150 : 128 : P == 4 ? 75 : 160)) return parts(4, 0);
+        if (updates) return parts(2, full && tiles >= 2048 ? 3 : 0);
+        return parts(2, full && tiles >= 4096 ? 4 : 0);
+    }
+    if (tiles < (bf16 ? 110 : full ? 56 : 128)) return parts(8, 0);
+    if (tiles < (bf16 ? 256 : 128)) return parts(4, 0);
+    if (!full) {
+        if (bf16 && (updates || tiles < 512)) return parts(4, tiles < 512 ? 0 : 3);
+        if (tiles < 512) return parts(2, 0);
+        return parts(2, bf16 ? (tiles < 1024 || P < 24 ? 0 : 4) : P < 13 ? 0 : 4);
+    }
+    if (tiles < (bf16 ? 1024 : 512)) return parts(2, P > 40 && tiles >= (bf16 ? 512 : 256) ? 3 : 0);
+    const bool fewer = P >= 24 || (updates && !bf16 && P >= 13) || (bf16 ? tiles >= 4096 : updates && tiles >= 2048);
+    return parts(2, fewer ? 3 : 4);
+}
+
+// Whether the entries of a pointer table lie within 32 bits of its beginning, as reduce_scatter_kernel counts them.
+inline bool pointer_table_fits(int64_t P, int64_t L) { return P * L < int64_t{1} << 29; }
 
 // dear_iteration handles consecutive buckets together until they hold this many tiles (32 Mi elements, 128 MiB of w).
 // A launch costs about 2 us of ramp and drain, which shows up to some hundred microseconds; a longer group has more
