@@ -42,6 +42,7 @@ struct dear_ctx_impl {
     int32_t max_workgroups = 0;  // 0: one workgroup per work item
     int32_t wave_priority = 0;   // wave priority (0..3) of bounded-grid kernels
     int64_t row_len = 0;
+    bool replicas_alike = true;  // almost all parts of an all-gather begin and end on 128-byte lines, alike in all replicas
     std::vector<int64_t> bucket_len, bucket_shard_len, bucket_shard_base;
     std::vector<int64_t> tile_begin;  // [B+1] range of bucket b's tiles in the tile table
     std::vector<int64_t> whole_begin;  // [B+1] how many of the tiles before bucket b are whole
@@ -777,7 +778,8 @@ __host__ __device__ __forceinline__ int line_shift(uintptr_t p) { return static_
 // fp32 P = 4 13.7 / 11.5, P = 8 18.3 / 16.1, P = 16 29.6 / 27.6; 8 M fp32 P = 8 108.6 / 103.1, P = 16 195 / 187.  bf16, run 0 / 1:
 // P = 4 1 M 12.1 / 10.7, 2 M 19.1 / 17.2, P = 8 1 M 16.1 / 14.7, 2 M 26.4 / 24.5, 3 M 36.0 / 34.6, P = 16 2 M 40.8 / 39.0;
 // beyond, the values have left L2, and writes in this order cost: P = 8 10 M 100.9 / 101.6, P = 16 6 M 109 / 111, 20 M 355 / 368.
-template <unsigned RUN>
+// EIGHTHS: in long launches every XCD takes an eighth of the chunk instead (all_gather_in_eighths).
+template <unsigned RUN, bool EIGHTHS>
 __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_kernel(
     const dear_tile *__restrict__ tiles, float *const *__restrict__ param_tab, int L, int p_first,
     unsigned n_p, const float *__restrict__ shard_param, unsigned n_parts, unsigned inv_n_p, unsigned len,
@@ -793,7 +795,8 @@ __global__ __launch_bounds__(DEAR_BLOCK) void all_gather_kernel(
         chunk = whole;
         q = divide(blockIdx.x - whole * CHUNK * n_p, len, inv_len, r);
     }
-    const unsigned id = chunk * CHUNK + all_gather_part(r, RUN);
+    const unsigned id =
+        chunk * CHUNK + (EIGHTHS ? all_gather_part_of_eighth(r, chunk < whole ? CHUNK : len) : all_gather_part(r, RUN));
     const dear_tile t = tiles[id / AG_SPLIT];
     const int part = id % AG_SPLIT;
     if (t.layer < 0 || id >= n_parts) return;  // behind the last part: a tile beyond the launch's, or the table's room
@@ -1237,9 +1240,11 @@ constexpr int64_t HOST_TILES = 3072;
 
 constexpr int64_t SHIFT_TILES = 8;
 
-// Writes into every run's bucket field what the all-gather wants to know about its tiles.
-void mark_runs(const dear_plan_s &plan, float *const *param_ptrs, dear_run *runs, int64_t n_runs)
+// Writes into every run's bucket field what the all-gather wants to know about its tiles.  True: nearly all elements
+// (seven eighths) are in runs whose cuts are lines in every replica, at the same elements (all_gather_in_eighths).
+bool mark_runs(const dear_plan_s &plan, float *const *param_ptrs, dear_run *runs, int64_t n_runs)
 {
+    int64_t elems = 0, alike = 0;
     for (dear_run *r = runs; r < runs + n_runs; ++r) {
         int flags = 0;
         if (r->layer >= 0) {
@@ -1253,10 +1258,14 @@ void mark_runs(const dear_plan_s &plan, float *const *param_ptrs, dear_run *runs
             // moved / not (not resolved better than 10 % around 6 tiles): 4 tiles 143 / 117, 5 121 / 107, 6 114 / 112
             // and 126, 8 118 / 124, 10 100 / 123, 21 97 / 117; P = 32: 8 tiles 408 / 501.
             // A first tile of less than a line could not give a shift away.
-            if (tiles_of_run(*r) < SHIFT_TILES || tile_of_run(*r, 0).count < 32) flags = 0;
+            const bool moved = tiles_of_run(*r) >= SHIFT_TILES && tile_of_run(*r, 0).count >= 32;
+            elems += r->count;
+            if (flags == 0 || (moved && flags != TILE_OWN_SHIFT)) alike += r->count;
+            if (!moved) flags = 0;
         }
         r->bucket = flags;
     }
+    return alike >= elems - elems / 8;
 }
 
 }  // namespace
@@ -1305,7 +1314,7 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
     dear_emit_runs(*plan, 0, plan->B, runs.data(), n_runs, &n_tiles, nullptr);
     for (const dear_run &r : runs) c->whole_begin[r.bucket + 1] += whole_tiles_of_run(r);
     std::partial_sum(c->whole_begin.begin(), c->whole_begin.end(), c->whole_begin.begin());
-    mark_runs(*plan, param_ptrs, runs.data(), n_runs);
+    c->replicas_alike = mark_runs(*plan, param_ptrs, runs.data(), n_runs);
     const bool on_host = n_tiles <= HOST_TILES;
     if (on_host) {
         dear_tile *tiles = reinterpret_cast<dear_tile *>(image.data());
@@ -1444,9 +1453,12 @@ int launch_all_gather(const dear_ctx_impl *c, tile_range t, const float *shard_p
         constexpr unsigned chunk = DEAR_AG_CHUNK_BYTES / (16 * DEAR_BLOCK);
         const unsigned n_parts = static_cast<unsigned>(count * AG_SPLIT), n_p = static_cast<unsigned>(n_workers);
         const unsigned whole = n_parts / chunk * chunk;
-        const unsigned run = all_gather_run(c->g, c->max_workgroups, t.all_elems, count, t.all_whole, n_workers, behind_update);
+        const bool eighths = c->replicas_alike && all_gather_in_eighths(t.all_elems * count / t.all_tiles, count, n_workers);
+        const unsigned run =
+            eighths ? 0 : all_gather_run(c->g, c->max_workgroups, t.all_elems, count, t.all_whole, n_workers, behind_update);
         const all_gather_order o = all_gather_numbering(run, c->max_workgroups, whole, n_parts, n_workers);
-        const auto kernel = o.run ? all_gather_kernel<1> : all_gather_kernel<0>;
+        const auto kernel = eighths && o.len % 8 == 0 ? all_gather_kernel<0, true>
+                            : o.run ? all_gather_kernel<1, false> : all_gather_kernel<0, false>;
         kernel<<<dim3((whole + o.len) * n_p), dim3(DEAR_BLOCK), 0, st>>>(
             tiles, c->d_param, c->L, first_worker, n_p, shard_param, n_parts, 0xffffffffu / n_p, o.len,
             0xffffffffu / (o.len ? o.len : 1));

@@ -1,0 +1,64 @@
+"""The all-gather in which each XCD takes an eighth of a chunk, on both sides of its lines, with last chunks of every length, in
+replicas that lie alike and in others, against the oracle (the same bits, and nothing around the tensors written)."""
+from __future__ import annotations
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_numbering_and_rule_on_the_host(tmp_path):
+    exe = str(tmp_path / "all_gather_eighths")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2302_12445_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "native", "all_gather_eighths.cpp"), "-o", exe], check=True)
+    assert "all_gather_eighths: ok" in subprocess.run([exe], check=True, capture_output=True, text=True).stdout
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,tiles", [(1, 2047), (2, 2048), (3, 2051), (5, 4097), (8, 2050), (12, 1598), (12, 1603), (24, 958), (24, 961), (33, 1025), (64, 963)])
+def test_around_the_lines_of_the_rule(P, tiles):
+    from test_gpu_parity import Pair, say, small_workload
+    import workloads as W
+    say("case: all-gather in eighths, P=%d, %d tiles" % (P, tiles))
+    sizes = [7, 9_000, 33, (tiles - P) * 4096 - 9_040 - 4099, 3, 4095]
+    pair = Pair(small_workload(sizes, P, W.NO_LIMIT, "f32" if P % 2 else "bf16"))
+    for route in ("calls", "iteration"):
+        pair.run(iterations=1, route=route, fused=route == "iteration")
+    pair.close()
+
+
+# replicas on lines; alike, off the lines; each elsewhere (parts as they fall)
+@pytest.mark.gpu
+@pytest.mark.parametrize("starts", [(0, 0, 0), (4, 4, 4), (28, 28, 28), (0, 12, 20)])
+@pytest.mark.parametrize("workers", [(0, 3), (1, 2)])
+def test_replicas_alike_and_not(starts, workers):
+    import numpy as np
+    import oracle
+    import torch
+    import paper_2302_12445_amd as dear
+    import workloads as W
+    from test_gpu_parity import DEV, _bits, say
+    say("case: all-gather in eighths, tensors at %s of a line, workers %s" % (starts, workers))
+    sizes, P = [9_000_003, 70_001], 3
+    op, plan = oracle.plan(sizes, P, W.NO_LIMIT, 4), dear.dear_plan(sizes, P, W.NO_LIMIT, 4)
+    assert 2048 <= len(dear.dear_plan_tiles(plan)[0]) < 5000
+    bufs = [[torch.full((n + 64,), 7.0, device=DEV) for n in sizes] for _ in range(P)]
+    ptrs = [b.data_ptr() + 4 * starts[p] for p in range(P) for b in bufs[p]]
+    ctx = dear.dear_ctx_create(plan, dear.DEAR_F32, ptrs, ptrs)
+    shards = torch.randn(P, op.total_shard_len, generator=torch.Generator().manual_seed(5))
+    dev = shards.to(DEV)
+    dear.dear_all_gather_workers(ctx, -1, dev.data_ptr(), workers[0], workers[1])
+    torch.cuda.synchronize()
+    params = [[np.full(n, 7.0, np.float32) for n in sizes] for _ in range(P)]
+    oracle.all_gather(op, -1, shards.numpy(), params, workers=range(workers[0], workers[0] + workers[1]))
+    for p in range(P):
+        for got, want in zip(bufs[p], params[p]):
+            whole = np.full(got.numel(), 7.0, np.float32)
+            whole[starts[p]:starts[p] + want.size] = want
+            assert np.array_equal(_bits(got.cpu().numpy()), _bits(whole)), p
+    ctx.destroy()
