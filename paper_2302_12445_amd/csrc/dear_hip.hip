@@ -578,7 +578,7 @@ __global__ __launch_bounds__(DEAR_BLOCK) void reduce_scatter_kernel(
     float inv_P, const rs_sink<MODE> o, unsigned n_items, unsigned run)
 {
     constexpr int SPLIT = DEAR_TILE_ELEMS / ((BF16 ? 8 : 4) * DEAR_BLOCK), STEP = TILES ? 1 : SPLIT;
-    const unsigned item = reduce_scatter_item(blockIdx.x, run, n_items);
+    const unsigned item = item_in_rows(blockIdx.x, run, n_items);
     const dear_tile t = tiles[item / STEP];
     const int first = item % STEP;
     if (__builtin_expect(t.layer >= 0 && t.count == DEAR_TILE_ELEMS, 1)) {  // first, where the code's lines come in order
@@ -621,15 +621,18 @@ __global__ __launch_bounds__(DEAR_BLOCK) void reduce_scatter_batch_kernel(
 }
 
 // SGD with momentum on contiguous shard slots (paper Eq. 1-2): v = mu*v + g; w = w - lr*v.
-// blockIdx.y selects the row (worker); each row segment is `vecs` 16-byte vectors long.
+// An item is a block of a row (worker); each row segment is `vecs` 16-byte vectors long.  Bound by HBM, three streams read and
+// two of them written; long launches over all buckets give each XCD items in a row (shard_update_run): 336 M elements 1117 -> 1068 us
+// (6.0 -> 6.3 TB/s of a copy's 6.7), 110 M 377 -> 350, 32 M 106.6 -> 100.2.
 constexpr int UPD_U = DEAR_UPD_U;      // vectors per lane, one workgroup per item
 constexpr int UPD_U_BOUNDED = 4;       // bounded grid: more loads in flight per lane
 template <int U, bool BOUNDED>
 __global__ __launch_bounds__(DEAR_BLOCK) void shard_update_kernel(
     const float *__restrict__ g, float *__restrict__ w, float *__restrict__ v, int64_t row_stride,
-    int64_t base, int64_t vecs, float lr, float mu, unsigned blocks_per_row, unsigned n_items, int prio)
+    int64_t base, int64_t vecs, float lr, float mu, unsigned blocks_per_row, unsigned n_items, int prio, unsigned run)
 {
-    for_each_item<BOUNDED>(n_items, prio, [&](unsigned item) {
+    for_each_item<BOUNDED>(n_items, prio, [&](unsigned index) {
+        const unsigned item = BOUNDED ? index : item_in_rows(index, run, n_items);
         const unsigned row = item / blocks_per_row, bx = item - row * blocks_per_row;
         const int64_t off = (int64_t)row * row_stride + base;
         const f4 *__restrict__ g4 = reinterpret_cast<const f4 *>(g + off);
@@ -1428,11 +1431,11 @@ int launch_update(const dear_ctx_impl *c, bucket_range r, const float *shard_gra
     if (bounded)
         shard_update_kernel<UPD_U_BOUNDED, true><<<dim3(c->max_workgroups), dim3(DEAR_BLOCK), 0, st>>>(
             shard_grad, shard_param, shard_mom, c->row_len, base, vecs, lr, momentum,
-            static_cast<unsigned>(blocks), static_cast<unsigned>(n_items), c->wave_priority);
+            static_cast<unsigned>(blocks), static_cast<unsigned>(n_items), c->wave_priority, 0);
     else
         shard_update_kernel<UPD_U, false><<<dim3(static_cast<unsigned>(n_items)), dim3(DEAR_BLOCK), 0, st>>>(
             shard_grad, shard_param, shard_mom, c->row_len, base, vecs, lr, momentum,
-            static_cast<unsigned>(blocks), static_cast<unsigned>(n_items), 0);
+            static_cast<unsigned>(blocks), static_cast<unsigned>(n_items), 0, shard_update_run(rows, n_items));
     return launch_status();
 }
 

@@ -291,14 +291,23 @@ inline int reduce_scatter_residency(bool bf16, bool updates, int64_t P, int64_t 
 // Parts of a tile in the reduce-scatter: one 16-byte vector a lane.
 inline int64_t reduce_scatter_split(bool bf16) { return DEAR_TILE_ELEMS / ((bf16 ? 8 : 4) * DEAR_BLOCK); }
 
-// Item that the workgroup of index b takes: XCD b % 8 takes 2^run items in a row out of every 8 * 2^run, and what does not fill
+// Item that the workgroup of index b takes, in the reduce-scatter and the update: XCD b % 8 takes 2^run items in a row out of every 8 * 2^run, and what does not fill
 // such a group goes as it falls.
-DEAR_HOST_DEVICE inline unsigned reduce_scatter_item(unsigned b, unsigned run, unsigned n_items)
+DEAR_HOST_DEVICE inline unsigned item_in_rows(unsigned b, unsigned run, unsigned n_items)
 {
     const unsigned group = 8u << run, first = b & ~(group - 1);
     if (n_items - first < group) return b;
     return first | (b & 7) << run | (b >> 3 & ((1u << run) - 1));
 }
+
+// The update's logarithm of the number of items (blocks of 1024 elements) in a row on an XCD: 2 MiB of each stream.  As they fall =
+// 1, 64 / 256 / 512 / 1024 / 4096 in a row, sets of buffers in turn, the update alone: 336 M elements 1.03 / 0.95 / 0.96 / 0.97 / 0.97, 110 M 0.94 / 0.93 / 0.93 /
+// 0.96 / 0.99, 64 M 0.95 / 0.94 / 0.92 / 0.97 / 1.03, 32 M 0.94 / 0.95 / 0.94 / 1.01 / 1.00, 25 M 0.99 / 0.96 / 0.95 / 1.03 / 1.00.  Pass of the three phases, 512: bf16 P = 8
+// 336 M and 32 M 0.99, P = 16 110 M 0.99, P = 4 64 M 0.97, P = 64 25 M 1.00; one state over and over 0.99 / 1.00 / 0.99 / 0.98 / 1.00.  Shorter launches lie
+// within 2 % either way (12 M 1.00 with 512, 8 M 1.00 with 256, one state over and over 1.02; 3 M 1.01 and 1.02) and keep their order.
+// So do launches over some of the buckets, where every worker's row begins at a place of its own: 16 rows of BERT-Base-shaped buckets 6560 GB/s as they
+// fall, 6337 with 512, 8 rows of BERT-Large-shaped ones 6315 and 6247.
+inline unsigned shard_update_run(int64_t rows, int64_t n_items) { return rows > 1 || n_items < 12000 ? 0 : 9; }
 
 // How an unbounded reduce-scatter goes: replicas in flight per lane (0: the batch kernel), workgroups that may share a CU (0: as
 // many as fit), the logarithm of the number of items in a row on an XCD, and whether a workgroup takes whole tiles.

@@ -1,4 +1,4 @@
-// Host-only check (dear_internal.h) of the reduce-scatter's rows of items, each item to exactly one workgroup whatever their
+// Host-only check (dear_internal.h) of the reduce-scatter's and the update's rows of items, each item to exactly one workgroup whatever their
 // number, and of the rule for its shape: never more replicas in flight than there are, and only what there are kernels for.
 // Exits non-zero on the first mistake.
 #include <cstdint>
@@ -10,11 +10,11 @@
 
 int main()
 {
-    for (unsigned run : {0u, 4u, 6u})
-        for (unsigned n = 1; n < 2100; n += n < 1100 ? 1 : 37) {
+    for (unsigned run : {0u, 4u, 6u, 9u})
+        for (unsigned n = 1; n < (run < 9 ? 2100 : 12400); n += n < 1100 ? 1 : 37) {
             std::vector<int> seen(n, 0);
             for (unsigned b = 0; b < n; ++b) {
-                const unsigned item = reduce_scatter_item(b, run, n);
+                const unsigned item = item_in_rows(b, run, n);
                 if (item >= n || seen[item]++) {
                     std::fprintf(stderr, "FAILED run=%u n=%u b=%u item=%u\n", run, n, b, item);
                     return 1;
@@ -24,7 +24,7 @@ int main()
     // one of the largest grids: the rows end where they do in small ones
     const unsigned most = static_cast<unsigned>(MAX_GRID), rest = most % (8u << 6);
     for (unsigned b = most - rest; b < most; ++b)
-        if (reduce_scatter_item(b, 6, most) != b) return 1;
+        if (item_in_rows(b, 6, most) != b) return 1;
     for (bool bf16 : {false, true})
         for (bool updates : {false, true})
             for (bool caches_w : {false, true})
@@ -43,6 +43,7 @@ int main()
                                 }
                             }
     if (!pointer_table_fits(1, (int64_t{1} << 29) - 1) || pointer_table_fits(2, int64_t{1} << 28)) return 1;
+    if (shard_update_run(1, 11999) != 0 || shard_update_run(1, 12000) != 9 || shard_update_run(1, MAX_GRID) != 9 || shard_update_run(2, 12000) != 0) return 1;
     std::printf("reduce_scatter_shapes: ok\n");
     return 0;
 }

@@ -1,5 +1,5 @@
 """The reduce-scatter in each depth, with and without a rest of replicas, in parts and in whole tiles, on both sides of the lines between
-them, against the oracle (the same bits)."""
+them, and the update on both sides of its line, against the oracle (the same bits)."""
 from __future__ import annotations
 
 import os
@@ -58,4 +58,17 @@ def test_every_shape_gives_the_oracles_bits(dtype, P, sizes):
         torch.cuda.synchronize()
         pair.compare_buffer("shard_grad, static call", em.shard_grad, pair.sg)
     assert np.isfinite(pair.sg).any()
+    pair.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,sizes,buckets", [(2, [11_990 * 1024], 1), (2, [12_300 * 1024 + 5], 1), (3, [12_100 * 1024 + 77] * 2, 2), (5, [11_000 * 1024, 12_289 * 1024], 2)])
+def test_update_in_rows_gives_the_oracles_bits(P, sizes, buckets):
+    import workloads as W
+    from test_gpu_parity import Pair, say, small_workload
+    say("case: update in rows, P=%d, %d buckets, %d elements" % (P, buckets, sum(sizes)))
+    pair = Pair(small_workload(sizes, P, W.NO_LIMIT if buckets == 1 else max(sizes) * 4, "f32"))
+    assert pair.em.plan.n_buckets == buckets
+    for per_bucket in (True, False):
+        pair.run(iterations=1, route="calls", per_bucket=per_bucket)
     pair.close()
