@@ -47,6 +47,14 @@ inline int64_t whole_tiles_of_run(const dear_run &r)
     return r.layer < 0 || n < 0 ? 0 : n;
 }
 
+// Those of its tiles that begin or end inside a 16-byte vector of `vector` gradients.
+inline int64_t cut_tiles_of_run(const dear_run &r, int64_t vector)
+{
+    if (r.layer < 0) return 0;
+    const bool begins = r.src_begin % vector != 0, ends = (r.src_begin + r.count) % vector != 0;
+    return tiles_of_run(r) > 1 ? begins + ends : begins || ends;
+}
+
 DEAR_HOST_DEVICE inline dear_tile tile_of_run(const dear_run &r, int64_t k)
 {
     const int64_t cut = (r.src_begin / DEAR_TILE_ELEMS + k) * DEAR_TILE_ELEMS, end = r.src_begin + r.count;
@@ -316,82 +324,107 @@ struct reduce_scatter_shape {
     bool tiles;
 };
 
-// HBM serves P streams at once best with 24 to 32 KiB of loads in flight per CU, as long as they never stop: D loads of 4 KiB for
-// each of the workgroups that share a CU.  With more the streams get into each other's way, with fewer the latency shows; a
-// launch that does not fill the chip wants more per workgroup.  So two replicas a lane and three or four workgroups a CU in
-// long launches, four or eight replicas in short ones.  2652 launches (0.3 MB to 1.5 GB of gradients, P = 1 to 64, one tensor, 60
-// ragged ones, tensors of 900 and of 5000 elements; GPU time, sets of buffers in turn) take 0.914 of what the batch kernel took in
-// the geometric mean, the best shape for each 0.896.  Where the lines come from, batch kernel = 1, depth / workgroups a CU (- as many as fit):
-//   full tiles, fp32 with update  P = 8  1024 tiles 2/4 0.94  4/3 0.96  8/- 1.00   2048  2/3 0.98  2/4 0.98  4/3 0.99
-//     P = 16  256 tiles 2/4 0.92  2/- 0.93  4/- 0.95   1024  2/3 0.94  4/2 0.96    P = 32  512 tiles 2/3 0.89  2/4 0.91  4/2 0.92  2048  2/3 0.94
-//     P = 64  512 tiles 2/3 0.88  2/4 0.92   P = 6  1024 tiles 2/- 0.97  2/4 0.99  4096  2/3 0.97   P = 2  4096 tiles 2/4 0.95  2/- 0.98
-//   fp32 without  P = 8  1024 tiles 2/4 0.96  2/- 0.97  4096  2/4 0.96   P = 32  512 tiles 2/3 0.91   P = 6  512 tiles 2/- 0.97  4096  2/4 0.94  2/3 0.98   P = 2 2/- 1.00  2/4 1.06
-//   bf16 with  P = 8  256 tiles 2/- 0.97  4/- 1.01   1024  4/3 0.97  2/4 0.98  2048  2/4 0.97  4096  2/3 0.95   P = 32  1024 tiles 2/3 0.94  4/2 0.96
-//     P = 64  1024 tiles 2/3 0.90   P = 6  1024 tiles 4/3 0.97  4096  4/3 0.96  4/2 0.95   P = 2  512 tiles 2/4 0.96
-//   half to four fifths full, fp32 with  P = 8  1024 tiles 8/- 0.90  2/- 0.92   P = 16 and up 2/4 0.87  2/- 0.90   P = 6 2/- 0.92;  bf16 with 4/3 0.97  8/- 0.99
-//   few full tiles, without / with update, depth 8, 4 and 2, as many workgroups as fit; the batch kernel keeps what it does best (0):
-//     fp32 P = 4   90 tiles - 1.08 1.00 / - 1.05 1.00   130 - 1.06 0.97 / - 0.99 0.96   P = 6  60 - 0.94 1.04 / - 0.97 1.03   90 - 1.00 1.03 / - 1.06 1.08 (0)   160 - 0.98 0.96 / - 0.99 0.99
-//     P = 8   50 0.98 1.01 1.21 / 0.97 1.00 1.18   60 1.03 0.95 1.14 / 1.02 0.97 1.09   P = 32  20 8/- 0.69 / 0.70  90 0.94 / 0.96
-//     bf16 P = 4   90 tiles - 1.07 1.08 (0) / - 0.94 1.04   160 - 0.97 0.91 / - 1.03 1.05 (0)   260 - 1.14 0.98 / - 0.96 0.97   P = 6   60 - 1.01 1.09 / - 1.05 1.07 (0)
-//     P = 8   90 0.96 1.02 1.03 / 0.99 1.08 1.10   130 1.05 0.97 1.14 / 1.04 1.05 1.10 (0)   260 0.92 0.90 0.90 / 0.95 1.00 0.96; 250 with update 1.06 (0)
-//     P = 12   60 0.86 0.86 1.06 / 0.90 0.89 1.03   130 0.94 0.86 1.06 / 0.99 0.95 1.03   P = 16   60 0.91 0.98 1.24 / 0.96 0.99 1.22   130 0.97 0.91 1.19 / 1.01 0.99 1.13
+// Where the batch kernel is the faster one still, below 2048 tiles: reduce_scatter_kernel gains by loads that never drain, and by
+// taking the elements of vectors that a run cuts (`cut`: an eighth of the tiles begin or end inside one) along with the vectors, where the
+// batch kernel has a pass of its own for them.  With up to eight replicas all loads of a workgroup are in flight at once anyway, so
+// with nothing cut there is nothing to gain, and with the update w and v are loads that never stop beside them.  Seven
+// replicas are two rounds of loads instead of one.  A launch that fills the chip less than once, and not by far, likes fewer, longer
+// workgroups.  4256 launches (P = 1 to 64, 20 to 2000 tiles; one tensor, five, ragged lists, weights with short vectors between them; buffers
+// in turn, cold), batch kernel = 1, mean (worst) of what would go instead:
+//   nothing cut, with update, fp32  P = 3 1.02 (1.14)  5 1.02 (1.10)  6 1.01 (1.11)  7 1.03 (1.21)  8 1.02 (1.10), above 160 tiles 1.00
+//     bf16  P = 3 1.05 (1.18)  5, 6 and 7 1.02 (1.25)  8 1.01 (1.12), 1 and 2 0.97, but from 128 to 700 tiles 1.02 (1.07)
+//   without, fp32 P = 3 1.04 (1.12)  4 to 8 below 160 tiles 1.04 (1.24), above 0.98;  bf16 P = 2 1.01 (1.13)  3 to 8 1.07 (1.24) and 0.94
+//   P = 7 below 160 tiles, cut  fp32 1.02 (1.07)  bf16 1.04 (1.09)
+//   nothing cut, fp32 P >= 12 with update, 64 to 160 tiles 1.06 (1.38), P >= 24 without 1.08 (1.39), P = 9 to 16 without 0.94
+//   nothing cut, bf16 with update P = 12 and 16 below 700 tiles 1.02 (1.13), P >= 24 from 132 to 288 1.04 (1.16); without, P = 12 and 16
+//     below 130 1.00 (1.09), P >= 24 from 132 to 160 1.02 (1.14)
+//   cut: fp32 P <= 8 below 160 tiles 0.97, from 9 on 0.84; bf16 from 9 on 0.82, P = 4 without update below 160 1.09, P = 5 to 7 with it
+//     from 40 to 300 1.05, P = 4 and 8 from 110 to 300 1.01
+inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles, bool cut)
+{
+    if (tiles >= 2048) return false;
+    if (P == 7 && tiles < 160) return true;
+    if (bf16 && updates && P <= 2) return !cut && tiles >= 128 && tiles < 700;
+    if (cut || (bf16 && updates && P == 4)) {
+        if (!bf16 || P < 4 || P > 8) return false;
+        return updates ? tiles >= (P % 4 ? 40 : 110) && tiles < 300 : P == 4 && tiles < 160;
+    }
+    if (P <= 8) return updates || P <= (bf16 ? 2 : 3) || tiles < 160;
+    if (!bf16) return P >= (updates ? 12 : 20) && tiles >= 64 && tiles < 160;
+    if (P < 24) return updates ? tiles < 700 : P >= 12 && tiles < 130;
+    return tiles >= 132 && tiles < (updates ? 288 : 160);
+}
+
+// HBM serves P streams at once best with 32 to 40 KiB of loads in flight per CU, as long as they never stop: D loads of 4 KiB for
+// each of the workgroups that share a CU (fp32 at `residency` 4: five of them).  With more the streams get into each other's way,
+// with fewer the latency shows; a launch that does not fill the chip wants more per workgroup.  So two replicas a lane and three or
+// four workgroups a CU in long launches, four or eight replicas in short ones.  Depth / workgroups a CU (- as many as fit, r in rows), batch
+// kernel = 1, means over the four kinds of lists, by tiles (the launches of batch_kernel_stays, and 1266 longer ones):
+//   fp32 without update  P = 9  20-45 8/- 0.81  4/- 0.88   64-90 0.84  0.83   P = 16  46-63 8/- 0.84  4/- 0.94   64-90 0.95  0.91   P = 32  46-63 0.77
+//       0.93   64-90 0.93  0.91   P = 16  91-127 4/- 0.94  2/- 1.13   128-170 0.94  0.91   P = 32  91-127 0.94  1.21   128-170 0.97  0.96
+//     320-1100 4/- | 2/- | 2/4  P = 4 1.00 | 1.00 | 1.06   5 0.98 | 1.00 | 1.07   6 0.99 | 0.99 | 1.03   7 0.99 | 1.00 | 1.05   8 0.98 | 1.00 | 1.02
+//     395-480 the same  P = 16 0.99 | 1.05 | 0.98   24 0.99 | 1.04 | 0.96   64 1.00 | 1.05 | 0.94
+//     3000-5900 2/4r | 2/3r | 2/-r | 4/2  P = 4 0.99 | 1.03 | 0.98 | 1.13   6 0.95 | 0.97 | 0.98 | 1.06   8 0.94 | 0.96 | 0.98 | 0.99   12 0.94 | 0.97 | 1.01 | 0.98
+//     24000 and more, one tensor, ragged, BERT-Base-shaped, the same  P = 8 1.02 | 0.99 | - | 0.98   12 1.02 | 1.01 | - | 1.01   16 1.03 | 1.02 | - | 0.99
+//   fp32 with update  3000-13000 2/4r | 2/3r | 2/-r | 4/2  P = 4 0.96 | 0.96 | 0.98 | 1.00   6 0.96 | 0.95 | 1.00 | 1.01   8 0.98 | 0.96 | 1.02 | 1.00
+//       12 0.99 | 0.98 | 1.05 | 1.02   16 0.98 | 0.96 | 1.04 | 0.99;  24000 and more P = 8 1.03 | 0.99 | - | 1.00, dear_iteration 1.03 | 1.00 | - | 1.00
+//   bf16 without  P = 16  80-109 8/- 0.93  4/- 1.00   110-131 0.94  0.94   P = 24  110-131 0.86  0.93   132-160 0.97  0.92   P = 64  110-131 0.71  0.88
+//       132-160 0.91  0.92   P = 16  161-287 4/- 0.87  2/- 1.00   288-400 0.95  0.91   P = 64  161-287 0.77  1.03   288-400 0.88  0.86
+//     780-1700 4/- | 2/- | 2/4r | 2/3r  P = 8 0.98 | 1.00 | 0.99 | 1.04   12 0.96 | 0.98 | 0.96 | 1.01   24 0.99 | 1.00 | 0.95 | 0.99   64 1.00 | 1.01 | 0.94 | 0.96
+//     1900-7000 2/4r | 2/3r  P = 8 0.97 | 1.01   12 0.95 | 0.99   24 0.94 | 0.97
+//   bf16 with  780-1700, as without  P = 8 0.98 | 0.99 | 0.98 | 1.01   24 0.99 | 0.98 | 0.96 | 0.98   64 0.99 | 0.98 | 0.93 | 0.93;  1900-7000 2/4r | 2/3r  P = 8
+//       0.97 | 0.98   12 0.98 | 0.98   24 0.97 | 0.96;  1000-2050 4/- | 4/3  P = 5 0.97 | 1.00   6 0.98 | 0.98   7 0.98 | 1.01
 // Tensors shorter than a tile leave most parts empty: a workgroup takes whole tiles then.  900 elements each, P = 8  560 tiles fp32
-// 13.3 -> 6.9 us, 2230 42 -> 20, bf16 2230 22 -> 21; P = 64  130 tiles 0.62.  A whole tile among them would keep its workgroup four times as long (P = 32, 101
-// tiles 22 % full 10.2 -> 13.5), and from a quarter (many tiles: two fifths) full on there are enough workgroups' worth (P = 64, 162 tiles 38 % full 21.7 -> 30).
+// 13.3 -> 6.9 us, 2230 42 -> 20, bf16 2230 22 -> 21; P = 64  130 tiles 0.62.  A whole tile among them would keep its workgroup four
+// times as long (P = 32, 101 tiles 22 % full 10.2 -> 13.5), and from a quarter (many tiles: two fifths) full on there are enough
+// workgroups' worth (P = 64, 162 tiles 38 % full 21.7 -> 30).
 // Sixty-four items in a row on an XCD, 256 KiB of each replica, whose lines of the tile table its L2 then has, and whose pages its
 // address translation: BERT-Large-shaped P = 8 bf16 5683 -> 6085 GB/s, with update 5787 -> 6063, BERT-Base-shaped P = 8 fp32 5731 -> 5909.
-// Not in launches so long that its rows of several replicas drift apart (fp32, P up to 16): BERT-Base-shaped, batch kernel = 1, tensors on
-// 256-byte boundaries / 16-byte ones, two replicas and three workgroups in rows of 64 | four and two as they fall: P = 8 all buckets
-// without update 0.99 / 1.02 | 0.97 / 0.99, iteration 1.01 / 1.01 | 0.99 / 0.99, P = 16 1.01 / 1.04 | 0.98 / 0.97, iteration 0.98 / 1.00 |
-// 0.99 / 0.99, P = 4 with update 1.03 / 1.01 | 0.99 / 0.99; P = 6 iteration 1.04 / 1.03 | 1.00 / 1.01 (the batch kernel keeps it), 64
-// replicas of ResNet-50 with update 0.94 / 0.93 | 0.98 / 0.99 (stay in rows).
-// Not where w of a launch fits the L2s (2048 tiles, 32 MiB): the all-gather behind it reads w in the L2 of the XCD that wrote it, if both
-// go through the tiles as they fall.  Pass = reduce-scatter with update, all-gather, one state over and over / three in turn, batch kernel = 1, as
-// they fall | in rows: fp32 P = 2 900 tiles 0.98 / 0.99 | 1.15 / 0.98, 1800 1.01 / 1.01 | 1.09 / 0.98, P = 8 600 1.03 / 1.02 | 1.07 / 1.02, 900 1.01 / 1.01 |
-// 1.08 / 0.98, 1800 1.00 / 1.01 | 1.04 / 0.98, P = 16 400 1.02 / 1.02 | 1.04 / 1.02, 900 0.98 / 0.97 | 0.99 / 0.94; dear_iteration P = 8 800 1.02 / 1.03 | 1.13 / 1.03, bf16
-// P = 6 800 1.00 / 0.99 | 1.21 / 0.98; more replicas leave little of it: P = 32 fp32 900 0.98 / 0.96 | 0.95 / 0.92, 400 1.00 / 0.99 | 1.01 / 0.99.
-// In dear_iteration where the all-gather comes next (caches_w) four replicas a lane and as many workgroups as fit, below 1600 tiles: fp32 P = 8
-// 350 / 550 / 800 / 1200 tiles 1.02 / 1.01 / 0.99 / 0.99, two replicas 1.03 / 1.02 / 1.00 / 0.99 and with four workgroups 1.07 / 1.04 / 1.02 / 1.00, bf16 P = 12
-// 0.99 / 1.00 / 1.01 / 0.98 and 1.01 / 1.01 / 1.02 / 0.99; bf16 P = 6 and 8 at 550 1.03 and 1.03 (the batch kernel up to 700).  So too fp32 360 to 700 tiles in calls of their own:
-// P = 8 400 1.00, two replicas and four workgroups 1.02; P = 32 400 0.99 / 0.98, two in rows 1.02 / 0.99.  bf16 from 1600 on two a lane: P = 7 4900 tiles four and three workgroups
-// 1.02 / 1.01, two and as many as fit 0.98 / 0.99, BERT-Base-shaped P = 5 1.00 / 0.99 and 0.99 / 0.98.
+// Not where w of a launch fits the L2s (2048 tiles, 32 MiB): the all-gather behind it reads w in the L2 of the XCD that wrote it, if
+// both go through the tiles as they fall.  Pass = reduce-scatter with update, all-gather, one state over and over / three in turn,
+// batch kernel = 1, as they fall | in rows: fp32 P = 2 900 tiles 0.98 / 0.99 | 1.15 / 0.98, 1800 1.01 / 1.01 | 1.09 / 0.98, P = 8 600
+// 1.03 / 1.02 | 1.07 / 1.02, 900 1.01 / 1.01 | 1.08 / 0.98, 1800 1.00 / 1.01 | 1.04 / 0.98, P = 16 400 1.02 / 1.02 | 1.04 / 1.02,
+// 900 0.98 / 0.97 | 0.99 / 0.94; dear_iteration P = 8 800 1.02 / 1.03 | 1.13 / 1.03, bf16 P = 6 800 1.00 / 0.99 | 1.21 / 0.98; more
+// replicas leave little of it: P = 32 fp32 900 0.98 / 0.96 | 0.95 / 0.92, 400 1.00 / 0.99 | 1.01 / 0.99.
+// In dear_iteration where the all-gather comes next (caches_w) four replicas a lane and as many workgroups as fit, below 1600 tiles
+// (fp32 from 8 replicas on 2048): fp32 P = 8 350 / 550 / 800 / 1200 tiles 1.02 / 1.01 / 0.99 / 0.99, two replicas 1.03 / 1.02 / 1.00 / 0.99 and with four
+// workgroups 1.07 / 1.04 / 1.02 / 1.00, P = 9 to 12 1600 two in rows 1.02 to 1.03; bf16 P = 6 and 8 at 550 1.03 (the batch kernel up to
+// 700), P = 9 to 20 320 to 450 1.02 to 1.05 (the rule without caches_w).  bf16 from 1600 on two a lane, P = 7 4900 tiles four and three
+// workgroups 1.02 / 1.01, two and as many as fit 0.98 / 0.99, BERT-Base-shaped P = 5 1.00 / 0.99 and 0.99 / 0.98, from 8 replicas on with four:
+// BERT-Large-shaped P = 8 0.98, as many as fit 0.99, three 0.98.
 inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, bool caches_w, int64_t P, int64_t elems, int64_t tiles,
-                                                    int64_t whole)
+                                                    int64_t whole, int64_t cut_tiles)
 {
     auto depth = [&](int most) { return P >= most ? most : P >= 4 ? 4 : P >= 2 ? 2 : 1; };
     auto filled = [&](int percent) { return elems * 100 >= tiles * DEAR_TILE_ELEMS * percent; };
     const int run = tiles < (P <= 8 ? 2048 : P <= 16 ? 1600 : 320) ? 0 : 6;
     auto parts = [&](int most, int residency) { return reduce_scatter_shape{depth(most), residency, run, false}; };
-    const bool full = filled(80);
+    const reduce_scatter_shape batch{0, 0, 0, false};
+    const bool full = filled(85), cut = cut_tiles * 8 >= tiles;
     if (!some_whole(whole, tiles) && tiles >= (P >= 8 ? 96 : 128) && !filled(tiles >= 512 ? 40 : 25))
         return {depth(tiles < (bf16 ? 512 : 256) ? 8 : 4), 0, 4, true};
-    if (!bf16 && full && P >= 4 && P <= 16 && tiles >= 6000 && (updates || P >= 8)) {
-        if (P > 4 && P < 8) return {0, 0, 0, false};
-        return {4, 2, 0, false};
+    if (!bf16 && full && !updates && P >= 8 && P <= 16 && tiles >= 24000) return {4, 2, 0, false};
+    if (caches_w && P >= 4 && filled(50)) {
+        if (bf16 && P <= 8 && tiles < 700 && tiles >= (P % 4 ? 40 : 110)) return batch;
+        if (tiles >= 256 && tiles < (bf16 || P < 8 ? 1600 : 2048) && P <= (bf16 ? 8 : 16)) return {4, 0, 0, false};
+        if (bf16 && tiles >= 1600) return parts(2, P < 8 || tiles < 2048 ? 0 : 4);
     }
+    if (!(caches_w && tiles >= 256 && (bf16 ? P >= 4 && P <= 8 : true)) && batch_kernel_stays(bf16, updates, P, tiles, cut)) return batch;
     if (P < 4) return parts(2, updates && (full || bf16) && tiles >= (bf16 ? 512 : P > 1 ? 4096 : 1024) ? 4 : 0);
-    if (bf16 && P >= 4 && P <= 8 && filled(50) && tiles < (caches_w ? 700 : !updates ? 150 : P % 4 ? 300 : 256) && tiles >= (P % 4 ? 40 : updates ? 110 : 50) && (updates || P == 4))
-        return {0, 0, 0, false};
-    if (caches_w && filled(50) && P >= 4 && tiles >= (P <= 16 ? 256 : 512) && tiles < 1600 && (bf16 || P <= 16)) return {4, 0, 0, false};
-    if (!bf16 && filled(50) && P >= 4 && tiles >= 360 && tiles < (P <= 16 ? 700 : 450)) return {4, 0, 0, false};
-    if (bf16 && caches_w && tiles >= 1600 && filled(50)) return parts(2, P < 8 || tiles < 2048 ? 0 : 4);
-    if (!bf16 && updates && P > 4 && P < 8 && full && tiles >= 75 && tiles < 120) return {0, 0, 0, false};
+    if (!bf16 && P > 4 && P <= 16 && tiles >= 320 && tiles < (P < 12 ? 1024 : 700)) return {4, 0, 0, false};
+    if (bf16 && P <= 16 && tiles >= (P < 8 ? 900 : 750) && tiles < (P <= 8 ? 2048 : 1600)) return {4, 0, 0, false};
     if (P < 8) {
         if (bf16 && updates) return parts(4, tiles >= 1024 ? 3 : 0);
-        if (tiles < (bf16 ? P == 4 ? 150 : 128 : P == 4 ? 75 : 160)) return parts(4, 0);
+        if (P == 4 ? !bf16 && tiles < 75 : tiles < (bf16 ? 256 : 160)) return parts(4, 0);
         if (updates) return parts(2, full && tiles >= 2048 ? 3 : 0);
         return parts(2, full && tiles >= 4096 ? 4 : 0);
     }
-    if (tiles < (bf16 ? 110 : full ? 56 : 128)) return parts(8, 0);
-    if (tiles < (bf16 ? 256 : 128)) return parts(4, 0);
-    if (!full) {
-        if (bf16 && (updates || tiles < 512)) return parts(4, tiles < 512 ? 0 : 3);
-        if (tiles < 512) return parts(2, 0);
-        return parts(2, bf16 ? (tiles < 1024 || P < 24 ? 0 : 4) : P < 13 ? 0 : 4);
-    }
-    if (tiles < (bf16 ? 1024 : 512)) return parts(2, P > 40 && tiles >= (bf16 ? 512 : 256) ? 3 : 0);
-    const bool fewer = P >= 24 || (updates && !bf16 && P >= 13) || (bf16 ? tiles >= 4096 : updates && tiles >= 2048);
-    return parts(2, fewer ? 3 : 4);
+    if (tiles < (!bf16 ? 64 : P < 24 ? 110 : 132)) return parts(8, 0);
+    if (tiles < (bf16 ? 288 : 128)) return parts(4, 0);
+    if (tiles < (bf16 ? 750 : P > 16 ? 400 : 512)) return parts(2, 0);
+    if (bf16) return parts(2, 4);
+    if (!full && P < 13 && tiles < 2048) return parts(2, 0);
+    return parts(2, (P >= 24 ? tiles >= 512 : updates && (P >= 13 || tiles >= 2048)) ? 3 : 4);
 }
 
 // Whether the entries of a pointer table lie within 32 bits of its beginning, as reduce_scatter_kernel counts them.

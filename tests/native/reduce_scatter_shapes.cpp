@@ -8,8 +8,71 @@
 
 #include "dear_internal.h"
 
-int main()
+// Asked for on stdin: bf16 updates caches_w P elems tiles whole cut, a line each; answered with depth, residency, run, tiles.
+static int answer()
 {
+    int bf16, updates, caches_w;
+    long long P, elems, tiles, whole, cut;
+    while (std::scanf("%d %d %d %lld %lld %lld %lld %lld", &bf16, &updates, &caches_w, &P, &elems, &tiles, &whole, &cut) == 8) {
+        const reduce_scatter_shape s = reduce_scatter_shape_of(bf16, updates, caches_w, P, elems, tiles, whole, cut);
+        std::printf("%d %d %d %d\n", s.depth, s.residency, s.run, static_cast<int>(s.tiles));
+    }
+    return 0;
+}
+
+// Tiles of a run that begin or end inside a vector, against its tiles one by one.
+static bool cut_tiles()
+{
+    for (int64_t vector : {4, 8})
+        for (int64_t begin : {0, 1, 4, 8, 4092, 4095, 4096, 12287})
+            for (int64_t count : {1, 3, 4, 8, 4096, 4097, 8192, 20000, 20004})
+                for (int32_t layer : {-1, 3}) {
+                    const dear_run r{layer < 0 ? 0 : begin, 7, count, 0, layer, 0, 0, 0};
+                    int64_t n = 0;
+                    for (int64_t k = 0; k < tiles_of_run(r); ++k) {
+                        const dear_tile t = tile_of_run(r, k);
+                        n += layer >= 0 && (t.src_begin % vector != 0 || (t.src_begin + t.count) % vector != 0);
+                    }
+                    if (cut_tiles_of_run(r, vector) != n) return false;
+                }
+    return true;
+}
+
+// Launches that the batch kernel keeps, and their neighbours that it does not: full tiles, nothing cut or all of them.
+static bool batch_kernel()
+{
+    struct { bool bf16, updates; int64_t P, tiles; bool cut, batch; } const at[] = {
+        // 25 MB buckets of a convolutional net, eight workers
+        {false, true, 8, 585, false, true},  {false, true, 8, 1116, false, true}, {false, true, 8, 1605, false, true},
+        {false, true, 8, 2047, false, true}, {false, true, 8, 2048, false, false}, {false, true, 8, 1116, true, false},
+        {false, true, 9, 1116, false, false}, {false, false, 8, 159, false, true}, {false, false, 8, 160, false, false},
+        {false, false, 3, 2047, false, true}, {false, false, 4, 1116, false, false}, {false, true, 12, 64, false, true},
+        {false, true, 12, 63, false, false}, {false, true, 64, 159, false, true}, {false, true, 64, 160, false, false},
+        {false, false, 12, 100, false, false}, {false, false, 20, 100, false, true}, {false, false, 7, 159, true, true},
+        {false, false, 7, 160, true, false}, {true, true, 8, 2047, false, true}, {true, true, 16, 699, false, true},
+        {true, true, 16, 700, false, false}, {true, true, 24, 131, false, false}, {true, true, 24, 132, false, true},
+        {true, true, 24, 287, false, true},  {true, true, 24, 288, false, false}, {true, false, 24, 159, false, true},
+        {true, false, 24, 160, false, false}, {true, true, 8, 109, true, false}, {true, true, 8, 299, true, true},
+        {true, true, 8, 300, true, false},   {true, false, 4, 159, true, true}, {true, false, 4, 160, true, false},
+        {true, true, 4, 110, false, true},   {true, true, 4, 1116, false, false}, {true, true, 1, 127, false, false},
+        {true, true, 2, 128, false, true},   {true, true, 2, 700, false, false}, {true, true, 2, 200, true, false},
+        {true, true, 3, 400, true, false},   {true, false, 2, 400, true, false}, {true, false, 2, 2047, false, true},
+    };
+    for (const auto &c : at) {
+        const int64_t elems = c.tiles * DEAR_TILE_ELEMS, cut = c.cut ? (c.tiles + 7) / 8 : (c.tiles - 1) / 8;
+        if ((reduce_scatter_shape_of(c.bf16, c.updates, false, c.P, elems, c.tiles, c.tiles, cut).depth == 0) != c.batch) {
+            std::fprintf(stderr, "FAILED batch kernel: bf16=%d updates=%d P=%lld tiles=%lld cut=%d\n", c.bf16, c.updates, (long long)c.P,
+                         (long long)c.tiles, c.cut);
+            return false;
+        }
+    }
+    return true;
+}
+
+int main(int argc, char **)
+{
+    if (argc > 1) return answer();
+    if (!cut_tiles() || !batch_kernel()) return 1;
     for (unsigned run : {0u, 4u, 6u, 9u})
         for (unsigned n = 1; n < (run < 9 ? 2100 : 12400); n += n < 1100 ? 1 : 37) {
             std::vector<int> seen(n, 0);
@@ -30,10 +93,11 @@ int main()
             for (bool caches_w : {false, true})
                 for (int64_t P = 1; P <= 130; ++P)
                     for (int64_t tiles : {1, 15, 16, 63, 64, 96, 127, 128, 191, 192, 255, 256, 319, 512, 1023, 1024, 2048, 4096, 5999, 6000, 30000})
-                        for (int64_t percent : {1, 24, 39, 50, 79, 80, 100})
+                        for (int64_t percent : {1, 24, 39, 50, 79, 80, 87, 100})
                             for (int64_t whole : {int64_t(0), tiles}) {
-                                const reduce_scatter_shape s =
-                                    reduce_scatter_shape_of(bf16, updates, caches_w, P, tiles * DEAR_TILE_ELEMS * percent / 100, tiles, whole);
+                                const int64_t cut = percent % 2 ? tiles : 0;
+                                const reduce_scatter_shape s = reduce_scatter_shape_of(
+                                    bf16, updates, caches_w, P, tiles * DEAR_TILE_ELEMS * percent / 100, tiles, whole, cut);
                                 const bool depth = s.depth == 0 || s.depth == 1 || s.depth == 2 || s.depth == 4 || s.depth == 8;
                                 if (!depth || s.depth > P || s.residency < 0 || s.residency > 4 || s.residency == 1 || s.run < 0 || s.run > 6 ||
                                     (s.tiles && (s.depth == 0 || whole))) {
