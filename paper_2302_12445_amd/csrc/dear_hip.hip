@@ -764,14 +764,6 @@ __device__ __forceinline__ unsigned divide(unsigned n, unsigned d, unsigned inv_
     return q;
 }
 
-// What the device's copy of a tile carries in the place of its bucket, for the all-gather.
-constexpr int TILE_FIRST = 1, TILE_LAST = 2;  // of its run: the tiles of one layer and shard
-constexpr int TILE_OWN_SHIFT = 4;             // the replicas' tensors lie differently: each has a shift of its own
-constexpr int TILE_SHIFT_BIT = 8;             // the replicas' common shift from this bit on
-
-// Elements between the last 128-byte line that begins at or before p, and p (16-byte aligned).
-__host__ __device__ __forceinline__ int line_shift(uintptr_t p) { return static_cast<int>((p >> 2) & 31); }
-
 // n_parts = tiles * AG_SPLIT; replicas p_first .. p_first+n_p-1 receive.  inv_n_p, inv_len: reciprocals (see divide)
 // of n_p and of len, the number of workgroups per replica in the short last chunk.
 // Workgroups go to the eight XCDs in turn, and a part of a chunk belongs on one XCD for all replicas, whose L2 then
@@ -1245,36 +1237,6 @@ void rs_launch(bool bf16, const rs_call &c, const rs_sink<MODE> &o)
 // for it: 93 tiles 12.9 / 17, 2700 tiles 28 / 31, 5100 (300 tensors) 38 / 29, 5000 (100 tensors) 34 / 21, 27000 150 / 45.
 constexpr int64_t HOST_TILES = 3072;
 
-constexpr int64_t SHIFT_TILES = 8;
-
-// Writes into every run's bucket field what the all-gather wants to know about its tiles.  True: nearly all elements
-// (seven eighths) are in runs whose cuts are lines in every replica, at the same elements (all_gather_in_eighths).
-bool mark_runs(const dear_plan_s &plan, float *const *param_ptrs, dear_run *runs, int64_t n_runs)
-{
-    int64_t elems = 0, alike = 0;
-    for (dear_run *r = runs; r < runs + n_runs; ++r) {
-        int flags = 0;
-        if (r->layer >= 0) {
-            const int shift = line_shift(reinterpret_cast<uintptr_t>(param_ptrs[r->layer]));
-            flags = shift << TILE_SHIFT_BIT;
-            for (int32_t p = 1; p < plan.P; ++p)
-                if (line_shift(reinterpret_cast<uintptr_t>(param_ptrs[static_cast<size_t>(p) * plan.L + r->layer])) != shift)
-                    flags = TILE_OWN_SHIFT;
-            // A short run has little to gain: most of its tiles are at an end, and moved ends take the long form.
-            // All-gather of 20 M elements in tensors of n tiles that start on 16-byte boundaries, P = 8, us, cuts
-            // moved / not (not resolved better than 10 % around 6 tiles): 4 tiles 143 / 117, 5 121 / 107, 6 114 / 112
-            // and 126, 8 118 / 124, 10 100 / 123, 21 97 / 117; P = 32: 8 tiles 408 / 501.
-            // A first tile of less than a line could not give a shift away.
-            const bool moved = tiles_of_run(*r) >= SHIFT_TILES && tile_of_run(*r, 0).count >= 32;
-            elems += r->count;
-            if (flags == 0 || (moved && flags != TILE_OWN_SHIFT)) alike += r->count;
-            if (!moved) flags = 0;
-        }
-        r->bucket = flags;
-    }
-    return alike >= elems - elems / 8;
-}
-
 }  // namespace
 
 struct dear_ctx_s : dear_ctx_impl {};
@@ -1326,7 +1288,7 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
     }
     std::partial_sum(c->whole_begin.begin(), c->whole_begin.end(), c->whole_begin.begin());
     std::partial_sum(c->cut_begin.begin(), c->cut_begin.end(), c->cut_begin.begin());
-    c->replicas_alike = mark_runs(*plan, param_ptrs, runs.data(), n_runs);
+    c->replicas_alike = dear_mark_runs(*plan, param_ptrs, runs.data(), n_runs);
     const bool on_host = n_tiles <= HOST_TILES;
     if (on_host) {
         dear_tile *tiles = reinterpret_cast<dear_tile *>(image.data());

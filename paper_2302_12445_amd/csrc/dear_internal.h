@@ -62,6 +62,14 @@ DEAR_HOST_DEVICE inline dear_tile tile_of_run(const dear_run &r, int64_t k)
     return {r.layer < 0 ? 0 : lo, r.dst_begin + (lo - r.src_begin), static_cast<int32_t>(hi - lo), r.layer, r.shard, r.bucket};
 }
 
+// What the device's copy of a tile carries in the place of its bucket, for the all-gather.
+constexpr int TILE_FIRST = 1, TILE_LAST = 2;  // of its run: the tiles of one layer and shard
+constexpr int TILE_OWN_SHIFT = 4;             // the replicas' tensors lie differently: each has a shift of its own
+constexpr int TILE_SHIFT_BIT = 8;             // the replicas' common shift from this bit on
+
+// Elements between the last 128-byte line that begins at or before p, and p (16-byte aligned).
+DEAR_HOST_DEVICE inline int line_shift(uintptr_t p) { return static_cast<int>((p >> 2) & 31); }
+
 constexpr int DEAR_BLOCK = 256;  // threads per workgroup = 4 wavefronts
 
 // ------------------------------------------------ which launches a call makes, by its sizes alone
@@ -254,6 +262,10 @@ int64_t dear_emit_runs(const dear_plan_s &pl, int32_t b_first, int32_t b_last, d
 int64_t dear_emit_tiles(const dear_plan_s &pl, int32_t b_first, int32_t b_last, dear_tile *out,
                         int64_t capacity, int64_t *tile_begin);
 void dear_build_tiles(const dear_plan_s &pl, std::vector<dear_tile> &tiles, std::vector<int64_t> &tile_begin);
+
+// Writes into every run's bucket field what the all-gather wants to know about its tiles.  True: nearly all elements
+// (seven eighths) are in runs whose cuts are lines in every replica, at the same elements (all_gather_in_eighths).
+bool dear_mark_runs(const dear_plan_s &pl, float *const *param_ptrs, dear_run *runs, int64_t n_runs);
 
 // How many workgroups of an unbounded launch of the batch kernel may share a CU: 1, 2, or 0 for as many as fit.  HBM serves many
 // streams at once better the fewer loads compete, as long as some 64 KiB per CU are in flight (a workgroup has

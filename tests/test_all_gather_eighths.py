@@ -15,7 +15,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 def test_numbering_and_rule_on_the_host(tmp_path):
     exe = str(tmp_path / "all_gather_eighths")
     subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2302_12445_amd", "csrc"),
-                    os.path.join(ROOT, "tests", "native", "all_gather_eighths.cpp"), "-o", exe], check=True)
+                    os.path.join(ROOT, "tests", "native", "all_gather_eighths.cpp"), os.path.join(ROOT, "paper_2302_12445_amd", "csrc", "plan.cpp"),
+                    "-o", exe], check=True)
     assert "all_gather_eighths: ok" in subprocess.run([exe], check=True, capture_output=True, text=True).stdout
 
 
