@@ -361,6 +361,7 @@ inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles
         if (!bf16 || P < 4 || P > 8) return false;
         return updates ? tiles >= (P % 4 ? 40 : 110) && tiles < 300 : P == 4 && tiles < 160;
     }
+    if (bf16 && updates && P >= 5 && P <= 7) return tiles < 900;
     if (P <= 8) return updates || P <= (bf16 ? 2 : 3) || tiles < 160;
     if (!bf16) return P >= (updates ? 12 : 20) && tiles >= 64 && tiles < 160;
     if (P < 24) return updates ? tiles < 700 : P >= 12 && tiles < 130;
@@ -398,12 +399,20 @@ inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles
 // 1.03 / 1.02 | 1.07 / 1.02, 900 1.01 / 1.01 | 1.08 / 0.98, 1800 1.00 / 1.01 | 1.04 / 0.98, P = 16 400 1.02 / 1.02 | 1.04 / 1.02,
 // 900 0.98 / 0.97 | 0.99 / 0.94; dear_iteration P = 8 800 1.02 / 1.03 | 1.13 / 1.03, bf16 P = 6 800 1.00 / 0.99 | 1.21 / 0.98; more
 // replicas leave little of it: P = 32 fp32 900 0.98 / 0.96 | 0.95 / 0.92, 400 1.00 / 0.99 | 1.01 / 0.99.
+// fp32 from 8 to 16 replicas on, 6000 tiles and more: four replicas, two workgroups, as they fall, whose rows of several replicas do not drift
+// apart.  Models' lists, 4/2 | 2/4r (without update) or 2/3r (with), and dear_iteration: ResNet-50-shaped (6342 tiles) P = 8 0.98 | 0.98, 1.00 | 0.99,
+// 0.99 | 1.01, P = 12 0.97 | 0.98, 1.02 | 1.01, 0.99 | 0.99, P = 16 0.99 | 1.01, 0.99 | 0.98, 0.98 | 0.98; Inception-v4-shaped (10732) P = 8
+// 0.99 | 0.97, 1.00 | 1.00, 0.97 | 0.99, P = 12 0.98 | 0.98, 1.01 | 1.00, 0.96 | 0.98, P = 16 0.99 | 1.00, 0.99 | 1.00, 0.95 | 0.96; BERT-Base-shaped (26988)
+// P = 8 0.98 | 1.00, 0.99 | 0.99, 0.99 | 1.01, P = 16 0.99 | 1.03, 0.99 | 0.97, 1.00 | 0.99; below, DenseNet-201-shaped (5242) P = 8 0.97 | 0.92,
+// 1.00 | 0.99, 0.99 | 0.97.  One tensor of 6000 to 13000 tiles likes rows (P = 8 with update 1.00 | 0.96).  bf16 from 6000 tiles on 2/3r: BERT-Large-shaped all
+// buckets 2/4r 0.91, 2/3r 0.89, with update 0.95 and 0.94, 12000 to 40000 tiles P = 8 0.97 and 0.94, 1.00 and 0.98, P = 16 1.03 and 1.00, 1.01 and 0.99.
 // In dear_iteration where the all-gather comes next (caches_w) four replicas a lane and as many workgroups as fit, below 1600 tiles
-// (fp32 from 8 replicas on 2048): fp32 P = 8 350 / 550 / 800 / 1200 tiles 1.02 / 1.01 / 0.99 / 0.99, two replicas 1.03 / 1.02 / 1.00 / 0.99 and with four
-// workgroups 1.07 / 1.04 / 1.02 / 1.00, P = 9 to 12 1600 two in rows 1.02 to 1.03; bf16 P = 6 and 8 at 550 1.03 (the batch kernel up to
-// 700), P = 9 to 20 320 to 450 1.02 to 1.05 (the rule without caches_w).  bf16 from 1600 on two a lane, P = 7 4900 tiles four and three
-// workgroups 1.02 / 1.01, two and as many as fit 0.98 / 0.99, BERT-Base-shaped P = 5 1.00 / 0.99 and 0.99 / 0.98, from 8 replicas on with four:
-// BERT-Large-shaped P = 8 0.98, as many as fit 0.99, three 0.98.
+// (fp32 from 8 replicas on 2048): fp32 P = 8 350 / 550 / 800 / 1200 tiles 1.02 / 1.01 / 0.99 / 0.99, two replicas 1.03 / 1.02 / 1.00 / 0.99
+// and with four workgroups 1.07 / 1.04 / 1.02 / 1.00, P = 9 to 12 1600 two in rows 1.02 to 1.03; bf16 P = 6 and 8 at 550 1.03 (the batch
+// kernel up to 700), P = 9 to 20 320 to 450 1.02 to 1.05 (the rule without caches_w).  Beyond 2048 tiles 2/4r | 2/3r | 2/-r: 604 ragged tensors bf16
+// P = 5 0.99 | 1.01 | 1.01, P = 6 0.99 | 1.01 | 1.02, P = 7 0.97 | 0.98 | 0.99, P = 8 1.00 | 1.00 | -, BERT-Large-shaped P = 8 0.98 | 0.98 | 0.99; fp32
+// ResNet-50-, Inception-v4- and DenseNet-201-shaped P = 4 0.99 | 0.98 | -, 1.00 | 1.00 | -, with gbar 1.03 | 1.01 | -, 0.99 | 1.01 | -, P = 5 1.00 | 1.00 | -
+// and 1.00 | 1.01 | -, P = 7 1.01 | 1.02 | - and 0.99 | 1.01 | -.
 inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, bool caches_w, int64_t P, int64_t elems, int64_t tiles,
                                                     int64_t whole, int64_t cut_tiles)
 {
@@ -415,18 +424,18 @@ inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, boo
     const bool full = filled(85), cut = cut_tiles * 8 >= tiles;
     if (!some_whole(whole, tiles) && tiles >= (P >= 8 ? 96 : 128) && !filled(tiles >= 512 ? 40 : 25))
         return {depth(tiles < (bf16 ? 512 : 256) ? 8 : 4), 0, 4, true};
-    if (!bf16 && full && !updates && P >= 8 && P <= 16 && tiles >= 24000) return {4, 2, 0, false};
+    if (!bf16 && full && P >= 8 && P <= 16 && tiles >= 6000) return {4, 2, 0, false};
     if (caches_w && P >= 4 && filled(50)) {
         if (bf16 && P <= 8 && tiles < 700 && tiles >= (P % 4 ? 40 : 110)) return batch;
         if (tiles >= 256 && tiles < (bf16 || P < 8 ? 1600 : 2048) && P <= (bf16 ? 8 : 16)) return {4, 0, 0, false};
-        if (bf16 && tiles >= 1600) return parts(2, P < 8 || tiles < 2048 ? 0 : 4);
+        if (tiles >= (bf16 ? 1600 : 2048)) return parts(2, tiles < 2048 ? 0 : !bf16 && P == 4 ? 3 : 4);
     }
     if (!(caches_w && tiles >= 256 && (bf16 ? P >= 4 && P <= 8 : true)) && batch_kernel_stays(bf16, updates, P, tiles, cut)) return batch;
     if (P < 4) return parts(2, updates && (full || bf16) && tiles >= (bf16 ? 512 : P > 1 ? 4096 : 1024) ? 4 : 0);
     if (!bf16 && P > 4 && P <= 16 && tiles >= 320 && tiles < (P < 12 ? 1024 : 700)) return {4, 0, 0, false};
-    if (bf16 && P <= 16 && tiles >= (P < 8 ? 900 : 750) && tiles < (P <= 8 ? 2048 : 1600)) return {4, 0, 0, false};
+    if (bf16 && P <= 16 && (P >= 8 || !updates) && tiles >= (P < 8 ? 900 : 750) && tiles < (P <= 8 ? 2048 : 1600)) return {4, 0, 0, false};
     if (P < 8) {
-        if (bf16 && updates) return parts(4, tiles >= 1024 ? 3 : 0);
+        if (bf16 && updates) return parts(4, tiles >= 2048 || (tiles >= 1024 && cut_tiles * 16 >= tiles) ? 3 : 0);
         if (P == 4 ? !bf16 && tiles < 75 : tiles < (bf16 ? 256 : 160)) return parts(4, 0);
         if (updates) return parts(2, full && tiles >= 2048 ? 3 : 0);
         return parts(2, full && tiles >= 4096 ? 4 : 0);
@@ -434,7 +443,7 @@ inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, boo
     if (tiles < (!bf16 ? 64 : P < 24 ? 110 : 132)) return parts(8, 0);
     if (tiles < (bf16 ? 288 : 128)) return parts(4, 0);
     if (tiles < (bf16 ? 750 : P > 16 ? 400 : 512)) return parts(2, 0);
-    if (bf16) return parts(2, 4);
+    if (bf16) return parts(2, tiles >= 6000 ? 3 : 4);
     if (!full && P < 13 && tiles < 2048) return parts(2, 0);
     return parts(2, (P >= 24 ? tiles >= 512 : updates && (P >= 13 || tiles >= 2048)) ? 3 : 4);
 }

@@ -56,6 +56,7 @@ static bool batch_kernel()
         {true, true, 8, 300, true, false},   {true, false, 4, 159, true, true}, {true, false, 4, 160, true, false},
         {true, true, 4, 110, false, true},   {true, true, 4, 1116, false, false}, {true, true, 1, 127, false, false},
         {true, true, 2, 128, false, true},   {true, true, 2, 700, false, false}, {true, true, 2, 200, true, false},
+        {true, true, 6, 899, false, true},   {true, true, 6, 900, false, false}, {true, true, 8, 900, false, true},
         {true, true, 3, 400, true, false},   {true, false, 2, 400, true, false}, {true, false, 2, 2047, false, true},
     };
     for (const auto &c : at) {
