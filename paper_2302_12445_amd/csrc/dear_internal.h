@@ -174,20 +174,28 @@ DEAR_HOST_DEVICE inline unsigned all_gather_part(unsigned r, unsigned run)
 DEAR_HOST_DEVICE inline unsigned all_gather_part_of_eighth(unsigned r, unsigned len) { return (r & 7) * (len >> 3) + (r >> 3); }
 
 // Where it is: an XCD then writes 2 MiB of a replica in a row and not every eighth 4 KiB, and of the lines that two
-// workgroups write in halves, at the ends of runs, both halves go through one L2.  Each next part = 1, the all-gather alone / a pass of reduce-scatter
-// with update and all-gather / dear_iteration, sets of buffers in turn, 20 ragged tensors: fp32 P = 4 2300 tiles 0.94 / 0.99 / 0.99  4500 0.97 / 0.98 / 0.99, P = 8 2300
-// 0.98 / 0.99 / 1.00  4500 0.99 / 1.00 / 0.99, P = 16 3000 0.97 / 0.99 / 0.99, P = 32 900 0.91 / 0.96 / 0.96  1800 0.93 / 0.97 / 0.97  3000 0.95 / 0.98 / 0.97, bf16 P = 16 2300 0.97 /
-// 0.98 / 0.98, P = 64 900 0.93 / 0.94 / 0.94  1800 0.89 / 0.93 / 0.92; ResNet-50-shaped P = 64 0.95 / 0.95 / 0.95, in one launch 0.91 (6200 -> 6830 GB/s), BERT-Base-shaped P = 16 0.99 / 0.99 / 0.99, in one
-// launch 0.94.  2^run parts in a row (all_gather_part) cost 1-16 % up to run = 5, and 8 is level with eighths.
-// Not below 2048 tiles, 32 MiB of w, whose values are read in the L2 of the XCD that wrote them, where each takes every eighth part: the same state over and over
-// fp32 P = 4 900 tiles dear_iteration 1.17, 1800 1.03, P = 8 900 1.10, 1300 1.03, 1800 1.00 (with update in calls of their own 1.10, 1.08, 1.05), bf16 P = 8 900 1.19; with more replicas
-// that weighs less: P = 12 1300 1.03, 1800 0.99, P = 16 1300 1.01, 1800 0.99, P = 32 900 0.94, bf16 1.02, 1300 0.99.  Nor with many short
-// tensors (900 elements each, alone, P = 16 and 64, 2250 tiles 1.04 and 1.06).  Few replicas lose a little in long launches (alone, P = 2 7800 tiles 1.04
-// to 1.05, P = 4 9000 1.01).  Nor where the parts do not end at the same lines in all replicas (dear_ctx_s::replicas_alike): ResNet-50-shaped P = 64,
-// replicas at multiples of 16 bytes that are none of 128 from one another 1.08, alike 0.94; 604 tensors on 16-byte boundaries P = 7 1.01 / 1.00 / 1.00, on lines 0.98 / 0.96 / 0.97.
+// workgroups write in halves, at the ends of runs, both halves go through one L2.  Each next part = 1, the all-gather alone / a pass of
+// reduce-scatter with update and all-gather / dear_iteration, sets of buffers in turn, 20 ragged tensors: fp32 P = 4 2300 tiles
+// 0.94 / 0.99 / 0.99  4500 0.97 / 0.98 / 0.99, P = 8 2300 0.98 / 0.99 / 1.00  4500 0.99 / 1.00 / 0.99, P = 16 3000 0.97 / 0.99 / 0.99,
+// P = 32 900 0.91 / 0.96 / 0.96  1800 0.93 / 0.97 / 0.97  3000 0.95 / 0.98 / 0.97, bf16 P = 16 2300 0.97 / 0.98 / 0.98, P = 64 900
+// 0.93 / 0.94 / 0.94  1800 0.89 / 0.93 / 0.92; ResNet-50-shaped P = 64 0.95 / 0.95 / 0.95, in one launch 0.91 (6200 -> 6830 GB/s),
+// BERT-Base-shaped P = 16 0.96 / 0.99 / 0.99, in one launch 0.94.  One tensor, whose runs share no lines, gains nothing (P = 16 to 32 2000
+// to 5000 tiles 1.01 to 1.03).  2^run parts in a row (all_gather_part) cost 1-16 % up to run = 5, and 8 is level with eighths.
+// Not below 2048 tiles, 32 MiB of w, whose values are read in the L2 of the XCD that wrote them, where each takes every eighth part:
+// the same state over and over fp32 P = 4 900 tiles dear_iteration 1.17, 1800 1.03, P = 8 900 1.10, 1300 1.03, 1800 1.00 (with update in
+// calls of their own 1.10, 1.08, 1.05), bf16 P = 8 900 1.19; with more replicas that weighs less: P = 12 1300 1.03, 1800 0.99, P = 16
+// 1300 1.01, 1800 0.99, P = 32 900 0.94, bf16 1.02, 1300 0.99.
+// Nor with many parts that short tensors leave empty, which give the XCDs unlike eighths: tensors of 900 elements, alone, P = 16 and 64,
+// 2250 tiles 1.04 and 1.06; weights with short vectors between them, 80 % full, P = 8 2050 / 2600 / 3300 / 5200 tiles 1.04 / 1.03 / 1.04 / 1.03, P = 16
+// 1.06 / 1.07 / 1.05 / 1.06, P = 24 1100 1.08, P = 64 960 / 2100 / 5300 1.07 / 1.07 / 1.07, though 6500 0.97, 0.93, - and 1.00.
+// Few replicas lose a little in long launches (alone, P = 4 9000 1.01), one and two in most (P = 1 2600 to 4000 1.03, P = 2 7800 1.04 to 1.05).
+// Nor where the parts do not end at the same lines in all replicas (dear_ctx_s::replicas_alike): ResNet-50-shaped P = 64, replicas at
+// multiples of 16 bytes that are none of 128 from one another 1.08, alike 0.94; 604 tensors on 16-byte boundaries P = 7 1.01 / 1.00 / 1.00,
+// on lines 0.98 / 0.96 / 0.97.
 inline bool all_gather_in_eighths(int64_t elems, int64_t tiles, int64_t n_workers)
 {
-    if (elems * 2 < tiles * DEAR_TILE_ELEMS || tiles < (n_workers >= 24 ? 960 : n_workers >= 12 ? 1600 : 2048)) return false;
+    if (elems * 8 < tiles * DEAR_TILE_ELEMS * (tiles < 6000 ? 7 : 4)) return false;
+    if (n_workers < 3 || tiles < (n_workers >= 24 ? 960 : n_workers >= 12 ? 1600 : 2048)) return false;
     return n_workers >= 5 || tiles < 5000;
 }
 

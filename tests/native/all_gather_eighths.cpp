@@ -67,12 +67,15 @@ int main()
                 }
         }
     for (int64_t P = 1; P < 100; ++P)
-        for (int64_t tiles : {1, 900, 959, 960, 1599, 1600, 2047, 2048, 30000})
-            if (all_gather_in_eighths(tiles * DEAR_TILE_ELEMS, tiles, P) != (tiles >= (P >= 24 ? 960 : P >= 12 ? 1600 : 2048) && (P >= 5 || tiles < 5000)) ||
-                all_gather_in_eighths(tiles * DEAR_TILE_ELEMS / 2 - 1, tiles, P)) {
+        for (int64_t tiles : {1, 900, 959, 960, 1599, 1600, 2047, 2048, 4999, 5000, 5999, 6000, 30000}) {
+            const bool long_enough = tiles >= (P >= 24 ? 960 : P >= 12 ? 1600 : 2048) && P >= 3 && (P >= 5 || tiles < 5000);
+            const int64_t room = tiles * DEAR_TILE_ELEMS, least = tiles < 6000 ? room / 8 * 7 : room / 2;
+            if (all_gather_in_eighths(room, tiles, P) != long_enough || all_gather_in_eighths(least, tiles, P) != long_enough ||
+                all_gather_in_eighths(least - 1, tiles, P)) {
                 std::fprintf(stderr, "FAILED rule tiles=%lld P=%lld\n", (long long)tiles, (long long)P);
                 return 1;
             }
+        }
     std::printf("all_gather_eighths: ok\n");
     return 0;
 }

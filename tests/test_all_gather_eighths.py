@@ -20,14 +20,25 @@ def test_numbering_and_rule_on_the_host(tmp_path):
     assert "all_gather_eighths: ok" in subprocess.run([exe], check=True, capture_output=True, text=True).stdout
 
 
+def _sizes_in_tiles(P, tiles):
+    """Six tensors, mostly one of them, that the planner cuts into this many tiles."""
+    import paper_2302_12445_amd as dear
+    for big in range((tiles - P - 16) * 4096 + 77, (tiles + 2) * 4096, 1024):
+        sizes = [7, 9_000, 33, big, 3, 4095]
+        if len(dear.dear_plan_tiles(dear.dear_plan(sizes, P, dear.DEAR_NO_LIMIT, 4))[0]) == tiles:
+            return sizes
+    raise AssertionError("no plan of %d tiles for %d workers" % (tiles, P))
+
+
+# one below each line of the rule and on it: by workers, the limit of few workers, and two workers, who never go in eighths
 @pytest.mark.gpu
-@pytest.mark.parametrize("P,tiles", [(1, 2047), (2, 2048), (3, 2051), (5, 4097), (8, 2050), (12, 1598), (12, 1603), (24, 958), (24, 961), (33, 1025), (64, 963)])
+@pytest.mark.parametrize("P,tiles", [(2, 2048), (3, 2047), (3, 2048), (4, 4999), (4, 5000), (5, 2047), (5, 5000), (8, 2050), (11, 2047), (12, 1599),
+                                     (12, 1600), (23, 1599), (24, 959), (24, 960), (33, 1025), (64, 959), (64, 963)])
 def test_around_the_lines_of_the_rule(P, tiles):
     from test_gpu_parity import Pair, say, small_workload
     import workloads as W
     say("case: all-gather in eighths, P=%d, %d tiles" % (P, tiles))
-    sizes = [7, 9_000, 33, (tiles - P) * 4096 - 9_040 - 4099, 3, 4095]
-    pair = Pair(small_workload(sizes, P, W.NO_LIMIT, "f32" if P % 2 else "bf16"))
+    pair = Pair(small_workload(_sizes_in_tiles(P, tiles), P, W.NO_LIMIT, "f32" if P % 2 else "bf16"))
     for route in ("calls", "iteration"):
         pair.run(iterations=1, route=route, fused=route == "iteration")
     pair.close()
