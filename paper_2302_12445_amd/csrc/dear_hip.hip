@@ -1411,9 +1411,9 @@ int launch_update(const dear_ctx_impl *c, bucket_range r, const float *shard_gra
     return launch_status();
 }
 
-// behind_update: the reduce-scatter + update of the same tiles is the launch before.
+// behind_update: the reduce-scatter + update of the same tiles is the launch before, with (caches_w) RS_W_NEXT.
 int launch_all_gather(const dear_ctx_impl *c, tile_range t, const float *shard_param, int32_t first_worker,
-                      int32_t n_workers, hipStream_t st, bool behind_update = false)
+                      int32_t n_workers, hipStream_t st, bool behind_update = false, bool caches_w = false)
 {
     const int64_t count = t.count;
     if (count == 0) return DEAR_OK;
@@ -1430,7 +1430,8 @@ int launch_all_gather(const dear_ctx_impl *c, tile_range t, const float *shard_p
         const unsigned whole = n_parts / chunk * chunk;
         const bool eighths = c->replicas_alike && all_gather_in_eighths(t.all_elems * count / t.all_tiles, count, n_workers);
         const unsigned run =
-            eighths ? 0 : all_gather_run(c->g, c->max_workgroups, t.all_elems, count, t.all_whole, n_workers, behind_update);
+            eighths ? 0 : all_gather_run(c->g, caches_w, c->max_workgroups, c->P, t.all_elems, count, t.all_whole, t.all_cut,
+                                         n_workers, behind_update);
         const all_gather_order o = all_gather_numbering(run, c->max_workgroups, whole, n_parts, n_workers);
         const auto kernel = eighths && o.len % 8 == 0 ? all_gather_kernel<0, true>
                             : o.run ? all_gather_kernel<1, false> : all_gather_kernel<0, false>;
@@ -1591,11 +1592,12 @@ extern "C" int dear_iteration(dear_ctx_t *c, int32_t bucket, float *shard_grad, 
             tile_range t = group;
             t.begin += group.count * i / pieces;
             t.count = group.begin + group.count * (i + 1) / pieces - t.begin;
-            if (iteration_caches_w(c->g, c->P, t.count, c->tile_begin[c->B]))
+            const bool caches_w = iteration_caches_w(c->g, c->P, t.count, c->tile_begin[c->B]);
+            if (caches_w)
                 rc = launch_reduce_scatter_update<RS_W_NEXT>(c, t, shard_grad, shard_param, shard_mom, lr, momentum, st);
             else
                 rc = launch_reduce_scatter_update<0>(c, t, shard_grad, shard_param, shard_mom, lr, momentum, st);
-            if (rc == DEAR_OK) rc = launch_all_gather(c, t, shard_param, 0, c->P, st, true);
+            if (rc == DEAR_OK) rc = launch_all_gather(c, t, shard_param, 0, c->P, st, true, caches_w);
         }
     }
     return rc;

@@ -108,30 +108,14 @@ inline bool some_whole(int64_t whole, int64_t tiles) { return whole * 64 >= tile
 // P = 32 of 1000 17.7 / 18.5, of 1600 20.2 / 18.3; P = 64 of 1000 35.2 / 37.5, of 1600 35.6 / 38.4, of 2400 42.9 / 38.5.
 // Reduce-scatter + update P = 10 396 tensors of 1430 9.33 / 10.08; in a dozen tiles empty halves cost nothing (P = 8 2460 elements in 5
 // tensors 5.96 / 5.64).
-inline bool reduce_scatter_half_tiles(bool updates, int64_t max_workgroups, int64_t elems, int64_t tiles, int64_t whole)
+inline bool half_tiles_filled(int64_t elems, int64_t tiles, int64_t whole)
 {
-    if (max_workgroups > 0 || tiles > (updates ? 1024 : 160)) return false;
     return tiles <= 16 || some_whole(whole, tiles) || elems >= tiles * (tiles <= 200 ? 1024 : 1536);
 }
 
-// Whether a replica's workgroups take two parts in a row (1) or each the next one (0) on an XCD (see all_gather_kernel): two are
-// what a workgroup of a bf16 reduce-scatter + update in half tiles wrote, and where that launch comes right before, as in
-// dear_iteration, they are in this XCD's L2.  The more replicas, and the emptier the tiles, the more the rounding to 16 parts costs.
-// One / two in a row:
-//   dear_iteration, us, one bucket of 100 / 200 / 400 / 850 full tiles  P = 8 8.5 / 8.3  12.6 / 12.1  22.1 / 20.1  39.5 / 38.4
-//     P = 24 16.0 / 16.0  24.7 / 24.2  45.9 / 44.4  92.3 / 88.7   P = 40 23.4 / 24.4  36.8 / 37.2  71.6 / 69.5  144 / 145   P = 48 28.5 / 28.9  43.9 / 45.2  82.5 / 83.1
-//     P = 64 38.7 / 39.4  57.4 / 59.0  108 / 109  225 / 221;  weights and short vectors, change in %: P = 3 -7 to 0, P = 8 up to 150 tiles 0, 340 to 430 full
-//     ones -4 to -8, P = 12 and 16 up to 230 tiles +1 to +3, 390 full ones -4, P = 24 +1 to +3, P = 32 +1 to +4, P = 48 and 64 +3 to +5
-//   all reduce-scatters, then all all-gathers, change of the whole pass in %: eight buckets or fewer of 40 / 100 / 200 / 400 / 850 full tiles
-//     P = 4 -7 / -3 / -2 / 0 / 0   P = 8 -9 / -4 / 0 / 0 / -1   P = 16 -3 / -2 / 0 / +1 / -2   P = 24 0 / 0 / +2 / +2 / -1   P = 32 +1 / +1 / +2 / +3 / -1
-//     P = 48 -1 / +1 / +3 / +3 / -1   P = 64 +2 / +3 / +3 / +3 / +3;  weights and short vectors P = 3 and 4 -6 to 0, P = 8 -3 to +2, with an update between
-//     +1 to +2.5, P = 12 and 16 +1 to +3, from P = 24 on +2 to +5
-inline unsigned all_gather_run(int grad_bytes, int64_t max_workgroups, int64_t elems, int64_t tiles, int64_t whole, int64_t n_workers,
-                               bool behind_update)
+inline bool reduce_scatter_half_tiles(bool updates, int64_t max_workgroups, int64_t elems, int64_t tiles, int64_t whole)
 {
-    if (grad_bytes != 2 || !reduce_scatter_half_tiles(true, max_workgroups, elems, tiles, whole)) return 0;
-    if (!behind_update) return n_workers <= (tiles <= 160 ? 8 : 4);
-    return n_workers <= 8 || (elems * 4 >= tiles * (3 * DEAR_TILE_ELEMS) && n_workers <= (tiles < 400 ? 32 : 47));
+    return max_workgroups == 0 && tiles <= (updates ? 1024 : 160) && half_tiles_filled(elems, tiles, whole);
 }
 
 // How the unbounded all-gather numbers its workgroups (see all_gather_kernel).  Where HIP would not take a launch with a
@@ -454,6 +438,35 @@ inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, boo
     if (bf16) return parts(2, tiles >= 6000 ? 3 : 4);
     if (!full && P < 13 && tiles < 2048) return parts(2, 0);
     return parts(2, (P >= 24 ? tiles >= 512 : updates && (P >= 13 || tiles >= 2048)) ? 3 : 4);
+}
+
+// Whether a replica's workgroups take two parts in a row (1) or each the next one (0) on an XCD (see all_gather_kernel): two are
+// what a workgroup of a bf16 reduce-scatter + update in halves of tiles wrote, and where that launch comes right before, as in
+// dear_iteration, they are in this XCD's L2.  The more replicas, and the emptier the tiles, the more the rounding to 16 parts costs.
+// One / two in a row:
+//   dear_iteration, us, one bucket of 100 / 200 / 400 / 850 full tiles  P = 8 8.5 / 8.3  12.6 / 12.1  22.1 / 20.1  39.5 / 38.4
+//     P = 24 16.0 / 16.0  24.7 / 24.2  45.9 / 44.4  92.3 / 88.7   P = 40 23.4 / 24.4  36.8 / 37.2  71.6 / 69.5  144 / 145   P = 48 28.5 / 28.9  43.9 / 45.2  82.5 / 83.1
+//     P = 64 38.7 / 39.4  57.4 / 59.0  108 / 109  225 / 221;  weights and short vectors, change in %: P = 3 -7 to 0, P = 8 up to 150 tiles 0, 340 to 430 full
+//     ones -4 to -8, P = 12 and 16 up to 230 tiles +1 to +3, 390 full ones -4, P = 24 +1 to +3, P = 32 +1 to +4, P = 48 and 64 +3 to +5
+//   all reduce-scatters, then all all-gathers, change of the whole pass in %: eight buckets or fewer of 40 / 100 / 200 / 400 / 850 full tiles
+//     P = 4 -7 / -3 / -2 / 0 / 0   P = 8 -9 / -4 / 0 / 0 / -1   P = 16 -3 / -2 / 0 / +1 / -2   P = 24 0 / 0 / +2 / +2 / -1   P = 32 +1 / +1 / +2 / +3 / -1
+//     P = 48 -1 / +1 / +3 / +3 / -1   P = 64 +2 / +3 / +3 / +3 / +3;  weights and short vectors P = 3 and 4 -6 to 0, P = 8 -3 to +2, with an update between
+//     +1 to +2.5, P = 12 and 16 +1 to +3, from P = 24 on +2 to +5
+// Beyond 1024 tiles where the launch before goes in halves of tiles as they fall; one / two in a row, dear_iteration, cold, change of the
+// whole pass against the batch kernel's in %, 1140 ragged tiles, 1200 of one tensor, 1520 ragged: P = 4 -5 / -8, -2 / -8, -5 / -9, P = 6 -3 / -8,
+// 0 / -2, -2 / -5, P = 8 -2 / -4, 0 / 0, -2 / -4, P = 12 -2 / -4, -1 / 0, -3 / -4, P = 16 -1 / -2, +1 / +3, 0 / -2; calls of their own 0 / +1.
+// Up to 1024 tiles also where that launch goes in rows (P = 24 660 full tiles +3 / 0, 910 +3 / 0, ragged 630 -2 / -1, 880 0 / -1, weights and
+// short vectors 660 -1 / 0, P = 32 670 and 930 full +5 / 0).
+inline unsigned all_gather_run(int grad_bytes, bool caches_w, int64_t max_workgroups, int64_t P, int64_t elems, int64_t tiles,
+                               int64_t whole, int64_t cut_tiles, int64_t n_workers, bool behind_update)
+{
+    if (grad_bytes != 2 || max_workgroups > 0 || tiles >= 2048 || !half_tiles_filled(elems, tiles, whole)) return 0;
+    if (!behind_update) return n_workers <= (tiles <= 160 ? 8 : tiles <= 1024 ? 4 : 0);
+    if (tiles > 1024) {
+        const reduce_scatter_shape s = reduce_scatter_shape_of(true, true, caches_w, P, elems, tiles, whole, cut_tiles);
+        return s.depth > 0 && s.run == 0 && !s.tiles && n_workers <= 12;
+    }
+    return n_workers <= 8 || (elems * 4 >= tiles * (3 * DEAR_TILE_ELEMS) && n_workers <= (tiles < 400 ? 32 : 47));
 }
 
 // Whether the entries of a pointer table lie within 32 bits of its beginning, as reduce_scatter_kernel counts them.

@@ -100,24 +100,32 @@ static void half_tiles()
     CHECK(reduce_scatter_half_tiles(true, 0, 406 * 1400, 406, 7));
 }
 
-// All-gathers in pairs of parts: where the bf16 reduce-scatter + update went in half tiles, and then mostly in dear_iteration.
+// All-gathers in pairs of parts: where the bf16 reduce-scatter + update went in halves of tiles, and then mostly in dear_iteration.
 static void pairs_of_parts()
 {
     struct { int64_t P, tiles, fill; bool behind, apart; } const at[] = {
         {1, 40, 4000, true, true},   {8, 160, 2000, true, true},    {9, 160, 4000, true, false},   {9, 160, 3071, false, false}, {9, 160, 3072, true, false},
         {4, 161, 2000, true, true},  {5, 161, 4000, true, false},   {32, 399, 4000, true, false},  {33, 399, 4000, false, false}, {47, 400, 4000, true, false},
-        {48, 400, 4000, false, false}, {4, 1024, 4000, true, true}, {8, 1024, 3000, true, false},  {8, 1025, 4000, false, false},
+        {48, 400, 4000, false, false}, {4, 1024, 4000, true, true}, {8, 1024, 3000, true, false},  {8, 1025, 4000, true, false},
+        {8, 2047, 4000, true, false},  {8, 2048, 4000, false, false}, {12, 1599, 4000, true, false}, {12, 1600, 4000, false, false},
+        {13, 1025, 4000, false, false}, {13, 1024, 4000, true, false}, {4, 1025, 4000, true, false}, {4, 1025, 1700, true, false},
     };
     for (const auto &c : at) {
         const int64_t elems = c.tiles * c.fill;
-        CHECK(all_gather_run(2, 0, elems, c.tiles, c.tiles / 2, c.P, true) == c.behind);
-        CHECK(all_gather_run(2, 0, elems, c.tiles, c.tiles / 2, c.P, false) == c.apart);
+        auto run = [&](int g, int64_t width, int64_t n, int64_t whole, bool behind) {
+            return all_gather_run(g, behind, width, c.P, n, c.tiles, whole, 0, c.P, behind);
+        };
+        CHECK(run(2, 0, elems, c.tiles / 2, true) == c.behind);
+        CHECK(run(2, 0, elems, c.tiles / 2, false) == c.apart);
         for (bool behind : {false, true}) {
-            CHECK(all_gather_run(4, 0, elems, c.tiles, c.tiles, c.P, behind) == 0);
-            CHECK(all_gather_run(2, 100000, elems, c.tiles, c.tiles, c.P, behind) == 0);
-            CHECK(all_gather_run(2, 0, c.tiles * 1000, c.tiles, 0, c.P, behind) == 0);
+            CHECK(run(4, 0, elems, c.tiles, behind) == 0);
+            CHECK(run(2, 100000, elems, c.tiles, behind) == 0);
+            CHECK(run(2, 0, c.tiles * 1000, 0, behind) == 0);
         }
     }
+    // a reduce-scatter in whole tiles beyond 1024 of them: the batch kernel, in calls of its own
+    CHECK(reduce_scatter_shape_of(true, true, false, 8, 1025 * 4096, 1025, 1025, 0).depth == 0);
+    CHECK(all_gather_run(2, false, 0, 8, 1025 * 4096, 1025, 1025, 0, 8, true) == 0 && all_gather_run(2, true, 0, 8, 1025 * 4096, 1025, 1025, 0, 8, true) == 1);
 }
 
 // dear_iteration: w is left in the cache only where it fits; gbar is read again only where many replicas are read.
