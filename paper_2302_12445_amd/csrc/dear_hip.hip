@@ -1144,11 +1144,8 @@ void rs_launch_batch_as(const rs_call &c, const rs_sink<MODE> &o)
     constexpr int SPLIT = DEAR_TILE_ELEMS / ((BF16 ? 8 : 4) * DEAR_BLOCK * U);
     const unsigned n_items = static_cast<unsigned>(c.n_tiles * SPLIT);
     const dim3 grid(grid_width(c.max_workgroups, n_items));
-    int residency = 0;
-    if ((MODE & RS_GATHER) != 0)
-        residency = iteration_at_once_residency(BF16, (MODE & RS_GBAR) != 0, c.P, c.all_elems, c.all_tiles);
-    else if (grid.x == n_items)
-        residency = reduce_scatter_residency(BF16, (MODE & RS_UPDATE) != 0, c.P, c.all_elems, c.all_tiles);
+    const int residency =
+        (MODE & RS_GATHER) == 0 ? 0 : iteration_at_once_residency(BF16, (MODE & RS_GBAR) != 0, c.P, c.all_elems, c.all_tiles);
     auto launch = [&](auto kernel) {
         kernel<<<grid, dim3(DEAR_BLOCK), residency_lds(residency), c.st>>>(
             c.tiles, c.grads, c.L, c.P, 1.0f / static_cast<float>(c.P), o, n_items, c.prio);

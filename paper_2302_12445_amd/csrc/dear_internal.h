@@ -259,47 +259,6 @@ void dear_build_tiles(const dear_plan_s &pl, std::vector<dear_tile> &tiles, std:
 // (seven eighths) are in runs whose cuts are lines in every replica, at the same elements (all_gather_in_eighths).
 bool dear_mark_runs(const dear_plan_s &pl, float *const *param_ptrs, dear_run *runs, int64_t n_runs);
 
-// How many workgroups of an unbounded launch of the batch kernel may share a CU: 1, 2, or 0 for as many as fit.  HBM serves many
-// streams at once better the fewer loads compete, as long as some 64 KiB per CU are in flight (a workgroup has
-// min(P, 8) * U loads of 4 KiB, 32 KiB in fp32 and 64 KiB in bf16 from P = 8 on).  Too few workgroups cost the
-// more the shorter the launch is, and where the workgroups are short ones, so it takes
-//   - enough gradient bytes in the launch.  Whole passes over N elements in four tensors, three sets of buffers in
-//     turn (spread 0.1-0.6 %), change of the time at 2 per CU / 1 per CU in %, without the update (reduce-scatter,
-//     update, all-gather) and with it (reduce-scatter + update, all-gather); MB of gradients beside N:
-//       fp32 without  P = 4  33 M  528  +4/+23   110 M 1760   +4/+24 | P = 8  13 M 416 +0.2/+12  33 M 1056 -0.6/+11
-//                     P = 12  6 M  312  +1/+19    13 M  624 -1.3/+18 | P = 16  4 M 256 -0.4/+7    6 M  416 -1.4/+6
-//                     P = 64  2 M  512 -0.6/+5     4 M 1024 -1.5/+6
-//       fp32 with     P = 4  26 M  416  +3/+19    33 M  528   -3/+13 | P = 8   6 M 208 +0.8/+11  13 M  416 -1.0/+9
-//                     P = 16  2 M  128  +1/+10     4 M  256 -1.2/+5  | P = 64  2 M 512 -0.4/+6    4 M 1024 -1.6/+6
-//       bf16 without  P = 5 110 M 1100 +0.3/+6  | P = 8  26 M  416 +0.2/+1.4  110 M 1760 -0.8/-0.2
-//                     P = 12 13 M  312 -0.5/+6    26 M  624 -1.2/+4  | P = 16 13 M 416 -0.1/-0.6 26 M  832 -1.0/-1.9
-//                     P = 64  4 M  512 -1.0/+0.2   8 M 1024 -1.6/-1.2
-//       bf16 with     P = 5   8 M   80 +0.1/+7    13 M  130 -0.9/+9  | P = 8   8 M 128 -0.5/+3   26 M  416 -0.9/+1.0
-//                     P = 8  33 M  528 -1.0/-1.0 110 M 1760 -0.5/-3  | P = 16 13 M 416 -1.0/-0.2 26 M  832 -1.2/-2.3
-//   - tiles that are four fifths full on average.  40 M elements in runs of one length, P = 8, the same passes:
-//     350 elements fp32 without 3319 / 5453 / 7787 us, bf16 with 2918 / 3441 / 4149; 2500 fp32 with 770 / 822 / 1079;
-//     9000 (73 % full) fp32 without 704 / 721 / 847, bf16 with 525 / 511 / 511; 20000 (98 %) fp32 with 610 / 580 / 643.
-// One per CU without the update takes eight replicas in flight at a time, which P = 12, 20, 28 have not.  Half tiles have half
-// the loads in flight and the same line: 960 of them with the update, P = 64, as many / 2 / 1 per CU 100 / 97 / 95, iteration 243 / 238 / 237.
-// Beside compute on another stream it does no harm: the DeAR schedule with unbounded grids, fp32 2048^3 products, us
-// as many as fit / by this rule: BERT-Base-shaped P = 16 12668 / 12414, BERT-Large-shaped P = 8 bf16 11759 / 11498.
-inline int reduce_scatter_residency(bool bf16, bool updates, int64_t P, int64_t elems, int64_t tiles)
-{
-    constexpr int64_t MB = 1000000;
-    const int64_t bytes = elems * P * (bf16 ? 2 : 4);
-    if (elems * 5 < tiles * (4 * DEAR_TILE_ELEMS)) return 0;
-    if (!bf16) {
-        if (updates) return P >= 4 && bytes >= (P >= 8 ? 400 : 500) * MB ? 2 : 0;
-        return P >= 8 && bytes >= (P >= 12 ? 400 : 800) * MB ? 2 : 0;
-    }
-    if (updates) {
-        if (P >= 8 && bytes >= 460 * MB) return 1;
-        return P >= 5 && bytes >= 160 * MB ? 2 : 0;
-    }
-    if (P >= 16 && P % 8 != 4 && bytes >= 500 * MB) return 1;
-    return P >= 8 && bytes >= 500 * MB ? 2 : 0;
-}
-
 // Parts of a tile in the reduce-scatter: one 16-byte vector a lane.
 inline int64_t reduce_scatter_split(bool bf16) { return DEAR_TILE_ELEMS / ((bf16 ? 8 : 4) * DEAR_BLOCK); }
 
@@ -577,7 +536,8 @@ inline bool iteration_gathers_at_once(int grad_bytes, int64_t P, int64_t elems, 
     return P <= 2 || (P == 3 && elems >= 25 * M) || (P == 4 && elems >= (with_gbar ? 64 : 40) * M);
 }
 
-// Workgroups per CU of such a launch (see reduce_scatter_residency), 0 for as many as fit: us at as many / 2 / 1, fp32
+// Workgroups that may share a CU in such a launch, 0 for as many as fit: HBM serves many streams at once better the fewer loads compete, in
+// launches long enough for it and whose tiles are four fifths full.  us at as many / 2 / 1, fp32
 // with gbar P = 2 5 M 32.8 / 31.6 / 38.9, 100 M 640 / 579 / 703, P = 3 100 M 788 / 722 / 878, without P = 4 100 M 854 / 776 / 876;
 // bf16 with gbar, half tiles, P = 2 30 M - / 180 / 161, 100 M 596 / 594 / 525.  bf16 P = 1 without gbar 26 M 97 / 93 / 106, 100 M 389 / 355 / 395,
 // 250 M - / 923 / 1017, with it 26 M 125 / 114 / 118, 80 M - / 354 / 358, 100 M 499 / 449 / 444, 150 M - / 702 / 683.

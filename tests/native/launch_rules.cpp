@@ -53,37 +53,6 @@ static void grids()
     CHECK(!all_gather_fits(65536, 64, 0) && all_gather_fits(65536, 64, 256));
 }
 
-// Bounding the workgroups per CU pays only in long launches of full tiles.
-static void residency()
-{
-    for (int bf16 = 0; bf16 < 2; ++bf16)
-        for (int updates = 0; updates < 2; ++updates)
-            for (int64_t P = 1; P <= 70; ++P) {
-                int before = 0;
-                for (int64_t elems = 1000; elems < int64_t(1) << 37; elems *= 2) {
-                    const int64_t full = elems / DEAR_TILE_ELEMS + 1;
-                    const int r = reduce_scatter_residency(bf16, updates, P, elems, full);
-                    CHECK(r == 0 || ((r == 2 || (r == 1 && bf16)) && elems * P * (bf16 ? 2 : 4) >= 160000000));
-                    if (P < 4) CHECK(r == 0);
-                    CHECK(before == 0 || (r != 0 && r <= before));  // longer launches: the same bound or a tighter one
-                    before = r;
-                    // the same elements in runs of 3000: three quarters full
-                    CHECK(reduce_scatter_residency(bf16, updates, P, elems, elems / 3000 + 1) == 0);
-                }
-            }
-    struct { bool bf16, updates; int64_t P, elems; int want; } const at[] = {
-        {false, true, 4, 31200000, 0},   {false, true, 4, 31300000, 2},   {false, true, 3, 110000000, 0},
-        {false, true, 8, 12400000, 0},   {false, true, 8, 12600000, 2},
-        {false, false, 4, 110000000, 0}, {false, false, 8, 24900000, 0},  {false, false, 8, 25100000, 2},
-        {false, false, 16, 6200000, 0},  {false, false, 16, 6300000, 2},  {true, true, 5, 15900000, 0},
-        {true, true, 5, 110000000, 2},   {true, true, 8, 28700000, 2},    {true, true, 8, 28800000, 1},
-        {true, false, 8, 110000000, 2},  {true, false, 16, 15600000, 0},  {true, false, 16, 15700000, 1},
-        {true, false, 12, 110000000, 2}, {true, false, 20, 110000000, 2}, {true, false, 17, 110000000, 1},
-    };
-    for (const auto &c : at)
-        CHECK(reduce_scatter_residency(c.bf16, c.updates, c.P, c.elems, c.elems / DEAR_TILE_ELEMS + c.P) == c.want);
-}
-
 // bf16 reduce-scatters in half tiles: short launches, some of whose tiles are whole or which are a quarter (many: three eighths) full.
 static void half_tiles()
 {
@@ -241,7 +210,6 @@ int main()
 {
     tables();
     grids();
-    residency();
     half_tiles();
     pairs_of_parts();
     iteration();

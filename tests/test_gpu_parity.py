@@ -505,8 +505,7 @@ def test_every_alignment_of_a_runs_ends(P, width, gather, dtype):
                                        ("bf16", 5, 16_100_000), ("bf16", 8, 31_300_000), ("bf16", 12, 20_900_000),
                                        ("bf16", 17, 14_800_000)])
 def test_launches_with_few_resident_workgroups(dtype, P, n):
-    """Sizes just above those from which launches bound the workgroups per CU (reduce_scatter_residency), in each
-    form of the reduce-scatter."""
+    """Long launches, which bound the workgroups per CU, with few and many replicas in each type."""
     say("case: few resident workgroups, %s, P=%d, %d elements" % (dtype, P, n))
     pair = Pair(small_workload([n - 77, 77], P, W.NO_LIMIT, dtype))
     for route in ("calls", "iteration"):
