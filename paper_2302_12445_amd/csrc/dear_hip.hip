@@ -570,9 +570,11 @@ __device__ __forceinline__ void reduce_scatter_part(const dear_tile &t, int part
 // delivers the partial sums of chunk s to its owner.  The accumulator starts as -0.0f,
 // the additive identity that keeps the first addend's bits (including a -0.0f).
 // Bound by HBM: P streams read once.  With batches of replicas waited for together (the kernel below) a workgroup's loads drained
-// before every next batch, and neighbouring tiles went to different XCDs.  us, that kernel / this one: ResNet-50-shaped fp32 P = 64 all
-// buckets with update 1209 / 1131 (6.1 TB/s of a plain read's 7.0), BERT-Large-shaped bf16 P = 8 without 1210 / 1074 (5.7 / 6.4 TB/s),
-// with 1882 / 1773, ResNet-50-shaped fp32 P = 8 155 / 150 and 204 / 201.  reduce_scatter_shape_of says which form goes when.
+// before every next batch, and neighbouring tiles went to different XCDs.  us, that kernel / this one, one launch over all buckets
+// (several sets of buffers in turn): BERT-Large-shaped bf16 P = 8 1190 / 1052 (5.7 / 6.4 TB/s of a plain read's 7.0), with update
+// 1848 / 1743, ResNet-50-shaped fp32 P = 64 1099 / 1073, with update 1226 / 1153, P = 8 149 / 146 and 200 / 200; a launch per bucket:
+// BERT-Large-shaped 1137 / 1094 and 1825 / 1772, ResNet-50-shaped P = 64 1120 / 1067 and 1207 / 1120, P = 8 157 / 157, with update the
+// kernel below, 211.  reduce_scatter_shape_of says which form goes when.
 template <bool BF16, int D, rest_of_replicas REST, bool TILES, rs_mode MODE>
 __global__ __launch_bounds__(DEAR_BLOCK) void reduce_scatter_kernel(
     const dear_tile *__restrict__ tiles, const void *const *__restrict__ grad_tab, int L, int P,
@@ -1738,8 +1740,8 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
     if (rc != DEAR_OK) return rc;
 
     // Where the tiles are few more bytes than the runs, as with hundreds of short tensors, the host cuts them.  Calls back to back,
-    // us, runs uploaded / tiles: 600 tensors P = 12 2 M elements (31 KB of tiles, 29 of runs) 45.4 / 43.0, 200 P = 16 3 M (28, 10) 35.1 /
-    // 35.8, 400 P = 8 20 M (164, 20) 143.2 / 152.8.
+    // us, runs uploaded / tiles: 600 tensors P = 12 2 M elements (31 KB of tiles, 29 of runs) 45.4 / 43.0, 200 P = 16 3 M (28, 10)
+    // 35.1 / 35.8, 400 P = 8 20 M (164, 20) 143.2 / 152.8.
     const bool on_host = n_tiles * sizeof(dear_tile) <= 2 * n_runs * sizeof(dear_run);
     if (on_host) {
         const dear_run *runs = reinterpret_cast<const dear_run *>(host_stage + runs_at);

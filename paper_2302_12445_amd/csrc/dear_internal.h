@@ -96,18 +96,19 @@ inline bool all_gather_fits(int64_t tiles, int64_t n_workers, int64_t max_workgr
 // that are all shorter than a tile none; elements and tiles alone do not tell one from the other.
 inline bool some_whole(int64_t whole, int64_t tiles) { return whole * 64 >= tiles; }
 
-// The batch kernel of the bf16 reduce-scatter takes half a tile a workgroup (one 16-byte vector a lane instead of two) where a launch is so
-// short that whole tiles leave CUs idle, unless its tensors are all so short that most second halves are empty.  GPU time, us,
+// The batch kernel of the bf16 reduce-scatter takes half a tile a workgroup (one 16-byte vector a lane instead of two) where a launch
+// is so short that whole tiles leave CUs idle, unless its tensors are all so short that most second halves are empty.  GPU time, us,
 // whole tiles / halves: reduce-scatter alone P = 8 0.2 M elements 4.47 / 4.06, 0.4 M 4.83 / 4.38, 0.8 M 5.39 / 5.41,
-// 1.6 M 7.32 / 7.71; P = 32 0.4 M 11.9 / 10.8, 1.6 M 21.6 / 22.5.  With the update the line lies further out, behind an all-gather that
-// follows at once or later: all reduce-scatters + updates, then all all-gathers of up to eight buckets of 150 / 300 / 550 / 850 tiles,
-// change in %: P = 4 -2 / -5 / -5 / -1, P = 8 -5 / -6 / -5 / -3, P = 16 -3 / -6 / -4 / -3, P = 32 -9 / -5 / +1 / -3, P = 48 -7 / -3 / +5 / +2,
-// P = 64 -7 / -7 / +4 / +1; iteration of one bucket P = 4 0 / -5 / -3 / +1, P = 8 -5 / -7 / -7 / -2, P = 32 -12 / -6 / -7 / -2, P = 64 -8 / -4 / -4 / -3;
-// one bucket of weights and short vectors, 15 to 90 % full, P = 3 to 64, 80 to 850 tiles -18 to +1.
+// 1.6 M 7.32 / 7.71; P = 32 0.4 M 11.9 / 10.8, 1.6 M 21.6 / 22.5.  With the update the line lies further out, behind an all-gather
+// that follows at once or later: all reduce-scatters + updates, then all all-gathers of up to eight buckets of 150 / 300 / 550 / 850
+// tiles, change in %: P = 4 -2 / -5 / -5 / -1, P = 8 -5 / -6 / -5 / -3, P = 16 -3 / -6 / -4 / -3, P = 32 -9 / -5 / +1 / -3, P = 48
+// -7 / -3 / +5 / +2, P = 64 -7 / -7 / +4 / +1; iteration of one bucket P = 4 0 / -5 / -3 / +1, P = 8 -5 / -7 / -7 / -2, P = 32
+// -12 / -6 / -7 / -2, P = 64 -8 / -4 / -4 / -3; one bucket of weights and short vectors, 15 to 90 % full, P = 3 to 64, 80 to 850 tiles
+// -18 to +1.
 // Short tensors, iteration in two launches: P = 9 60 of 400 elements 8.20 / 8.62, of 1000 8.90 / 9.33, of 1600 9.85 / 9.08;
 // P = 32 of 1000 17.7 / 18.5, of 1600 20.2 / 18.3; P = 64 of 1000 35.2 / 37.5, of 1600 35.6 / 38.4, of 2400 42.9 / 38.5.
-// Reduce-scatter + update P = 10 396 tensors of 1430 9.33 / 10.08; in a dozen tiles empty halves cost nothing (P = 8 2460 elements in 5
-// tensors 5.96 / 5.64).
+// Reduce-scatter + update P = 10 396 tensors of 1430 9.33 / 10.08; in a dozen tiles empty halves cost nothing (P = 8 2460 elements in
+// 5 tensors 5.96 / 5.64).
 inline bool half_tiles_filled(int64_t elems, int64_t tiles, int64_t whole)
 {
     return tiles <= 16 || some_whole(whole, tiles) || elems >= tiles * (tiles <= 200 ? 1024 : 1536);
@@ -130,7 +131,8 @@ constexpr int TILES_BEHIND = 4;
 // Offsets of a context's device tables in their one allocation: tiles first; from `uploaded` on, what the host sends (the
 // tiles, or the runs that a kernel cuts into them); layer places, gradient and parameter pointers; `end` bytes in all.
 // Every table starts on a multiple of 256 bytes.  Packed behind the runs, of 48 bytes each, the pointer tables started anywhere on
-// 16 bytes: ResNet-50, P = 8 fp32, a bucket at a time, us per iteration packed / aligned 355.2 / 354.5, 357.7 / 356.7 and 354.1 / 353.5 (spread 0.1).
+// 16 bytes: ResNet-50, P = 8 fp32, a bucket at a time, us per iteration packed / aligned 355.2 / 354.5, 357.7 / 356.7 and
+// 354.1 / 353.5 (spread 0.1).
 struct table_layout {
     size_t uploaded, places, grad, param, end;
 };
@@ -154,28 +156,31 @@ DEAR_HOST_DEVICE inline unsigned all_gather_part(unsigned r, unsigned run)
     return (r & ~((8u << run) - 1)) | (r & 7) << run | (r >> 3 & ((1u << run) - 1));
 }
 
-// The same where every XCD takes an eighth of the chunk, its parts in a row: len, the chunk's workgroups per replica, is a multiple of 8.
+// The same where every XCD takes an eighth of the chunk, its parts in a row: len, the chunk's workgroups per replica, is a multiple of
+// 8.
 DEAR_HOST_DEVICE inline unsigned all_gather_part_of_eighth(unsigned r, unsigned len) { return (r & 7) * (len >> 3) + (r >> 3); }
 
 // Where it is: an XCD then writes 2 MiB of a replica in a row and not every eighth 4 KiB, and of the lines that two
-// workgroups write in halves, at the ends of runs, both halves go through one L2.  Each next part = 1, the all-gather alone / a pass of
-// reduce-scatter with update and all-gather / dear_iteration, sets of buffers in turn, 20 ragged tensors: fp32 P = 4 2300 tiles
+// workgroups write in halves, at the ends of runs, both halves go through one L2.  Each next part = 1, the all-gather alone / a pass
+// of reduce-scatter with update and all-gather / dear_iteration, sets of buffers in turn, 20 ragged tensors: fp32 P = 4 2300 tiles
 // 0.94 / 0.99 / 0.99  4500 0.97 / 0.98 / 0.99, P = 8 2300 0.98 / 0.99 / 1.00  4500 0.99 / 1.00 / 0.99, P = 16 3000 0.97 / 0.99 / 0.99,
 // P = 32 900 0.91 / 0.96 / 0.96  1800 0.93 / 0.97 / 0.97  3000 0.95 / 0.98 / 0.97, bf16 P = 16 2300 0.97 / 0.98 / 0.98, P = 64 900
 // 0.93 / 0.94 / 0.94  1800 0.89 / 0.93 / 0.92; ResNet-50-shaped P = 64 0.95 / 0.95 / 0.95, in one launch 0.91 (6200 -> 6830 GB/s),
-// BERT-Base-shaped P = 16 0.96 / 0.99 / 0.99, in one launch 0.94.  One tensor, whose runs share no lines, gains nothing (P = 16 to 32 2000
-// to 5000 tiles 1.01 to 1.03).  2^run parts in a row (all_gather_part) cost 1-16 % up to run = 5, and 8 is level with eighths.
+// BERT-Base-shaped P = 16 0.96 / 0.99 / 0.99, in one launch 0.94.  One tensor, whose runs share no lines, gains nothing (P = 16 to 32
+// 2000 to 5000 tiles 1.01 to 1.03).  2^run parts in a row (all_gather_part) cost 1-16 % up to run = 5, and 8 is level with eighths.
 // Not below 2048 tiles, 32 MiB of w, whose values are read in the L2 of the XCD that wrote them, where each takes every eighth part:
-// the same state over and over fp32 P = 4 900 tiles dear_iteration 1.17, 1800 1.03, P = 8 900 1.10, 1300 1.03, 1800 1.00 (with update in
-// calls of their own 1.10, 1.08, 1.05), bf16 P = 8 900 1.19; with more replicas that weighs less: P = 12 1300 1.03, 1800 0.99, P = 16
-// 1300 1.01, 1800 0.99, P = 32 900 0.94, bf16 1.02, 1300 0.99.
-// Nor with many parts that short tensors leave empty, which give the XCDs unlike eighths: tensors of 900 elements, alone, P = 16 and 64,
-// 2250 tiles 1.04 and 1.06; weights with short vectors between them, 80 % full, P = 8 2050 / 2600 / 3300 / 5200 tiles 1.04 / 1.03 / 1.04 / 1.03, P = 16
-// 1.06 / 1.07 / 1.05 / 1.06, P = 24 1100 1.08, P = 64 960 / 2100 / 5300 1.07 / 1.07 / 1.07, though 6500 0.97, 0.93, - and 1.00.
-// Few replicas lose a little in long launches (alone, P = 4 9000 1.01), one and two in most (P = 1 2600 to 4000 1.03, P = 2 7800 1.04 to 1.05).
+// the same state over and over fp32 P = 4 900 tiles dear_iteration 1.17, 1800 1.03, P = 8 900 1.10, 1300 1.03, 1800 1.00 (with update
+// in calls of their own 1.10, 1.08, 1.05), bf16 P = 8 900 1.19; with more replicas that weighs less: P = 12 1300 1.03, 1800 0.99,
+// P = 16 1300 1.01, 1800 0.99, P = 32 900 0.94, bf16 1.02, 1300 0.99.
+// Nor with many parts that short tensors leave empty, which give the XCDs unlike eighths: tensors of 900 elements, alone, P = 16 and
+// 64, 2250 tiles 1.04 and 1.06; weights with short vectors between them, 80 % full, P = 8 2050 / 2600 / 3300 / 5200 tiles
+// 1.04 / 1.03 / 1.04 / 1.03, P = 16 1.06 / 1.07 / 1.05 / 1.06, P = 24 1100 1.08, P = 64 960 / 2100 / 5300 1.07 / 1.07 / 1.07, though
+// 6500 0.97, 0.93, - and 1.00.
+// Few replicas lose a little in long launches (alone, P = 4 9000 1.01), one and two in most (P = 1 2600 to 4000 1.03, P = 2 7800 1.04
+// to 1.05).
 // Nor where the parts do not end at the same lines in all replicas (dear_ctx_s::replicas_alike): ResNet-50-shaped P = 64, replicas at
-// multiples of 16 bytes that are none of 128 from one another 1.08, alike 0.94; 604 tensors on 16-byte boundaries P = 7 1.01 / 1.00 / 1.00,
-// on lines 0.98 / 0.96 / 0.97.
+// multiples of 16 bytes that are none of 128 from one another 1.08, alike 0.94; 604 tensors on 16-byte boundaries P = 7
+// 1.01 / 1.00 / 1.00, on lines 0.98 / 0.96 / 0.97.
 inline bool all_gather_in_eighths(int64_t elems, int64_t tiles, int64_t n_workers)
 {
     if (elems * 8 < tiles * DEAR_TILE_ELEMS * (tiles < 6000 ? 7 : 4)) return false;
@@ -200,14 +205,16 @@ inline all_gather_order all_gather_numbering(unsigned run, int64_t max_workgroup
 // kernel / two:
 //   one tensor a bucket  P = 4 2.3 M elements 211 / 216  9 M 169 / 168   P = 5 1.8 M 193 / 202  2.8 M 175.7 / 175.9  3.4 M 171 / 164
 //                        7.2 M 160 / 154
-//                        P = 8 1.6 M 171 / 169  1.75 M 152 / 153  2.1 M 149 / 145 (2 of 12 buckets, the others smaller, 251 / 257)  4.5 M 142 / 135
-//                        P = 12 0.9 M 153 / 166  1.3 M 161 / 153  (in 76 tensors 1.6 M 32.8 / 33.9)
-//                        P = 16 0.8 M 140 / 150  1 M 150 / 149  1.1 M 133 / 126  2.3 M 127 / 114   P = 32 0.9 M 89 / 92  1 M 105 / 99   P = 64 0.7 M 63 / 67  0.9 M 79 / 80  1 M 96 / 89
-//   tensors of 3500      P = 5 2.2 M 28.8 / 31.8  5 M 63.1 / 61.8   P = 8 2.2 M 38.6 / 40.7  5 M 86.2 / 82.0   P = 16 1 M 31.8 / 33.6  5 M 149 / 135
-//   tensors of 5000 (61 % full)  P = 8 2.2 M 45.4 / 46.6  5 M 90.5 / 97.8  16 M 294 / 299   P = 16 2.2 M 73 / 78   P = 32 2.2 M 131 / 141
-//   tensors of 3000 (73 %)       P = 5 5 M 62.1 / 64.9   P = 8 2.2 M 37.7 / 43.1  16 M 267 / 261   P = 12 2.2 M 50.8 / 56.3  5 M 117 / 114   P = 32 1 M 56 / 61
-//   tensors of 2400-9400 (74 %)  P = 6 5 M 76.4 / 72.0   P = 8 3.8 M 69.0 / 66.0
-//   weights and short vectors P = 6 3.5 M (78 %) 53.8 / 49.6, P = 8 2.5 M (89 %) 44.6 / 42.2  2.6 M (58 %) 53.0 / 51.9   P = 12 1.9 M (62 %) 50.3 / 52.4   P = 16 1.1 M (59 %) 36.5 / 40.9
+//                        P = 8 1.6 M 171 / 169  1.75 M 152 / 153  2.1 M 149 / 145 (2 of 12 buckets, the others smaller, 251 / 257)
+//                        4.5 M 142 / 135 P = 12 0.9 M 153 / 166  1.3 M 161 / 153  (in 76 tensors 1.6 M 32.8 / 33.9)
+//                        P = 16 0.8 M 140 / 150  1 M 150 / 149  1.1 M 133 / 126  2.3 M 127 / 114   P = 32 0.9 M 89 / 92  1 M 105 / 99
+//                        P = 64 0.7 M 63 / 67  0.9 M 79 / 80  1 M 96 / 89
+//   tensors of 3500      P = 5 2.2 M 28.8 / 31.8  5 M 63.1 / 61.8   P = 8 2.2 M 38.6 / 40.7  5 M 86.2 / 82.0   P = 16 1 M 31.8 / 33.6
+//   5 M 149 / 135 tensors of 5000 (61 % full)  P = 8 2.2 M 45.4 / 46.6  5 M 90.5 / 97.8  16 M 294 / 299   P = 16 2.2 M 73 / 78
+//   P = 32 2.2 M 131 / 141 tensors of 3000 (73 %)       P = 5 5 M 62.1 / 64.9   P = 8 2.2 M 37.7 / 43.1  16 M 267 / 261   P = 12 2.2 M
+//   50.8 / 56.3  5 M 117 / 114   P = 32 1 M 56 / 61 tensors of 2400-9400 (74 %)  P = 6 5 M 76.4 / 72.0   P = 8 3.8 M 69.0 / 66.0
+//   weights and short vectors P = 6 3.5 M (78 %) 53.8 / 49.6, P = 8 2.5 M (89 %) 44.6 / 42.2  2.6 M (58 %) 53.0 / 51.9   P = 12 1.9 M
+//   (62 %) 50.3 / 52.4   P = 16 1.1 M (59 %) 36.5 / 40.9
 //                        P = 32 2.6 M (58 %) 133 / 125
 //   tensors of 2500 (61 %)       P = 5 16 M 195 / 211   P = 8 16 M 273 / 293   P = 32 2.2 M 129 / 143
 // Beyond the largest all-gather the one kernel, whose grid is the tile count alone, still takes the call.
@@ -232,10 +239,12 @@ inline bool update_all_gather_splits(int64_t elems, int64_t tiles, int64_t whole
 //     P = 16 125 13.6 / 12.8  165 14.2 / 13.3  288 16.0 / 15.7  440 (60 % full) 36.5 / 37.9   P = 24 322 28.8 / 26.1  660 54.0 / 51.5
 //     P = 32 106 19.9 / 18.2  138 22.5 / 23.6  238 24.1 / 26.3   P = 48 87 (eleven buckets) 283 / 259  132 28.9 / 30.0
 //     P = 64 83 (nearly empty) 20.7 / 19.2  120 (two buckets) 65.8 / 66.7  138 37.4 / 43.1
-//   eight buckets (fewer from P = 32 on) of one tensor  P = 2 24 tiles 47.5 / 39.7  64 51.7 / 50.7  110 59.0 / 57.8  150 63.4 / 65.3   P = 4 24 52.8 / 43.8
-//     110 68.6 / 69.3  150 74.6 / 78.9   P = 8 24 62.6 / 51.5  110 84.0 / 84.8  150 99.0 / 101.1   P = 16 24 85.5 / 68.7  150 155.2 / 157.2
-//     P = 32 24 127 / 103  110 221 / 233   P = 64 24 193 / 189  64 246 / 252  97 109 / 111
-//   of tensors of one length, 3000  P = 4 64 61.1 / 52.1  128 68.9 / 66.3   P = 16 64 96 / 82  128 107 / 106  143 123 / 126;  900  P = 2 32 47.4 / 47.3
+//   eight buckets (fewer from P = 32 on) of one tensor  P = 2 24 tiles 47.5 / 39.7  64 51.7 / 50.7  110 59.0 / 57.8  150 63.4 / 65.3
+//   P = 4 24 52.8 / 43.8
+//     110 68.6 / 69.3  150 74.6 / 78.9   P = 8 24 62.6 / 51.5  110 84.0 / 84.8  150 99.0 / 101.1   P = 16 24 85.5 / 68.7  150
+//     155.2 / 157.2 P = 32 24 127 / 103  110 221 / 233   P = 64 24 193 / 189  64 246 / 252  97 109 / 111
+//   of tensors of one length, 3000  P = 4 64 61.1 / 52.1  128 68.9 / 66.3   P = 16 64 96 / 82  128 107 / 106  143 123 / 126;  900
+//   P = 2 32 47.4 / 47.3
 //     64 49.5 / 50.7   P = 8 56 60.8 / 60.0  72 65.4 / 65.7   P = 16 80 93.1 / 93.7  96 100 / 105   P = 24 104 141 / 132;  beyond
 //     P = 2 800 of 1200 13.3 / 17.7   P = 8 400 of 1200 15.6 / 19.3  800 24.9 / 32.8
 inline bool update_all_gather_quarters(int64_t elems, int64_t tiles, int64_t whole, int64_t P, int64_t max_workgroups)
@@ -262,8 +271,8 @@ bool dear_mark_runs(const dear_plan_s &pl, float *const *param_ptrs, dear_run *r
 // Parts of a tile in the reduce-scatter: one 16-byte vector a lane.
 inline int64_t reduce_scatter_split(bool bf16) { return DEAR_TILE_ELEMS / ((bf16 ? 8 : 4) * DEAR_BLOCK); }
 
-// Item that the workgroup of index b takes, in the reduce-scatter and the update: XCD b % 8 takes 2^run items in a row out of every 8 * 2^run, and what does not fill
-// such a group goes as it falls.
+// Item that the workgroup of index b takes, in the reduce-scatter and the update: XCD b % 8 takes 2^run items in a row out of every 8
+// * 2^run, and what does not fill such a group goes as it falls.
 DEAR_HOST_DEVICE inline unsigned item_in_rows(unsigned b, unsigned run, unsigned n_items)
 {
     const unsigned group = 8u << run, first = b & ~(group - 1);
@@ -272,12 +281,14 @@ DEAR_HOST_DEVICE inline unsigned item_in_rows(unsigned b, unsigned run, unsigned
 }
 
 // The update's logarithm of the number of items (blocks of 1024 elements) in a row on an XCD: 2 MiB of each stream.  As they fall =
-// 1, 64 / 256 / 512 / 1024 / 4096 in a row, sets of buffers in turn, the update alone: 336 M elements 1.03 / 0.95 / 0.96 / 0.97 / 0.97, 110 M 0.94 / 0.93 / 0.93 /
-// 0.96 / 0.99, 64 M 0.95 / 0.94 / 0.92 / 0.97 / 1.03, 32 M 0.94 / 0.95 / 0.94 / 1.01 / 1.00, 25 M 0.99 / 0.96 / 0.95 / 1.03 / 1.00.  Pass of the three phases, 512: bf16 P = 8
-// 336 M and 32 M 0.99, P = 16 110 M 0.99, P = 4 64 M 0.97, P = 64 25 M 1.00; one state over and over 0.99 / 1.00 / 0.99 / 0.98 / 1.00.  Shorter launches lie
-// within 2 % either way (12 M 1.00 with 512, 8 M 1.00 with 256, one state over and over 1.02; 3 M 1.01 and 1.02) and keep their order.
-// So do launches over some of the buckets, where every worker's row begins at a place of its own: 16 rows of BERT-Base-shaped buckets 6560 GB/s as they
-// fall, 6337 with 512, 8 rows of BERT-Large-shaped ones 6315 and 6247.
+// 1, 64 / 256 / 512 / 1024 / 4096 in a row, sets of buffers in turn, the update alone: 336 M elements 1.03 /
+// 0.95 / 0.96 / 0.97 / 0.97, 110 M 0.94 / 0.93 / 0.93 / 0.96 / 0.99, 64 M 0.95 / 0.94 / 0.92 / 0.97 / 1.03, 32 M
+// 0.94 / 0.95 / 0.94 / 1.01 / 1.00, 25 M 0.99 / 0.96 / 0.95 / 1.03 / 1.00.  Pass of the three phases, 512: bf16 P = 8 336 M and 32 M
+// 0.99, P = 16 110 M 0.99, P = 4 64 M 0.97, P = 64 25 M 1.00; one state over and over 0.99 / 1.00 / 0.99 / 0.98 / 1.00.  Shorter
+// launches lie within 2 % either way (12 M 1.00 with 512, 8 M 1.00 with 256, one state over and over 1.02; 3 M 1.01 and 1.02) and keep
+// their order.
+// So do launches over some of the buckets, where every worker's row begins at a place of its own: 16 rows of BERT-Base-shaped buckets
+// 6560 GB/s as they fall, 6337 with 512, 8 rows of BERT-Large-shaped ones 6315 and 6247.
 inline unsigned shard_update_run(int64_t rows, int64_t n_items) { return rows > 1 || n_items < 12000 ? 0 : 9; }
 
 // How an unbounded reduce-scatter goes: replicas in flight per lane (0: the batch kernel), workgroups that may share a CU (0: as
@@ -288,20 +299,23 @@ struct reduce_scatter_shape {
 };
 
 // Where the batch kernel is the faster one still, below 2048 tiles: reduce_scatter_kernel gains by loads that never drain, and by
-// taking the elements of vectors that a run cuts (`cut`: an eighth of the tiles begin or end inside one) along with the vectors, where the
-// batch kernel has a pass of its own for them.  With up to eight replicas all loads of a workgroup are in flight at once anyway, so
-// with nothing cut there is nothing to gain, and with the update w and v are loads that never stop beside them.  Seven
+// taking the elements of vectors that a run cuts (`cut`: an eighth of the tiles begin or end inside one) along with the vectors, where
+// the batch kernel has a pass of its own for them.  With up to eight replicas all loads of a workgroup are in flight at once anyway,
+// so with nothing cut there is nothing to gain, and with the update w and v are loads that never stop beside them.  Seven
 // replicas are two rounds of loads instead of one.  A launch that fills the chip less than once, and not by far, likes fewer, longer
-// workgroups.  4256 launches (P = 1 to 64, 20 to 2000 tiles; one tensor, five, ragged lists, weights with short vectors between them; buffers
-// in turn, cold), batch kernel = 1, mean (worst) of what would go instead:
-//   nothing cut, with update, fp32  P = 3 1.02 (1.14)  5 1.02 (1.10)  6 1.01 (1.11)  7 1.03 (1.21)  8 1.02 (1.10), above 160 tiles 1.00
+// workgroups.  4256 launches (P = 1 to 64, 20 to 2000 tiles; one tensor, five, ragged lists, weights with short vectors between them;
+// buffers in turn, cold), batch kernel = 1, mean (worst) of what would go instead:
+//   nothing cut, with update, fp32  P = 3 1.02 (1.14)  5 1.02 (1.10)  6 1.01 (1.11)  7 1.03 (1.21)  8 1.02 (1.10), above 160 tiles
+//   1.00
 //     bf16  P = 3 1.05 (1.18)  5, 6 and 7 1.02 (1.25)  8 1.01 (1.12), 1 and 2 0.97, but from 128 to 700 tiles 1.02 (1.07)
-//   without, fp32 P = 3 1.04 (1.12)  4 to 8 below 160 tiles 1.04 (1.24), above 0.98;  bf16 P = 2 1.01 (1.13)  3 to 8 1.07 (1.24) and 0.94
-//   P = 7 below 160 tiles, cut  fp32 1.02 (1.07)  bf16 1.04 (1.09)
+//   without, fp32 P = 3 1.04 (1.12)  4 to 8 below 160 tiles 1.04 (1.24), above 0.98;  bf16 P = 2 1.01 (1.13)  3 to 8 1.07 (1.24) and
+//   0.94 P = 7 below 160 tiles, cut  fp32 1.02 (1.07)  bf16 1.04 (1.09)
 //   nothing cut, fp32 P >= 12 with update, 64 to 160 tiles 1.06 (1.38), P >= 24 without 1.08 (1.39), P = 9 to 16 without 0.94
-//   nothing cut, bf16 with update P = 12 and 16 below 700 tiles 1.02 (1.13), P >= 24 from 132 to 288 1.04 (1.16); without, P = 12 and 16
+//   nothing cut, bf16 with update P = 12 and 16 below 700 tiles 1.02 (1.13), P >= 24 from 132 to 288 1.04 (1.16); without, P = 12 and
+//   16
 //     below 130 1.00 (1.09), P >= 24 from 132 to 160 1.02 (1.14)
-//   cut: fp32 P <= 8 below 160 tiles 0.97, from 9 on 0.84; bf16 from 9 on 0.82, P = 4 without update below 160 1.09, P = 5 to 7 with it
+//   cut: fp32 P <= 8 below 160 tiles 0.97, from 9 on 0.84; bf16 from 9 on 0.82, P = 4 without update below 160 1.09, P = 5 to 7 with
+//   it
 //     from 40 to 300 1.05, P = 4 and 8 from 110 to 300 1.01
 inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles, bool cut)
 {
@@ -322,48 +336,64 @@ inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles
 // HBM serves P streams at once best with 32 to 40 KiB of loads in flight per CU, as long as they never stop: D loads of 4 KiB for
 // each of the workgroups that share a CU (fp32 at `residency` 4: five of them).  With more the streams get into each other's way,
 // with fewer the latency shows; a launch that does not fill the chip wants more per workgroup.  So two replicas a lane and three or
-// four workgroups a CU in long launches, four or eight replicas in short ones.  Depth / workgroups a CU (- as many as fit, r in rows), batch
-// kernel = 1, means over the four kinds of lists, by tiles (the launches of batch_kernel_stays, and 1266 longer ones):
-//   fp32 without update  P = 9  20-45 8/- 0.81  4/- 0.88   64-90 0.84  0.83   P = 16  46-63 8/- 0.84  4/- 0.94   64-90 0.95  0.91   P = 32  46-63 0.77
-//       0.93   64-90 0.93  0.91   P = 16  91-127 4/- 0.94  2/- 1.13   128-170 0.94  0.91   P = 32  91-127 0.94  1.21   128-170 0.97  0.96
-//     320-1100 4/- | 2/- | 2/4  P = 4 1.00 | 1.00 | 1.06   5 0.98 | 1.00 | 1.07   6 0.99 | 0.99 | 1.03   7 0.99 | 1.00 | 1.05   8 0.98 | 1.00 | 1.02
-//     395-480 the same  P = 16 0.99 | 1.05 | 0.98   24 0.99 | 1.04 | 0.96   64 1.00 | 1.05 | 0.94
-//     3000-5900 2/4r | 2/3r | 2/-r | 4/2  P = 4 0.99 | 1.03 | 0.98 | 1.13   6 0.95 | 0.97 | 0.98 | 1.06   8 0.94 | 0.96 | 0.98 | 0.99   12 0.94 | 0.97 | 1.01 | 0.98
-//     24000 and more, one tensor, ragged, BERT-Base-shaped, the same  P = 8 1.02 | 0.99 | - | 0.98   12 1.02 | 1.01 | - | 1.01   16 1.03 | 1.02 | - | 0.99
-//   fp32 with update  3000-13000 2/4r | 2/3r | 2/-r | 4/2  P = 4 0.96 | 0.96 | 0.98 | 1.00   6 0.96 | 0.95 | 1.00 | 1.01   8 0.98 | 0.96 | 1.02 | 1.00
-//       12 0.99 | 0.98 | 1.05 | 1.02   16 0.98 | 0.96 | 1.04 | 0.99;  24000 and more P = 8 1.03 | 0.99 | - | 1.00, dear_iteration 1.03 | 1.00 | - | 1.00
-//   bf16 without  P = 16  80-109 8/- 0.93  4/- 1.00   110-131 0.94  0.94   P = 24  110-131 0.86  0.93   132-160 0.97  0.92   P = 64  110-131 0.71  0.88
-//       132-160 0.91  0.92   P = 16  161-287 4/- 0.87  2/- 1.00   288-400 0.95  0.91   P = 64  161-287 0.77  1.03   288-400 0.88  0.86
-//     780-1700 4/- | 2/- | 2/4r | 2/3r  P = 8 0.98 | 1.00 | 0.99 | 1.04   12 0.96 | 0.98 | 0.96 | 1.01   24 0.99 | 1.00 | 0.95 | 0.99   64 1.00 | 1.01 | 0.94 | 0.96
-//     1900-7000 2/4r | 2/3r  P = 8 0.97 | 1.01   12 0.95 | 0.99   24 0.94 | 0.97
-//   bf16 with  780-1700, as without  P = 8 0.98 | 0.99 | 0.98 | 1.01   24 0.99 | 0.98 | 0.96 | 0.98   64 0.99 | 0.98 | 0.93 | 0.93;  1900-7000 2/4r | 2/3r  P = 8
-//       0.97 | 0.98   12 0.98 | 0.98   24 0.97 | 0.96;  1000-2050 4/- | 4/3  P = 5 0.97 | 1.00   6 0.98 | 0.98   7 0.98 | 1.01
+// four workgroups a CU in long launches, four or eight replicas in short ones.  Depth / workgroups a CU (- as many as fit, r in rows),
+// batch kernel = 1, means over the four kinds of lists, by tiles (the launches of batch_kernel_stays, and 1266 longer ones):
+//   fp32 without update, 8/- | 4/- | 2/-
+//     P = 9   20-45  0.81 | 0.88 | 1.07   46-63 0.80 | 0.85 | 1.03    64-90   0.84 | 0.83 | 0.97   128-170 0.90 | 0.89 | 0.90
+//     P = 16  46-63  0.84 | 0.94 | 1.26   64-90 0.95 | 0.91 | 1.16    91-127  0.99 | 0.94 | 1.13   128-170 0.95 | 0.94 | 0.91
+//     P = 32  46-63  0.77 | 0.93 | 1.36   64-90 0.93 | 0.91 | 1.22    91-127  0.99 | 0.94 | 1.21   128-170 0.98 | 0.97 | 0.96
+//   4/- | 2/- | 2/4
+//     320-1100  P = 4  1.00 | 1.00 | 1.06   P = 5  0.98 | 1.00 | 1.07   P = 6  0.99 | 0.99 | 1.03   P = 7  0.99 | 1.00 | 1.05
+//               P = 8  0.98 | 1.00 | 1.02   395-480  P = 16 0.99 | 1.05 | 0.98   P = 24 0.99 | 1.04 | 0.96   P = 64 1.00 | 1.05 | 0.94
+//   2/4r | 2/3r | 2/-r | 4/2
+//     3000-5900  P = 4 0.99 | 1.03 | 0.98 | 1.13   P = 6 0.95 | 0.97 | 0.98 | 1.06   P = 8 0.94 | 0.96 | 0.98 | 0.99
+//                P = 12 0.94 | 0.97 | 1.01 | 0.98   P = 16 0.96 | 0.98 | 1.02 | 0.99
+//     24000 and more (one tensor, ragged, BERT-Base-shaped)  P = 8 1.02 | 0.99 | - | 0.98   P = 12 1.02 | 1.01 | - | 1.01
+//                P = 16 1.03 | 1.02 | - | 0.99
+//   fp32 with update, the same
+//     3000-13000 P = 4 0.96 | 0.96 | 0.98 | 1.00   P = 6 0.96 | 0.95 | 1.00 | 1.01   P = 8 0.98 | 0.96 | 1.02 | 1.00
+//                P = 12 0.99 | 0.98 | 1.05 | 1.02   P = 16 0.98 | 0.96 | 1.04 | 0.99
+//     24000 and more  P = 8 1.03 | 0.99 | - | 1.00, dear_iteration 1.03 | 1.00 | - | 1.00
+//   bf16 without, 8/- | 4/- | 2/-
+//     P = 16  80-109 0.93 | 1.00 | 1.31   110-131 0.94 | 0.94 | 1.21   161-287 0.91 | 0.87 | 1.00   288-400 0.96 | 0.95 | 0.91
+//     P = 24  80-109 0.85 | 0.94 | 1.30   110-131 0.86 | 0.93 | 1.27   132-160 0.97 | 0.92 | 1.21   161-287 0.86 | 0.82 | 0.98
+//     P = 64  80-109 0.70 | 0.92 | 1.45   110-131 0.71 | 0.88 | 1.36   132-160 0.91 | 0.92 | 1.33   161-287 0.81 | 0.77 | 1.03
+//   4/- | 2/- | 2/4r | 2/3r, without update, then with
+//     780-1700   P = 8 0.98 | 1.00 | 0.99 | 1.04, 0.98 | 0.99 | 0.98 | 1.01   P = 12 0.96 | 0.98 | 0.96 | 1.01, 0.99 | 0.99 | 0.99 |
+//     1.02
+//                P = 24 0.99 | 1.00 | 0.95 | 0.99, 0.99 | 0.98 | 0.96 | 0.98   P = 64 1.00 | 1.01 | 0.94 | 0.96, 0.99 | 0.98 | 0.93 |
+//                0.93
+//     1900-7000  P = 8 - | - | 0.97 | 1.01, - | - | 0.97 | 0.98   P = 12 - | - | 0.95 | 0.99, - | - | 0.98 | 0.98
+//     1000-2050 with update, 4/- | 4/3  P = 5 0.97 | 1.00   P = 6 0.98 | 0.98   P = 7 0.98 | 1.01
 // Tensors shorter than a tile leave most parts empty: a workgroup takes whole tiles then.  900 elements each, P = 8  560 tiles fp32
 // 13.3 -> 6.9 us, 2230 42 -> 20, bf16 2230 22 -> 21; P = 64  130 tiles 0.62.  A whole tile among them would keep its workgroup four
 // times as long (P = 32, 101 tiles 22 % full 10.2 -> 13.5), and from a quarter (many tiles: two fifths) full on there are enough
 // workgroups' worth (P = 64, 162 tiles 38 % full 21.7 -> 30).
 // Sixty-four items in a row on an XCD, 256 KiB of each replica, whose lines of the tile table its L2 then has, and whose pages its
-// address translation: BERT-Large-shaped P = 8 bf16 5683 -> 6085 GB/s, with update 5787 -> 6063, BERT-Base-shaped P = 8 fp32 5731 -> 5909.
+// address translation: BERT-Large-shaped P = 8 bf16 5683 -> 6085 GB/s, with update 5787 -> 6063, BERT-Base-shaped P = 8 fp32 5731 ->
+// 5909.
 // Not where w of a launch fits the L2s (2048 tiles, 32 MiB): the all-gather behind it reads w in the L2 of the XCD that wrote it, if
 // both go through the tiles as they fall.  Pass = reduce-scatter with update, all-gather, one state over and over / three in turn,
 // batch kernel = 1, as they fall | in rows: fp32 P = 2 900 tiles 0.98 / 0.99 | 1.15 / 0.98, 1800 1.01 / 1.01 | 1.09 / 0.98, P = 8 600
 // 1.03 / 1.02 | 1.07 / 1.02, 900 1.01 / 1.01 | 1.08 / 0.98, 1800 1.00 / 1.01 | 1.04 / 0.98, P = 16 400 1.02 / 1.02 | 1.04 / 1.02,
 // 900 0.98 / 0.97 | 0.99 / 0.94; dear_iteration P = 8 800 1.02 / 1.03 | 1.13 / 1.03, bf16 P = 6 800 1.00 / 0.99 | 1.21 / 0.98; more
 // replicas leave little of it: P = 32 fp32 900 0.98 / 0.96 | 0.95 / 0.92, 400 1.00 / 0.99 | 1.01 / 0.99.
-// fp32 from 8 to 16 replicas on, 6000 tiles and more: four replicas, two workgroups, as they fall, whose rows of several replicas do not drift
-// apart.  Models' lists, 4/2 | 2/4r (without update) or 2/3r (with), and dear_iteration: ResNet-50-shaped (6342 tiles) P = 8 0.98 | 0.98, 1.00 | 0.99,
-// 0.99 | 1.01, P = 12 0.97 | 0.98, 1.02 | 1.01, 0.99 | 0.99, P = 16 0.99 | 1.01, 0.99 | 0.98, 0.98 | 0.98; Inception-v4-shaped (10732) P = 8
-// 0.99 | 0.97, 1.00 | 1.00, 0.97 | 0.99, P = 12 0.98 | 0.98, 1.01 | 1.00, 0.96 | 0.98, P = 16 0.99 | 1.00, 0.99 | 1.00, 0.95 | 0.96; BERT-Base-shaped (26988)
-// P = 8 0.98 | 1.00, 0.99 | 0.99, 0.99 | 1.01, P = 16 0.99 | 1.03, 0.99 | 0.97, 1.00 | 0.99; below, DenseNet-201-shaped (5242) P = 8 0.97 | 0.92,
-// 1.00 | 0.99, 0.99 | 0.97.  One tensor of 6000 to 13000 tiles likes rows (P = 8 with update 1.00 | 0.96).  bf16 from 6000 tiles on 2/3r: BERT-Large-shaped all
-// buckets 2/4r 0.91, 2/3r 0.89, with update 0.95 and 0.94, 12000 to 40000 tiles P = 8 0.97 and 0.94, 1.00 and 0.98, P = 16 1.03 and 1.00, 1.01 and 0.99.
+// fp32 from 8 to 16 replicas on, 6000 tiles and more: four replicas, two workgroups, as they fall, whose rows of several replicas do
+// not drift apart.  Models' lists, 4/2 | 2/4r (without update) or 2/3r (with), and dear_iteration: ResNet-50-shaped (6342 tiles) P = 8
+// 0.98 | 0.98, 1.00 | 0.99, 0.99 | 1.01, P = 12 0.97 | 0.98, 1.02 | 1.01, 0.99 | 0.99, P = 16 0.99 | 1.01, 0.99 | 0.98, 0.98 | 0.98;
+// Inception-v4-shaped (10732) P = 8 0.99 | 0.97, 1.00 | 1.00, 0.97 | 0.99, P = 12 0.98 | 0.98, 1.01 | 1.00, 0.96 | 0.98, P = 16 0.99 |
+// 1.00, 0.99 | 1.00, 0.95 | 0.96; BERT-Base-shaped (26988) P = 8 0.98 | 1.00, 0.99 | 0.99, 0.99 | 1.01, P = 16 0.99 | 1.03, 0.99 |
+// 0.97, 1.00 | 0.99; below, DenseNet-201-shaped (5242) P = 8 0.97 | 0.92, 1.00 | 0.99, 0.99 | 0.97.  One tensor of 6000 to 13000 tiles
+// likes rows (P = 8 with update 1.00 | 0.96).  bf16 from 6000 tiles on 2/3r: BERT-Large-shaped all buckets 2/4r 0.91, 2/3r 0.89, with
+// update 0.95 and 0.94, 12000 to 40000 tiles P = 8 0.97 and 0.94, 1.00 and 0.98, P = 16 1.03 and 1.00, 1.01 and 0.99.
 // In dear_iteration where the all-gather comes next (caches_w) four replicas a lane and as many workgroups as fit, below 1600 tiles
-// (fp32 from 8 replicas on 2048): fp32 P = 8 350 / 550 / 800 / 1200 tiles 1.02 / 1.01 / 0.99 / 0.99, two replicas 1.03 / 1.02 / 1.00 / 0.99
-// and with four workgroups 1.07 / 1.04 / 1.02 / 1.00, P = 9 to 12 1600 two in rows 1.02 to 1.03; bf16 P = 6 and 8 at 550 1.03 (the batch
-// kernel up to 700), P = 9 to 20 320 to 450 1.02 to 1.05 (the rule without caches_w).  Beyond 2048 tiles 2/4r | 2/3r | 2/-r: 604 ragged tensors bf16
-// P = 5 0.99 | 1.01 | 1.01, P = 6 0.99 | 1.01 | 1.02, P = 7 0.97 | 0.98 | 0.99, P = 8 1.00 | 1.00 | -, BERT-Large-shaped P = 8 0.98 | 0.98 | 0.99; fp32
-// ResNet-50-, Inception-v4- and DenseNet-201-shaped P = 4 0.99 | 0.98 | -, 1.00 | 1.00 | -, with gbar 1.03 | 1.01 | -, 0.99 | 1.01 | -, P = 5 1.00 | 1.00 | -
-// and 1.00 | 1.01 | -, P = 7 1.01 | 1.02 | - and 0.99 | 1.01 | -.
+// (fp32 from 8 replicas on 2048): fp32 P = 8 350 / 550 / 800 / 1200 tiles 1.02 / 1.01 / 0.99 / 0.99, two replicas
+// 1.03 / 1.02 / 1.00 / 0.99 and with four workgroups 1.07 / 1.04 / 1.02 / 1.00, P = 9 to 12 1600 two in rows 1.02 to 1.03; bf16 P = 6
+// and 8 at 550 1.03 (the batch kernel up to 700), P = 9 to 20 320 to 450 1.02 to 1.05 (the rule without caches_w).  Beyond 2048 tiles
+// 2/4r | 2/3r | 2/-r: 604 ragged tensors bf16 P = 5 0.99 | 1.01 | 1.01, P = 6 0.99 | 1.01 | 1.02, P = 7 0.97 | 0.98 | 0.99, P = 8 1.00
+// | 1.00 | -, BERT-Large-shaped P = 8 0.98 | 0.98 | 0.99; fp32 ResNet-50-, Inception-v4- and DenseNet-201-shaped P = 4 0.99 | 0.98 |
+// -, 1.00 | 1.00 | -, with gbar 1.03 | 1.01 | -, 0.99 | 1.01 | -, P = 5 1.00 | 1.00 | - and 1.00 | 1.01 | -, P = 7 1.01 | 1.02 | - and
+// 0.99 | 1.01 | -.
 inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, bool caches_w, int64_t P, int64_t elems, int64_t tiles,
                                                     int64_t whole, int64_t cut_tiles)
 {
@@ -404,18 +434,21 @@ inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, boo
 // dear_iteration, they are in this XCD's L2.  The more replicas, and the emptier the tiles, the more the rounding to 16 parts costs.
 // One / two in a row:
 //   dear_iteration, us, one bucket of 100 / 200 / 400 / 850 full tiles  P = 8 8.5 / 8.3  12.6 / 12.1  22.1 / 20.1  39.5 / 38.4
-//     P = 24 16.0 / 16.0  24.7 / 24.2  45.9 / 44.4  92.3 / 88.7   P = 40 23.4 / 24.4  36.8 / 37.2  71.6 / 69.5  144 / 145   P = 48 28.5 / 28.9  43.9 / 45.2  82.5 / 83.1
-//     P = 64 38.7 / 39.4  57.4 / 59.0  108 / 109  225 / 221;  weights and short vectors, change in %: P = 3 -7 to 0, P = 8 up to 150 tiles 0, 340 to 430 full
-//     ones -4 to -8, P = 12 and 16 up to 230 tiles +1 to +3, 390 full ones -4, P = 24 +1 to +3, P = 32 +1 to +4, P = 48 and 64 +3 to +5
-//   all reduce-scatters, then all all-gathers, change of the whole pass in %: eight buckets or fewer of 40 / 100 / 200 / 400 / 850 full tiles
-//     P = 4 -7 / -3 / -2 / 0 / 0   P = 8 -9 / -4 / 0 / 0 / -1   P = 16 -3 / -2 / 0 / +1 / -2   P = 24 0 / 0 / +2 / +2 / -1   P = 32 +1 / +1 / +2 / +3 / -1
-//     P = 48 -1 / +1 / +3 / +3 / -1   P = 64 +2 / +3 / +3 / +3 / +3;  weights and short vectors P = 3 and 4 -6 to 0, P = 8 -3 to +2, with an update between
-//     +1 to +2.5, P = 12 and 16 +1 to +3, from P = 24 on +2 to +5
-// Beyond 1024 tiles where the launch before goes in halves of tiles as they fall; one / two in a row, dear_iteration, cold, change of the
-// whole pass against the batch kernel's in %, 1140 ragged tiles, 1200 of one tensor, 1520 ragged: P = 4 -5 / -8, -2 / -8, -5 / -9, P = 6 -3 / -8,
-// 0 / -2, -2 / -5, P = 8 -2 / -4, 0 / 0, -2 / -4, P = 12 -2 / -4, -1 / 0, -3 / -4, P = 16 -1 / -2, +1 / +3, 0 / -2; calls of their own 0 / +1.
-// Up to 1024 tiles also where that launch goes in rows (P = 24 660 full tiles +3 / 0, 910 +3 / 0, ragged 630 -2 / -1, 880 0 / -1, weights and
-// short vectors 660 -1 / 0, P = 32 670 and 930 full +5 / 0).
+//     P = 24 16.0 / 16.0  24.7 / 24.2  45.9 / 44.4  92.3 / 88.7   P = 40 23.4 / 24.4  36.8 / 37.2  71.6 / 69.5  144 / 145   P = 48
+//     28.5 / 28.9  43.9 / 45.2  82.5 / 83.1 P = 64 38.7 / 39.4  57.4 / 59.0  108 / 109  225 / 221;  weights and short vectors, change
+//     in %: P = 3 -7 to 0, P = 8 up to 150 tiles 0, 340 to 430 full ones -4 to -8, P = 12 and 16 up to 230 tiles +1 to +3, 390 full
+//     ones -4, P = 24 +1 to +3, P = 32 +1 to +4, P = 48 and 64 +3 to +5
+//   all reduce-scatters, then all all-gathers, change of the whole pass in %: eight buckets or fewer of 40 / 100 / 200 / 400 / 850
+//   full tiles
+//     P = 4 -7 / -3 / -2 / 0 / 0   P = 8 -9 / -4 / 0 / 0 / -1   P = 16 -3 / -2 / 0 / +1 / -2   P = 24 0 / 0 / +2 / +2 / -1   P = 32
+//     +1 / +1 / +2 / +3 / -1 P = 48 -1 / +1 / +3 / +3 / -1   P = 64 +2 / +3 / +3 / +3 / +3;  weights and short vectors P = 3 and 4 -6
+//     to 0, P = 8 -3 to +2, with an update between +1 to +2.5, P = 12 and 16 +1 to +3, from P = 24 on +2 to +5
+// Beyond 1024 tiles where the launch before goes in halves of tiles as they fall; one / two in a row, dear_iteration, cold, change of
+// the whole pass against the batch kernel's in %, 1140 ragged tiles, 1200 of one tensor, 1520 ragged: P = 4 -5 / -8, -2 / -8, -5 / -9,
+// P = 6 -3 / -8, 0 / -2, -2 / -5, P = 8 -2 / -4, 0 / 0, -2 / -4, P = 12 -2 / -4, -1 / 0, -3 / -4, P = 16 -1 / -2, +1 / +3, 0 / -2;
+// calls of their own 0 / +1.
+// Up to 1024 tiles also where that launch goes in rows (P = 24 660 full tiles +3 / 0, 910 +3 / 0, ragged 630 -2 / -1, 880 0 / -1,
+// weights and short vectors 660 -1 / 0, P = 32 670 and 930 full +5 / 0).
 inline unsigned all_gather_run(int grad_bytes, bool caches_w, int64_t max_workgroups, int64_t P, int64_t elems, int64_t tiles,
                                int64_t whole, int64_t cut_tiles, int64_t n_workers, bool behind_update)
 {
@@ -462,11 +495,12 @@ inline bool iteration_caches_w(int grad_bytes, int64_t P, int64_t group_tiles, i
 
 // A bucket beyond ITERATION_TILES is handled in pieces of its tiles, whatever layers and shards they belong to, if that
 // leaves each piece's w in the last-level cache for its all-gather.  us per iteration without and with gbar, one launch pair /
-// pieces, one bucket (two runs of one side differ by up to 5 %): bf16 P = 3 50 M 321 / 295 and 370 / 338, 100 M 640 / 586 and 740 / 674, P = 4 50 M 369 / 344
-// and 419 / 386, P = 5 36 M 295 / 281 and 332 / 312, P = 6 60 M 543 / 511 and 610 / 561, P = 8 50 M 536 / 524 and 577 / 554, 110 M 1155 / 1128 and
-// 1263 / 1197; with a bounded grid of 256 P = 3 50 M 336 / 322 and 385 / 365, P = 8 110 M 1442 / 1328 and 1537 / 1404, of 1024 P = 8 60 M 803 / 724.
-// Not where w is stored non-temporally anyway: bf16 P = 16 100 M 1766 / 1768 and 1868 / 1848, fp32 P = 5 36 M 336 / 344 and 359 / 366, P = 8 100 M 1284 / 1312
-// and 1370 / 1388.  Pieces of 4096 and 12288 tiles are level to 1 %.
+// pieces, one bucket (two runs of one side differ by up to 5 %): bf16 P = 3 50 M 321 / 295 and 370 / 338, 100 M 640 / 586 and
+// 740 / 674, P = 4 50 M 369 / 344 and 419 / 386, P = 5 36 M 295 / 281 and 332 / 312, P = 6 60 M 543 / 511 and 610 / 561, P = 8 50 M
+// 536 / 524 and 577 / 554, 110 M 1155 / 1128 and 1263 / 1197; with a bounded grid of 256 P = 3 50 M 336 / 322 and 385 / 365, P = 8 110
+// M 1442 / 1328 and 1537 / 1404, of 1024 P = 8 60 M 803 / 724.
+// Not where w is stored non-temporally anyway: bf16 P = 16 100 M 1766 / 1768 and 1868 / 1848, fp32 P = 5 36 M 336 / 344 and 359 / 366,
+// P = 8 100 M 1284 / 1312 and 1370 / 1388.  Pieces of 4096 and 12288 tiles are level to 1 %.
 inline int64_t iteration_pieces(int grad_bytes, int64_t P, int64_t group_tiles, int64_t all_tiles)
 {
     if (!iteration_caches_w(grad_bytes, P, ITERATION_TILES, all_tiles) || grad_bytes != 2) return 1;
@@ -495,26 +529,29 @@ inline bool iteration_updates_apart(int grad_bytes, int64_t P, int64_t group_til
 //         P = 4 1 M 11.3 / 9.8  3 M 26.8 / 26.8  6 M 48.1 / 50.0  20 M 155 / 160  50 M 402 / 383 (with gbar 429 / 430)
 //         P = 8 0.2 M 7.5 / 6.7  1 M 15.9 / 15.2  1.5 M 22.2 / 22.8  6 M 78.8 / 85.5  P = 12 0.5 M 13.4 / 13.2  1 M 22.6 / 23.8
 //         P = 16 0.2 M 11.3 / 11.8  1 M 27.1 / 30.8
-//         P = 8 from 6 to 9 M copied elements, where only 240 to 258 tiles, of four workgroups each, fill the 256 CUs evenly: one tensor 223 tiles 13.1 / 14.1  242 13.7 / 13.3  258 14.9 / 13.8  262 15.8 / 16.1  277 16.0 / 17.2, 23 tensors
-//         230 14.3 / 14.2  248 15.4 / 14.3  257 15.6 / 14.4  267 16.5 / 16.7  281 16.9 / 17.4
-//         open tiles: P = 8 1 M in 500 tensors 27.3 / 22.4, 2 M in 200 34.2 / 34.1, 3 M in 500 50.2 / 50.7;
-//         P = 16 1 M in 500 47.8 / 39.7, in 60 29.0 / 32.0, 3 M in 500 86.3 / 93.2
+//         P = 8 from 6 to 9 M copied elements, where only 240 to 258 tiles, of four workgroups each, fill the 256 CUs evenly: one
+//         tensor 223 tiles 13.1 / 14.1  242 13.7 / 13.3  258 14.9 / 13.8  262 15.8 / 16.1  277 16.0 / 17.2, 23 tensors 230 14.3 / 14.2
+//         248 15.4 / 14.3  257 15.6 / 14.4  267 16.5 / 16.7  281 16.9 / 17.4 open tiles: P = 8 1 M in 500 tensors 27.3 / 22.4, 2 M in
+//         200 34.2 / 34.1, 3 M in 500 50.2 / 50.7; P = 16 1 M in 500 47.8 / 39.7, in 60 29.0 / 32.0, 3 M in 500 86.3 / 93.2
 //   bf16  P = 2 1 M 8.9 / 6.6  6 M 33.4 / 31.0  20 M 92.2 / 97.1  30 M 150 / 145  100 M 514 / 481
 //         P = 4 1 M 10.7 / 8.7  3 M 24.1 / 22.8  6 M 42.8 / 43.9  P = 8 0.5 M 10.3 / 9.2  1.5 M 19.3 / 18.5  3 M 34.3 / 35.2
 //         P = 12 0.5 M 13.2 / 12.8  1 M 18.6 / 19.2  P = 16 0.2 M 11.2 / 11.9  1 M 22.9 / 25.3, in 500 tensors 46.2 / 37.7
-// From 9 (bf16) or 10 replicas on a launch of few tiles is slower so: each of its few workgroups writes them all, one after another.  One
-// launch behind start of the two, GPU time without gbar:
-//   fp32  P = 12 20 tiles 7.5 / 8.1  33 6.8 / 6.2   P = 16 26 tiles 7.7 / 8.6  46 9.0 / 9.3  61 9.8 / 9.6   P = 32 42 tiles 12.2 / 15.3  77 17.3 / 17.8  92 18.4 / 17.8
+// From 9 (bf16) or 10 replicas on a launch of few tiles is slower so: each of its few workgroups writes them all, one after another.
+// One launch behind start of the two, GPU time without gbar:
+//   fp32  P = 12 20 tiles 7.5 / 8.1  33 6.8 / 6.2   P = 16 26 tiles 7.7 / 8.6  46 9.0 / 9.3  61 9.8 / 9.6   P = 32 42 tiles
+//   12.2 / 15.3  77 17.3 / 17.8  92 18.4 / 17.8
 //         P = 64 72 tiles 25.1 / 27.8  94 32.9 / 32.4
-//   bf16  P = 8 18 tiles 5.0 / 5.2  39 5.4 / 5.2   P = 10 18 tiles 5.5 / 6.1  40 8.6 / 8.7  76 9.9 / 9.5   P = 16 46 tiles 9.4 / 10.0  76 10.8 / 10.5
+//   bf16  P = 8 18 tiles 5.0 / 5.2  39 5.4 / 5.2   P = 10 18 tiles 5.5 / 6.1  40 8.6 / 8.7  76 9.9 / 9.5   P = 16 46 tiles 9.4 / 10.0
+//   76 10.8 / 10.5
 //         P = 32 62 tiles 15.6 / 17.2  92 18.5 / 18.3  112 20.6 / 18.9   P = 64 94 tiles 32.3 / 31.9  124 37.5 / 33.1
-// And bf16 beyond what the last-level cache holds of the pass's elems * (6 P + 20) bytes: tensors of 2000 elements P = 8 2 M without / with
-// gbar 44 / 38 and 48 / 45, 6 M 99.8 / 100 and 112 / 125, P = 32 0.6 M 44 / 40, 2 M 108 / 130, P = 64 0.3 M in 18 47.5 / 49.3, 2 M 212 / 254;
-// of 2600 P = 6 2.6 M 39.9 / 40.7 and 44.7 / 48.5, P = 8 0.8 M 17.0 / 15.4, 2.6 M 46 / 50 and 51 / 58; whole P = 5 2 M (493 tiles) 17.2 / 15.8, 2.1 M (517)
-// 18.2 / 19.7, P = 4 2.3 M (566) 17.6 / 18.9, 3 M (737) 23.1 / 21.0; weights and short
-// vectors P = 5 4 M (71 %) 41.8 / 39.2, P = 8 1.7 M (88 %) 22.5 / 21.4, P = 11 1.3 M (51 %) 34.4 / 31.0 and 35.9 / 33.4.  Of 1500 and less one launch is faster at any size (P = 8 4.5 M
-// 90 / 65, P = 32 1.5 M 102 / 94), as in fp32 (P = 64 1.5 M 272 / 266), where half full tiles cost from 25 replicas on (135 tensors of
-// 3500 in 246 tiles P = 64 75.7 / 78.7, 1 M in 500 160 / 169; weights and short vectors 40 % full P = 64 52.5 / 59.3).
+// And bf16 beyond what the last-level cache holds of the pass's elems * (6 P + 20) bytes: tensors of 2000 elements P = 8 2 M
+// without / with gbar 44 / 38 and 48 / 45, 6 M 99.8 / 100 and 112 / 125, P = 32 0.6 M 44 / 40, 2 M 108 / 130, P = 64 0.3 M in 18
+// 47.5 / 49.3, 2 M 212 / 254; of 2600 P = 6 2.6 M 39.9 / 40.7 and 44.7 / 48.5, P = 8 0.8 M 17.0 / 15.4, 2.6 M 46 / 50 and 51 / 58;
+// whole P = 5 2 M (493 tiles) 17.2 / 15.8, 2.1 M (517) 18.2 / 19.7, P = 4 2.3 M (566) 17.6 / 18.9, 3 M (737) 23.1 / 21.0; weights and
+// short vectors P = 5 4 M (71 %) 41.8 / 39.2, P = 8 1.7 M (88 %) 22.5 / 21.4, P = 11 1.3 M (51 %) 34.4 / 31.0 and 35.9 / 33.4.  Of
+// 1500 and less one launch is faster at any size (P = 8 4.5 M 90 / 65, P = 32 1.5 M 102 / 94), as in fp32 (P = 64 1.5 M 272 / 266),
+// where half full tiles cost from 25 replicas on (135 tensors of 3500 in 246 tiles P = 64 75.7 / 78.7, 1 M in 500 160 / 169; weights
+// and short vectors 40 % full P = 64 52.5 / 59.3).
 inline bool iteration_gathers_at_once(int grad_bytes, int64_t P, int64_t elems, int64_t tiles, bool with_gbar, int64_t max_workgroups)
 {
     constexpr int64_t M = 1000000;
@@ -536,11 +573,11 @@ inline bool iteration_gathers_at_once(int grad_bytes, int64_t P, int64_t elems, 
     return P <= 2 || (P == 3 && elems >= 25 * M) || (P == 4 && elems >= (with_gbar ? 64 : 40) * M);
 }
 
-// Workgroups that may share a CU in such a launch, 0 for as many as fit: HBM serves many streams at once better the fewer loads compete, in
-// launches long enough for it and whose tiles are four fifths full.  us at as many / 2 / 1, fp32
+// Workgroups that may share a CU in such a launch, 0 for as many as fit: HBM serves many streams at once better the fewer loads
+// compete, in launches long enough for it and whose tiles are four fifths full.  us at as many / 2 / 1, fp32
 // with gbar P = 2 5 M 32.8 / 31.6 / 38.9, 100 M 640 / 579 / 703, P = 3 100 M 788 / 722 / 878, without P = 4 100 M 854 / 776 / 876;
-// bf16 with gbar, half tiles, P = 2 30 M - / 180 / 161, 100 M 596 / 594 / 525.  bf16 P = 1 without gbar 26 M 97 / 93 / 106, 100 M 389 / 355 / 395,
-// 250 M - / 923 / 1017, with it 26 M 125 / 114 / 118, 80 M - / 354 / 358, 100 M 499 / 449 / 444, 150 M - / 702 / 683.
+// bf16 with gbar, half tiles, P = 2 30 M - / 180 / 161, 100 M 596 / 594 / 525.  bf16 P = 1 without gbar 26 M 97 / 93 / 106, 100 M
+// 389 / 355 / 395, 250 M - / 923 / 1017, with it 26 M 125 / 114 / 118, 80 M - / 354 / 358, 100 M 499 / 449 / 444, 150 M - / 702 / 683.
 inline int iteration_at_once_residency(bool bf16, bool with_gbar, int64_t P, int64_t elems, int64_t tiles)
 {
     if (elems * 5 < tiles * (4 * DEAR_TILE_ELEMS)) return 0;
