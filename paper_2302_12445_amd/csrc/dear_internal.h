@@ -156,8 +156,8 @@ DEAR_HOST_DEVICE inline unsigned all_gather_part(unsigned r, unsigned run)
     return (r & ~((8u << run) - 1)) | (r & 7) << run | (r >> 3 & ((1u << run) - 1));
 }
 
-// The same where every XCD takes an eighth of the chunk, its parts in a row: len, the chunk's workgroups per replica, is a multiple of
-// 8.
+// The same where every XCD takes an eighth of the chunk, its parts in a row: len, the chunk's workgroups per replica, is a
+// multiple of 8.
 DEAR_HOST_DEVICE inline unsigned all_gather_part_of_eighth(unsigned r, unsigned len) { return (r & 7) * (len >> 3) + (r >> 3); }
 
 // Where it is: an XCD then writes 2 MiB of a replica in a row and not every eighth 4 KiB, and of the lines that two
@@ -206,16 +206,19 @@ inline all_gather_order all_gather_numbering(unsigned run, int64_t max_workgroup
 //   one tensor a bucket  P = 4 2.3 M elements 211 / 216  9 M 169 / 168   P = 5 1.8 M 193 / 202  2.8 M 175.7 / 175.9  3.4 M 171 / 164
 //                        7.2 M 160 / 154
 //                        P = 8 1.6 M 171 / 169  1.75 M 152 / 153  2.1 M 149 / 145 (2 of 12 buckets, the others smaller, 251 / 257)
-//                        4.5 M 142 / 135 P = 12 0.9 M 153 / 166  1.3 M 161 / 153  (in 76 tensors 1.6 M 32.8 / 33.9)
-//                        P = 16 0.8 M 140 / 150  1 M 150 / 149  1.1 M 133 / 126  2.3 M 127 / 114   P = 32 0.9 M 89 / 92  1 M 105 / 99
-//                        P = 64 0.7 M 63 / 67  0.9 M 79 / 80  1 M 96 / 89
-//   tensors of 3500      P = 5 2.2 M 28.8 / 31.8  5 M 63.1 / 61.8   P = 8 2.2 M 38.6 / 40.7  5 M 86.2 / 82.0   P = 16 1 M 31.8 / 33.6
-//   5 M 149 / 135 tensors of 5000 (61 % full)  P = 8 2.2 M 45.4 / 46.6  5 M 90.5 / 97.8  16 M 294 / 299   P = 16 2.2 M 73 / 78
-//   P = 32 2.2 M 131 / 141 tensors of 3000 (73 %)       P = 5 5 M 62.1 / 64.9   P = 8 2.2 M 37.7 / 43.1  16 M 267 / 261   P = 12 2.2 M
-//   50.8 / 56.3  5 M 117 / 114   P = 32 1 M 56 / 61 tensors of 2400-9400 (74 %)  P = 6 5 M 76.4 / 72.0   P = 8 3.8 M 69.0 / 66.0
-//   weights and short vectors P = 6 3.5 M (78 %) 53.8 / 49.6, P = 8 2.5 M (89 %) 44.6 / 42.2  2.6 M (58 %) 53.0 / 51.9   P = 12 1.9 M
-//   (62 %) 50.3 / 52.4   P = 16 1.1 M (59 %) 36.5 / 40.9
-//                        P = 32 2.6 M (58 %) 133 / 125
+//                        4.5 M 142 / 135
+//                        P = 12 0.9 M 153 / 166  1.3 M 161 / 153  (in 76 tensors 1.6 M 32.8 / 33.9)
+//                        P = 16 0.8 M 140 / 150  1 M 150 / 149  1.1 M 133 / 126  2.3 M 127 / 114
+//                        P = 32 0.9 M 89 / 92  1 M 105 / 99   P = 64 0.7 M 63 / 67  0.9 M 79 / 80  1 M 96 / 89
+//   tensors of 3500      P = 5 2.2 M 28.8 / 31.8  5 M 63.1 / 61.8   P = 8 2.2 M 38.6 / 40.7  5 M 86.2 / 82.0
+//                        P = 16 1 M 31.8 / 33.6  5 M 149 / 135
+//   tensors of 5000 (61 % full)  P = 8 2.2 M 45.4 / 46.6  5 M 90.5 / 97.8  16 M 294 / 299   P = 16 2.2 M 73 / 78
+//                                P = 32 2.2 M 131 / 141
+//   tensors of 3000 (73 %)       P = 5 5 M 62.1 / 64.9   P = 8 2.2 M 37.7 / 43.1  16 M 267 / 261
+//                                P = 12 2.2 M 50.8 / 56.3  5 M 117 / 114   P = 32 1 M 56 / 61
+//   tensors of 2400-9400 (74 %)  P = 6 5 M 76.4 / 72.0   P = 8 3.8 M 69.0 / 66.0
+//   weights and short vectors    P = 6 3.5 M (78 %) 53.8 / 49.6   P = 8 2.5 M (89 %) 44.6 / 42.2  2.6 M (58 %) 53.0 / 51.9
+//                                P = 12 1.9 M (62 %) 50.3 / 52.4   P = 16 1.1 M (59 %) 36.5 / 40.9   P = 32 2.6 M (58 %) 133 / 125
 //   tensors of 2500 (61 %)       P = 5 16 M 195 / 211   P = 8 16 M 273 / 293   P = 32 2.2 M 129 / 143
 // Beyond the largest all-gather the one kernel, whose grid is the tile count alone, still takes the call.
 constexpr int64_t UAG_SPLIT_P = 5;
@@ -239,14 +242,16 @@ inline bool update_all_gather_splits(int64_t elems, int64_t tiles, int64_t whole
 //     P = 16 125 13.6 / 12.8  165 14.2 / 13.3  288 16.0 / 15.7  440 (60 % full) 36.5 / 37.9   P = 24 322 28.8 / 26.1  660 54.0 / 51.5
 //     P = 32 106 19.9 / 18.2  138 22.5 / 23.6  238 24.1 / 26.3   P = 48 87 (eleven buckets) 283 / 259  132 28.9 / 30.0
 //     P = 64 83 (nearly empty) 20.7 / 19.2  120 (two buckets) 65.8 / 66.7  138 37.4 / 43.1
-//   eight buckets (fewer from P = 32 on) of one tensor  P = 2 24 tiles 47.5 / 39.7  64 51.7 / 50.7  110 59.0 / 57.8  150 63.4 / 65.3
-//   P = 4 24 52.8 / 43.8
-//     110 68.6 / 69.3  150 74.6 / 78.9   P = 8 24 62.6 / 51.5  110 84.0 / 84.8  150 99.0 / 101.1   P = 16 24 85.5 / 68.7  150
-//     155.2 / 157.2 P = 32 24 127 / 103  110 221 / 233   P = 64 24 193 / 189  64 246 / 252  97 109 / 111
-//   of tensors of one length, 3000  P = 4 64 61.1 / 52.1  128 68.9 / 66.3   P = 16 64 96 / 82  128 107 / 106  143 123 / 126;  900
-//   P = 2 32 47.4 / 47.3
-//     64 49.5 / 50.7   P = 8 56 60.8 / 60.0  72 65.4 / 65.7   P = 16 80 93.1 / 93.7  96 100 / 105   P = 24 104 141 / 132;  beyond
-//     P = 2 800 of 1200 13.3 / 17.7   P = 8 400 of 1200 15.6 / 19.3  800 24.9 / 32.8
+//   eight buckets (fewer from P = 32 on) of one tensor
+//     P = 2  24 tiles 47.5 / 39.7  64 51.7 / 50.7  110 59.0 / 57.8  150 63.4 / 65.3   P = 4  24 52.8 / 43.8  110 68.6 / 69.3
+//            150 74.6 / 78.9
+//     P = 8  24 62.6 / 51.5  110 84.0 / 84.8  150 99.0 / 101.1   P = 16 24 85.5 / 68.7  150 155.2 / 157.2
+//     P = 32 24 127 / 103  110 221 / 233   P = 64 24 193 / 189  64 246 / 252  97 109 / 111
+//   of tensors of one length
+//     3000   P = 4 64 61.1 / 52.1  128 68.9 / 66.3   P = 16 64 96 / 82  128 107 / 106  143 123 / 126
+//     900    P = 2 32 47.4 / 47.3  64 49.5 / 50.7   P = 8 56 60.8 / 60.0  72 65.4 / 65.7   P = 16 80 93.1 / 93.7  96 100 / 105
+//            P = 24 104 141 / 132
+//     beyond P = 2 800 of 1200 13.3 / 17.7   P = 8 400 of 1200 15.6 / 19.3  800 24.9 / 32.8
 inline bool update_all_gather_quarters(int64_t elems, int64_t tiles, int64_t whole, int64_t P, int64_t max_workgroups)
 {
     if (max_workgroups > 0 && tiles * 4 > max_workgroups) return false;
@@ -305,18 +310,19 @@ struct reduce_scatter_shape {
 // replicas are two rounds of loads instead of one.  A launch that fills the chip less than once, and not by far, likes fewer, longer
 // workgroups.  4256 launches (P = 1 to 64, 20 to 2000 tiles; one tensor, five, ragged lists, weights with short vectors between them;
 // buffers in turn, cold), batch kernel = 1, mean (worst) of what would go instead:
-//   nothing cut, with update, fp32  P = 3 1.02 (1.14)  5 1.02 (1.10)  6 1.01 (1.11)  7 1.03 (1.21)  8 1.02 (1.10), above 160 tiles
-//   1.00
-//     bf16  P = 3 1.05 (1.18)  5, 6 and 7 1.02 (1.25)  8 1.01 (1.12), 1 and 2 0.97, but from 128 to 700 tiles 1.02 (1.07)
-//   without, fp32 P = 3 1.04 (1.12)  4 to 8 below 160 tiles 1.04 (1.24), above 0.98;  bf16 P = 2 1.01 (1.13)  3 to 8 1.07 (1.24) and
-//   0.94 P = 7 below 160 tiles, cut  fp32 1.02 (1.07)  bf16 1.04 (1.09)
-//   nothing cut, fp32 P >= 12 with update, 64 to 160 tiles 1.06 (1.38), P >= 24 without 1.08 (1.39), P = 9 to 16 without 0.94
-//   nothing cut, bf16 with update P = 12 and 16 below 700 tiles 1.02 (1.13), P >= 24 from 132 to 288 1.04 (1.16); without, P = 12 and
-//   16
-//     below 130 1.00 (1.09), P >= 24 from 132 to 160 1.02 (1.14)
-//   cut: fp32 P <= 8 below 160 tiles 0.97, from 9 on 0.84; bf16 from 9 on 0.82, P = 4 without update below 160 1.09, P = 5 to 7 with
-//   it
-//     from 40 to 300 1.05, P = 4 and 8 from 110 to 300 1.01
+//   nothing cut, up to eight replicas
+//     fp32 with update  P = 3 1.02 (1.14)  5 1.02 (1.10)  6 1.01 (1.11)  7 1.03 (1.21)  8 1.02 (1.10), above 160 tiles 1.00
+//     bf16 with update  P = 3 1.05 (1.18)  5, 6 and 7 1.02 (1.25)  8 1.01 (1.12)  1 and 2 0.97, but from 128 to 700 tiles 1.02 (1.07)
+//     fp32 without      P = 3 1.04 (1.12)  4 to 8 below 160 tiles 1.04 (1.24), above 0.98
+//     bf16 without      P = 2 1.01 (1.13)  3 to 8 below 160 tiles 1.07 (1.24), above 0.94
+//   nothing cut, more
+//     fp32, 64 to 160 tiles  with update P >= 12 1.06 (1.38)   without P = 9 to 16 0.94  P >= 24 1.08 (1.39)
+//     bf16 with update       P = 12 and 16 below 700 tiles 1.02 (1.13)   P >= 24 from 132 to 288 1.04 (1.16)
+//     bf16 without           P = 12 and 16 below 130 tiles 1.00 (1.09)   P >= 24 from 132 to 160 1.02 (1.14)
+//   cut
+//     fp32                   P <= 8 below 160 tiles 0.97, but 7 1.02 (1.07)   from 9 on 0.84
+//     bf16                   from 9 on 0.82   P = 4 without update below 160 tiles 1.09   P = 7 below 160 1.04 (1.09)
+//     bf16 with update       P = 5 to 7 from 40 to 300 tiles 1.05   P = 4 and 8 from 110 to 300 1.01
 inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles, bool cut)
 {
     if (tiles >= 2048) return false;
@@ -333,9 +339,10 @@ inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles
     return tiles >= 132 && tiles < (updates ? 288 : 160);
 }
 
-// HBM serves P streams at once best with 32 to 40 KiB of loads in flight per CU, as long as they never stop: D loads of 4 KiB for
-// each of the workgroups that share a CU (fp32 at `residency` 4: five of them).  With more the streams get into each other's way,
-// with fewer the latency shows; a launch that does not fill the chip wants more per workgroup.  So two replicas a lane and three or
+// HBM serves P streams at once best with 24 to 48 KiB of loads in flight per CU, as long as they never stop: D loads of 4 KiB for
+// each of the workgroups that share a CU, so 2/3 24 KiB, 2/4 32 in bf16 and 40 in fp32 (whose `residency` 4 lets five in), 4/2 32,
+// 4/3 48, and with the update those of w and v beside them.  With more the streams get into each other's way, with fewer the
+// latency shows; a launch that does not fill the chip wants more per workgroup.  So two replicas a lane and three or
 // four workgroups a CU in long launches, four or eight replicas in short ones.  Depth / workgroups a CU (- as many as fit, r in rows),
 // batch kernel = 1, means over the four kinds of lists, by tiles (the launches of batch_kernel_stays, and 1266 longer ones):
 //   fp32 without update, 8/- | 4/- | 2/-
@@ -359,10 +366,10 @@ inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles
 //     P = 24  80-109 0.85 | 0.94 | 1.30   110-131 0.86 | 0.93 | 1.27   132-160 0.97 | 0.92 | 1.21   161-287 0.86 | 0.82 | 0.98
 //     P = 64  80-109 0.70 | 0.92 | 1.45   110-131 0.71 | 0.88 | 1.36   132-160 0.91 | 0.92 | 1.33   161-287 0.81 | 0.77 | 1.03
 //   4/- | 2/- | 2/4r | 2/3r, without update, then with
-//     780-1700   P = 8 0.98 | 1.00 | 0.99 | 1.04, 0.98 | 0.99 | 0.98 | 1.01   P = 12 0.96 | 0.98 | 0.96 | 1.01, 0.99 | 0.99 | 0.99 |
-//     1.02
-//                P = 24 0.99 | 1.00 | 0.95 | 0.99, 0.99 | 0.98 | 0.96 | 0.98   P = 64 1.00 | 1.01 | 0.94 | 0.96, 0.99 | 0.98 | 0.93 |
-//                0.93
+//     780-1700   P = 8  0.98 | 1.00 | 0.99 | 1.04, 0.98 | 0.99 | 0.98 | 1.01
+//                P = 12 0.96 | 0.98 | 0.96 | 1.01, 0.99 | 0.99 | 0.99 | 1.02
+//                P = 24 0.99 | 1.00 | 0.95 | 0.99, 0.99 | 0.98 | 0.96 | 0.98
+//                P = 64 1.00 | 1.01 | 0.94 | 0.96, 0.99 | 0.98 | 0.93 | 0.93
 //     1900-7000  P = 8 - | - | 0.97 | 1.01, - | - | 0.97 | 0.98   P = 12 - | - | 0.95 | 0.99, - | - | 0.98 | 0.98
 //     1000-2050 with update, 4/- | 4/3  P = 5 0.97 | 1.00   P = 6 0.98 | 0.98   P = 7 0.98 | 1.01
 // Tensors shorter than a tile leave most parts empty: a workgroup takes whole tiles then.  900 elements each, P = 8  560 tiles fp32
@@ -378,7 +385,7 @@ inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles
 // 1.03 / 1.02 | 1.07 / 1.02, 900 1.01 / 1.01 | 1.08 / 0.98, 1800 1.00 / 1.01 | 1.04 / 0.98, P = 16 400 1.02 / 1.02 | 1.04 / 1.02,
 // 900 0.98 / 0.97 | 0.99 / 0.94; dear_iteration P = 8 800 1.02 / 1.03 | 1.13 / 1.03, bf16 P = 6 800 1.00 / 0.99 | 1.21 / 0.98; more
 // replicas leave little of it: P = 32 fp32 900 0.98 / 0.96 | 0.95 / 0.92, 400 1.00 / 0.99 | 1.01 / 0.99.
-// fp32 from 8 to 16 replicas on, 6000 tiles and more: four replicas, two workgroups, as they fall, whose rows of several replicas do
+// fp32 with 8 to 16 replicas, 6000 tiles and more: four replicas, two workgroups, as they fall, whose rows of several replicas do
 // not drift apart.  Models' lists, 4/2 | 2/4r (without update) or 2/3r (with), and dear_iteration: ResNet-50-shaped (6342 tiles) P = 8
 // 0.98 | 0.98, 1.00 | 0.99, 0.99 | 1.01, P = 12 0.97 | 0.98, 1.02 | 1.01, 0.99 | 0.99, P = 16 0.99 | 1.01, 0.99 | 0.98, 0.98 | 0.98;
 // Inception-v4-shaped (10732) P = 8 0.99 | 0.97, 1.00 | 1.00, 0.97 | 0.99, P = 12 0.98 | 0.98, 1.01 | 1.00, 0.96 | 0.98, P = 16 0.99 |
@@ -434,15 +441,16 @@ inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, boo
 // dear_iteration, they are in this XCD's L2.  The more replicas, and the emptier the tiles, the more the rounding to 16 parts costs.
 // One / two in a row:
 //   dear_iteration, us, one bucket of 100 / 200 / 400 / 850 full tiles  P = 8 8.5 / 8.3  12.6 / 12.1  22.1 / 20.1  39.5 / 38.4
-//     P = 24 16.0 / 16.0  24.7 / 24.2  45.9 / 44.4  92.3 / 88.7   P = 40 23.4 / 24.4  36.8 / 37.2  71.6 / 69.5  144 / 145   P = 48
-//     28.5 / 28.9  43.9 / 45.2  82.5 / 83.1 P = 64 38.7 / 39.4  57.4 / 59.0  108 / 109  225 / 221;  weights and short vectors, change
-//     in %: P = 3 -7 to 0, P = 8 up to 150 tiles 0, 340 to 430 full ones -4 to -8, P = 12 and 16 up to 230 tiles +1 to +3, 390 full
-//     ones -4, P = 24 +1 to +3, P = 32 +1 to +4, P = 48 and 64 +3 to +5
-//   all reduce-scatters, then all all-gathers, change of the whole pass in %: eight buckets or fewer of 40 / 100 / 200 / 400 / 850
+//     P = 24 16.0 / 16.0  24.7 / 24.2  45.9 / 44.4  92.3 / 88.7   P = 40 23.4 / 24.4  36.8 / 37.2  71.6 / 69.5  144 / 145
+//     P = 48 28.5 / 28.9  43.9 / 45.2  82.5 / 83.1   P = 64 38.7 / 39.4  57.4 / 59.0  108 / 109  225 / 221
+//   the same, weights and short vectors, change in %: P = 3 -7 to 0, P = 8 up to 150 tiles 0, 340 to 430 full ones -4 to -8,
+//     P = 12 and 16 up to 230 tiles +1 to +3, 390 full ones -4, P = 24 +1 to +3, P = 32 +1 to +4, P = 48 and 64 +3 to +5
+//   all reduce-scatters, then all all-gathers, change of the whole pass in %, eight buckets or fewer of 40 / 100 / 200 / 400 / 850
 //   full tiles
-//     P = 4 -7 / -3 / -2 / 0 / 0   P = 8 -9 / -4 / 0 / 0 / -1   P = 16 -3 / -2 / 0 / +1 / -2   P = 24 0 / 0 / +2 / +2 / -1   P = 32
-//     +1 / +1 / +2 / +3 / -1 P = 48 -1 / +1 / +3 / +3 / -1   P = 64 +2 / +3 / +3 / +3 / +3;  weights and short vectors P = 3 and 4 -6
-//     to 0, P = 8 -3 to +2, with an update between +1 to +2.5, P = 12 and 16 +1 to +3, from P = 24 on +2 to +5
+//     P = 4 -7 / -3 / -2 / 0 / 0   P = 8 -9 / -4 / 0 / 0 / -1   P = 16 -3 / -2 / 0 / +1 / -2   P = 24 0 / 0 / +2 / +2 / -1
+//     P = 32 +1 / +1 / +2 / +3 / -1   P = 48 -1 / +1 / +3 / +3 / -1   P = 64 +2 / +3 / +3 / +3 / +3
+//   the same, weights and short vectors: P = 3 and 4 -6 to 0, P = 8 -3 to +2, with an update between +1 to +2.5,
+//     P = 12 and 16 +1 to +3, from P = 24 on +2 to +5
 // Beyond 1024 tiles where the launch before goes in halves of tiles as they fall; one / two in a row, dear_iteration, cold, change of
 // the whole pass against the batch kernel's in %, 1140 ragged tiles, 1200 of one tensor, 1520 ragged: P = 4 -5 / -8, -2 / -8, -5 / -9,
 // P = 6 -3 / -8, 0 / -2, -2 / -5, P = 8 -2 / -4, 0 / 0, -2 / -4, P = 12 -2 / -4, -1 / 0, -3 / -4, P = 16 -1 / -2, +1 / +3, 0 / -2;
@@ -531,18 +539,18 @@ inline bool iteration_updates_apart(int grad_bytes, int64_t P, int64_t group_til
 //         P = 16 0.2 M 11.3 / 11.8  1 M 27.1 / 30.8
 //         P = 8 from 6 to 9 M copied elements, where only 240 to 258 tiles, of four workgroups each, fill the 256 CUs evenly: one
 //         tensor 223 tiles 13.1 / 14.1  242 13.7 / 13.3  258 14.9 / 13.8  262 15.8 / 16.1  277 16.0 / 17.2, 23 tensors 230 14.3 / 14.2
-//         248 15.4 / 14.3  257 15.6 / 14.4  267 16.5 / 16.7  281 16.9 / 17.4 open tiles: P = 8 1 M in 500 tensors 27.3 / 22.4, 2 M in
-//         200 34.2 / 34.1, 3 M in 500 50.2 / 50.7; P = 16 1 M in 500 47.8 / 39.7, in 60 29.0 / 32.0, 3 M in 500 86.3 / 93.2
+//         248 15.4 / 14.3  257 15.6 / 14.4  267 16.5 / 16.7  281 16.9 / 17.4
+//         open tiles: P = 8 1 M in 500 tensors 27.3 / 22.4, 2 M in 200 34.2 / 34.1, 3 M in 500 50.2 / 50.7
+//                     P = 16 1 M in 500 47.8 / 39.7, in 60 29.0 / 32.0, 3 M in 500 86.3 / 93.2
 //   bf16  P = 2 1 M 8.9 / 6.6  6 M 33.4 / 31.0  20 M 92.2 / 97.1  30 M 150 / 145  100 M 514 / 481
 //         P = 4 1 M 10.7 / 8.7  3 M 24.1 / 22.8  6 M 42.8 / 43.9  P = 8 0.5 M 10.3 / 9.2  1.5 M 19.3 / 18.5  3 M 34.3 / 35.2
 //         P = 12 0.5 M 13.2 / 12.8  1 M 18.6 / 19.2  P = 16 0.2 M 11.2 / 11.9  1 M 22.9 / 25.3, in 500 tensors 46.2 / 37.7
 // From 9 (bf16) or 10 replicas on a launch of few tiles is slower so: each of its few workgroups writes them all, one after another.
 // One launch behind start of the two, GPU time without gbar:
-//   fp32  P = 12 20 tiles 7.5 / 8.1  33 6.8 / 6.2   P = 16 26 tiles 7.7 / 8.6  46 9.0 / 9.3  61 9.8 / 9.6   P = 32 42 tiles
-//   12.2 / 15.3  77 17.3 / 17.8  92 18.4 / 17.8
-//         P = 64 72 tiles 25.1 / 27.8  94 32.9 / 32.4
-//   bf16  P = 8 18 tiles 5.0 / 5.2  39 5.4 / 5.2   P = 10 18 tiles 5.5 / 6.1  40 8.6 / 8.7  76 9.9 / 9.5   P = 16 46 tiles 9.4 / 10.0
-//   76 10.8 / 10.5
+//   fp32  P = 12 20 tiles 7.5 / 8.1  33 6.8 / 6.2   P = 16 26 tiles 7.7 / 8.6  46 9.0 / 9.3  61 9.8 / 9.6
+//         P = 32 42 tiles 12.2 / 15.3  77 17.3 / 17.8  92 18.4 / 17.8   P = 64 72 tiles 25.1 / 27.8  94 32.9 / 32.4
+//   bf16  P = 8 18 tiles 5.0 / 5.2  39 5.4 / 5.2   P = 10 18 tiles 5.5 / 6.1  40 8.6 / 8.7  76 9.9 / 9.5
+//         P = 16 46 tiles 9.4 / 10.0  76 10.8 / 10.5
 //         P = 32 62 tiles 15.6 / 17.2  92 18.5 / 18.3  112 20.6 / 18.9   P = 64 94 tiles 32.3 / 31.9  124 37.5 / 33.1
 // And bf16 beyond what the last-level cache holds of the pass's elems * (6 P + 20) bytes: tensors of 2000 elements P = 8 2 M
 // without / with gbar 44 / 38 and 48 / 45, 6 M 99.8 / 100 and 112 / 125, P = 32 0.6 M 44 / 40, 2 M 108 / 130, P = 64 0.3 M in 18
