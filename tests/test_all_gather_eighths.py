@@ -44,10 +44,10 @@ def test_around_the_lines_of_the_rule(P, tiles):
     pair.close()
 
 
-# replicas on lines; alike, off the lines; each elsewhere (parts as they fall)
+# replicas on lines; alike, off the lines; each elsewhere (parts as they fall), as they do for two workers
 @pytest.mark.gpu
-@pytest.mark.parametrize("starts", [(0, 0, 0), (4, 4, 4), (28, 28, 28), (0, 12, 20)])
-@pytest.mark.parametrize("workers", [(0, 3), (1, 2)])
+@pytest.mark.parametrize("starts", [(0, 0, 0, 0), (4, 4, 4, 4), (28, 28, 28, 28), (0, 12, 20, 4)])
+@pytest.mark.parametrize("workers", [(0, 4), (1, 3), (1, 2)])
 def test_replicas_alike_and_not(starts, workers):
     import numpy as np
     import oracle
@@ -56,7 +56,7 @@ def test_replicas_alike_and_not(starts, workers):
     import workloads as W
     from test_gpu_parity import DEV, _bits, say
     say("case: all-gather in eighths, tensors at %s of a line, workers %s" % (starts, workers))
-    sizes, P = [9_000_003, 70_001], 3
+    sizes, P = [9_000_003, 70_001], 4
     op, plan = oracle.plan(sizes, P, W.NO_LIMIT, 4), dear.dear_plan(sizes, P, W.NO_LIMIT, 4)
     assert 2048 <= len(dear.dear_plan_tiles(plan)[0]) < 5000
     bufs = [[torch.full((n + 64,), 7.0, device=DEV) for n in sizes] for _ in range(P)]
