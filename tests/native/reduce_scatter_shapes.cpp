@@ -1,5 +1,6 @@
 // Host-only check (dear_internal.h) of the reduce-scatter's and the update's rows of items, each item to exactly one workgroup whatever their
-// number, and of the rule for its shape: never more replicas in flight than there are, and only what there are kernels for.
+// number, and of the rule for its shape: never more replicas in flight than there are, and only what there are kernels for (one in flight is
+// for one replica).
 // Exits non-zero on the first mistake.
 #include <cstdint>
 #include <cstdio>
@@ -100,7 +101,7 @@ int main(int argc, char **)
                                 const reduce_scatter_shape s = reduce_scatter_shape_of(
                                     bf16, updates, caches_w, P, tiles * DEAR_TILE_ELEMS * percent / 100, tiles, whole, cut);
                                 const bool depth = s.depth == 0 || s.depth == 1 || s.depth == 2 || s.depth == 4 || s.depth == 8;
-                                if (!depth || s.depth > P || s.residency < 0 || s.residency > 4 || s.residency == 1 || s.run < 0 || s.run > 6 ||
+                                if (!depth || s.depth > P || (s.depth == 1 && P > 1) || s.residency < 0 || s.residency > 4 || s.residency == 1 || s.run < 0 || s.run > 6 ||
                                     (s.tiles && (s.depth == 0 || whole))) {
                                     std::fprintf(stderr, "FAILED bf16=%d updates=%d P=%lld tiles=%lld percent=%lld\n", bf16, updates,
                                                  (long long)P, (long long)tiles, (long long)percent);
