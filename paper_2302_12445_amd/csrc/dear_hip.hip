@@ -46,6 +46,7 @@ struct dear_ctx_impl {
     std::vector<int64_t> bucket_len, bucket_shard_len, bucket_shard_base;
     std::vector<int64_t> tile_begin;  // [B+1] range of bucket b's tiles in the tile table
     std::vector<int64_t> whole_begin;  // [B+1] how many of the tiles before bucket b are whole,
+    std::vector<int64_t> long_begin;   // [B+1] how many lie in more than one part of the reduce-scatter,
     std::vector<int64_t> cut_begin;    // [B+1] and how many begin or end inside a vector of gradients
     std::vector<int64_t> layer_sizes;
     void *d_tables = nullptr;         // one allocation: the four tables below
@@ -1078,6 +1079,7 @@ bucket_range buckets_of(const dear_ctx_impl *c, int32_t bucket)
 int64_t tiles_of(const dear_ctx_impl *c, bucket_range r) { return c->tile_begin[r.end] - c->tile_begin[r.begin]; }
 
 int64_t whole_tiles_of(const dear_ctx_impl *c, bucket_range r) { return c->whole_begin[r.end] - c->whole_begin[r.begin]; }
+int64_t long_tiles_of(const dear_ctx_impl *c, bucket_range r) { return c->long_begin[r.end] - c->long_begin[r.begin]; }
 int64_t cut_tiles_of(const dear_ctx_impl *c, bucket_range r) { return c->cut_begin[r.end] - c->cut_begin[r.begin]; }
 
 int64_t elements_of(const std::vector<int64_t> &bucket_len, bucket_range r)
@@ -1128,15 +1130,15 @@ unsigned residency_lds(int residency)
 }
 
 // What a reduce-scatter launch is made from.  tiles, grads: device tables (a context's, or the static scratch's).  The
-// launch may be one of several over all_tiles tiles, which hold all_elems elements and of which all_whole are whole and all_cut cut
-// inside a vector.
+// launch may be one of several over all_tiles tiles, which hold all_elems elements and of which all_whole are whole, all_long lie in
+// more than one part and all_cut are cut inside a vector.
 struct rs_call {
     int P, L;
     const void *const *grads;
     int32_t max_workgroups;
     int prio;
     const dear_tile *tiles;
-    int64_t n_tiles, all_tiles, all_elems, all_whole, all_cut;
+    int64_t n_tiles, all_tiles, all_elems, all_whole, all_long, all_cut;
     hipStream_t st;
 };
 
@@ -1213,7 +1215,7 @@ void rs_launch_type(const rs_call &c, const rs_sink<MODE> &o)
         const int64_t parts = c.n_tiles * reduce_scatter_split(BF16);
         if (parts <= MAX_GRID && (c.max_workgroups == 0 || parts <= c.max_workgroups) && pointer_table_fits(c.P, c.L)) {
             const reduce_scatter_shape shape =
-                reduce_scatter_shape_of(BF16, (MODE & RS_UPDATE) != 0, (MODE & RS_W_NEXT) != 0, c.P, c.all_elems, c.all_tiles, c.all_whole,
+                reduce_scatter_shape_of(BF16, (MODE & RS_UPDATE) != 0, (MODE & RS_W_NEXT) != 0, c.P, c.all_elems, c.all_tiles, c.all_long,
                                         c.all_cut);
             if (shape.depth > 0) return rs_launch_parts<BF16, MODE>(c, o, shape);
         }
@@ -1270,6 +1272,7 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
         c->layer_sizes = plan->layer_sizes;
         c->tile_begin.assign(plan->B + 1, 0);
         c->whole_begin.assign(plan->B + 1, 0);
+        c->long_begin.assign(plan->B + 1, 0);
         c->cut_begin.assign(plan->B + 1, 0);
         n_runs = dear_emit_runs(*plan, 0, plan->B, nullptr, 0, &n_tiles, c->tile_begin.data());
         runs.resize(n_runs);
@@ -1283,9 +1286,11 @@ extern "C" int dear_ctx_create(const dear_plan_t *plan, int32_t grad_dtype,
     dear_emit_runs(*plan, 0, plan->B, runs.data(), n_runs, &n_tiles, nullptr);
     for (const dear_run &r : runs) {
         c->whole_begin[r.bucket + 1] += whole_tiles_of_run(r);
+        c->long_begin[r.bucket + 1] += long_tiles_of_run(r, 16 / c->g);
         c->cut_begin[r.bucket + 1] += cut_tiles_of_run(r, 16 / c->g);
     }
     std::partial_sum(c->whole_begin.begin(), c->whole_begin.end(), c->whole_begin.begin());
+    std::partial_sum(c->long_begin.begin(), c->long_begin.end(), c->long_begin.begin());
     std::partial_sum(c->cut_begin.begin(), c->cut_begin.end(), c->cut_begin.begin());
     c->replicas_alike = dear_mark_runs(*plan, param_ptrs, runs.data(), n_runs);
     const bool on_host = n_tiles <= HOST_TILES;
@@ -1361,13 +1366,13 @@ namespace {
 
 // What a launch goes over: tiles begin .. begin+count-1 of the table, part of a call's `all_tiles` with `all_elems`.
 struct tile_range {
-    int64_t begin, count, all_tiles, all_elems, all_whole, all_cut;
+    int64_t begin, count, all_tiles, all_elems, all_whole, all_long, all_cut;
 };
 
 tile_range range_of(const dear_ctx_impl *c, bucket_range r)
 {
-    return {c->tile_begin[r.begin],        tiles_of(c, r),       tiles_of(c, r),
-            elements_of(c->bucket_len, r), whole_tiles_of(c, r), cut_tiles_of(c, r)};
+    return {c->tile_begin[r.begin], tiles_of(c, r),      tiles_of(c, r),     elements_of(c->bucket_len, r),
+            whole_tiles_of(c, r),   long_tiles_of(c, r), cut_tiles_of(c, r)};
 }
 
 template <rs_mode MODE>
@@ -1375,7 +1380,7 @@ int launch_reduce_scatter(const dear_ctx_impl *c, tile_range t, const rs_sink<MO
 {
     if (t.count == 0) return DEAR_OK;
     const rs_call call{c->P, c->L, c->d_grad, c->max_workgroups, c->wave_priority, c->d_tiles + t.begin, t.count,
-                       t.all_tiles, t.all_elems, t.all_whole, t.all_cut, st};
+                       t.all_tiles, t.all_elems, t.all_whole, t.all_long, t.all_cut, st};
     rs_launch<MODE>(c->g == 2, call, o);
     return launch_status();
 }
@@ -1429,7 +1434,7 @@ int launch_all_gather(const dear_ctx_impl *c, tile_range t, const float *shard_p
         const unsigned whole = n_parts / chunk * chunk;
         const bool eighths = c->replicas_alike && all_gather_in_eighths(t.all_elems * count / t.all_tiles, count, n_workers);
         const unsigned run =
-            eighths ? 0 : all_gather_run(c->g, caches_w, c->max_workgroups, c->P, t.all_elems, count, t.all_whole, t.all_cut,
+            eighths ? 0 : all_gather_run(c->g, caches_w, c->max_workgroups, c->P, t.all_elems, count, t.all_whole, t.all_long, t.all_cut,
                                          n_workers, behind_update);
         const all_gather_order o = all_gather_numbering(run, c->max_workgroups, whole, n_parts, n_workers);
         const auto kernel = eighths && o.len % 8 == 0 ? all_gather_kernel<0, true>
@@ -1726,10 +1731,11 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
                                           STATIC_MAX_TILES, &n_tiles, nullptr);
     if (n_tiles > static_cast<int64_t>(STATIC_MAX_TILES)) return DEAR_ETOOBIG;
     if (n_tiles == 0) return DEAR_OK;
-    int64_t n_whole = 0, n_cut = 0;
+    int64_t n_whole = 0, n_long = 0, n_cut = 0;
     for (int64_t i = 0; i < n_runs; ++i) {
         const dear_run &r = reinterpret_cast<const dear_run *>(host_stage + runs_at)[i];
         n_whole += whole_tiles_of_run(r);
+        n_long += long_tiles_of_run(r, 16 / plan->g);
         n_cut += cut_tiles_of_run(r, 16 / plan->g);
     }
 
@@ -1775,7 +1781,7 @@ extern "C" int dear_reduce_scatter_static(const dear_plan_t *plan, int32_t grad_
     const void *const *grad_tab = reinterpret_cast<const void *const *>(dev);
     const rs_sink<RS_GBAR> o{shard_grad, nullptr, nullptr, 0.0f, 0.0f, nullptr};
     const int64_t elems = elements_of(plan->bucket_len, bucket_range{b_first, b_last});
-    rs_launch<RS_GBAR>(plan->g == 2, rs_call{plan->P, plan->L, grad_tab, 0, 0, tiles, n_tiles, n_tiles, elems, n_whole, n_cut, st}, o);
+    rs_launch<RS_GBAR>(plan->g == 2, rs_call{plan->P, plan->L, grad_tab, 0, 0, tiles, n_tiles, n_tiles, elems, n_whole, n_long, n_cut, st}, o);
     rc = launch_status();
     if (hipEventSynchronize(uploaded_on_device[device]) != hipSuccess) {
         (void)hipGetLastError();

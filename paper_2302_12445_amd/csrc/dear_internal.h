@@ -62,6 +62,20 @@ DEAR_HOST_DEVICE inline dear_tile tile_of_run(const dear_run &r, int64_t k)
     return {r.layer < 0 ? 0 : lo, r.dst_begin + (lo - r.src_begin), static_cast<int32_t>(hi - lo), r.layer, r.shard, r.bucket};
 }
 
+constexpr int DEAR_BLOCK = 256;  // threads per workgroup = 4 wavefronts
+
+// Those of its tiles that lie in more than one part of the reduce-scatter, DEAR_BLOCK vectors of `vector` gradients.
+inline int64_t long_tiles_of_run(const dear_run &r, int64_t vector)
+{
+    if (r.layer < 0) return 0;
+    const int64_t n = tiles_of_run(r);
+    auto is_long = [&](int64_t k) {
+        const dear_tile t = tile_of_run(r, k);
+        return (t.src_begin + t.count - 1) / vector - t.src_begin / vector >= DEAR_BLOCK;
+    };
+    return n > 1 ? n - 2 + is_long(0) + is_long(n - 1) : is_long(0);
+}
+
 // What the device's copy of a tile carries in the place of its bucket, for the all-gather.
 constexpr int TILE_FIRST = 1, TILE_LAST = 2;  // of its run: the tiles of one layer and shard
 constexpr int TILE_OWN_SHIFT = 4;             // the replicas' tensors lie differently: each has a shift of its own
@@ -69,8 +83,6 @@ constexpr int TILE_SHIFT_BIT = 8;             // the replicas' common shift from
 
 // Elements between the last 128-byte line that begins at or before p, and p (16-byte aligned).
 DEAR_HOST_DEVICE inline int line_shift(uintptr_t p) { return static_cast<int>((p >> 2) & 31); }
-
-constexpr int DEAR_BLOCK = 256;  // threads per workgroup = 4 wavefronts
 
 // ------------------------------------------------ which launches a call makes, by its sizes alone
 //
@@ -373,9 +385,20 @@ inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles
 //     1900-7000  P = 8 - | - | 0.97 | 1.01, - | - | 0.97 | 0.98   P = 12 - | - | 0.95 | 0.99, - | - | 0.98 | 0.98
 //     1000-2050 with update, 4/- | 4/3  P = 5 0.97 | 1.00   P = 6 0.98 | 0.98   P = 7 0.98 | 1.01
 // Tensors shorter than a tile leave most parts empty: a workgroup takes whole tiles then.  900 elements each, P = 8  560 tiles fp32
-// 13.3 -> 6.9 us, 2230 42 -> 20, bf16 2230 22 -> 21; P = 64  130 tiles 0.62.  A whole tile among them would keep its workgroup four
-// times as long (P = 32, 101 tiles 22 % full 10.2 -> 13.5), and from a quarter (many tiles: two fifths) full on there are enough
-// workgroups' worth (P = 64, 162 tiles 38 % full 21.7 -> 30).
+// 13.3 -> 6.9 us, 2230 42 -> 20, bf16 2230 22 -> 21; P = 64  130 tiles 0.62.  A tile of several parts (long_tiles) keeps its workgroup
+// up to four times as long, and a short launch with it: weights and short vectors, batch kernel = 1, whole tiles | four replicas and
+// as many workgroups as fit, in parts, in rows, by the share of long tiles, means (worst) of P = 2 to 64, with and without update:
+//   fp32  none 0.50 (0.85) | 0.90 (1.01)
+//         2 to 7 %   below 700 tiles 1.07 (1.42) | 0.89 (1.12)   to 1600 0.82 (0.93) | 0.90 (0.96)   beyond 0.59 (0.65) | 0.89 (0.94)
+//         7 to 15 %  below 700 tiles 1.23 (1.60) | 0.92 (1.29)   to 1600 0.88 (1.02) | 0.93 (0.99)   beyond 0.70 (0.75) | 0.94 (0.99)
+//         15 to 30 % below 700 tiles 1.34 (1.70) | 0.94 (1.06)   beyond 1600 0.96 (1.22) | 0.94 (1.01)
+//   bf16  none 0.92 (1.15) | 1.06 (1.44)
+//         2 to 7 %   below 700 tiles 1.02 (1.22) | 0.86 (1.08)   to 1600 0.99 (1.17) | 1.00 (1.10)   beyond 0.98 (1.08) | 1.09 (1.16)
+//   1 % (one to six of 505 tiles) fp32 P = 2 to 12 1.20 to 1.51 | 0.85 to 1.02;  3 % of 940 bf16 P = 24 with update 1.41 | 1.15
+// Nor do few workgroups that share a CU, or two replicas, go with tiles that are less than half full: most have nothing to load and
+// the others wait for room.  The rule for full tiles had up to 2.1 times the batch kernel's time there (P = 32 581 tiles 22.4 -> 31.4 us,
+// 1500 tensors 1.4 and 2.0 at P = 16 to 64), this one 0.90 (4 replicas, 806 launches), the pass 0.97; below 320 tiles rows are not
+// even (P = 64 219 tiles 1.29).
 // Sixty-four items in a row on an XCD, 256 KiB of each replica, whose lines of the tile table its L2 then has, and whose pages its
 // address translation: BERT-Large-shaped P = 8 bf16 5683 -> 6085 GB/s, with update 5787 -> 6063, BERT-Base-shaped P = 8 fp32 5731 ->
 // 5909.
@@ -402,7 +425,7 @@ inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles
 // -, 1.00 | 1.00 | -, with gbar 1.03 | 1.01 | -, 0.99 | 1.01 | -, P = 5 1.00 | 1.00 | - and 1.00 | 1.01 | -, P = 7 1.01 | 1.02 | - and
 // 0.99 | 1.01 | -.
 inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, bool caches_w, int64_t P, int64_t elems, int64_t tiles,
-                                                    int64_t whole, int64_t cut_tiles)
+                                                    int64_t long_tiles, int64_t cut_tiles)
 {
     auto depth = [&](int most) { return P >= most ? most : P >= 4 ? 4 : P >= 2 ? 2 : 1; };
     auto filled = [&](int percent) { return elems * 100 >= tiles * DEAR_TILE_ELEMS * percent; };
@@ -410,8 +433,8 @@ inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, boo
     auto parts = [&](int most, int residency) { return reduce_scatter_shape{depth(most), residency, run, false}; };
     const reduce_scatter_shape batch{0, 0, 0, false};
     const bool full = filled(85), cut = cut_tiles * 8 >= tiles;
-    if (!some_whole(whole, tiles) && tiles >= (P >= 8 ? 96 : 128) && !filled(tiles >= 512 ? 40 : 25))
-        return {depth(tiles < (bf16 ? 512 : 256) ? 8 : 4), 0, 4, true};
+    if (tiles >= (P >= 8 ? 96 : 128) && !filled(50) && long_tiles * (bf16 ? 15 : 7) <= (tiles < 1600 ? 0 : tiles))
+        return {depth(8), 0, 4, true};
     if (!bf16 && full && P >= 8 && P <= 16 && tiles >= 6000) return {4, 2, 0, false};
     if (caches_w && P >= 4 && filled(50)) {
         if (bf16 && P <= 8 && tiles < 700 && tiles >= (P % 4 ? 40 : 110)) return batch;
@@ -419,6 +442,7 @@ inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, boo
         if (tiles >= (bf16 ? 1600 : 2048)) return parts(2, tiles < 2048 ? 0 : !bf16 && P == 4 ? 3 : 4);
     }
     if (!(caches_w && tiles >= 256 && (bf16 ? P >= 4 && P <= 8 : true)) && batch_kernel_stays(bf16, updates, P, tiles, cut)) return batch;
+    if (tiles >= 128 && !filled(50)) return {depth(4), 0, tiles < 320 ? 0 : 6, false};
     if (P < 4) return parts(2, updates && (full || bf16) && tiles >= (bf16 ? 512 : P > 1 ? 4096 : 1024) ? 4 : 0);
     if (!bf16 && P > 4 && P <= 16 && tiles >= 320 && tiles < (P < 12 ? 1024 : 700)) return {4, 0, 0, false};
     if (bf16 && P <= 16 && (P >= 8 || !updates) && tiles >= (P < 8 ? 900 : 750) && tiles < (P <= 8 ? 2048 : 1600)) return {4, 0, 0, false};
@@ -458,12 +482,12 @@ inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, boo
 // Up to 1024 tiles also where that launch goes in rows (P = 24 660 full tiles +3 / 0, 910 +3 / 0, ragged 630 -2 / -1, 880 0 / -1,
 // weights and short vectors 660 -1 / 0, P = 32 670 and 930 full +5 / 0).
 inline unsigned all_gather_run(int grad_bytes, bool caches_w, int64_t max_workgroups, int64_t P, int64_t elems, int64_t tiles,
-                               int64_t whole, int64_t cut_tiles, int64_t n_workers, bool behind_update)
+                               int64_t whole, int64_t long_tiles, int64_t cut_tiles, int64_t n_workers, bool behind_update)
 {
     if (grad_bytes != 2 || max_workgroups > 0 || tiles >= 2048 || !half_tiles_filled(elems, tiles, whole)) return 0;
     if (!behind_update) return n_workers <= (tiles <= 160 ? 8 : tiles <= 1024 ? 4 : 0);
     if (tiles > 1024) {
-        const reduce_scatter_shape s = reduce_scatter_shape_of(true, true, caches_w, P, elems, tiles, whole, cut_tiles);
+        const reduce_scatter_shape s = reduce_scatter_shape_of(true, true, caches_w, P, elems, tiles, long_tiles, cut_tiles);
         return s.depth > 0 && s.run == 0 && !s.tiles && n_workers <= 12;
     }
     return n_workers <= 8 || (elems * 4 >= tiles * (3 * DEAR_TILE_ELEMS) && n_workers <= (tiles < 400 ? 32 : 47));

@@ -77,12 +77,12 @@ static void pairs_of_parts()
         {4, 161, 2000, true, true},  {5, 161, 4000, true, false},   {32, 399, 4000, true, false},  {33, 399, 4000, false, false}, {47, 400, 4000, true, false},
         {48, 400, 4000, false, false}, {4, 1024, 4000, true, true}, {8, 1024, 3000, true, false},  {8, 1025, 4000, true, false},
         {8, 2047, 4000, true, false},  {8, 2048, 4000, false, false}, {12, 1599, 4000, true, false}, {12, 1600, 4000, false, false},
-        {13, 1025, 4000, false, false}, {13, 1024, 4000, true, false}, {4, 1025, 4000, true, false}, {4, 1025, 1700, true, false},
+        {13, 1025, 4000, false, false}, {13, 1024, 4000, true, false}, {4, 1025, 4000, true, false}, {4, 1025, 2048, true, false}, {4, 1025, 2047, false, false},
     };
     for (const auto &c : at) {
         const int64_t elems = c.tiles * c.fill;
         auto run = [&](int g, int64_t width, int64_t n, int64_t whole, bool behind) {
-            return all_gather_run(g, behind, width, c.P, n, c.tiles, whole, 0, c.P, behind);
+            return all_gather_run(g, behind, width, c.P, n, c.tiles, whole, c.tiles, 0, c.P, behind);
         };
         CHECK(run(2, 0, elems, c.tiles / 2, true) == c.behind);
         CHECK(run(2, 0, elems, c.tiles / 2, false) == c.apart);
@@ -94,7 +94,7 @@ static void pairs_of_parts()
     }
     // a reduce-scatter in whole tiles beyond 1024 of them: the batch kernel, in calls of its own
     CHECK(reduce_scatter_shape_of(true, true, false, 8, 1025 * 4096, 1025, 1025, 0).depth == 0);
-    CHECK(all_gather_run(2, false, 0, 8, 1025 * 4096, 1025, 1025, 0, 8, true) == 0 && all_gather_run(2, true, 0, 8, 1025 * 4096, 1025, 1025, 0, 8, true) == 1);
+    CHECK(all_gather_run(2, false, 0, 8, 1025 * 4096, 1025, 1025, 1025, 0, 8, true) == 0 && all_gather_run(2, true, 0, 8, 1025 * 4096, 1025, 1025, 1025, 0, 8, true) == 1);
 }
 
 // dear_iteration: w is left in the cache only where it fits; gbar is read again only where many replicas are read.

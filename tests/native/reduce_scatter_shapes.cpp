@@ -9,32 +9,35 @@
 
 #include "dear_internal.h"
 
-// Asked for on stdin: bf16 updates caches_w P elems tiles whole cut, a line each; answered with depth, residency, run, tiles.
+// Asked for on stdin: bf16 updates caches_w P elems tiles long cut, a line each; answered with depth, residency, run, tiles.
 static int answer()
 {
     int bf16, updates, caches_w;
-    long long P, elems, tiles, whole, cut;
-    while (std::scanf("%d %d %d %lld %lld %lld %lld %lld", &bf16, &updates, &caches_w, &P, &elems, &tiles, &whole, &cut) == 8) {
-        const reduce_scatter_shape s = reduce_scatter_shape_of(bf16, updates, caches_w, P, elems, tiles, whole, cut);
+    long long P, elems, tiles, long_tiles, cut;
+    while (std::scanf("%d %d %d %lld %lld %lld %lld %lld", &bf16, &updates, &caches_w, &P, &elems, &tiles, &long_tiles, &cut) == 8) {
+        const reduce_scatter_shape s = reduce_scatter_shape_of(bf16, updates, caches_w, P, elems, tiles, long_tiles, cut);
         std::printf("%d %d %d %d\n", s.depth, s.residency, s.run, static_cast<int>(s.tiles));
     }
     return 0;
 }
 
-// Tiles of a run that begin or end inside a vector, against its tiles one by one.
-static bool cut_tiles()
+// Tiles of a run that begin or end inside a vector, or lie in more than one part, against its tiles one by one.
+static bool counted_tiles()
 {
     for (int64_t vector : {4, 8})
-        for (int64_t begin : {0, 1, 4, 8, 4092, 4095, 4096, 12287})
-            for (int64_t count : {1, 3, 4, 8, 4096, 4097, 8192, 20000, 20004})
+        for (int64_t begin : {0, 1, 4, 8, 3072, 4092, 4095, 4096, 12287})
+            for (int64_t count : {1, 3, 4, 8, 1023, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 20000, 20004})
                 for (int32_t layer : {-1, 3}) {
                     const dear_run r{layer < 0 ? 0 : begin, 7, count, 0, layer, 0, 0, 0};
-                    int64_t n = 0;
+                    int64_t n = 0, n_long = 0;
                     for (int64_t k = 0; k < tiles_of_run(r); ++k) {
                         const dear_tile t = tile_of_run(r, k);
                         n += layer >= 0 && (t.src_begin % vector != 0 || (t.src_begin + t.count) % vector != 0);
+                        int64_t parts = 0;
+                        for (int64_t first = t.src_begin / vector; first * vector < t.src_begin + t.count; first += DEAR_BLOCK) ++parts;
+                        n_long += layer >= 0 && parts > 1;
                     }
-                    if (cut_tiles_of_run(r, vector) != n) return false;
+                    if (cut_tiles_of_run(r, vector) != n || long_tiles_of_run(r, vector) != n_long) return false;
                 }
     return true;
 }
@@ -74,7 +77,7 @@ static bool batch_kernel()
 int main(int argc, char **)
 {
     if (argc > 1) return answer();
-    if (!cut_tiles() || !batch_kernel()) return 1;
+    if (!counted_tiles() || !batch_kernel()) return 1;
     for (unsigned run : {0u, 4u, 6u, 9u})
         for (unsigned n = 1; n < (run < 9 ? 2100 : 12400); n += n < 1100 ? 1 : 37) {
             std::vector<int> seen(n, 0);
@@ -96,13 +99,13 @@ int main(int argc, char **)
                 for (int64_t P = 1; P <= 130; ++P)
                     for (int64_t tiles : {1, 15, 16, 63, 64, 96, 127, 128, 191, 192, 255, 256, 319, 512, 1023, 1024, 2048, 4096, 5999, 6000, 30000})
                         for (int64_t percent : {1, 24, 39, 50, 79, 80, 87, 100})
-                            for (int64_t whole : {int64_t(0), tiles}) {
+                            for (int64_t long_tiles : {int64_t(0), tiles / 12, tiles}) {
                                 const int64_t cut = percent % 2 ? tiles : 0;
                                 const reduce_scatter_shape s = reduce_scatter_shape_of(
-                                    bf16, updates, caches_w, P, tiles * DEAR_TILE_ELEMS * percent / 100, tiles, whole, cut);
+                                    bf16, updates, caches_w, P, tiles * DEAR_TILE_ELEMS * percent / 100, tiles, long_tiles, cut);
                                 const bool depth = s.depth == 0 || s.depth == 1 || s.depth == 2 || s.depth == 4 || s.depth == 8;
                                 if (!depth || s.depth > P || (s.depth == 1 && P > 1) || s.residency < 0 || s.residency > 4 || s.residency == 1 || s.run < 0 || s.run > 6 ||
-                                    (s.tiles && (s.depth == 0 || whole))) {
+                                    (s.tiles && (s.depth == 0 || long_tiles == tiles))) {
                                     std::fprintf(stderr, "FAILED bf16=%d updates=%d P=%lld tiles=%lld percent=%lld\n", bf16, updates,
                                                  (long long)P, (long long)tiles, (long long)percent);
                                     return 1;

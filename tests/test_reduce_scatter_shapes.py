@@ -28,7 +28,7 @@ def full(tiles):
 
 
 SHORT = [900, 3, 911, 1]  # per tensor and shard far less than a tile
-SOME = SHORT * 60 + [16_400] + SHORT * 60  # and a few whole tiles among them, less than one in 64
+SOME = (SHORT * 60 + [16_400] + SHORT * 60) * 4  # and a few whole tiles among them, in a launch long enough for it
 ODD = [4101, 9_003, 6_555]  # most tiles begin or end inside a vector
 
 # replicas a lane: 1; 2 alone, with batches, with a rest; 4; 8; then rows (512 items and some behind them); whole tiles; very long launches
@@ -43,7 +43,10 @@ CASES = [("f32", 1, full(1030)), ("f32", 2, full(40)), ("f32", 3, full(321)), ("
          ("f32", 1, ODD * 3), ("f32", 2, ODD * 3), ("f32", 16, full(40)), ("bf16", 1, ODD * 3), ("bf16", 2, ODD * 3), ("bf16", 16, full(40)),
          ("f32", 1, SHORT * 150), ("f32", 2, SHORT * 150), ("f32", 4, SHORT * 100), ("f32", 8, SHORT * 80), ("bf16", 1, SHORT * 200),
          ("bf16", 8, SHORT * 200), ("bf16", 11, SHORT * 250), ("f32", 2, SOME), ("f32", 3, SOME), ("f32", 8, SOME), ("f32", 9, SOME),
-         ("bf16", 2, SOME), ("bf16", 3, SOME), ("bf16", 8, SOME), ("bf16", 9, SOME)]
+         ("bf16", 2, SOME), ("bf16", 3, SOME), ("bf16", 8, SOME), ("bf16", 9, SOME), ("bf16", 4, SHORT * 200), ("bf16", 5, SHORT * 200),
+         # weights of some parts with short vectors between them: in parts, then so many that tiles go whole
+         ("f32", 8, [2900, 33, 900] * 60), ("bf16", 16, [2900, 33, 900] * 90), ("f32", 3, ([2900] + [33, 900] * 6) * 90),
+         ("bf16", 5, ([3900] + [33, 900] * 8) * 50)]
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
@@ -58,9 +61,10 @@ def test_the_cases_reach_every_form(tmp_path):
         tiles = dear.dear_plan_tiles(dear.dear_plan(sizes, P, dear.DEAR_NO_LIMIT, g))[0]
         runs = [t for t in tiles if t.layer >= 0]
         whole = sum(t.count == 4096 for t in runs)
+        several = sum((t.src_begin + t.count - 1) // v - t.src_begin // v >= 256 for t in runs)  # parts
         cut = sum(t.src_begin % v != 0 or (t.src_begin + t.count) % v != 0 for t in runs)
         for updates in (0, 1):
-            asked.append("%d %d 0 %d %d %d %d %d\n" % (g == 2, updates, P, sum(t.count for t in runs), len(tiles), whole, cut))
+            asked.append("%d %d 0 %d %d %d %d %d\n" % (g == 2, updates, P, sum(t.count for t in runs), len(tiles), several, cut))
             of.append((dtype, P, whole))
     said = subprocess.run([_shapes_program(tmp_path), "ask"], input="".join(asked), check=True, capture_output=True, text=True).stdout.splitlines()
     reached, whole_among_short = set(), set()
