@@ -398,7 +398,8 @@ inline bool batch_kernel_stays(bool bf16, bool updates, int64_t P, int64_t tiles
 // Nor do few workgroups that share a CU, or two replicas, go with tiles that are less than half full: most have nothing to load and
 // the others wait for room.  The rule for full tiles had up to 2.1 times the batch kernel's time there (P = 32 581 tiles 22.4 -> 31.4 us,
 // 1500 tensors 1.4 and 2.0 at P = 16 to 64), this one 0.90 (4 replicas, 806 launches), the pass 0.97; below 320 tiles rows are not
-// even (P = 64 219 tiles 1.29).
+// even (P = 64 219 tiles 1.29).  From 50 to 60 % full four replicas are still the better ones, 0.97 to 1.00 where 2/3r has 1.02 to
+// 1.21, with rows where full tiles have them: elsewhere a pass is 1.05 with rows and 1.03 without (P = 2 to 8).
 // Sixty-four items in a row on an XCD, 256 KiB of each replica, whose lines of the tile table its L2 then has, and whose pages its
 // address translation: BERT-Large-shaped P = 8 bf16 5683 -> 6085 GB/s, with update 5787 -> 6063, BERT-Base-shaped P = 8 fp32 5731 ->
 // 5909.
@@ -442,7 +443,7 @@ inline reduce_scatter_shape reduce_scatter_shape_of(bool bf16, bool updates, boo
         if (tiles >= (bf16 ? 1600 : 2048)) return parts(2, tiles < 2048 ? 0 : !bf16 && P == 4 ? 3 : 4);
     }
     if (!(caches_w && tiles >= 256 && (bf16 ? P >= 4 && P <= 8 : true)) && batch_kernel_stays(bf16, updates, P, tiles, cut)) return batch;
-    if (tiles >= 128 && !filled(50)) return {depth(4), 0, tiles < 320 ? 0 : 6, false};
+    if (tiles >= 128 && !filled(60)) return {depth(4), 0, filled(50) ? run : tiles < 320 ? 0 : 6, false};
     if (P < 4) return parts(2, updates && (full || bf16) && tiles >= (bf16 ? 512 : P > 1 ? 4096 : 1024) ? 4 : 0);
     if (!bf16 && P > 4 && P <= 16 && tiles >= 320 && tiles < (P < 12 ? 1024 : 700)) return {4, 0, 0, false};
     if (bf16 && P <= 16 && (P >= 8 || !updates) && tiles >= (P < 8 ? 900 : 750) && tiles < (P <= 8 ? 2048 : 1600)) return {4, 0, 0, false};
