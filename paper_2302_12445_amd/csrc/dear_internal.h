@@ -47,11 +47,12 @@ inline int64_t whole_tiles_of_run(const dear_run &r)
     return r.layer < 0 || n < 0 ? 0 : n;
 }
 
-// Those of its tiles that begin or end inside a 16-byte vector of `vector` gradients.
+// Those of its tiles that begin or end inside a 16-byte vector of `vector` gradients, 4 or 8: masks, as a static call counts hundreds
+// of runs and does not know the type when it is compiled.
 inline int64_t cut_tiles_of_run(const dear_run &r, int64_t vector)
 {
     if (r.layer < 0) return 0;
-    const bool begins = r.src_begin % vector != 0, ends = (r.src_begin + r.count) % vector != 0;
+    const bool begins = (r.src_begin & (vector - 1)) != 0, ends = ((r.src_begin + r.count) & (vector - 1)) != 0;
     return tiles_of_run(r) > 1 ? begins + ends : begins || ends;
 }
 
@@ -71,7 +72,7 @@ inline int64_t long_tiles_of_run(const dear_run &r, int64_t vector)
     const int64_t n = tiles_of_run(r);
     auto is_long = [&](int64_t k) {
         const dear_tile t = tile_of_run(r, k);
-        return (t.src_begin + t.count - 1) / vector - t.src_begin / vector >= DEAR_BLOCK;
+        return ((t.src_begin + t.count - 1) & -vector) - (t.src_begin & -vector) >= DEAR_BLOCK * vector;
     };
     return n > 1 ? n - 2 + is_long(0) + is_long(n - 1) : is_long(0);
 }
